@@ -94,28 +94,4 @@ __device__ __forceinline__ float wave_sum(float x, int lane) {
     return x;
 }
 
-// Bitonic sort of one key per lane across the wavefront, descending: lane 0 ends with the largest.
-// 21 compare-exchange steps; equal keys (only the empty key 0 repeats) may end in any order.
-template <int SIZE, int STRIDE>
-__device__ __forceinline__ u64 bitonic_step(u64 x, int lane) {
-    const uint32_t lo = xor_lane<STRIDE>((uint32_t)x, lane), hi = xor_lane<STRIDE>((uint32_t)(x >> 32), lane);
-    const u64 y = ((u64)hi << 32) | lo;
-    const bool lower = (lane & STRIDE) == 0;             // this lane is the smaller index of its pair
-    const bool desc = (lane & SIZE) == 0;                // its block is being sorted downwards
-    const bool gt = x > y;
-    return (gt == (lower == desc)) ? x : y;              // lower lane of a descending block keeps the larger
-}
-__device__ __forceinline__ u64 wave_sort_desc(u64 x, int lane) {
-    x = bitonic_step<2, 1>(x, lane);
-    x = bitonic_step<4, 2>(x, lane);  x = bitonic_step<4, 1>(x, lane);
-    x = bitonic_step<8, 4>(x, lane);  x = bitonic_step<8, 2>(x, lane);  x = bitonic_step<8, 1>(x, lane);
-    x = bitonic_step<16, 8>(x, lane); x = bitonic_step<16, 4>(x, lane); x = bitonic_step<16, 2>(x, lane);
-    x = bitonic_step<16, 1>(x, lane);
-    x = bitonic_step<32, 16>(x, lane); x = bitonic_step<32, 8>(x, lane); x = bitonic_step<32, 4>(x, lane);
-    x = bitonic_step<32, 2>(x, lane);  x = bitonic_step<32, 1>(x, lane);
-    x = bitonic_step<64, 32>(x, lane); x = bitonic_step<64, 16>(x, lane); x = bitonic_step<64, 8>(x, lane);
-    x = bitonic_step<64, 4>(x, lane);  x = bitonic_step<64, 2>(x, lane);  x = bitonic_step<64, 1>(x, lane);
-    return x;
-}
-
 }  // namespace evospec

@@ -551,19 +551,55 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
 //   logZ = M + log(sum_t s_t * exp(m_t - M)),  M = max_t m_t
 //   top-k = the k largest of all slab candidates (keys are unique, so the order is total).
 // Candidates come from up to two partial sets (a shared core and a per-sequence extension in the
-// batched variant).  Every slab's list is sorted, so its head is its maximum: per block of 256
-// lists the k-th largest head (together with the running result) bounds the answer from below,
-// at most k lists reach above that bound, and only their entries are ranked exactly.
+// batched variant).
+//
+// The kernel is bound by latency, so it is built around ONE trip to memory: every thread fetches its
+// candidates at once (the first kEager keys of a sorted list, or eight whole 16-byte pieces of the
+// unsorted lists, which lie one after the other and are read a line at a time).  The largest of the
+// 64 per-thread maxima of a wavefront, found bit by bit with ballots, give a bound that k candidates
+// reach; what reaches it (some 20 keys of 2,560 at 256 lists of 10) goes to a list in LDS and is ranked
+// by counting.  Only a thread whose last fetched key still reaches the bound goes back to memory.
+// Measured on MI355X against ordering the list heads with sorting networks and reading the qualifying
+// lists afterwards (a second trip): 60 rows x 256 lists of 10 7.3 -> 6.8 us, 37 x 251 of 20 11.8 -> 7.0,
+// 60 x 950 of 10 19.3 -> 13.2, 960 x (256 unsorted + 15 sorted) 26.7 -> 14.8.  What is left at the
+// first size: 1.4 us launch, 0.6 arguments, 2.0 memory, 0.6 bound, 2 exchange, ranking and stores.
 
 // An unranked list slot holds (logit bits << 32) | id; all ones = empty.
 __device__ __forceinline__ u64 pair_key(uint32_t zbits, uint32_t id) {
     return id == 0xffffffffu ? 0ull : make_key(__uint_as_float(zbits), (int32_t)id);
 }
 
+// The q-th largest (1 <= q <= 64) of the 64 keys of a wavefront: the largest value that q keys reach
+// (0 if fewer than q lanes hold a key).  The high words first; when a single lane holds the word that
+// was found, its key is the answer, else the low words decide among the lanes that share it.
+__device__ __forceinline__ u64 wave_kth_key(u64 key, int q) {
+    const uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key;
+    uint32_t th = 0;
+#pragma unroll
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t c = th | (1u << bit);
+        if (__popcll(__ballot(hi >= c)) >= q) th = c;            // (uniform)
+    }
+    const u64 same = __ballot(hi == th);
+    if (__popcll(same) == 1)
+        return ((u64)th << 32) | (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)__builtin_ctzll(same));
+    const int need = q - __popcll(__ballot(hi > th));            // >= 1: fewer than q lanes lie above th
+    uint32_t tl = 0;
+#pragma unroll
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t c = tl | (1u << bit);
+        if (__popcll(__ballot(hi == th && lo >= c)) >= need) tl = c;
+    }
+    return ((u64)th << 32) | tl;
+}
+
+constexpr int kEager = 4;              // keys of a sorted list that a thread fetches up front
+constexpr int kPieces = 8;             // 16-byte pieces (two slots) of unsorted lists, likewise
+
 template <int NT>
 __global__ void __launch_bounds__(NT)
 lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_keys, size_t a_pass_stats,
-                    size_t b_chunk_keys, size_t b_chunk_stats, int k, int pend_cap,
+                    size_t b_chunk_keys, size_t b_chunk_stats, int k, int parts_log2, int pend_cap,
                     float* __restrict__ out_vals, int32_t* __restrict__ out_ids,
                     float* __restrict__ out_logz, GatherArgs upd) {
     // The blocks of grid row cb.n (present only when an update rides along) insert the rows of a
@@ -574,155 +610,215 @@ lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_key
         return;
     }
     constexpr int NWV = NT / 64;
-    __shared__ u64 run[2][kKMax];                    // running k best, descending
-    __shared__ u64 cand[(NWV + 1) * kKMax];          // per-wave best heads, then the running list
-    // entries that reach the bound: at most k lists of max_len entries, plus the running k
-    // (dynamic LDS, sized by the launcher, so that small k leaves room for many workgroups per CU)
     extern __shared__ __align__(16) unsigned char merge_smem[];
-    u64* pend = reinterpret_cast<u64*>(merge_smem);
-    const int kPendCap = pend_cap;
-    __shared__ const u64* qual[kKMax];             // lists whose head reaches the bound
-    __shared__ int qual_len[kKMax];
-    __shared__ u64 tau_s;
-    __shared__ int npend, nqual;
+    u64* pend = reinterpret_cast<u64*>(merge_smem);      // candidates that reach the bound
+    __shared__ u64 run[kKMax];                           // the k best of earlier rounds, descending
+    __shared__ u64 wave_tau[NWV];
     __shared__ float wave_m[NWV], wave_s[NWV];
+    __shared__ int npend, count_s;
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     // row blockIdx.x of chunk blockIdx.y: where its partials sit in the two sets
     const int chunk = blockIdx.y;
     if ((int)blockIdx.x >= cb.rows[chunk]) return;                 // uniform: the grid spans the longest chunk
     const int out_row = cb.m0[chunk] + blockIdx.x;
-    A.keys += (size_t)cb.a_pass[chunk] * a_pass_keys;
-    A.stats += (size_t)cb.a_pass[chunk] * a_pass_stats;
-    B.keys += (size_t)chunk * b_chunk_keys;
-    B.stats += (size_t)chunk * b_chunk_stats;
     const int slotA = A.row_base + cb.a_slot[chunk] + blockIdx.x, slotB = B.row_base + blockIdx.x;
+    const u64* keysA = A.keys + (size_t)cb.a_pass[chunk] * a_pass_keys + (size_t)slotA * A.key_row;
+    const u64* keysB = B.keys + (size_t)chunk * b_chunk_keys + (size_t)slotB * B.key_row;
+    const float2* statsA = A.stats + (size_t)cb.a_pass[chunk] * a_pass_stats + (size_t)slotA * A.stat_row;
+    const float2* statsB = B.stats + (size_t)chunk * b_chunk_stats + (size_t)slotB * B.stat_row;
     const int total = A.n_slabs + B.n_slabs;
 
-    auto list_of = [&](int L) -> const u64* {
-        return L < A.n_slabs ? A.keys + (size_t)L * A.key_slab + (size_t)slotA * A.key_row
-                             : B.keys + (size_t)(L - A.n_slabs) * B.key_slab + (size_t)slotB * B.key_row;
-    };
-    auto len_of = [&](int L) { return L < A.n_slabs ? A.list_len : B.list_len; };
-    auto sorted_of = [&](int L) { return (L < A.n_slabs ? A.sorted : B.sorted) != 0; };
-    // a list's best key: its first slot if it is sorted, else the maximum over its slots (an even
-    // number of (logit, id) pairs, 16-byte aligned)
-    auto head_of = [&](int L) -> u64 {
-        const u64* p = list_of(L);
-        if (sorted_of(L)) return p[0];
-        u64 hd = 0;
-        const int n = len_of(L);
-        for (int j0 = 0; j0 < n; j0 += 16) {            // 8 loads in flight (list lengths are 16, 32 or 64)
-            u32x4 q[8];
+    // Sorted lists (set B, and set A unless it is unsorted), 2^parts_log2 threads to a list: thread
+    // part p takes the entries p, p + P, ..., which descend.
+    const int parts = 1 << parts_log2, part = tid & (parts - 1);
+    const int sortedA = A.sorted ? A.n_slabs : 0, n_sorted = sortedA + B.n_slabs;
+    // Unsorted lists (set A only): contiguous, taken as one array of 16-byte pieces.
+    const int n_pieces = A.sorted ? 0 : A.n_slabs * (A.list_len / 2);
+    const int step_sorted = NT >> parts_log2, step_pieces = NT * kPieces;
+
+    int len = 0;
+    const u64* lst = nullptr;                            // this thread's sorted list of the round, from its own part on
+    u64 se[kEager];
+    u32x4 up[kPieces];
+    auto fetch = [&](int round) {
+        const int L = round * step_sorted + (tid >> parts_log2);
+        const bool inA = L < sortedA;
+        lst = (inA ? keysA + (size_t)L * A.key_slab : keysB + (size_t)(L - sortedA) * B.key_slab) + part;
+        len = L < n_sorted ? (inA ? A.list_len : B.list_len) - part : 0;       // entries are lst[0], lst[parts], ... below len
 #pragma unroll
-            for (int u = 0; u < 8; ++u) q[u] = *(gvec_ptr)(p + j0 + 2 * u);
+        for (int j = 0; j < kEager; ++j) se[j] = (j << parts_log2) < len ? lst[j << parts_log2] : 0ull;
+        if (n_pieces) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const u64 k0 = pair_key(q[u][1], q[u][0]), k1 = pair_key(q[u][3], q[u][2]);
-                hd = k0 > hd ? k0 : hd;
-                hd = k1 > hd ? k1 : hd;
+            for (int j = 0; j < kPieces; ++j) {
+                const int q = round * step_pieces + j * NT + tid;
+                up[j] = u32x4{~0u, ~0u, ~0u, ~0u};
+                if (q < n_pieces) up[j] = *(gvec_ptr)(keysA + 2 * (size_t)q);
             }
         }
-        return hd;
     };
-    const int max_len = A.list_len > B.list_len ? A.list_len : B.list_len;
-    // the first block's list heads are fetched together with the statistics (one memory round trip)
-    const u64 head_first = tid < total ? head_of(tid) : 0;
+    fetch(0);
 
     // ---- log-normaliser: online (max, scaled sum) per thread, fixed-shape reduction
-    float mx = -INFINITY, sm = 0.f;
-    for (int t = tid; t < total; t += NT) {
-        const float2 st = t < A.n_slabs ? A.stats[(size_t)t * A.stat_slab + (size_t)slotA * A.stat_row]
-                                        : B.stats[(size_t)(t - A.n_slabs) * B.stat_slab + (size_t)slotB * B.stat_row];
-        const float nm = fmaxf(mx, st.x);
-        sm = (mx == -INFINITY ? 0.f : sm * __expf(mx - nm)) + st.y * __expf(st.x - nm);
-        mx = nm;
-    }
-    {   // wavefront: the maximum first, then one rescale per lane and a plain sum
+    {
+        float mx = -INFINITY, sm = 0.f;
+        for (int t = tid; t < total; t += NT) {
+            const float2 st = t < A.n_slabs ? statsA[(size_t)t * A.stat_slab] : statsB[(size_t)(t - A.n_slabs) * B.stat_slab];
+            const float nm = fmaxf(mx, st.x);
+            sm = (mx == -INFINITY ? 0.f : sm * __expf(mx - nm)) + st.y * __expf(st.x - nm);
+            mx = nm;
+        }
+        // wavefront: the maximum first, then one rescale per lane and a plain sum
         const float wm_ = wave_max(mx, lane);
         sm = mx == -INFINITY ? 0.f : sm * __expf(mx - wm_);
         sm = wave_sum(sm, lane);
-        mx = wm_;
-    }
-    if (lane == 0) { wave_m[w] = mx; wave_s[w] = sm; }
-    if (tid == 0) { npend = 0; nqual = 0; }
-    __syncthreads();
-    if (tid == 0) {
-        float gm_ = wave_m[0], gs = wave_s[0];
-        for (int i = 1; i < NWV; ++i) {
-            const float nm = fmaxf(gm_, wave_m[i]);
-            gs = (gm_ == -INFINITY ? 0.f : gs * __expf(gm_ - nm)) + (wave_m[i] == -INFINITY ? 0.f : wave_s[i] * __expf(wave_m[i] - nm));
-            gm_ = nm;
-        }
-        out_logz[out_row] = gm_ + __logf(gs);
+        if (lane == 0) { wave_m[w] = wm_; wave_s[w] = sm; }
     }
 
     // ---- top-k
-    int nrun = 0, cur = 0;
-    u64 thr = 0;                                     // running k-th best (0 until k entries are known)
-    for (int base = 0; base < total; base += NT) {
-        const int L = base + tid;
-        const u64* lst = L < total ? list_of(L) : nullptr;
-        u64 head = base == 0 ? head_first : (lst ? head_of(L) : 0);
-        if (head <= thr) head = 0;                   // cannot improve the running result
-        // (1) the wave's 64 heads, sorted across the lanes; its k best go to cand
+    // The bound: the q-th largest per-thread maximum of every wavefront; with q * kSets >= k, the kSets-th
+    // largest of these values is reached by k candidates.  (Half of the wavefronts: some 20 candidates
+    // reach it at k = 10, whatever the number of wavefronts; with one wavefront's k-th largest alone it is
+    // 30 for four wavefronts and 110 for sixteen.)
+    constexpr int kSets = NWV / 2;
+    const int q = (k + kSets - 1) / kSets;
+    const int rounds_s = (n_sorted + step_sorted - 1) / step_sorted, rounds_p = (n_pieces + step_pieces - 1) / step_pieces;
+    const int rounds = rounds_s > rounds_p ? rounds_s : rounds_p;
+    int nrun = 0;
+    for (int round = 0; round < rounds; ++round) {
+        if (round > 0) fetch(round);
+        // (1) the bound: k candidates of some wavefront reach it
+        u64 best = se[0];
+        if (n_pieces) {
+            // any large candidate of the thread serves: plain float compares (false for empty slots: NaN)
+            float bz = -INFINITY;
+            uint32_t bid = ~0u;
+#pragma unroll
+            for (int j = 0; j < kPieces; ++j)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float z = __uint_as_float(up[j][2 * h + 1]);
+                    const bool up_ = z > bz;
+                    bz = up_ ? z : bz;
+                    bid = up_ ? up[j][2 * h] : bid;
+                }
+            const u64 kb = pair_key(__float_as_uint(bz), bid);
+            best = kb > best ? kb : best;
+        }
+        const u64 wt = wave_kth_key(best, q);
+        if (lane == 0) wave_tau[w] = wt;
+        if (tid == 0) npend = 0;
+        __syncthreads();
+        u64 tau;
         {
-            const u64 sorted = wave_sort_desc(head, lane);
-            if (lane < k) cand[w * k + lane] = sorted;
+            const u64 mine = lane < NWV ? wave_tau[lane] : 0ull;
+            int ge = 0;
+#pragma unroll
+            for (int i = 0; i < NWV; ++i) ge += wave_tau[i] >= mine ? 1 : 0;
+            const u64 hit = __ballot(lane < NWV && mine != 0ull && ge == kSets);     // (keys are distinct: at most one lane)
+            const int src = hit ? (int)__builtin_ctzll(hit) : 63;
+            tau = hit ? ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), src) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, src)
+                      : 0ull;
+            if (nrun == k && run[k - 1] > tau) tau = run[k - 1];
         }
-        if (tid < nrun) cand[NWV * k + tid] = run[cur][tid];
-        __syncthreads();
-        // (2) bound = k-th largest of (wave bests + running list): k real candidates are >= it
-        const int ne = NWV * k + nrun;
-        if (ne <= 64) {                                  // one more sort by the first wavefront
-            if (w == 0) {
-                const u64 c = wave_sort_desc(lane < ne ? cand[lane] : 0ull, lane);
-                if (lane == k - 1) tau_s = c;
+        // (2) what reaches the bound goes to pend; use(key) sees every candidate of the thread that does
+        auto each = [&](u64 t, auto use) {
+            bool more = true;                            // sorted entries: stop at the first one below t
+#pragma unroll
+            for (int j = 0; j < kEager; ++j) {
+                more = more && se[j] != 0ull && se[j] >= t;
+                if (more) use(se[j]);
             }
-        } else {
-            for (int e = tid; e < ne; e += NT) {
-                const u64 mine = cand[e];
-                int r = 0;
-                for (int j = 0; j < ne; ++j) { const u64 o = cand[j]; r += (o > mine) || (o == mine && j < e); }   // zeros tie: keep the index order
-                if (r == k - 1) tau_s = mine;
+            for (int j = kEager << parts_log2; more && j < len; j += parts) {
+                const u64 key = lst[j];
+                more = key != 0ull && key >= t;
+                if (more) use(key);
             }
+            if (n_pieces) {
+                const float tz = t ? ordered_to_f32((uint32_t)(t >> 32)) : -INFINITY;
+#pragma unroll
+                for (int j = 0; j < kPieces; ++j)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        // (a NaN logit is no smaller than anything, as in the keys)
+                        if (!(__uint_as_float(up[j][2 * h + 1]) < tz) && up[j][2 * h] != ~0u) {
+                            const u64 key = pair_key(up[j][2 * h + 1], up[j][2 * h]);
+                            if (key >= t) use(key);
+                        }
+                    }
+            }
+            if (tid < nrun && run[tid] >= t) use(run[tid]);
+        };
+        auto collect = [&](u64 t) {
+            // room for all of a thread's candidates with one atomic add, then stores that wait for nothing
+            int n = 0;
+            each(t, [&](u64) { ++n; });
+            if (n == 0) return;
+            int p = atomicAdd(&npend, n);
+            each(t, [&](u64 key) { if (p < pend_cap) pend[p] = key; ++p; });
+        };
+        collect(tau);
+        __syncthreads();
+        if (npend > pend_cap) {
+            // More candidates than the list holds (they crowd into few lists, many wavefronts over, with a
+            // large k): the exact k-th largest, one bit at a time, leaves k of them.
+            u64 t = tau;
+            u64 found = 0;
+            for (int bit = 63; bit >= 0; --bit) {
+                const u64 c = found | (1ull << bit);
+                __syncthreads();
+                if (tid == 0) count_s = 0;
+                __syncthreads();
+                int mine = 0;
+                each(c > t ? c : t, [&](u64 key) { mine += key >= c ? 1 : 0; });
+                if (mine) atomicAdd(&count_s, mine);
+                __syncthreads();
+                if (count_s >= k) found = c;
+            }
+            tau = found > t ? found : t;
+            __syncthreads();
+            if (tid == 0) npend = 0;
+            __syncthreads();
+            collect(tau);
+            __syncthreads();
         }
-        __syncthreads();
-        // (3) lists (at most k of them) and running entries that reach the bound feed pend; the
-        //     qualifying lists are read by all threads at once (one entry per thread and round)
-        const u64 t = tau_s;
-        // (capacity checks only matter if the caller broke the unique-id precondition)
-        if (head != 0 && head >= t) { const int qi = atomicAdd(&nqual, 1); if (qi < kKMax) { qual[qi] = lst; qual_len[qi] = sorted_of(L) ? len_of(L) : -len_of(L); } }
-        if (tid < nrun && run[cur][tid] >= t) pend[atomicAdd(&npend, 1)] = run[cur][tid];
-        __syncthreads();
-        const int nq = nqual < kKMax ? nqual : kKMax;
-        for (int e = tid; e < nq * max_len; e += NT) {
-            const int li = e / max_len, j = e - li * max_len;
-            const int ql = qual_len[li];                // negative: (logit, id) pairs
-            u64 key = j < (ql < 0 ? -ql : ql) ? qual[li][j] : 0;
-            if (ql < 0) key = pair_key((uint32_t)(key >> 32), (uint32_t)key);
-            if (key != 0 && key >= t) { const int pi = atomicAdd(&npend, 1); if (pi < kPendCap) pend[pi] = key; }
-        }
-        __syncthreads();
-        // (4) exact order among pend -> new running list
-        const int np = npend < kPendCap ? npend : kPendCap;
+        // (3) exact order among pend: the rank of a key is the number of larger ones
+        const int np = npend < pend_cap ? npend : pend_cap;
+        const bool last = round + 1 == rounds;
+        if (!last) __syncthreads();                      // (run has been read: it is rewritten below)
         for (int e = tid; e < np; e += NT) {
             const u64 mine = pend[e];
-            int r = 0;
-            for (int j = 0; j < np; ++j) r += pend[j] > mine;
-            if (r < k) run[cur ^ 1][r] = mine;
+            int r = 0, j = 0;
+            for (; j < np; j += 8) {                     // (the list is a whole number of eights long; past np: stale, not counted)
+                ulonglong2 q[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const ulonglong2*>(pend + j + 2 * u);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    r += (q[u].x > mine && j + 2 * u < np ? 1 : 0) + (q[u].y > mine && j + 2 * u + 1 < np ? 1 : 0);
+            }
+            if (r < k) {
+                if (last) {
+                    out_vals[(size_t)out_row * k + r] = key_value(mine);
+                    out_ids[(size_t)out_row * k + r] = key_id(mine);
+                } else {
+                    run[r] = mine;
+                }
+            }
         }
-        __syncthreads();
-        cur ^= 1;
         nrun = np < k ? np : k;
-        thr = nrun == k ? run[cur][k - 1] : 0;
-        if (tid == 0) { npend = 0; nqual = 0; }
-        __syncthreads();
+        if (!last) __syncthreads();
     }
-    for (int j = tid; j < k; j += NT) {
-        const u64 key = j < nrun ? run[cur][j] : 0;
-        out_vals[(size_t)out_row * k + j] = key ? key_value(key) : -INFINITY;
-        out_ids[(size_t)out_row * k + j] = key ? key_id(key) : -1;
+    // the log-normaliser over the wavefronts, by the one that has least to rank
+    if (w == NWV - 1) {
+        const float m_ = lane < NWV ? wave_m[lane] : -INFINITY, gm_ = wave_max(m_, lane);
+        const float gs = wave_sum(m_ == -INFINITY ? 0.f : wave_s[lane] * __expf(m_ - gm_), lane);
+        if (lane == 0) out_logz[out_row] = gm_ + __logf(gs);
+    }
+    for (int j = nrun + tid; j < k; j += NT) {           // fewer than k candidates in all
+        out_vals[(size_t)out_row * k + j] = -INFINITY;
+        out_ids[(size_t)out_row * k + j] = -1;
     }
 }
 
@@ -814,6 +910,7 @@ hipError_t launch_merge_batch(const MergeSet& a, size_t a_pass_bytes, const Merg
     if ((a.list_len != 0 && (a.list_len < k || a.list_len > kKMax || (a.list_len & 15))) ||
         (b.list_len != 0 && (b.list_len < k || b.list_len > kKMax || (b.list_len & 15))))
         return hipErrorInvalidValue;
+    if (b.list_len != 0 || (a.list_len != 0 && !a.row_major)) return hipErrorInvalidValue;   // unsorted: one contiguous set
     auto as_set = [&](const MergeSet& m) {
         PartialSet p;
         p.keys = static_cast<const u64*>(m.keys);
@@ -832,18 +929,26 @@ hipError_t launch_merge_batch(const MergeSet& a, size_t a_pass_bytes, const Merg
         return p;
     };
     const PartialSet A = as_set(a), B = as_set(b);
-    const int max_len = A.list_len > B.list_len ? A.list_len : B.list_len;
-    const int pend_cap = k * max_len + k + 8;      // k qualifying lists in full, the running k (8-byte keys: < 34 KB)
     const int gx = max_rows > upd.n ? max_rows : upd.n;
-    // enough threads to take all lists of a row in one round where possible (one list per thread and round)
-    const int total = A.n_slabs + B.n_slabs;
+    // Enough threads to take all lists of a row in one round where possible: a thread takes one sorted
+    // list, or 16 slots of the unsorted ones.  Fewer sorted lists than threads: several threads share one.
+    const int n_sorted = (A.sorted ? A.n_slabs : 0) + B.n_slabs;
+    const int n_pieces = A.sorted ? 0 : A.n_slabs * (A.list_len / 2);
+    const int units = n_sorted > n_pieces / 8 ? n_sorted : (n_pieces + 7) / 8;
+    const int nt = units <= 256 ? 256 : (units <= 512 ? 512 : 1024);
+    const int max_len = A.list_len > B.list_len ? A.list_len : B.list_len;
+    int parts_log2 = 0;
+    while (n_sorted > 0 && parts_log2 < 4 && (n_sorted << (parts_log2 + 1)) <= nt && (2 << parts_log2) <= max_len) ++parts_log2;
+    // room for what usually reaches the bound, up to 32 KB (more is handled, slowly), and the running k
+    int pend_cap = nt / 64 * k * (max_len > 16 ? max_len : 16);
+    pend_cap = ((pend_cap < 4096 ? pend_cap : 4096) + k + 7) & ~7;
     const dim3 grid(gx, cb.n + (upd.n > 0 ? 1 : 0));
 #define EVOSPEC_MERGE(NT_)                                                                                  \
     hipLaunchKernelGGL(lmhead_merge_kernel<NT_>, grid, dim3(NT_), (size_t)pend_cap * 8, stream, A, B, cb,    \
-                       a_pass_bytes / 8, a_pass_bytes / 8, b_chunk_bytes / 8, b_chunk_bytes / 8, k, pend_cap, \
-                       out_vals, out_ids, out_logz, upd)
-    if (total <= 256) EVOSPEC_MERGE(256);
-    else if (total <= 512) EVOSPEC_MERGE(512);
+                       a_pass_bytes / 8, a_pass_bytes / 8, b_chunk_bytes / 8, b_chunk_bytes / 8, k, parts_log2, \
+                       pend_cap, out_vals, out_ids, out_logz, upd)
+    if (nt == 256) EVOSPEC_MERGE(256);
+    else if (nt == 512) EVOSPEC_MERGE(512);
     else EVOSPEC_MERGE(1024);
 #undef EVOSPEC_MERGE
     return hipGetLastError();
