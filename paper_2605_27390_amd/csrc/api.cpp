@@ -149,8 +149,14 @@ int evospec_active_lmhead_partials(const void* h, int M, int d, const void* W_ac
     int num_cu = 0;
     rc = device_num_cu(&num_cu);
     if (rc) return rc;
-    const Plan p = make_plan(M, V_act, d, k, num_cu);
     char* ws = static_cast<char*>(workspace);
+    if (use_narrow(M, d)) {
+        const NarrowPlan np = make_narrow_plan(M, V_act, k, num_cu);
+        hipError_t e = launch_narrow_partials(np, h, M, d, W_act, ids, V_act, k, ws + np.keys_off, ws + np.stats_off,
+                                              static_cast<hipStream_t>(stream), layout == EVOSPEC_PACKED);
+        return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);
+    }
+    const Plan p = make_plan(M, V_act, d, k, num_cu);
     hipError_t e = launch_partials(p, h, M, d, W_act, ids, V_act, k, ws + p.keys_off, ws + p.stats_off,
                                    static_cast<hipStream_t>(stream), layout == EVOSPEC_PACKED);
     return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);
@@ -168,10 +174,15 @@ int evospec_active_lmhead_merge(int M, int V_act, int d, int k, float* out_vals,
     int num_cu = 0;
     int rc = device_num_cu(&num_cu);
     if (rc) return rc;
-    const Plan p = make_plan(M, V_act, d, k, num_cu);
     const char* ws = static_cast<const char*>(workspace);
-    MergeSet a{ws + p.keys_off, ws + p.stats_off, p.n_slabs, 0, kMTile};
-    MergeSet none{};
+    MergeSet a{}, none{};
+    if (use_narrow(M, d)) {
+        const NarrowPlan np = make_narrow_plan(M, V_act, k, num_cu);
+        a = MergeSet{ws + np.keys_off, ws + np.stats_off, np.n_slabs, 0, M, 0, true};
+    } else {
+        const Plan p = make_plan(M, V_act, d, k, num_cu);
+        a = MergeSet{ws + p.keys_off, ws + p.stats_off, p.n_slabs, 0, kMTile};
+    }
     hipError_t e = launch_merge(a, none, k, out_vals, out_ids, out_logz, 0, M, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);
 }
@@ -210,12 +221,20 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
     }
     for (int m0 = 0; m0 < M; m0 += kMTile) {            // passes of 64 draft rows share the scratch
         const int rows = (M - m0) < kMTile ? (M - m0) : kMTile;
-        const Plan p = make_plan(rows, V_act, d, k, num_cu);
-        hipError_t e = launch_partials(p, hp + (size_t)m0 * d, rows, d, W_act, ids, V_act, k,
-                                       ws + p.keys_off, ws + p.stats_off, st, packed);
+        MergeSet a{}, none{};
+        hipError_t e;
+        if (use_narrow(rows, d)) {
+            const NarrowPlan np = make_narrow_plan(rows, V_act, k, num_cu);
+            e = launch_narrow_partials(np, hp + (size_t)m0 * d, rows, d, W_act, ids, V_act, k, ws + np.keys_off,
+                                       ws + np.stats_off, st, packed);
+            a = MergeSet{ws + np.keys_off, ws + np.stats_off, np.n_slabs, 0, rows, 0, true};
+        } else {
+            const Plan p = make_plan(rows, V_act, d, k, num_cu);
+            e = launch_partials(p, hp + (size_t)m0 * d, rows, d, W_act, ids, V_act, k, ws + p.keys_off, ws + p.stats_off,
+                                st, packed);
+            a = MergeSet{ws + p.keys_off, ws + p.stats_off, p.n_slabs, 0, kMTile};
+        }
         if (e != hipSuccess) return hip_fail(e);
-        MergeSet a{ws + p.keys_off, ws + p.stats_off, p.n_slabs, 0, kMTile};
-        MergeSet none{};
         e = launch_merge(a, none, k, out_vals, out_ids, out_logz, m0, rows, st, m0 + kMTile >= M ? update : nullptr);
         if (e != hipSuccess) return hip_fail(e);
     }

@@ -140,18 +140,6 @@ __device__ __forceinline__ T wg_sort_desc(T x, T* buf) {
     return x;
 }
 
-// The q-th largest (counting repeats, 1 <= q <= 64) of the 64 values of a wavefront: the largest t
-// that at least q values reach, found bit by bit.  One vector compare per bit, the rest is scalar:
-// with 8 wavefronts per SIMD this costs a fifth of sorting the 64 values.
-__device__ __forceinline__ uint32_t wave_kth_largest(uint32_t v, int q) {
-    uint32_t t = 0;
-#pragma unroll
-    for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t c = t | (1u << bit);
-        if (__popcll(__ballot(v >= c)) >= q) t = c;              // (uniform)
-    }
-    return t;
-}
 // A lower bound of the K-th largest (counting repeats) of the 1024 values v, one per thread, without
 // a selection over the workgroup: with q = ceil(K / 16), each of the 16 wavefronts holds q values at or
 // above its own q-th largest, so K values reach the smallest of the 16.  (Looser than the exact K-th

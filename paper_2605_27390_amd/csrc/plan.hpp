@@ -68,6 +68,17 @@ inline size_t matrix_elems(size_t rows, int d, bool packed) {
     return packed ? packed_rows(rows) * (size_t)packed_d(d) : rows * (size_t)d;
 }
 
+// Whether a launch loads its weights past the caches.  A set well below the 256 MB memory-side cache is
+// still there when a decode loop comes back to it, and non-temporal loads find it more slowly (7,086 x
+// 1,536, 22 MB, 53 rows: 18.0 us with ordinary loads, 18.3 without); a larger one only drags itself through
+// (151,936 x 4,096 at one row 207 against 185 us, 36,864 x 4,096 at 60 rows 60.0 against 54.3, and against
+// 54.8 -> 53.0 when the same 302 MB are read again at once).  Row-major rows that do not start on
+// 128-byte lines share lines between loads, which want the cache (20,011 x 3,000 at 8 rows: 28.3 us
+// through it, 31.8 past it).
+inline bool streams_once(size_t rows, int d, bool packed) {
+    return (packed || d % 64 == 0) && matrix_elems(rows, d, packed) * 2 >= ((size_t)128 << 20);
+}
+
 // One dynamic-buffer update: n rows W_act[slots[i]] <- W_lm[src_ids[i]], act_ids[slots[i]] <- src_ids[i]
 // (slots == nullptr: slot i).  Device pointers; row_vec = d / 8.  packed: layout of W_act (W_lm is
 // always row-major).
@@ -165,6 +176,41 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
     best.total_bytes = best.stats_off + align_up((size_t)best.n_slabs * kMTile * 8, 256);
     return best;
 }
+
+// Few draft rows (narrow.hip): workgroups of kNarrowWaves wavefronts, each a run of 16-row tiles, one
+// partial per workgroup and draft row; keys [M][n_slabs][k], stats [M][n_slabs].  One workgroup per
+// compute unit, the tiles dealt out evenly (the first rem_tiles workgroups take one more); more rounds
+// where the logits of a workgroup would not fit its LDS.
+constexpr int kNarrowRows = 16;
+constexpr int kNarrowWaves = 8;
+constexpr int kNarrowGroup = 8;            // tiles whose partial sums share the LDS
+constexpr int kNarrowMaxTiles = 40;        // tiles of a workgroup (logits in LDS: 16 rows x 640 x 4 bytes)
+constexpr int kNarrowMaxD = 4096;          // h of a wavefront in registers: 16 k-steps
+inline bool use_narrow(int M, int d) { return M <= kNarrowRows && d <= kNarrowMaxD; }
+
+struct NarrowPlan {
+    int n_slabs = 0, base_tiles = 0, rem_tiles = 0;
+    int z_stride = 0;                      // logits per draft row in LDS
+    size_t lds_bytes = 0;
+    size_t keys_off = 0, stats_off = 0, total_bytes = 0;
+};
+inline NarrowPlan make_narrow_plan(int M, int V_act, int k, int num_cu) {
+    NarrowPlan p;
+    const int tiles = (V_act + 15) / 16;
+    const int rounds = (tiles + num_cu * kNarrowMaxTiles - 1) / (num_cu * kNarrowMaxTiles);
+    p.n_slabs = tiles < num_cu * rounds ? tiles : num_cu * rounds;
+    p.base_tiles = tiles / p.n_slabs;
+    p.rem_tiles = tiles - p.base_tiles * p.n_slabs;
+    const int most = p.base_tiles + (p.rem_tiles > 0 ? 1 : 0);
+    p.z_stride = most * 16 + 4;
+    // partial sums of a group (later the candidate lists), logits, ids
+    const size_t red = (size_t)kNarrowGroup * kNarrowWaves * 1024, lists = (size_t)kNarrowWaves * p.z_stride * 8;
+    p.lds_bytes = align_up(red > lists ? red : lists, 16) + (size_t)M * p.z_stride * 4 + (size_t)most * 16 * 4;
+    p.stats_off = align_up((size_t)p.n_slabs * M * k * 8, 256);
+    p.total_bytes = p.stats_off + align_up((size_t)p.n_slabs * M * 8, 256);
+    return p;
+}
+static_assert((size_t)kNarrowWaves * (kNarrowMaxTiles * 16 + 4) * 8 <= (size_t)kNarrowGroup * kNarrowWaves * 1024, "lists fit the group's partial sums");
 
 // Large-M path: 256 x 256 tiles, one partial per 128 active rows and draft row, all M rows in
 // one launch.  Taken from kGemmMinRows draft rows on, where the contraction, not the stream of
