@@ -190,7 +190,7 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 // ---------------------------------------------------------------------------------------
 // Pass 1 of the restricted head: one workgroup streams one slab of RT = 16*NW*RGW rows of
 // W_act (each wave its own 16*RGW rows, loaded from HBM straight into MFMA operand layout
-// with 128-bit loads), contracts it with up to 16*MB draft rows of h (K-chunks of h staged
+// with 128-bit loads that do not stay in the caches: 60.0 -> 54.3 us at 36,864 x 4,096 packed and 60 rows), contracts it with up to 16*MB draft rows of h (K-chunks of h staged
 // in LDS, double buffered, shared by all waves), and reduces the slab's logits, which stay in
 // the accumulators, to
 //   part_stats[slab][m] = (max_i z, sum_i exp(z - max))         over the slab's rows
@@ -252,6 +252,8 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     if (tid < RT && row0 + tid < V_act) id_reg = ids ? ids[row0 + tid] : row0 + tid;
 
     const uint16_t* wp[RGW];
+    const uint16_t* wp2[RGW];                              // (row-major only)
+    const int e1 = (g + ((n16 >> 3) << 2)) * 8, e2 = (g + (((n16 >> 3) ^ 1) << 2)) * 8;   // elements within the line
 #pragma unroll
     for (int rg = 0; rg < RGW; ++rg) {
         if constexpr (PACKED) {
@@ -259,9 +261,10 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
             const int tile = min((row0 >> 4) + w * RGW + rg, (V_act - 1) >> 4);   // tail slab: a valid tile, masked later
             wp[rg] = W + (size_t)tile * kPackRows * dp + lane * 8;
         } else {
-            int r = row0 + (w * RGW + rg) * 16 + n16;
-            r = min(r, V_act - 1);                         // tail slab: duplicate a valid row, masked later
-            wp[rg] = W + (size_t)r * d + g * 8;
+            // whole lines: rows n16 % 8 (first load of a pair of k-steps) and 8 + n16 % 8 (second), see pick_bank
+            const int r = row0 + (w * RGW + rg) * 16 + (n16 & 7);
+            wp[rg] = W + (size_t)min(r, V_act - 1) * d;    // tail slab: duplicate a valid row, masked later
+            wp2[rg] = W + (size_t)min(r + 8, V_act - 1) * d;
         }
     }
 
@@ -289,16 +292,31 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         hsrc[p] = (gvec_ptr)(h + (size_t)min(m, rows - 1) * d + c8 * 8);
         hdst[p] = m * kHStride + c8 * 8;
     }
-    gvec_ptr wsrc[RGW];
+    gvec_ptr wsrc[RGW];                                     // (packed only)
 #pragma unroll
     for (int rg = 0; rg < RGW; ++rg) wsrc[rg] = (gvec_ptr)(wp[rg]);
 
-    // Loads past the end of a row (only when d is not a multiple of KC) are redirected to the
-    // row's last 16 bytes and replaced by zeros, so that no load is conditional.
-    auto load_h = [&](int c) {
+    // The chunk of the hidden dimension that step c works on.  Workgroups start at different chunks and wrap
+    // around: rows are usually a power of two apart, so that at the same chunk all workgroups would read
+    // the same few memory channels.  Measured at 60 rows, together with whole-line loads of row-major rows:
+    // 36,864 x 4,096 row-major 65.1 -> 58.9 us, 151,936 x 4,096 254 -> 236, 32,256 x 2,048 34.9 -> 31.6; packed
+    // 8,448 x 4,096 27.8 -> 26.4, 36,864 the same.  (Neighbouring workgroups a chunk apart instead of eight:
+    // 60.2, 238, 32.0 us.  d not a multiple of KC: rows are not a power of two apart, and the partial chunk
+    // stays last.)
+    const int rot = FULLK ? (int)(blockIdx.x >> 3) % nchunks : 0;
+    auto chunk_of = [&](int c) {
+        if constexpr (!FULLK) return c;
+        const int x = c + rot;
+        return x >= nchunks ? x - nchunks : x;
+    };
+    // Loads past the end of a row (only in the last chunk when d is not a multiple of KC: `whole` says that
+    // this one is not it) are redirected to the row's last 16 bytes and replaced by zeros, so that no load is
+    // conditional.
+    auto load_h = [&](int step, auto whole) {
+        const int c = chunk_of(step);
 #pragma unroll
         for (int p = 0; p < HP; ++p) {
-            if constexpr (FULLK) {
+            if constexpr (decltype(whole)::value) {
                 hreg[p] = hsrc[p][c * (KC / 8)];
             } else {
                 const int kk = c * KC + hcol[p];
@@ -314,18 +332,24 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
             *reinterpret_cast<u32x4*>(Hs + (size_t)buf * MR * kHStride + hdst[p]) = hreg[p];
     };
     // k-step s (0..7) of chunk c goes to ring slot (c % RC) * KSTEPS + s
-    auto load_w_step = [&](int slot, int c, int s) {
-        const int koff = c * KC + s * 32;
+    auto load_w_step = [&](int slot, int step, int s, auto whole) {
+        const int koff = chunk_of(step) * KC + s * 32;
 #pragma unroll
         for (int rg = 0; rg < RGW; ++rg) {
             if constexpr (PACKED) {
-                wr[rg][slot] = wsrc[rg][(koff / 32) * 64];       // rows are padded to whole chunks
-            } else if constexpr (FULLK) {
-                wr[rg][slot] = wsrc[rg][koff / 8];
+                wr[rg][slot] = load_once(wsrc[rg] + (koff / 32) * 64);       // rows are padded to whole chunks
             } else {
-                const bool in = koff + g * 8 < d;
-                const u32x4 v = *(wsrc[rg] + ((in ? koff + g * 8 : d - 8) - g * 8) / 8);
-                wr[rg][slot] = in ? v : zero4;
+                // k-steps s, s + 1 (s even) together: line koff / 64 of the row pair
+                const uint16_t* row = (s & 1) ? wp2[rg] : wp[rg];
+                const int e = (koff & ~63) + ((s & 1) ? e2 : e1);
+                if constexpr (FULLK) {
+                    wr[rg][slot] = load_once((gvec_ptr)(row + e));
+                } else if constexpr (decltype(whole)::value) {
+                    wr[rg][slot] = *(gvec_ptr)(row + e);     // rows may start within a line: two loads share it
+                } else {
+                    const u32x4 v = *(gvec_ptr)(row + (e < d ? e : d - 8));
+                    wr[rg][slot] = e < d ? v : zero4;
+                }
             }
         }
     };
@@ -337,7 +361,14 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     auto mfma_step = [&](int slot, const bf16x8 (&b)[MB]) {
 #pragma unroll
         for (int rg = 0; rg < RGW; ++rg) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, wr[rg][slot]);
+            u32x4 av = wr[rg][slot];
+            if constexpr (!PACKED) {
+                const int even = slot & ~1;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    av[i] = (slot & 1) ? pick_bank_ror8(wr[rg][even][i], wr[rg][even + 1][i]) : pick_bank(wr[rg][even][i], wr[rg][even + 1][i]);
+            }
+            const bf16x8 a = __builtin_bit_cast(bf16x8, av);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
                 acc[rg][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[mb], acc[rg][mb], 0, 0, 0);
@@ -356,25 +387,26 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         const bool pw = STEADY || (c + RC < nchunks);
         const bool ph = STEADY || (c + 1 < nchunks);
         const int buf = c & 1;
+        constexpr std::bool_constant<FULLK || STEADY> whole{};
         bf16x8 b0[MB], b1[MB];
-        if (ph) load_h(c + 1);
+        if (ph) load_h(c + 1, whole);
         load_b(b0, buf, 0);
 #pragma unroll
         for (int s = 0; s < KSTEPS; s += 2) {
             load_b(b1, buf, s + 1);
             __builtin_amdgcn_sched_barrier(0);
             mfma_step(SLOT * KSTEPS + s, b0);
-            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s, c + RC, s);
+            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s, c + RC, s, whole);
             if (s + 2 < KSTEPS) load_b(b0, buf, s + 2);
             __builtin_amdgcn_sched_barrier(0);
             mfma_step(SLOT * KSTEPS + s + 1, b1);
-            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s + 1, c + RC, s + 1);
+            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s + 1, c + RC, s + 1, whole);
         }
         if (!PACKED && pw) {
             // row-major rows: the chunk's 8 requests go out together, so that the 512 bytes they
             // take from each row reach the memory side close in time (measured: 3.5 us of 73)
 #pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) load_w_step(SLOT * KSTEPS + s, c + RC, s);
+            for (int s = 0; s < KSTEPS; ++s) load_w_step(SLOT * KSTEPS + s, c + RC, s, whole);
         }
         if (ph) store_h(buf ^ 1);
         lds_barrier();
@@ -391,12 +423,13 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     };
     static_assert(RC >= 1 && RC <= 4, "ring depth");
 
-    load_h(0);
+    constexpr std::bool_constant<FULLK> first{};
+    load_h(0, first);
 #pragma unroll
     for (int i = 0; i < RC; ++i) {
         if (i < nchunks) {
 #pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) load_w_step(i * KSTEPS + s, i, s);
+            for (int s = 0; s < KSTEPS; ++s) load_w_step(i * KSTEPS + s, i, s, first);
         }
     }
     for (int i = tid; i < MR * NGS; i += NT) gm[i] = -INFINITY;      // padding of the group-maximum rows
@@ -404,7 +437,8 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     store_h(0);
     lds_barrier();
     int c = 0;
-    for (; c + 2 * RC <= nchunks; c += RC) chunk_group(c, std::true_type{});     // every prefetch target exists
+    const int nwhole = d / KC;
+    for (; c + 2 * RC <= nwhole; c += RC) chunk_group(c, std::true_type{});      // every prefetch target exists, and whole
     for (; c < nchunks; c += RC) chunk_group(c, std::false_type{});
     // every wave is past its last read of Hs (the loop ends on a barrier): region U is free
 
