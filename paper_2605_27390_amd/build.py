@@ -9,8 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libevospec.so")
-SOURCES = ["kernels.hip", "gemm.hip", "narrow.hip", "klgate.hip", "noalloc.hip", "api.cpp", "arc.cpp", "path_a.cpp"]
-HEADERS = ["plan.hpp", "launch.hpp", "common.hpp", os.path.join(ROOT, "include", "evospec.h"),
+SOURCES = ["kernels.hip", "gemm.hip", "tile.hip", "narrow.hip", "klgate.hip", "noalloc.hip", "api.cpp", "arc.cpp", "path_a.cpp"]
+HEADERS = ["plan.hpp", "launch.hpp", "common.hpp", "slab_epilogue.hpp", os.path.join(ROOT, "include", "evospec.h"),
            os.path.join(ROOT, "include", "evospec_arc.h")]
 
 HIPCC_FLAGS = [

@@ -226,6 +226,20 @@ inline bool use_gemm(int M, int d) { return M >= kGemmMinRows && d % (2 * kGemmK
 // reaches a lower bound of the slab's k-th best, unranked; rarely more than k + a few.
 inline int gemm_list_len(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 
+// Tiles of 128 x 128 (tile.hip) instead of 256 x 256 (gemm.hip); same partials.  A round of one workgroup
+// per compute unit costs a large tile kTileCost times what it costs a small one (measured at d = 4,096:
+// 125 us against 38; 512 x 32,768 in one round of large tiles 138 us, in four of small ones 161; 960 x
+// 32,768 251 and 282; 200 x 16,384 130 and 52; 300 x 20,000 x 2,048 223 and 64).
+constexpr int kTileRows = 128;
+constexpr double kTileCost = 3.3;
+inline bool use_small_tiles(int M, int V_act, int num_cu) {
+    auto rounds = [&](int v, int m) {
+        const long n = (long)((V_act + v - 1) / v) * ((M + m - 1) / m);
+        return (n + num_cu - 1) / num_cu;
+    };
+    return (double)rounds(kGemmSlab, kTileRows) < kTileCost * (double)rounds(kGemmTile, kGemmTile);
+}
+
 struct GemmPlan {
     int n_slabs = 0;
     int list_len = 0;
