@@ -190,16 +190,16 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Pass 1 of the restricted head: one workgroup streams one slab of RT = 16*NW*RGW rows of
-// W_act (each wave its own 16*RGW rows, loaded from HBM straight into MFMA operand layout
+// Pass 1 of the restricted head: one workgroup streams one slab of RT = 16*TW rows of
+// W_act (KS wavefronts to a tile of 16 rows, its elements loaded from HBM straight into MFMA operand layout
 // with 128-bit loads that do not stay in the caches: 60.0 -> 54.3 us at 36,864 x 4,096 packed and 60 rows), contracts it with up to 16*MB draft rows of h (K-chunks of h staged
 // in LDS, double buffered, shared by all waves), and reduces the slab's logits, which stay in
 // the accumulators, to
 //   part_stats[slab][m] = (max_i z, sum_i exp(z - max))         over the slab's rows
 //   part_keys[slab][m][0..k) = the slab's k best keys, descending (0 = none)
 // Logits never leave the CU.
-template <int NW, int RGW, int RC, int MB, bool FULLK, bool PACKED>
-__global__ void __launch_bounds__(NW * 64)
+template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE>
+__global__ void __launch_bounds__(TW * KS * 64)
 lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int seq_rows,
                        size_t chunk_keys, size_t chunk_stats, int d,
                        const uint16_t* __restrict__ W_all, const int32_t* __restrict__ ids_all,
@@ -218,11 +218,15 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     const int32_t* __restrict__ ids = ids_all ? ids_all + seq_row0 : nullptr;
     u64* __restrict__ part_keys = keys_all + (size_t)ci * chunk_keys;
     float2* __restrict__ part_stats = stats_all + (size_t)ci * chunk_stats;
+    constexpr int NW = TW * KS;                    // wavefronts: KS of them share a tile, each a part of every chunk's k-steps
     constexpr int NT = NW * 64;
-    constexpr int RT = 16 * NW * RGW;
+    constexpr int RT = 16 * TW;
+    static_assert(MB % KS == 0, "after the stream each wavefront of a tile keeps MB / KS blocks of draft rows");
+    constexpr int MBW = MB / KS;
     constexpr int MR = 16 * MB;
     constexpr int KC = kKC;
-    constexpr int KSTEPS = KC / 32;
+    constexpr int KSTEPS = KC / 32 / KS;           // k-steps of a chunk that a wavefront takes
+    static_assert(KSTEPS % 2 == 0, "row-major k-steps are loaded in pairs");
     constexpr int HPIECES = MR * (KC / 8);
     constexpr int HP = (HPIECES + NT - 1) / NT;
 
@@ -234,15 +238,17 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     constexpr size_t hs_bytes = 2ull * MR * kHStride * 2;
     constexpr size_t list_bytes = (size_t)MR * list_stride(RT) * 8;
     constexpr size_t u_bytes = align_up(hs_bytes > list_bytes ? hs_bytes : list_bytes, 16);
-    constexpr int NGS = 4 * NW;                                               // row stride of gm
+    constexpr int NGS = 8 * TW;                                               // row stride of gm
     float* gm = reinterpret_cast<float*>(smem + u_bytes);                     // [MR][NGS] group maxima
-    float* wsum = gm + (size_t)MR * NGS;                                      // [NW][MR] per-wave sum-exp
-    int32_t* Ids = reinterpret_cast<int32_t*>(wsum + (size_t)NW * MR);        // [RT]
+    float* wsum = gm + (size_t)MR * NGS;                                      // [TW][MR] sum-exp of each tile
+    int32_t* Ids = reinterpret_cast<int32_t*>(wsum + (size_t)TW * MR);        // [RT]
     float* tau = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(Ids) + align_up((size_t)RT * 4, 16));  // [MR]
     float* vmax = tau + MR;                                                   // [MR]
     int* cnt = reinterpret_cast<int*>(vmax + MR);                             // [MR]
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = (tid >> 6) / KS, kq = KS > 1 ? (tid >> 6) % KS : 0;          // this wavefront's tile, and its part of the k-steps
+    const int s0 = kq * KSTEPS;                                               // first of its k-steps in a chunk
     const int n16 = lane & 15, g = lane >> 4;
     const int row0 = blockIdx.x * RT;
     const int n_valid = min(RT, V_act - row0);
@@ -253,33 +259,33 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     int id_reg = 0x7fffffff;
     if (tid < RT && row0 + tid < V_act) id_reg = ids ? ids[row0 + tid] : row0 + tid;
 
-    const uint16_t* wp[RGW];
-    const uint16_t* wp2[RGW];                              // (row-major only)
+    const uint16_t* wp;
+    const uint16_t* wp2;                                   // (row-major only)
     const int e1 = (g + ((n16 >> 3) << 2)) * 8, e2 = (g + (((n16 >> 3) ^ 1) << 2)) * 8;   // elements within the line
-#pragma unroll
-    for (int rg = 0; rg < RGW; ++rg) {
-        if constexpr (PACKED) {
-            // the wavefront's tile: 1 KB operand blocks in k-step order, lane l at byte 16 l
-            const int tile = min((row0 >> 4) + w * RGW + rg, (V_act - 1) >> 4);   // tail slab: a valid tile, masked later
-            wp[rg] = W + (size_t)tile * kPackRows * dp + lane * 8;
-        } else {
-            // whole lines: rows n16 % 8 (first load of a pair of k-steps) and 8 + n16 % 8 (second), see pick_bank
-            const int r = row0 + (w * RGW + rg) * 16 + (n16 & 7);
-            wp[rg] = W + (size_t)min(r, V_act - 1) * d;    // tail slab: duplicate a valid row, masked later
-            wp2[rg] = W + (size_t)min(r + 8, V_act - 1) * d;
-        }
+    if constexpr (PACKED) {
+        // the wavefront's tile: 1 KB operand blocks in k-step order, lane l at byte 16 l
+        const int tile = min((row0 >> 4) + w, (V_act - 1) >> 4);   // tail slab: a valid tile, masked later
+        wp = W + (size_t)tile * kPackRows * dp + lane * 8;
+        wp2 = wp;
+    } else {
+        // whole lines: rows n16 % 8 (first load of a pair of k-steps) and 8 + n16 % 8 (second), see pick_bank
+        const int r = row0 + w * 16 + (n16 & 7);
+        wp = W + (size_t)min(r, V_act - 1) * d;            // tail slab: duplicate a valid row, masked later
+        wp2 = W + (size_t)min(r + 8, V_act - 1) * d;
     }
 
-    f32x4 acc[RGW][MB];
+    f32x4 acc[MB];
 #pragma unroll
-    for (int rg = 0; rg < RGW; ++rg)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[rg][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nchunks = (d + KC - 1) / KC;
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    u32x4 hreg[HP];
-    u32x4 wr[RGW][RC * KSTEPS];           // ring of W operands: k-steps of RC consecutive chunks
+    // chunks that h is requested ahead of its use (13 to 16 wavefronts have 128 registers each, which three pieces
+    // per thread twice over exceed)
+    constexpr int HA = KS > 1 && (NT <= 768 || HP <= 2) ? 2 : 1;
+    static_assert(RC % HA == 0, "the register set of a chunk's h is known at compile time");
+    u32x4 hreg[HA][HP];
+    u32x4 wr[RC * KSTEPS];                // ring of W operands: this wavefront's k-steps of RC consecutive chunks
 
     // this thread's pieces (16 B each) of an h chunk: global source, LDS destination
     gvec_ptr hsrc[HP];
@@ -294,9 +300,6 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         hsrc[p] = (gvec_ptr)(h + (size_t)min(m, rows - 1) * d + c8 * 8);
         hdst[p] = m * kHStride + c8 * 8;
     }
-    gvec_ptr wsrc[RGW];                                     // (packed only)
-#pragma unroll
-    for (int rg = 0; rg < RGW; ++rg) wsrc[rg] = (gvec_ptr)(wp[rg]);
 
     // The chunk of the hidden dimension that step c works on.  Workgroups start at different chunks and wrap
     // around: rows are usually a power of two apart, so that at the same chunk all workgroups would read
@@ -314,74 +317,66 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     // Loads past the end of a row (only in the last chunk when d is not a multiple of KC: `whole` says that
     // this one is not it) are redirected to the row's last 16 bytes and replaced by zeros, so that no load is
     // conditional.
-    auto load_h = [&](int step, auto whole) {
+    auto load_h = [&](u32x4 (&hr)[HP], int step, auto whole) {
         const int c = chunk_of(step);
 #pragma unroll
         for (int p = 0; p < HP; ++p) {
             if constexpr (decltype(whole)::value) {
-                hreg[p] = hsrc[p][c * (KC / 8)];
+                hr[p] = hsrc[p][c * (KC / 8)];
             } else {
                 const int kk = c * KC + hcol[p];
                 const bool in = kk < d;
                 const u32x4 v = *(hsrc[p] + ((in ? kk : d - 8) - hcol[p]) / 8);
-                hreg[p] = in ? v : zero4;
+                hr[p] = in ? v : zero4;
             }
         }
     };
-    auto store_h = [&](int buf) {
+    auto store_h = [&](const u32x4 (&hr)[HP], int buf) {
 #pragma unroll
         for (int p = 0; p < HP; ++p)
-            *reinterpret_cast<u32x4*>(Hs + (size_t)buf * MR * kHStride + hdst[p]) = hreg[p];
+            *reinterpret_cast<u32x4*>(Hs + (size_t)buf * MR * kHStride + hdst[p]) = hr[p];
     };
-    // k-step s (0..7) of chunk c goes to ring slot (c % RC) * KSTEPS + s
+    // k-step s (0..KSTEPS-1 of this wavefront) of chunk c goes to ring slot (c % RC) * KSTEPS + s
+    auto load_w = [&](gvec_ptr p) { return ONCE ? load_once(p) : *p; };
     auto load_w_step = [&](int slot, int step, int s, auto whole) {
-        const int koff = chunk_of(step) * KC + s * 32;
-#pragma unroll
-        for (int rg = 0; rg < RGW; ++rg) {
-            if constexpr (PACKED) {
-                wr[rg][slot] = load_once(wsrc[rg] + (koff / 32) * 64);       // rows are padded to whole chunks
+        const int koff = chunk_of(step) * KC + (s0 + s) * 32;
+        if constexpr (PACKED) {
+            wr[slot] = load_w((gvec_ptr)wp + (koff / 32) * 64);          // rows are padded to whole chunks
+        } else {
+            // k-steps s, s + 1 (s even) together: line koff / 64 of the row pair
+            const uint16_t* row = (s & 1) ? wp2 : wp;
+            const int e = (koff & ~63) + ((s & 1) ? e2 : e1);
+            if constexpr (decltype(whole)::value) {
+                wr[slot] = load_w((gvec_ptr)(row + e));
             } else {
-                // k-steps s, s + 1 (s even) together: line koff / 64 of the row pair
-                const uint16_t* row = (s & 1) ? wp2[rg] : wp[rg];
-                const int e = (koff & ~63) + ((s & 1) ? e2 : e1);
-                if constexpr (FULLK) {
-                    wr[rg][slot] = load_once((gvec_ptr)(row + e));
-                } else if constexpr (decltype(whole)::value) {
-                    wr[rg][slot] = *(gvec_ptr)(row + e);     // rows may start within a line: two loads share it
-                } else {
-                    const u32x4 v = *(gvec_ptr)(row + (e < d ? e : d - 8));
-                    wr[rg][slot] = e < d ? v : zero4;
-                }
+                const u32x4 v = *(gvec_ptr)(row + (e < d ? e : d - 8));
+                wr[slot] = e < d ? v : zero4;
             }
         }
     };
     auto load_b = [&](bf16x8 (&b)[MB], int buf, int s) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
-            b[mb] = *reinterpret_cast<const bf16x8*>(Hs + ((size_t)buf * MR + mb * 16 + n16) * kHStride + s * 32 + g * 8);
+            b[mb] = *reinterpret_cast<const bf16x8*>(Hs + ((size_t)buf * MR + mb * 16 + n16) * kHStride + (s0 + s) * 32 + g * 8);
     };
     auto mfma_step = [&](int slot, const bf16x8 (&b)[MB]) {
+        u32x4 av = wr[slot];
+        if constexpr (!PACKED) {
+            const int even = slot & ~1;
 #pragma unroll
-        for (int rg = 0; rg < RGW; ++rg) {
-            u32x4 av = wr[rg][slot];
-            if constexpr (!PACKED) {
-                const int even = slot & ~1;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    av[i] = (slot & 1) ? pick_bank_ror8(wr[rg][even][i], wr[rg][even + 1][i]) : pick_bank(wr[rg][even][i], wr[rg][even + 1][i]);
-            }
-            const bf16x8 a = __builtin_bit_cast(bf16x8, av);
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-                acc[rg][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[mb], acc[rg][mb], 0, 0, 0);
+            for (int i = 0; i < 4; ++i)
+                av[i] = (slot & 1) ? pick_bank_ror8(wr[even][i], wr[even + 1][i]) : pick_bank(wr[even][i], wr[even + 1][i]);
         }
+        const bf16x8 a = __builtin_bit_cast(bf16x8, av);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[mb], acc[mb], 0, 0, 0);
     };
-    // One chunk (8 k-steps).  Ring part SLOT (= c % RC) holds this chunk's W operands, loaded RC
+    // One chunk (KSTEPS k-steps of this wavefront).  Ring part SLOT (= c % RC) holds this chunk's W operands, loaded RC
     // chunks ago; each slot is refilled with the same k-step of chunk c+RC right after the MFMAs
     // that consumed it were issued (packed matrix) or all slots at the end of the chunk (row-major
-    // matrix), so up to RC*KSTEPS*RGW 16-byte loads per lane stay in flight.
-    // The h chunk c+1 is fetched into registers meanwhile and published to the other LDS buffer
-    // at the end.  In the steady state (chunks c+1 and c+RC exist) there is no branch in here;
+    // matrix), so up to RC*KSTEPS 16-byte loads per lane stay in flight.
+    // The h chunk c+HA is requested meanwhile, and chunk c+1 goes from registers to the other LDS buffer
+    // at the end.  (One chunk ahead is enough while a chunk takes longer than a trip to L2, about 1 us.)  In the steady state (chunks c+1 and c+RC exist) there is no branch in here;
     // the last chunks test for them at run time.
     auto chunk = [&](auto slot_c, int c, auto steady) {
         constexpr int SLOT = decltype(slot_c)::value;
@@ -391,7 +386,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         const int buf = c & 1;
         constexpr std::bool_constant<FULLK || STEADY> whole{};
         bf16x8 b0[MB], b1[MB];
-        if (ph) load_h(c + 1, whole);
+        if (STEADY || c + HA < nchunks) load_h(hreg[(SLOT + HA) % HA], c + HA, whole);
         load_b(b0, buf, 0);
 #pragma unroll
         for (int s = 0; s < KSTEPS; s += 2) {
@@ -410,7 +405,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
 #pragma unroll
             for (int s = 0; s < KSTEPS; ++s) load_w_step(SLOT * KSTEPS + s, c + RC, s, whole);
         }
-        if (ph) store_h(buf ^ 1);
+        if (ph) store_h(hreg[(SLOT + 1) % HA], buf ^ 1);
         lds_barrier();
     };
     // RC consecutive chunks starting at `base` (a multiple of RC), ring parts 0..RC-1
@@ -426,7 +421,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     static_assert(RC >= 1 && RC <= 4, "ring depth");
 
     constexpr std::bool_constant<FULLK> first{};
-    load_h(0, first);
+    load_h(hreg[0], 0, first);
 #pragma unroll
     for (int i = 0; i < RC; ++i) {
         if (i < nchunks) {
@@ -436,7 +431,10 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     }
     for (int i = tid; i < MR * NGS; i += NT) gm[i] = -INFINITY;      // padding of the group-maximum rows
     if (tid < RT) Ids[tid] = id_reg;
-    store_h(0);
+    store_h(hreg[0], 0);
+    if constexpr (HA > 1) {
+        if (nchunks > 1) load_h(hreg[1], 1, first);
+    }
     lds_barrier();
     int c = 0;
     const int nwhole = d / KC;
@@ -444,34 +442,54 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     for (; c < nchunks; c += RC) chunk_group(c, std::false_type{});
     // every wave is past its last read of Hs (the loop ends on a barrier): region U is free
 
-    // ---- slab epilogue.  The slab's logits stay in the accumulators: lane (n16, g) holds, for each
-    // block mb of 16 draft rows, 4*RGW logits of draft row mb*16+n16 (slab rows 4g..4g+3 of each of
-    // the wave's 16-row groups).
+    // ---- the wavefronts of a tile add up: wavefront kq keeps the blocks kq * MBW .. + MBW of draft rows, the
+    // parts are added in the order of kq
+    if constexpr (KS > 1) {
+        f32x4* red = reinterpret_cast<f32x4*>(smem);               // [TW][KS][MB][64] (fits region U)
+        static_assert((size_t)TW * KS * MB * 1024 <= u_bytes, "partial sums fit region U");
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) red[((size_t)(w * KS + kq) * MB + mb) * 64 + lane] = acc[mb];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MBW; ++i) {
+            f32x4 x = red[((size_t)(w * KS) * MB + kq * MBW + i) * 64 + lane];
+#pragma unroll
+            for (int q = 1; q < KS; ++q) x += red[((size_t)(w * KS + q) * MB + kq * MBW + i) * 64 + lane];
+            acc[i] = x;
+        }
+    }
+
+    // ---- slab epilogue.  The slab's logits stay in the accumulators: lane (n16, g) holds, for each of its
+    // blocks mb of 16 draft rows, 4 logits of draft row mb*16+n16 (rows 4g..4g+3 of the tile).
+    const int mb0 = kq * MBW;                                      // this wavefront's first block
     if (n_valid < RT) {                                  // tail slab: rows past V_act never win
 #pragma unroll
-        for (int rg = 0; rg < RGW; ++rg)
+        for (int j = 0; j < 4; ++j)
+            if (w * 16 + 4 * g + j >= n_valid) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if ((w * RGW + rg) * 16 + 4 * g + j >= n_valid) {
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) acc[rg][mb][j] = -INFINITY;
-                }
+                for (int i = 0; i < MBW; ++i) acc[i][j] = -INFINITY;
+            }
     }
-    // (1) group maxima (level GL: lane, lane pair or wave)
-    const int NG = NW << (2 - GL);
+    // (1) group maxima (level GL: lane, lane pair or wave; pairs of a lane's logits when there are too few
+    // lanes for k, or the bound would let nearly everything through: at k = 20 the ranking of 80 rows took 3.8 us)
+    const bool fine = GL == 0 && 4 * TW < k + k / 2;
+    const int NG = fine ? 8 * TW : TW << (2 - GL);
     {
         const int gidx = GL == 0 ? w * 4 + g : (GL == 1 ? w * 2 + (g >> 1) : w);
         const bool owner = GL == 0 ? true : (GL == 1 ? (g & 1) == 0 : g == 0);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            float lm = -INFINITY;
-#pragma unroll
-            for (int rg = 0; rg < RGW; ++rg)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) lm = fmaxf(lm, acc[rg][mb][j]);
+        for (int i = 0; i < MBW; ++i) {
+            const float l0 = fmaxf(acc[i][0], acc[i][1]), l1 = fmaxf(acc[i][2], acc[i][3]);
+            float* gr = gm + ((mb0 + i) * 16 + n16) * NGS;
+            if (fine) {                                            // (uniform)
+                gr[2 * gidx] = l0;
+                gr[2 * gidx + 1] = l1;
+                continue;
+            }
+            float lm = fmaxf(l0, l1);
             if (GL >= 1) lm = fmaxf(lm, __uint_as_float(xor_lane<16>(__float_as_uint(lm), lane)));
             if (GL >= 2) lm = fmaxf(lm, __uint_as_float(xor_lane<32>(__float_as_uint(lm), lane)));
-            if (owner) gm[(mb * 16 + n16) * NGS + gidx] = lm;
+            if (owner) gr[gidx] = lm;
         }
     }
     if (tid < MR) { cnt[tid] = 0; tau[tid] = -INFINITY; }
@@ -503,49 +521,41 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     //     One LDS atomic per lane and draft-row block reserves room for the lane's candidates, which
     //     are then stored without branches or dependent loads.
     {
-        int4 id4[RGW];
+        const int4 id4 = *reinterpret_cast<const int4*>(Ids + w * 16 + 4 * g);
+        const int idv[4] = {id4.x, id4.y, id4.z, id4.w};
+        uint32_t pick[MBW];
+        int base[MBW];
 #pragma unroll
-        for (int rg = 0; rg < RGW; ++rg) id4[rg] = *reinterpret_cast<const int4*>(Ids + (w * RGW + rg) * 16 + 4 * g);
-        uint32_t pick[MB];
-        int base[MB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int m = mb * 16 + n16;
-            pick[mb] = 0;
-            if (mb * 16 < rows) {                            // uniform: skip blocks of padding draft rows
+        for (int i = 0; i < MBW; ++i) {
+            const int m = (mb0 + i) * 16 + n16;
+            pick[i] = 0;
+            if ((mb0 + i) * 16 < rows) {                     // uniform: skip blocks of padding draft rows
                 const bool live = m < rows;
                 const float t = live ? tau[m] : INFINITY;
                 const float vm = live ? vmax[m] : 0.f;
                 float se = 0.f;
 #pragma unroll
-                for (int rg = 0; rg < RGW; ++rg)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float x = acc[rg][mb][j];
-                        const int rl = (w * RGW + rg) * 16 + 4 * g + j;
-                        se += __expf(x - vm);
-                        pick[mb] |= (x >= t && rl < n_valid) ? 1u << (rg * 4 + j) : 0u;
-                    }
+                for (int j = 0; j < 4; ++j) {
+                    const float x = acc[i][j];
+                    const int rl = w * 16 + 4 * g + j;
+                    se += __expf(x - vm);
+                    pick[i] |= (x >= t && rl < n_valid) ? 1u << j : 0u;
+                }
                 se += __uint_as_float(xor_lane<16>(__float_as_uint(se), lane));
                 se += __uint_as_float(xor_lane<32>(__float_as_uint(se), lane));
                 if (g == 0) wsum[w * MR + m] = se;
             }
         }
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-            base[mb] = pick[mb] ? atomicAdd(&cnt[mb * 16 + n16], __popc(pick[mb])) : 0;
+        for (int i = 0; i < MBW; ++i)
+            base[i] = pick[i] ? atomicAdd(&cnt[(mb0 + i) * 16 + n16], __popc(pick[i])) : 0;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            u64* dst = list + (size_t)(mb * 16 + n16) * LS + base[mb];
+        for (int i = 0; i < MBW; ++i) {
+            u64* dst = list + (size_t)((mb0 + i) * 16 + n16) * LS + base[i];
 #pragma unroll
-            for (int rg = 0; rg < RGW; ++rg) {
-                const int idv[4] = {id4[rg].x, id4[rg].y, id4[rg].z, id4[rg].w};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int e = rg * 4 + j;
-                    const u64 key = make_key(acc[rg][mb][j], idv[j]);
-                    if (pick[mb] >> e & 1u) dst[__popc(pick[mb] & ((1u << e) - 1u))] = key;
-                }
+            for (int j = 0; j < 4; ++j) {
+                const u64 key = make_key(acc[i][j], idv[j]);
+                if (pick[i] >> j & 1u) dst[__popc(pick[i] & ((1u << j) - 1u))] = key;
             }
         }
     }
@@ -576,7 +586,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
             for (int j = c; j < k; ++j) outk[j] = 0;               // slab holds fewer than k rows
             float sum = 0.f;
 #pragma unroll
-            for (int ww = 0; ww < NW; ++ww) sum += wsum[ww * MR + m];
+            for (int ww = 0; ww < TW; ++ww) sum += wsum[ww * MR + m];
             part_stats[(size_t)blockIdx.x * kMTile + m] = make_float2(vmax[m], sum);
         }
     }
@@ -867,13 +877,20 @@ lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_key
 namespace evospec {
 
 namespace {
+// Wavefronts per tile for every slab shape: X(tiles, with four blocks of draft rows, with two); one block: 1.
+// A workgroup with few tiles has too few wavefronts to hide the operand reads and the trips to L2 for h, so
+// several share a tile, up to 16 wavefronts in all (measured at 60 rows, all x 4,096 unless said: 8,448 rows
+// 26.8 -> 25.0 us, 18,432 33.9 -> 32.5, 24,000 41.9 -> 39.4, 12,000 x 1,024 16.3 -> 13.2; 37 rows, 20,011 x
+// 3,000 41.8 -> 34.8; 20 rows, 16,384 28.5 -> 26.4.  A ring of four chunks instead of two: 1 to 12 us slower).
+#define EVOSPEC_SPLITS(X) X(4, 4, 2) X(5, 2, 2) X(6, 2, 2) X(7, 2, 2) X(8, 2, 2) X(9, 1, 1) X(10, 1, 1) X(12, 1, 1)
+constexpr int kRing = 2;                       // chunks in the W-operand ring
 constexpr int kMaxDevices = 64;
 
-template <int NW, int RGW, int RC, int MB, bool FULLK, bool PACKED>
+template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE>
 hipError_t launch_partials_k(const Plan& p, const void* h, const ChunkBatch& cb, const BatchLayout& bl, int d,
                              const void* W, const int32_t* ids, int V_act, int k, void* keys, void* stats,
                              hipStream_t stream) {
-    auto kern = lmhead_partials_kernel<NW, RGW, RC, MB, FULLK, PACKED>;
+    auto kern = lmhead_partials_kernel<TW, KS, RC, MB, FULLK, PACKED, ONCE>;
     static std::atomic<bool> attr_set[kMaxDevices] = {};      // concurrent first calls may both set the (idempotent) attribute
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -884,28 +901,31 @@ hipError_t launch_partials_k(const Plan& p, const void* h, const ChunkBatch& cb,
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(p.n_slabs, cb.n), dim3(NW * 64), p.lds_bytes, stream,
+    hipLaunchKernelGGL(kern, dim3(p.n_slabs, cb.n), dim3(TW * KS * 64), p.lds_bytes, stream,
                        static_cast<const uint16_t*>(h), cb, bl.seq_rows, bl.chunk_bytes / 8, bl.chunk_bytes / 8, d,
                        static_cast<const uint16_t*>(W), ids,
                        V_act, k, p.gl, static_cast<u64*>(keys), static_cast<float2*>(stats));
     return hipGetLastError();
 }
 
-template <int NW, int RGW, int RC>
+template <int TW, int KS4, int KS2>
 hipError_t launch_partials_shape(const Plan& p, const void* h, const ChunkBatch& cb, const BatchLayout& bl, int d,
                                  const void* W, const int32_t* ids, int V_act, int k, void* keys, void* stats,
                                  hipStream_t stream) {
     const bool full = d % kKC == 0;
+    const bool once = streams_once((size_t)V_act * (bl.seq_rows ? cb.n : 1), d, bl.packed);
 #define EVOSPEC_ARGS p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream
-#define EVOSPEC_MB(MB_)                                                                              \
-    if (p.mb == MB_) {                                                                               \
-        if (bl.packed)                                                                               \
-            return full ? launch_partials_k<NW, RGW, RC, MB_, true, true>(EVOSPEC_ARGS)              \
-                        : launch_partials_k<NW, RGW, RC, MB_, false, true>(EVOSPEC_ARGS);            \
-        return full ? launch_partials_k<NW, RGW, RC, MB_, true, false>(EVOSPEC_ARGS)                 \
-                    : launch_partials_k<NW, RGW, RC, MB_, false, false>(EVOSPEC_ARGS);               \
+#define EVOSPEC_MB(MB_, KS_)                                                                                    \
+    if (p.mb == MB_) {                                                                                          \
+        if (bl.packed)                                                                                          \
+            return !full ? launch_partials_k<TW, KS_, kRing, MB_, false, true, false>(EVOSPEC_ARGS)               \
+                         : (once ? launch_partials_k<TW, KS_, kRing, MB_, true, true, true>(EVOSPEC_ARGS)         \
+                                 : launch_partials_k<TW, KS_, kRing, MB_, true, true, false>(EVOSPEC_ARGS));      \
+        return !full ? launch_partials_k<TW, KS_, kRing, MB_, false, false, false>(EVOSPEC_ARGS)                  \
+                     : (once ? launch_partials_k<TW, KS_, kRing, MB_, true, false, true>(EVOSPEC_ARGS)            \
+                             : launch_partials_k<TW, KS_, kRing, MB_, true, false, false>(EVOSPEC_ARGS));         \
     }
-    EVOSPEC_MB(1) EVOSPEC_MB(2) EVOSPEC_MB(4)
+    EVOSPEC_MB(1, 1) EVOSPEC_MB(2, KS2) EVOSPEC_MB(4, KS4)
 #undef EVOSPEC_MB
 #undef EVOSPEC_ARGS
     return hipErrorInvalidValue;
@@ -916,12 +936,13 @@ hipError_t launch_partials_batch(const Plan& p, const void* h, const ChunkBatch&
                                  int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
                                  void* stats, hipStream_t stream) {
     if (cb.n < 1 || cb.n > kMaxChunks || bl.chunk_bytes % 8 != 0) return hipErrorInvalidValue;
-#define EVOSPEC_SHAPE(NW_, RGW_, RC_)                                                          \
-    if (p.nw == NW_ && p.rgw == RGW_ && p.rc == RC_)                                           \
-        return launch_partials_shape<NW_, RGW_, RC_>(p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream);
-    EVOSPEC_SLAB_SHAPES(EVOSPEC_SHAPE)
+    switch (p.nw) {
+#define EVOSPEC_SHAPE(TW_, KS4_, KS2_)                                                          \
+    case TW_: return launch_partials_shape<TW_, KS4_, KS2_>(p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream);
+        EVOSPEC_SPLITS(EVOSPEC_SHAPE)
 #undef EVOSPEC_SHAPE
-    return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_partials(const Plan& p, const void* h, int rows, int d, const void* W,

@@ -20,9 +20,10 @@ constexpr int kRowsMinSlab = 64;    // smallest slab any plan uses (workspace up
 constexpr int kLdsLimit = 160 * 1024;
 constexpr int kRoundRows = 37;      // fixed cost of a round of workgroups, in slab rows (see make_plan)
 
-// Slab shapes that have a compiled kernel: X(nw, rgw, rc) with nw wavefronts per workgroup, rgw
-// 16-row groups per wavefront (RT = 16 * nw * rgw rows per slab) and a W-operand ring of rc chunks
-// of kKC hidden elements per lane.  (Measured on MI355X: more waves per CU beat a deeper ring per wave.)
+// Slab shapes that have a compiled kernel: X(nw, rgw, rc) with nw * rgw tiles of 16 rows per workgroup
+// (RT = 16 * nw * rgw rows per slab; the launcher decides how many wavefronts share a tile) and a W-operand
+// ring of rc chunks of kKC hidden elements per lane.  (Measured on MI355X: more waves per CU beat a deeper
+// ring per wave.)
 #define EVOSPEC_SLAB_SHAPES(X) \
     X(4, 1, 2) X(5, 1, 2) X(6, 1, 2) X(7, 1, 2) X(8, 1, 2) X(9, 1, 2) X(10, 1, 2) X(12, 1, 2)
 struct SlabShape { int nw; int rgw; int rc; };
@@ -102,7 +103,7 @@ struct InlineRows {
 };
 
 struct Plan {
-    int nw = 0, rgw = 0;     // wavefronts per workgroup, 16-row groups per wavefront
+    int nw = 0, rgw = 0;     // tiles per workgroup: nw groups of rgw 16-row tiles
     int rc = 0;              // chunks in the W-operand ring
     int mb = 0;              // 16-row blocks of draft rows held in accumulators (1, 2 or 4)
     int rt = 0;              // slab rows
@@ -138,7 +139,7 @@ inline size_t lds_bytes_for(int nw, int rgw, int mb) {
     size_t hs = 2ull * mrows * kHStride * 2;                 // h chunk, double buffered
     size_t list = (size_t)mrows * list_stride(rt) * 8;       // surviving keys per draft row
     size_t u = hs > list ? hs : list;                        // the two never live together
-    size_t gm = (size_t)mrows * 4 * nw * 4;                  // group maxima
+    size_t gm = (size_t)mrows * 8 * nw * 4;                  // group maxima
     size_t wsum = (size_t)nw * mrows * 4;                    // per-wave sum-exp
     size_t small = align_up((size_t)rt * 4, 16) + (size_t)mrows * 3 * 4;   // ids, tau, vmax, counters
     return align_up(u, 16) + gm + wsum + small;
