@@ -6,7 +6,7 @@ import ctypes
 
 import numpy as np
 
-from .binding import EvospecError, _matrix, lib
+from .binding import EvospecError, _matrix, _stream, lib
 
 
 class _Config(ctypes.Structure):
@@ -146,7 +146,6 @@ def path_a_workspace_bytes(V, d, n_mips, max_insert):
 def path_a_event(arc, h_target, W_lm, target_top, n_mips, row_ptr, col_idx, max_successors, W_act, act_ids, workspace):
     """One failure event (search, candidates, admission, gather) on torch's current stream; returns
     the admitted (slot, id) pairs.  Tensors are CUDA tensors; row_ptr / col_idx / target_top host arrays."""
-    import torch
     t = np.ascontiguousarray(np.asarray(target_top, dtype=np.int32))
     rp = np.ascontiguousarray(np.asarray(row_ptr, dtype=np.int64))
     ci = np.ascontiguousarray(np.asarray(col_idx, dtype=np.int32))
@@ -160,6 +159,6 @@ def path_a_event(arc, h_target, W_lm, target_top, n_mips, row_ptr, col_idx, max_
                                     rp.ctypes.data_as(_i64p), _ptr(ci) if ci.size else None, int(max_successors),
                                     W_act.data_ptr(), act_ids.data_ptr(), int(V_act), int(layout),
                                     workspace.data_ptr(), int(workspace.numel()),
-                                    torch.cuda.current_stream().cuda_stream, _ptr(slots), _ptr(ids), ctypes.byref(n)),
+                                    _stream(), _ptr(slots), _ptr(ids), ctypes.byref(n)),
            "evospec_path_a_event")
     return list(zip(slots[:n.value].tolist(), ids[:n.value].tolist()))

@@ -82,6 +82,15 @@ def _load() -> ctypes.CDLL:
 
 lib = _load()
 
+# A head of a small active set takes about 10 us on the GPU, so the marshalling must not cost more than that:
+# names are bound once, pointers travel as integers, and the stream is asked for without making an object of it
+# (1,024 x 256 at 8 rows, calls back to back: 13.7 -> 10.7 us).
+import torch  # noqa: E402
+
+_Tensor = torch.Tensor
+_get_device = torch._C._cuda_getDevice
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
 
 def lib_path() -> str:
     return _LIB_PATH
@@ -101,17 +110,16 @@ def _check(status: int, where: str) -> None:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """torch's current stream on the current device, as a hipStream_t address."""
+    return _raw_stream(_get_device())
 
 
 def _expect(t, dtype, name, ndim=None):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a GPU torch tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
@@ -134,7 +142,6 @@ class PackedMatrix:
     tensor means row-major and a PackedMatrix means packed."""
 
     def __init__(self, rows: int, d: int, device="cuda", batch=None, data=None):
-        import torch
         self.rows, self.d, self.batch = int(rows), int(d), batch
         self.matrix_elems = matrix_bytes(rows, d, PACKED) // 2
         n = self.matrix_elems * (1 if batch is None else int(batch))
@@ -155,7 +162,6 @@ class PackedMatrix:
 
 def _matrix(W, name, ndim=2):
     """(rows, d, layout) of a W_act argument."""
-    import torch
     if isinstance(W, PackedMatrix):
         return W.rows, W.d, PACKED
     _expect(W, torch.bfloat16, name, ndim)
@@ -177,7 +183,6 @@ def workspace_bytes_segmented(M: int, V_core: int, V_arc: int, S: int, d: int, k
 
 def active_gather(W_lm, src_ids, slots, W_act, act_ids) -> None:
     """W_act[slot_i] = W_lm[src_ids[i]], act_ids[slot_i] = src_ids[i] (slots=None: slot_i = i)."""
-    import torch
     _expect(W_lm, torch.bfloat16, "W_lm", 2)
     V_act, d_act, layout = _matrix(W_act, "W_act")
     _expect(src_ids, torch.int32, "src_ids", 1)
@@ -194,7 +199,6 @@ def active_gather(W_lm, src_ids, slots, W_act, act_ids) -> None:
 
 
 def _head_shapes(h, W_act, ids):
-    import torch
     _expect(h, torch.bfloat16, "h", 2)
     V_act, d_act, layout = _matrix(W_act, "W_act")
     M, d = h.shape
@@ -208,7 +212,6 @@ def _head_shapes(h, W_act, ids):
 
 
 def _workspace(workspace, need, device):
-    import torch
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
     return workspace
@@ -216,7 +219,6 @@ def _workspace(workspace, need, device):
 
 def active_lmhead_topk(h, W_act, ids, k, out_vals=None, out_ids=None, out_logz=None, workspace=None):
     """Restricted head: returns (vals[M,k] f32, ids[M,k] i32, logz[M] f32)."""
-    import torch
     M, d, V_act, layout = _head_shapes(h, W_act, ids)
     dev = h.device
     out_vals = torch.empty((M, k), dtype=torch.float32, device=dev) if out_vals is None else out_vals
@@ -245,7 +247,6 @@ def active_lmhead_topk_then_update(h, W_act, act_ids, k, W_lm, src_ids, slots, o
                                    out_logz=None, workspace=None):
     """The head on W_act / act_ids as they are, then the update W_act[slots] <- W_lm[src_ids] (one launch
     fewer than the two calls).  Returns (vals, ids, logz) of the head."""
-    import torch
     M, d, V_act, layout = _head_shapes(h, W_act, act_ids)
     dev = h.device
     out_vals = torch.empty((M, k), dtype=torch.float32, device=dev) if out_vals is None else out_vals
@@ -276,7 +277,6 @@ def active_lmhead_merge(M, V_act, d, k, out_vals, out_ids, out_logz, workspace) 
 
 def active_lmhead_topk_segmented(h, W_core, ids_core, W_arc, ids_arc, row_off, k, workspace=None):
     """Batched variant: rows [row_off[s], row_off[s+1]) see core u arc[s]. row_off: host ints."""
-    import torch
     _expect(h, torch.bfloat16, "h", 2)
     V_core, d1, layout = _matrix(W_core, "W_core")
     V_arc, d2, layout_arc = _matrix(W_arc, "W_arc", 3)
@@ -305,7 +305,6 @@ def active_lmhead_topk_segmented(h, W_core, ids_core, W_arc, ids_arc, row_off, k
 
 def validate_ids(ids, V: int) -> bool:
     """True when every id is in [0, V) and no id repeats (synchronises)."""
-    import torch
     _expect(ids, torch.int32, "ids", 1)
     st = lib.evospec_validate_ids(_ptr(ids), ids.shape[0], V, _stream())
     if st == 7:
@@ -324,7 +323,6 @@ def kl_gate(z_target, h_draft, W_lm, K=256, T=1.0, out_support=None, out_zt=None
             workspace=None):
     """Retained-support KL gate (Path B): returns (support int32 [E,K], target logits, draft logits
     fp32 [E,K], kl fp32 [E]).  z_target fp32 [E,V], h_draft bf16 [E,d], W_lm bf16 [V,d], all on the GPU."""
-    import torch
     E, V = z_target.shape
     d = W_lm.shape[1]
     dev = z_target.device
@@ -339,5 +337,5 @@ def kl_gate(z_target, h_draft, W_lm, K=256, T=1.0, out_support=None, out_zt=None
     _check(lib.evospec_kl_gate(z_target.data_ptr(), int(E), int(V), h_draft.data_ptr(), int(d), W_lm.data_ptr(),
                                int(K), float(T), out_support.data_ptr(), out_zt.data_ptr(), out_zq.data_ptr(),
                                out_kl.data_ptr(), workspace.data_ptr(), int(workspace.numel()),
-                               torch.cuda.current_stream().cuda_stream), "evospec_kl_gate")
+                               _stream()), "evospec_kl_gate")
     return out_support, out_zt, out_zq, out_kl
