@@ -53,8 +53,8 @@ struct PartialSet {
 };
 
 // x of lane (lane ^ STRIDE), STRIDE a power of two below 64, without a trip through LDS (a
-// ds_bpermute costs its full latency at every step of a dependent chain: 42 of them made the sort
-// below 3,500 cycles long).  Strides 1 and 2 are quad permutes; 4 is a mirror of each group of 8
+// ds_bpermute costs its full latency at every step of a dependent chain: 42 of them made a 64-lane sort
+// 3,500 cycles long).  Strides 1 and 2 are quad permutes; 4 is a mirror of each group of 8
 // lanes (lane ^ 7) followed by a reversal within quads (lane ^ 3); 8 is a rotation by 8 within the
 // 16-lane row; 16 and 32 are the row / half swaps of gfx950: v_permlane16_swap(x, x) returns the even
 // rows' values in all rows and the odd rows' values in all rows, v_permlane32_swap(x, x) the lower and
