@@ -250,8 +250,10 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
         basep[hf] = (g > 0 ? q[0] : 0u) + (g > 1 ? q[1] : 0u) + (g > 2 ? q[2] : 0u);
         Lp[hf] = q[0] + q[1] + q[2] + q[3];
     }
-    // rows whose survivors fit a list go straight out
-    const int cap = list_len <= kGFastLen ? list_len : 0;
+    // rows whose survivors fit a list go straight out.  The staged lists have kGFastLen slots: where those of the
+    // workspace are longer (k > 16) no row may take that way, one without survivors neither (its 16 empty slots
+    // would land in the list of another row, and its own would keep what the workspace held before).
+    const int cap = list_len == kGFastLen ? kGFastLen : -1;
     bool rare = false;
 
     repin();
@@ -334,7 +336,9 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
             const int i0 = 2 * n16, a0 = 16 * (i0 >> 2) + 4 * g + (i0 & 3);
             const float2 z = *reinterpret_cast<const float2*>(zpark + (r + 16 * g) * 32 + i0);
             const int2 id = *reinterpret_cast<const int2*>(Ids + a0);
-            const uint32_t o0 = a0 < nvalid ? f32_to_ordered(z.x) : 0u, o1 = a0 + 1 < nvalid ? f32_to_ordered(z.y) : 0u;
+            // (a NaN with its sign set, below -inf in this order, is no survivor above and no candidate here)
+            auto ordered = [](float x) { const uint32_t o = f32_to_ordered(x); return o >= 0x007fffffu ? o : 0u; };
+            const uint32_t o0 = a0 < nvalid ? ordered(z.x) : 0u, o1 = a0 + 1 < nvalid ? ordered(z.y) : 0u;
             // a value that at least q and at most `most` of the 128 reach, if there is one; else the largest that
             // q reach (found bit by bit; between 10 and 16 of 128 it takes some 12 of the 32 steps)
             auto kth = [&](uint32_t x0, uint32_t x1, int q, int most) {

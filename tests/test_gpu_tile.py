@@ -29,3 +29,30 @@ def test_few_hundred_rows(ev, oracle_mod, layout, V_act, d, M, k):
     ev.active_gather(to_dev_bf16(full), to_dev_i32(ids), None, W_act, act_ids)
     v, i, l = (x.cpu().numpy() for x in ev.active_lmhead_topk(to_dev_bf16(h), W_act, act_ids, k))
     check_head(v, i, l, oracle_mod.logits(h, W), ids, k, f"{layout} V_act={V_act} d={d} M={M} k={k}")
+
+
+@pytest.mark.parametrize("M,V_act,d,k", [
+    (200, 700, 128, 33),      # 128 x 128 tiles, lists of 64 slots
+    (200, 700, 128, 17),      # lists of 32
+    (200, 700, 128, 10),      # lists of 16: the staged ones
+    (1999, 6230, 64, 33),     # 256 x 256 tiles
+])
+def test_a_row_of_nans_leaves_the_others_alone(ev, oracle_mod, M, V_act, d, k):
+    """A draft row of NaNs with the sign set has no candidate at all: its lists come out empty, at their own
+    places.  The workspace starts full of candidates that would beat everything, so a list that nobody writes
+    shows, and so does one that another row's overwrites."""
+    import torch
+    W, h, ids = problem(800 + M + k, V_act, d, M, V=V_act + 9)
+    bad = [5, 130]
+    hb = h.copy()
+    hb[bad] = 0xFFC0
+    ws = torch.empty(ev.workspace_bytes(M, V_act, d, k) // 8, dtype=torch.int64, device="cuda")
+    ws.fill_((0x7149F2CA << 32) | 7654321)                 # (1e30, id 7654321)
+    v, i, l = (x.cpu().numpy() for x in ev.active_lmhead_topk(to_dev_bf16(hb), to_dev_bf16(W), to_dev_i32(ids), k,
+                                                              workspace=ws.view(torch.uint8)))
+    good = np.setdiff1d(np.arange(M), bad)
+    check_head(v[good], i[good], l[good], oracle_mod.logits(h[good], W), ids, k, f"M={M} V_act={V_act} k={k}")
+    assert not np.isfinite(l[bad]).any()                   # (NaN, or -inf: a maximum takes no notice of a NaN)
+    # the sign of a NaN that goes through the matrix cores is not ours to say: no candidates, or NaNs of active rows
+    empty = i[bad] == -1
+    assert np.all(np.isneginf(v[bad][empty])) and np.all(np.isnan(v[bad][~empty])) and np.isin(i[bad][~empty], ids).all()
