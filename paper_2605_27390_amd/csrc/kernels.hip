@@ -278,6 +278,9 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // Every workgroup takes the chunks in the same order: equal rows of different slabs must tie exactly.
+    // (Start chunks rotated by workgroup spread row-major rows a power of two apart over the memory channels,
+    // 36,864 x 4,096 at 60 rows 68.6 -> 59.1 us, but the order of a logit's sum then depends on its slab.)
     const int nchunks = (d + KC - 1) / KC;
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
     // chunks that h is requested ahead of its use (13 to 16 wavefronts have 128 registers each, which three pieces
@@ -301,24 +304,10 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         hdst[p] = m * kHStride + c8 * 8;
     }
 
-    // The chunk of the hidden dimension that step c works on.  Workgroups start at different chunks and wrap
-    // around: rows are usually a power of two apart, so that at the same chunk all workgroups would read
-    // the same few memory channels.  Measured at 60 rows, together with whole-line loads of row-major rows:
-    // 36,864 x 4,096 row-major 65.1 -> 58.9 us, 151,936 x 4,096 254 -> 236, 32,256 x 2,048 34.9 -> 31.6; packed
-    // 8,448 x 4,096 27.8 -> 26.4, 36,864 the same.  (Neighbouring workgroups a chunk apart instead of eight:
-    // 60.2, 238, 32.0 us.  d not a multiple of KC: rows are not a power of two apart, and the partial chunk
-    // stays last.)
-    const int rot = FULLK ? (int)(blockIdx.x >> 3) % nchunks : 0;
-    auto chunk_of = [&](int c) {
-        if constexpr (!FULLK) return c;
-        const int x = c + rot;
-        return x >= nchunks ? x - nchunks : x;
-    };
     // Loads past the end of a row (only in the last chunk when d is not a multiple of KC: `whole` says that
     // this one is not it) are redirected to the row's last 16 bytes and replaced by zeros, so that no load is
     // conditional.
-    auto load_h = [&](u32x4 (&hr)[HP], int step, auto whole) {
-        const int c = chunk_of(step);
+    auto load_h = [&](u32x4 (&hr)[HP], int c, auto whole) {
 #pragma unroll
         for (int p = 0; p < HP; ++p) {
             if constexpr (decltype(whole)::value) {
@@ -338,8 +327,8 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     };
     // k-step s (0..KSTEPS-1 of this wavefront) of chunk c goes to ring slot (c % RC) * KSTEPS + s
     auto load_w = [&](gvec_ptr p) { return ONCE ? load_once(p) : *p; };
-    auto load_w_step = [&](int slot, int step, int s, auto whole) {
-        const int koff = chunk_of(step) * KC + (s0 + s) * 32;
+    auto load_w_step = [&](int slot, int c, int s, auto whole) {
+        const int koff = c * KC + (s0 + s) * 32;
         if constexpr (PACKED) {
             wr[slot] = load_w((gvec_ptr)wp + (koff / 32) * 64);          // rows are padded to whole chunks
         } else {
