@@ -866,13 +866,6 @@ lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_key
 namespace evospec {
 
 namespace {
-// Wavefronts per tile for every slab shape: X(tiles, with four blocks of draft rows, with two); one block: 1.
-// A workgroup with few tiles has too few wavefronts to hide the operand reads and the trips to L2 for h, so
-// several share a tile, up to 16 wavefronts in all (measured at 60 rows, all x 4,096 unless said: 8,448 rows
-// 26.8 -> 25.0 us, 18,432 33.9 -> 32.5, 24,000 41.9 -> 39.4, 12,000 x 1,024 16.3 -> 13.2; 37 rows, 20,011 x
-// 3,000 41.8 -> 34.8; 20 rows, 16,384 28.5 -> 26.4.  A ring of four chunks instead of two: 1 to 12 us slower).
-#define EVOSPEC_SPLITS(X) X(4, 4, 2) X(5, 2, 2) X(6, 2, 2) X(7, 2, 2) X(8, 2, 2) X(9, 1, 1) X(10, 1, 1) X(12, 1, 1)
-constexpr int kRing = 2;                       // chunks in the W-operand ring
 constexpr int kMaxDevices = 64;
 
 template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE>
@@ -897,7 +890,7 @@ hipError_t launch_partials_k(const Plan& p, const void* h, const ChunkBatch& cb,
     return hipGetLastError();
 }
 
-template <int TW, int KS4, int KS2>
+template <int TW, int RC, int KS4, int KS2>
 hipError_t launch_partials_shape(const Plan& p, const void* h, const ChunkBatch& cb, const BatchLayout& bl, int d,
                                  const void* W, const int32_t* ids, int V_act, int k, void* keys, void* stats,
                                  hipStream_t stream) {
@@ -905,16 +898,18 @@ hipError_t launch_partials_shape(const Plan& p, const void* h, const ChunkBatch&
     const bool once = streams_once((size_t)V_act * (bl.seq_rows ? cb.n : 1), d, bl.packed);
 #define EVOSPEC_ARGS p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream
 #define EVOSPEC_MB(MB_, KS_)                                                                                    \
-    if (p.mb == MB_) {                                                                                          \
+    if (p.mb == MB_ && p.ks == KS_) {                                                                           \
         if (bl.packed)                                                                                          \
-            return !full ? launch_partials_k<TW, KS_, kRing, MB_, false, true, false>(EVOSPEC_ARGS)               \
-                         : (once ? launch_partials_k<TW, KS_, kRing, MB_, true, true, true>(EVOSPEC_ARGS)         \
-                                 : launch_partials_k<TW, KS_, kRing, MB_, true, true, false>(EVOSPEC_ARGS));      \
-        return !full ? launch_partials_k<TW, KS_, kRing, MB_, false, false, false>(EVOSPEC_ARGS)                  \
-                     : (once ? launch_partials_k<TW, KS_, kRing, MB_, true, false, true>(EVOSPEC_ARGS)            \
-                             : launch_partials_k<TW, KS_, kRing, MB_, true, false, false>(EVOSPEC_ARGS));         \
+            return !full ? launch_partials_k<TW, KS_, RC, MB_, false, true, false>(EVOSPEC_ARGS)               \
+                         : (once ? launch_partials_k<TW, KS_, RC, MB_, true, true, true>(EVOSPEC_ARGS)         \
+                                 : launch_partials_k<TW, KS_, RC, MB_, true, true, false>(EVOSPEC_ARGS));      \
+        return !full ? launch_partials_k<TW, KS_, RC, MB_, false, false, false>(EVOSPEC_ARGS)                  \
+                     : (once ? launch_partials_k<TW, KS_, RC, MB_, true, false, true>(EVOSPEC_ARGS)            \
+                             : launch_partials_k<TW, KS_, RC, MB_, true, false, false>(EVOSPEC_ARGS));         \
     }
-    EVOSPEC_MB(1, 1) EVOSPEC_MB(2, KS2) EVOSPEC_MB(4, KS4)
+    EVOSPEC_MB(1, 1) EVOSPEC_MB(2, 1) EVOSPEC_MB(4, 1)
+    if constexpr (KS2 > 1) { EVOSPEC_MB(2, KS2) }
+    if constexpr (KS4 > 1) { EVOSPEC_MB(4, KS4) }
 #undef EVOSPEC_MB
 #undef EVOSPEC_ARGS
     return hipErrorInvalidValue;
@@ -926,9 +921,10 @@ hipError_t launch_partials_batch(const Plan& p, const void* h, const ChunkBatch&
                                  void* stats, hipStream_t stream) {
     if (cb.n < 1 || cb.n > kMaxChunks || bl.chunk_bytes % 8 != 0) return hipErrorInvalidValue;
     switch (p.nw) {
-#define EVOSPEC_SHAPE(TW_, KS4_, KS2_)                                                          \
-    case TW_: return launch_partials_shape<TW_, KS4_, KS2_>(p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream);
-        EVOSPEC_SPLITS(EVOSPEC_SHAPE)
+#define EVOSPEC_SHAPE(TW_, RGW_, RC_, KS4_, KS2_)                                               \
+    static_assert(RGW_ == 1, "the kernel gives a wavefront one tile");                          \
+    case TW_: return launch_partials_shape<TW_, RC_, KS4_, KS2_>(p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream);
+        EVOSPEC_SLAB_SHAPES(EVOSPEC_SHAPE)
 #undef EVOSPEC_SHAPE
         default: return hipErrorInvalidValue;
     }

@@ -20,14 +20,18 @@ constexpr int kRowsMinSlab = 64;    // smallest slab any plan uses (workspace up
 constexpr int kLdsLimit = 160 * 1024;
 constexpr int kRoundRows = 37;      // fixed cost of a round of workgroups, in slab rows (see make_plan)
 
-// Slab shapes that have a compiled kernel: X(nw, rgw, rc) with nw * rgw tiles of 16 rows per workgroup
-// (RT = 16 * nw * rgw rows per slab; the launcher decides how many wavefronts share a tile) and a W-operand
-// ring of rc chunks of kKC hidden elements per lane.  (Measured on MI355X: more waves per CU beat a deeper
-// ring per wave.)
+// Slab shapes that have a compiled kernel: X(nw, rgw, rc, ks4, ks2) with nw * rgw tiles of 16 rows per workgroup
+// (RT = 16 * nw * rgw rows per slab) and a W-operand ring of rc chunks of kKC hidden elements per lane.  (Measured
+// on MI355X: more waves per CU beat a deeper ring per wave.)  ks4 / ks2: wavefronts that may share a tile with
+// four / two blocks of draft rows.  A workgroup with few tiles has too few wavefronts to hide the operand reads
+// and the trips to L2 for h, so several share a tile, up to 16 wavefronts in all (measured at 60 rows, all x
+// 4,096 unless said: 8,448 rows 26.8 -> 25.0 us, 18,432 33.9 -> 32.5, 24,000 41.9 -> 39.4, 12,000 x 1,024 16.3 ->
+// 13.2; 37 rows, 20,011 x 3,000 41.8 -> 34.8; 20 rows, 16,384 28.5 -> 26.4.  A ring of four chunks instead of
+// two: 1 to 12 us slower).
 #define EVOSPEC_SLAB_SHAPES(X) \
-    X(4, 1, 2) X(5, 1, 2) X(6, 1, 2) X(7, 1, 2) X(8, 1, 2) X(9, 1, 2) X(10, 1, 2) X(12, 1, 2)
-struct SlabShape { int nw; int rgw; int rc; };
-#define EVOSPEC_SHAPE_ENTRY(NW_, RGW_, RC_) {NW_, RGW_, RC_},
+    X(4, 1, 2, 4, 2) X(5, 1, 2, 2, 2) X(6, 1, 2, 2, 2) X(7, 1, 2, 2, 2) X(8, 1, 2, 2, 2) X(9, 1, 2, 1, 1) X(10, 1, 2, 1, 1) X(12, 1, 2, 1, 1)
+struct SlabShape { int nw; int rgw; int rc; int ks4; int ks2; };
+#define EVOSPEC_SHAPE_ENTRY(NW_, RGW_, RC_, KS4_, KS2_) {NW_, RGW_, RC_, KS4_, KS2_},
 constexpr SlabShape kShapes[] = {EVOSPEC_SLAB_SHAPES(EVOSPEC_SHAPE_ENTRY)};
 #undef EVOSPEC_SHAPE_ENTRY
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
@@ -105,6 +109,7 @@ struct InlineRows {
 struct Plan {
     int nw = 0, rgw = 0;     // tiles per workgroup: nw groups of rgw 16-row tiles
     int rc = 0;              // chunks in the W-operand ring
+    int ks = 1;              // wavefronts that share a tile, each a part of the hidden dimension
     int mb = 0;              // 16-row blocks of draft rows held in accumulators (1, 2 or 4)
     int rt = 0;              // slab rows
     int n_slabs = 0;
@@ -152,8 +157,11 @@ inline size_t lds_bytes_for(int nw, int rgw, int mb) {
 // whose bytes are a multiple of 1 MiB is charged one eighth more: all workgroups then walk through
 // memory at the same offset within a MiB and meet at the same memory channels (measured on MI355X
 // at 32,256 x 4,096: 8 wavefronts = 1 MiB slabs 59 us, 9 wavefronts on fewer CUs 56 us).
+// share: several wavefronts may share a tile.  Their parts of a logit's sum are added at the end, another order
+// than one wavefront's, so launches whose logits meet in one result must not differ in it: the calls that merge
+// two partial sets (a core and an extension) go without.
 inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, int d, int k, int num_cu,
-                      int replicas = 1 /*chunks that share the launch*/) {
+                      int replicas = 1 /*chunks that share the launch*/, bool share = true) {
     Plan best;
     long best_cost = -1;
     const int mb = mb_for_rows(rows);
@@ -168,7 +176,9 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
         if (((size_t)rt * (size_t)d * 2) % ((size_t)1 << 20) == 0) cost += cost / 8;
         if (best_cost < 0 || cost < best_cost || (cost == best_cost && rt > best.rt)) {
             best_cost = cost;
-            best.nw = nw; best.rgw = rgw; best.rc = kShapes[i].rc; best.mb = mb; best.rt = rt; best.n_slabs = n_slabs;
+            best.nw = nw; best.rgw = rgw; best.rc = kShapes[i].rc; best.mb = mb;
+            best.ks = !share || mb == 1 ? 1 : (mb == 2 ? kShapes[i].ks2 : kShapes[i].ks4);
+            best.rt = rt; best.n_slabs = n_slabs;
             best.gl = group_level_for(k, nw); best.lds_bytes = lds;
         }
     }

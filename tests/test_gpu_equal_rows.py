@@ -67,3 +67,32 @@ def test_equal_rows_and_order(ev, layout, V_act, d, M, k):
     v1, i1, l1 = head(ids[rng.permutation(V_act)])
     assert np.array_equal(i0, i1) and np.array_equal(v0, v1)
     np.testing.assert_allclose(l0, l1, rtol=1e-6)
+
+
+@pytest.mark.parametrize("layout", ["packed", "row_major"])
+@pytest.mark.parametrize("V_core,V_arc,d,lens", [
+    (16000, 400, 512, [20, 1, 40]),          # core in one pass of slabs of 4 tiles
+    (36864, 900, 1024, [33, 64, 10]),        # core of 9 tiles, extensions of 4
+    (2000, 2000, 2048, [60, 17, 60, 8]),     # 128 x 128 tiles and slabs
+    (300, 17000, 256, [64]),
+])
+def test_equal_rows_in_core_and_extension(ev, layout, V_core, V_arc, d, lens):
+    """Copies of one row in the shared core and in an extension tie as well."""
+    import torch
+    S, M, k = len(lens), sum(lens), 12
+    W, group = scattered_copies(V_core + V_arc, 4, d, V_core + d)
+    rng = np.random.default_rng(d)
+    ids = rng.permutation(2 * (V_core + V_arc)).astype(np.int32)
+    W_lm = torch.zeros((len(ids), d), dtype=torch.bfloat16, device="cuda")
+    core, first_arc = ids[:V_core], ids[V_core:V_core + V_arc]
+    W_lm[torch.from_numpy(ids[:V_core + V_arc]).cuda().long()] = W
+    h = torch.empty((M, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(M))
+    W_core, ids_core = new_matrix(ev, V_core, d, layout), torch.empty(V_core, dtype=torch.int32, device="cuda")
+    ev.active_gather(W_lm, to_dev_i32(core), None, W_core, ids_core)
+    W_arc, ids_arc = new_matrix(ev, V_arc, d, layout, batch=S), torch.empty((S, V_arc), dtype=torch.int32, device="cuda")
+    for s in range(S):                                       # every sequence the same extension, in another order
+        ev.active_gather(W_lm, to_dev_i32(first_arc[rng.permutation(V_arc)]), None,
+                         W_arc.sub(s) if layout == "packed" else W_arc[s], ids_arc[s])
+    row_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    v, i, _ = (x.cpu().numpy() for x in ev.active_lmhead_topk_segmented(h, W_core, ids_core, W_arc, ids_arc, row_off, k))
+    check_equal_rows(v, i, ids[:V_core + V_arc], group, f"{layout} V_core={V_core} V_arc={V_arc} d={d}")
