@@ -270,7 +270,7 @@ int evospec_active_lmhead_topk_then_update(const void* h, int M, int d, void* W_
         if (rc || n == 0) return rc;
         return evospec_active_gather(W_lm, V, d, src_ids, slots, n, W_act, act_ids, V_act, layout, stream);
     }
-    const GatherArgs upd{W_lm, V, d / 8, src_ids, slots, n, W_act, act_ids, V_act, layout == EVOSPEC_PACKED ? 1 : 0};
+    const GatherArgs upd = gather_args(W_lm, V, d, src_ids, slots, n, W_act, act_ids, V_act, layout == EVOSPEC_PACKED);
     return head_impl(h, M, d, W_act, act_ids, V_act, layout, k, out_vals, out_ids, out_logz, workspace, workspace_bytes,
                      stream, &upd);
 }

@@ -23,11 +23,13 @@ namespace evospec {
 // Row insertion  W_act[slot] <- W_lm[id], act_ids[slot] <- id  (bit copy, 16 B per lane).
 // One workgroup per row.  Into a packed W_act the row's pieces go to their places in the operand
 // tiles (16-byte stores 256 bytes apart) and the pieces between d and the padded row length are
-// zeroed.  The stores bypass the caches: a short kernel that leaves its rows dirty in L2 waits for their
-// write-back at its end (measured: 256 rows of 8 KB 16.8 -> 5.8 us packed, 16.4 -> 4.0 row-major; 32 rows
-// 5.9 -> 3.9).
-__device__ __forceinline__ void gather_row(const GatherArgs& g, int32_t id, int32_t s) {
-    if (id < 0 || id >= g.V || s < 0 || s >= g.V_act) return;      // uniform per workgroup
+// zeroed.  PAST: the stores bypass the caches (see update_past_caches).
+template <bool PAST>
+__device__ __forceinline__ void copy_row(const GatherArgs& g, int32_t id, int32_t s) {
+    auto put = [](u32x4 v, u32x4* p) {
+        if constexpr (PAST) __builtin_nontemporal_store(v, p);
+        else *p = v;
+    };
     const u32x4* src = static_cast<const u32x4*>(g.W_lm) + (size_t)id * g.row_vec;
     const int nt = blockDim.x;
     if (g.packed) {
@@ -44,7 +46,7 @@ __device__ __forceinline__ void gather_row(const GatherArgs& g, int32_t id, int3
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int c = c0 + u * nt + threadIdx.x;
-                if (c < dp_vec) __builtin_nontemporal_store(v[u], dst + (c >> 2) * 64 + (c & 3) * 16);
+                if (c < dp_vec) put(v[u], dst + (c >> 2) * 64 + (c & 3) * 16);
             }
         }
     } else {
@@ -59,10 +61,15 @@ __device__ __forceinline__ void gather_row(const GatherArgs& g, int32_t id, int3
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int c = c0 + u * nt + threadIdx.x;
-                if (c < g.row_vec) __builtin_nontemporal_store(v[u], dst + c);
+                if (c < g.row_vec) put(v[u], dst + c);
             }
         }
     }
+}
+__device__ __forceinline__ void gather_row(const GatherArgs& g, int32_t id, int32_t s) {
+    if (id < 0 || id >= g.V || s < 0 || s >= g.V_act) return;      // uniform per workgroup
+    if (g.past_caches) copy_row<true>(g, id, s);
+    else copy_row<false>(g, id, s);
     if (threadIdx.x == 0) g.act_ids[s] = id;
 }
 __device__ __forceinline__ void gather_one_row(const GatherArgs& g, int i) {
@@ -1005,7 +1012,7 @@ hipError_t launch_merge(const MergeSet& a, const MergeSet& b, int k, float* out_
 
 hipError_t launch_gather(const void* W_lm, int V, int d, const int32_t* src_ids, const int32_t* slots,
                          int n, void* W_act, int32_t* act_ids, int V_act, hipStream_t stream, bool packed) {
-    const GatherArgs g{W_lm, V, d / 8, src_ids, slots, n, W_act, act_ids, V_act, packed ? 1 : 0};
+    const GatherArgs g = gather_args(W_lm, V, d, src_ids, slots, n, W_act, act_ids, V_act, packed);
     if (packed && !slots) {                      // rebuild: whole operand tiles per workgroup
         const int tiles = (n + kPackRows - 1) / kPackRows;
         hipLaunchKernelGGL(gather_tiles_kernel, dim3(tiles < 4096 ? tiles : 4096), dim3(256), 0, stream, g);
@@ -1024,7 +1031,7 @@ hipError_t launch_gather_inline(const void* W_lm, int V, int d, const int32_t* h
                                 int n, void* W_act, int32_t* act_ids, int V_act, hipStream_t stream, bool packed) {
     if (n < 0 || n > kInlineRows) return hipErrorInvalidValue;
     if (n == 0) return hipSuccess;
-    const GatherArgs g{W_lm, V, d / 8, nullptr, nullptr, n, W_act, act_ids, V_act, packed ? 1 : 0};
+    const GatherArgs g = gather_args(W_lm, V, d, nullptr, nullptr, n, W_act, act_ids, V_act, packed);
     InlineRows r{};
     for (int i = 0; i < n; ++i) { r.slot[i] = host_slots[i]; r.id[i] = host_ids[i]; }
     hipLaunchKernelGGL(gather_rows_inline_kernel, dim3(n), dim3(256), 0, stream, g, r);

@@ -97,7 +97,27 @@ struct GatherArgs {
     int32_t* act_ids = nullptr;
     int V_act = 0;
     int packed = 0;
+    int past_caches = 0;     // the rows are stored past the caches (update_past_caches)
 };
+
+// Whether the rows of an update are stored past the caches.  What matters is what the update adds to the head that
+// follows it.  A set that the heads stream past the caches finds nothing of the update there, and lines left dirty
+// in L2 are written back in its way (36,864 x 4,096 at 60 rows, added by 32 / 256 / 512 scattered rows: packed 4.1 /
+// 17.8 / 20.0 us through the caches, 2.6 / 6.9 / 11.0 past them; row-major 2.9 / 4.2 / 6.0 and 2.8 / 2.9 / 3.4).  In a packed
+// matrix neighbouring rows share lines, which only the caches can put together: from some 700 rows on that is
+// worth more (1,024 / 4,096 / 8,192 rows 25 / 48 / 88 us and 22 / 80 / 184; 75,000 x 2,048: 768 rows 10.0 and 10.0,
+// 2,048 rows 16.1 and 22.2; 18,000 x 8,192: 512 rows 26 and 21, 1,024 rows 32 and 41).  A smaller set is read
+// through the caches, where the rows then are (18,432 x 1,024, packed, 32 / 1,024 rows: 2.6 / 4.0 and 2.9 / 4.7;
+// 9,000 x 2,048: 2.0 / 5.2 and 3.0 / 9.4).
+constexpr int kDirectUpdateRows = 512;
+inline bool update_past_caches(int n, int V_act, int d, bool packed) {
+    return streams_once((size_t)V_act, d, packed) && (!packed || n <= kDirectUpdateRows);
+}
+inline GatherArgs gather_args(const void* W_lm, int V, int d, const int32_t* src_ids, const int32_t* slots, int n, void* W_act,
+                              int32_t* act_ids, int V_act, bool packed) {
+    return GatherArgs{W_lm, V, d / 8, src_ids, slots, n, W_act, act_ids, V_act, packed ? 1 : 0,
+                      update_past_caches(n, V_act, d, packed) ? 1 : 0};
+}
 
 // Rows of a small update passed to the kernel by value (see launch_gather_inline).
 constexpr int kInlineRows = 32;

@@ -45,6 +45,10 @@ int main() {
     REQUIRE(packed_d(4096) == 4096 && packed_d(8) == 256 && packed_d(264) == 512, "packed_d");
     REQUIRE(packed_rows(36864) == 36864 && packed_rows(1) == 16 && packed_rows(17) == 32, "packed_rows");
     REQUIRE(matrix_elems(33, 72, true) == 48u * 256u && matrix_elems(33, 72, false) == 33u * 72u, "matrix_elems");
+    // updates past the caches: sets of 128 MiB and more, packed ones up to 512 rows
+    REQUIRE(update_past_caches(512, 16384, 4096, true) && !update_past_caches(513, 16384, 4096, true), "packed updates");
+    REQUIRE(update_past_caches(9000, 16384, 4096, false) && !update_past_caches(8, 16383, 4096, false), "row-major updates");
+    REQUIRE(!update_past_caches(8, 16368, 4096, true) && !update_past_caches(8, 40000, 2056, false), "small sets, ragged rows");
     // large-M plan: lists and statistics do not overlap, one slab per 128 rows
     for (int M : {129, 960, 4096})
         for (int V_act : {1, 127, 128, 129, 32768, 151936}) {

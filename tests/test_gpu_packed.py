@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import evospec_inputs as gi
-from helpers import NAN_BITS, bf16_dev_to_bits, check_head, new_matrix, to_dev_bf16, to_dev_i32, unpack_bits
+from helpers import NAN_BITS, bf16_dev_to_bits, check_head, matrix_bits, new_matrix, to_dev_bf16, to_dev_i32, unpack_bits
 from test_gpu_parity import ev, problem  # noqa: F401  (fixture and helper)
 
 pytestmark = pytest.mark.gpu
@@ -103,6 +103,30 @@ def test_packed_gather_skips_out_of_range_entries(ev):
     assert np.array_equal(got[0], W[3]) and np.array_equal(got[1], W[6]) and np.array_equal(got[4], W[7])
     for r in (2, 3, 5, 6, 7):
         assert np.all(got[r] == NAN_BITS)
+
+
+@pytest.mark.parametrize("layout", ["packed", "row_major"])
+@pytest.mark.parametrize("V_act,d", [
+    (16400, 4096),            # a set whose rows an update stores past the caches, up to 512 of them if it is packed
+    (16370, 4096),            # below 128 MiB: never
+])
+def test_updates_of_every_size_bit_exact(ev, layout, V_act, d):
+    import torch
+    V = V_act + 4000
+    g = torch.Generator(device="cuda").manual_seed(V_act)
+    W = torch.empty((V, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    bits = bf16_dev_to_bits(W)
+    W_act = new_matrix(ev, V_act, d, layout)
+    act_ids = torch.empty(V_act, dtype=torch.int32, device="cuda")
+    rng = np.random.default_rng(V_act)
+    ids = rng.permutation(V)[:V_act].astype(np.int32)
+    ev.active_gather(W, to_dev_i32(ids), None, W_act, act_ids)
+    for n in (1, 512, 513, 3000):
+        slots = rng.permutation(V_act)[:n].astype(np.int32)
+        ids[slots] = rng.permutation(V)[:n]
+        ev.active_gather(W, to_dev_i32(ids[slots]), to_dev_i32(slots), W_act, act_ids)
+    assert np.array_equal(act_ids.cpu().numpy(), ids)
+    assert np.array_equal(matrix_bits(W_act), bits[ids])
 
 
 # ------------------------------------------------------------------ head on a packed matrix
