@@ -88,8 +88,9 @@ lib = _load()
 import torch  # noqa: E402
 
 _Tensor = torch.Tensor
-_get_device = torch._C._cuda_getDevice
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# (None in a torch built without GPU support, where the host-only calls still work)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def lib_path() -> str:

@@ -179,3 +179,17 @@ def test_validate_ids_argument_errors(ev):
     assert L.evospec_validate_ids(None, 0, 10, None) == 0
     assert L.evospec_validate_ids(None, 5, 10, None) == 1
     assert L.evospec_validate_ids(None, -1, 10, None) == 2
+
+
+def test_host_calls_work_with_a_torch_that_has_no_gpu_support():
+    """The package imports, and its host side works, where torch has no stream functions to offer."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "del torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream\n"
+            "import paper_2605_27390_amd as ev\n"
+            "assert ev.workspace_bytes(60, 36864, 4096, 10) > 0\n"
+            "m = ev.ArcManager(slot_base=100, core=[1, 2])\n"
+            "assert m is not None\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
