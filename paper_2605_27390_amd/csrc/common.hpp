@@ -79,7 +79,7 @@ __device__ __forceinline__ uint32_t xor_lane(uint32_t x, int lane) {
         return (lane & 32) ? a[0] : a[1];
     }
 }
-// Two MFMA operands (k-steps 2p and 2p + 1 of 16 row-major rows) from whole 128-byte lines: lane (n, g)
+// For narrow.hip: two MFMA operands (k-steps 2p and 2p + 1 of 16 row-major rows) from whole 128-byte lines: lane (n, g)
 // loads piece g (n < 8) or g + 4 of line p of row n % 8 into `a`, and piece g + 4 (n < 8) or g of row
 // 8 + n % 8 into `b`.  The first operand is then the lane's own a or b, the second that of lane l ^ 8.
 // lanes l with (l & 8) set take `b`, the others `a`

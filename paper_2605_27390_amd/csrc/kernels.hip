@@ -199,12 +199,18 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 // ---------------------------------------------------------------------------------------
 // Pass 1 of the restricted head: one workgroup streams one slab of RT = 16*TW rows of
 // W_act (KS wavefronts to a tile of 16 rows, its elements loaded from HBM straight into MFMA operand layout
-// with 128-bit loads that do not stay in the caches: 60.0 -> 54.3 us at 36,864 x 4,096 packed and 60 rows), contracts it with up to 16*MB draft rows of h (K-chunks of h staged
+// with 128-bit loads), contracts it with up to 16*MB draft rows of h (K-chunks of h staged
 // in LDS, double buffered, shared by all waves), and reduces the slab's logits, which stay in
 // the accumulators, to
 //   part_stats[slab][m] = (max_i z, sum_i exp(z - max))         over the slab's rows
 //   part_keys[slab][m][0..k) = the slab's k best keys, descending (0 = none)
 // Logits never leave the CU.
+// ONCE (packed, see streams_once): the weights bypass the caches, 60.0 -> 54.3 us at 36,864 x 4,096 and 60 rows.  On a
+// row-major matrix a load takes half lines of 16 rows, the other half of which must be found in the caches again.
+// (Whole lines of 8 rows, permuted into operands within 16 lanes, past the caches: as fast or slower at 33 to 64
+// rows, 32,256 x 2,048 42.9 -> 44.1 us for the head, full vocabulary 275 -> 280, and a set below 256 MB that is read
+// again at once loses what the memory-side cache holds of it, 60,000 x 2,048 59.6 -> 72.0; 24 rows gain, 36,864 x
+// 4,096 72.1 -> 68.0.)
 template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE>
 __global__ void __launch_bounds__(TW * KS * 64)
 lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int seq_rows,
@@ -233,7 +239,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     constexpr int MR = 16 * MB;
     constexpr int KC = kKC;
     constexpr int KSTEPS = KC / 32 / KS;           // k-steps of a chunk that a wavefront takes
-    static_assert(KSTEPS % 2 == 0, "row-major k-steps are loaded in pairs");
+    static_assert(KSTEPS % 2 == 0, "the B operands of two k-steps alternate");
     constexpr int HPIECES = MR * (KC / 8);
     constexpr int HP = (HPIECES + NT - 1) / NT;
 
@@ -267,18 +273,12 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     if (tid < RT && row0 + tid < V_act) id_reg = ids ? ids[row0 + tid] : row0 + tid;
 
     const uint16_t* wp;
-    const uint16_t* wp2;                                   // (row-major only)
-    const int e1 = (g + ((n16 >> 3) << 2)) * 8, e2 = (g + (((n16 >> 3) ^ 1) << 2)) * 8;   // elements within the line
     if constexpr (PACKED) {
         // the wavefront's tile: 1 KB operand blocks in k-step order, lane l at byte 16 l
         const int tile = min((row0 >> 4) + w, (V_act - 1) >> 4);   // tail slab: a valid tile, masked later
         wp = W + (size_t)tile * kPackRows * dp + lane * 8;
-        wp2 = wp;
     } else {
-        // whole lines: rows n16 % 8 (first load of a pair of k-steps) and 8 + n16 % 8 (second), see pick_bank
-        const int r = row0 + w * 16 + (n16 & 7);
-        wp = W + (size_t)min(r, V_act - 1) * d;            // tail slab: duplicate a valid row, masked later
-        wp2 = W + (size_t)min(r + 8, V_act - 1) * d;
+        wp = W + (size_t)min(row0 + w * 16 + n16, V_act - 1) * d + g * 8;   // tail slab: duplicate a valid row, masked later
     }
 
     f32x4 acc[MB];
@@ -339,14 +339,12 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         if constexpr (PACKED) {
             wr[slot] = load_w((gvec_ptr)wp + (koff / 32) * 64);          // rows are padded to whole chunks
         } else {
-            // k-steps s, s + 1 (s even) together: line koff / 64 of the row pair
-            const uint16_t* row = (s & 1) ? wp2 : wp;
-            const int e = (koff & ~63) + ((s & 1) ? e2 : e1);
             if constexpr (decltype(whole)::value) {
-                wr[slot] = load_w((gvec_ptr)(row + e));
+                wr[slot] = load_w((gvec_ptr)(wp + koff));
             } else {
-                const u32x4 v = *(gvec_ptr)(row + (e < d ? e : d - 8));
-                wr[slot] = e < d ? v : zero4;
+                const bool in = koff + g * 8 < d;
+                const u32x4 v = *(gvec_ptr)(wp + (in ? koff : d - 8 - g * 8));
+                wr[slot] = in ? v : zero4;
             }
         }
     };
@@ -356,14 +354,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
             b[mb] = *reinterpret_cast<const bf16x8*>(Hs + ((size_t)buf * MR + mb * 16 + n16) * kHStride + (s0 + s) * 32 + g * 8);
     };
     auto mfma_step = [&](int slot, const bf16x8 (&b)[MB]) {
-        u32x4 av = wr[slot];
-        if constexpr (!PACKED) {
-            const int even = slot & ~1;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                av[i] = (slot & 1) ? pick_bank_ror8(wr[even][i], wr[even + 1][i]) : pick_bank(wr[even][i], wr[even + 1][i]);
-        }
-        const bf16x8 a = __builtin_bit_cast(bf16x8, av);
+        const bf16x8 a = __builtin_bit_cast(bf16x8, wr[slot]);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[mb], acc[mb], 0, 0, 0);
     };
@@ -910,9 +901,8 @@ hipError_t launch_partials_shape(const Plan& p, const void* h, const ChunkBatch&
             return !full ? launch_partials_k<TW, KS_, RC, MB_, false, true, false>(EVOSPEC_ARGS)               \
                          : (once ? launch_partials_k<TW, KS_, RC, MB_, true, true, true>(EVOSPEC_ARGS)         \
                                  : launch_partials_k<TW, KS_, RC, MB_, true, true, false>(EVOSPEC_ARGS));      \
-        return !full ? launch_partials_k<TW, KS_, RC, MB_, false, false, false>(EVOSPEC_ARGS)                  \
-                     : (once ? launch_partials_k<TW, KS_, RC, MB_, true, false, true>(EVOSPEC_ARGS)            \
-                             : launch_partials_k<TW, KS_, RC, MB_, true, false, false>(EVOSPEC_ARGS));         \
+        return full ? launch_partials_k<TW, KS_, RC, MB_, true, false, false>(EVOSPEC_ARGS)                    \
+                    : launch_partials_k<TW, KS_, RC, MB_, false, false, false>(EVOSPEC_ARGS);                  \
     }
     EVOSPEC_MB(1, 1) EVOSPEC_MB(2, 1) EVOSPEC_MB(4, 1)
     if constexpr (KS2 > 1) { EVOSPEC_MB(2, KS2) }

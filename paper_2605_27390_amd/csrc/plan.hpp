@@ -73,7 +73,7 @@ inline size_t matrix_elems(size_t rows, int d, bool packed) {
     return packed ? packed_rows(rows) * (size_t)packed_d(d) : rows * (size_t)d;
 }
 
-// Whether a launch loads its weights past the caches.  A set well below the 256 MB memory-side cache is
+// Whether a launch loads its weights past the caches (the slab kernel: of packed matrices only).  A set well below the 256 MB memory-side cache is
 // still there when a decode loop comes back to it, and non-temporal loads find it more slowly (7,086 x
 // 1,536, 22 MB, 53 rows: 18.0 us with ordinary loads, 18.3 without); a larger one only drags itself through
 // (151,936 x 4,096 at one row 207 against 185 us, 36,864 x 4,096 at 60 rows 60.0 against 54.3, and against
@@ -103,7 +103,7 @@ struct GatherArgs {
 // Whether the rows of an update are stored past the caches.  What matters is what the update adds to the head that
 // follows it.  A set that the heads stream past the caches finds nothing of the update there, and lines left dirty
 // in L2 are written back in its way (36,864 x 4,096 at 60 rows, added by 32 / 256 / 512 scattered rows: packed 4.1 /
-// 17.8 / 20.0 us through the caches, 2.6 / 6.9 / 11.0 past them; row-major 2.9 / 4.2 / 6.0 and 2.8 / 2.9 / 3.4).  In a packed
+// 17.8 / 20.0 us through the caches, 2.6 / 6.9 / 11.0 past them; row-major, 32 / 256 / 1,024 rows 3.2 / 5.1 / 10.0 and 3.1 / 3.5 / 6.0).  In a packed
 // matrix neighbouring rows share lines, which only the caches can put together: from some 700 rows on that is
 // worth more (1,024 / 4,096 / 8,192 rows 25 / 48 / 88 us and 22 / 80 / 184; 75,000 x 2,048: 768 rows 10.0 and 10.0,
 // 2,048 rows 16.1 and 22.2; 18,000 x 8,192: 512 rows 26 and 21, 1,024 rows 32 and 41).  A smaller set is read
