@@ -27,7 +27,10 @@ constexpr int kRoundRows = 37;      // fixed cost of a round of workgroups, in s
 // and the trips to L2 for h, so several share a tile, up to 16 wavefronts in all (measured at 60 rows, all x
 // 4,096 unless said: 8,448 rows 26.8 -> 25.0 us, 18,432 33.9 -> 32.5, 24,000 41.9 -> 39.4, 12,000 x 1,024 16.3 ->
 // 13.2; 37 rows, 20,011 x 3,000 41.8 -> 34.8; 20 rows, 16,384 28.5 -> 26.4.  A ring of four chunks instead of
-// two: 1 to 12 us slower).
+// two: 1 to 12 us slower).  With two blocks of draft rows two workgroups fit a compute unit unless their tiles are
+// shared, so that a launch of several rounds goes without (17 rows, 128,105 x 256 26.2 -> 17.1 us for the slabs;
+// 24 rows, 51,446 x 512 17.4 -> 14.5; 32 rows, 124,638 x 1,536 72.1 -> 61.3; with four blocks 59,624 x 4,096 119 shared,
+// 124 not).
 #define EVOSPEC_SLAB_SHAPES(X) \
     X(4, 1, 2, 4, 2) X(5, 1, 2, 2, 2) X(6, 1, 2, 2, 2) X(7, 1, 2, 2, 2) X(8, 1, 2, 2, 2) X(9, 1, 2, 1, 1) X(10, 1, 2, 1, 1) X(12, 1, 2, 1, 1)
 struct SlabShape { int nw; int rgw; int rc; int ks4; int ks2; };
@@ -197,7 +200,7 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
         if (best_cost < 0 || cost < best_cost || (cost == best_cost && rt > best.rt)) {
             best_cost = cost;
             best.nw = nw; best.rgw = rgw; best.rc = kShapes[i].rc; best.mb = mb;
-            best.ks = !share || mb == 1 ? 1 : (mb == 2 ? kShapes[i].ks2 : kShapes[i].ks4);
+            best.ks = !share || mb == 1 || (mb == 2 && rounds > 1) ? 1 : (mb == 2 ? kShapes[i].ks2 : kShapes[i].ks4);
             best.rt = rt; best.n_slabs = n_slabs;
             best.gl = group_level_for(k, nw); best.lds_bytes = lds;
         }

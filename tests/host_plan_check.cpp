@@ -41,6 +41,10 @@ int main() {
     REQUIRE(make_plan(8, 18432, 4096, 10, 256).nw == 5, "18,432 rows");
     REQUIRE(make_plan(60, 8448, 4096, 10, 256).nw == 4, "8,448 rows");
     REQUIRE(make_plan(60, 151936, 4096, 10, 256).nw == 10, "151,936 rows");
+    // wavefronts that share a tile: not with one block of draft rows, not on several rounds with two, not on request
+    REQUIRE(make_plan(60, 8448, 4096, 10, 256).ks == 4 && make_plan(60, 18432, 4096, 10, 256).ks == 2 && make_plan(60, 36864, 4096, 10, 256).ks == 1, "shared tiles");
+    REQUIRE(make_plan(24, 8448, 4096, 10, 256).ks == 2 && make_plan(24, 51446, 512, 10, 256).ks == 1 && make_plan(60, 51446, 512, 10, 256).ks == 2, "rounds");
+    REQUIRE(make_plan(16, 8448, 4096, 10, 256).ks == 1 && make_plan(60, 8448, 4096, 10, 256, 1, false).ks == 1, "no shared tiles");
     // packed layout sizes
     REQUIRE(packed_d(4096) == 4096 && packed_d(8) == 256 && packed_d(264) == 512, "packed_d");
     REQUIRE(packed_rows(36864) == 36864 && packed_rows(1) == 16 && packed_rows(17) == 32, "packed_rows");
