@@ -251,7 +251,8 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     constexpr size_t hs_bytes = 2ull * MR * kHStride * 2;
     constexpr size_t list_bytes = (size_t)MR * list_stride(RT) * 8;
     constexpr size_t u_bytes = align_up(hs_bytes > list_bytes ? hs_bytes : list_bytes, 16);
-    constexpr int NGS = 8 * TW;                                               // row stride of gm
+    const bool fine = fine_groups(k, TW);                                     // (then GL is 0)
+    const int NGS = fine ? 8 * TW : 4 * TW;                                   // row stride of gm
     float* gm = reinterpret_cast<float*>(smem + u_bytes);                     // [MR][NGS] group maxima
     float* wsum = gm + (size_t)MR * NGS;                                      // [TW][MR] sum-exp of each tile
     int32_t* Ids = reinterpret_cast<int32_t*>(wsum + (size_t)TW * MR);        // [RT]
@@ -457,9 +458,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
                 for (int i = 0; i < MBW; ++i) acc[i][j] = -INFINITY;
             }
     }
-    // (1) group maxima (level GL: lane, lane pair or wave; pairs of a lane's logits when there are too few
-    // lanes for k, or the bound would let nearly everything through: at k = 20 the ranking of 80 rows took 3.8 us)
-    const bool fine = GL == 0 && 4 * TW < k + k / 2;
+    // (1) group maxima (level GL: lane, lane pair or wave; fine: pairs of a lane's logits)
     const int NG = fine ? 8 * TW : TW << (2 - GL);
     {
         const int gidx = GL == 0 ? w * 4 + g : (GL == 1 ? w * 2 + (g >> 1) : w);

@@ -161,13 +161,20 @@ inline int group_level_for(int k, int nw) {
 // the same list position spread over all banks (a stride of rt keys maps every row to two banks).
 constexpr int list_stride(int rt) { return rt + 2; }
 
-inline size_t lds_bytes_for(int nw, int rgw, int mb) {
+// Whether the groups of the bound are pairs of a lane's logits: where the 4 * nw lanes that hold a draft row are no more
+// than k, so that their maxima bound nothing (or next to nothing: k of k).  Twice as many groups cost four times as
+// much to rank, which pays from there on and not before (slab kernel, x 1,024, 60 rows: 9 tiles, k = 34 / 36 / 40 39.4 / 51.0 /
+// 56.0 us by lanes, 42.1 / 42.5 / 44.2 by pairs; 12 tiles, k = 36 / 48 37.3 / 66.7 and 51.0 / 54.2; 4 tiles, k = 14 / 16 11.9 /
+// 13.8 and 13.0 / 12.7).
+constexpr bool fine_groups(int k, int nw) { return k >= 4 * nw; }
+
+inline size_t lds_bytes_for(int nw, int rgw, int mb, int k) {
     const int rt = 16 * nw * rgw;
     const int mrows = 16 * mb;
     size_t hs = 2ull * mrows * kHStride * 2;                 // h chunk, double buffered
     size_t list = (size_t)mrows * list_stride(rt) * 8;       // surviving keys per draft row
     size_t u = hs > list ? hs : list;                        // the two never live together
-    size_t gm = (size_t)mrows * 8 * nw * 4;                  // group maxima
+    size_t gm = (size_t)mrows * (fine_groups(k, nw) ? 8 : 4) * nw * 4;   // group maxima
     size_t wsum = (size_t)nw * mrows * 4;                    // per-wave sum-exp
     size_t small = align_up((size_t)rt * 4, 16) + (size_t)mrows * 3 * 4;   // ids, tau, vmax, counters
     return align_up(u, 16) + gm + wsum + small;
@@ -192,7 +199,7 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
         const int nw = kShapes[i].nw, rgw = kShapes[i].rgw;
         const int rt = 16 * nw * rgw;
         const int n_slabs = (V_act + rt - 1) / rt;
-        const size_t lds = lds_bytes_for(nw, rgw, mb);
+        const size_t lds = lds_bytes_for(nw, rgw, mb, k);
         if (lds > (size_t)kLdsLimit) continue;
         const long rounds = ((long)n_slabs * replicas + num_cu - 1) / num_cu;
         long cost = rounds * (rt + kRoundRows) * 8;

@@ -45,6 +45,12 @@ int main() {
     REQUIRE(make_plan(60, 8448, 4096, 10, 256).ks == 4 && make_plan(60, 18432, 4096, 10, 256).ks == 2 && make_plan(60, 36864, 4096, 10, 256).ks == 1, "shared tiles");
     REQUIRE(make_plan(24, 8448, 4096, 10, 256).ks == 2 && make_plan(24, 51446, 512, 10, 256).ks == 1 && make_plan(60, 51446, 512, 10, 256).ks == 2, "rounds");
     REQUIRE(make_plan(16, 8448, 4096, 10, 256).ks == 1 && make_plan(60, 8448, 4096, 10, 256, 1, false).ks == 1, "no shared tiles");
+    // the bound's groups: pairs of a lane's logits from k = lanes of a draft row on; then they are no coarser than a lane
+    for (int nw = 4; nw <= 12; ++nw)
+        for (int k = 1; k <= 64; ++k) {
+            REQUIRE(fine_groups(k, nw) == (k >= 4 * nw), "fine_groups");
+            REQUIRE(!fine_groups(k, nw) || group_level_for(k, nw) == 0, "level of pairs");
+        }
     // packed layout sizes
     REQUIRE(packed_d(4096) == 4096 && packed_d(8) == 256 && packed_d(264) == 512, "packed_d");
     REQUIRE(packed_rows(36864) == 36864 && packed_rows(1) == 16 && packed_rows(17) == 32, "packed_rows");
