@@ -631,7 +631,7 @@ constexpr int kPieces = 8;             // 16-byte pieces (two slots) of unsorted
 template <int NT>
 __global__ void __launch_bounds__(NT)
 lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_keys, size_t a_pass_stats,
-                    size_t b_chunk_keys, size_t b_chunk_stats, int k, int parts_log2, int pend_cap,
+                    size_t b_chunk_keys, size_t b_chunk_stats, int k, int parts_log2, int deal, int pend_cap,
                     float* __restrict__ out_vals, int32_t* __restrict__ out_ids,
                     float* __restrict__ out_logz, GatherArgs upd) {
     // The blocks of grid row cb.n (present only when an update rides along) insert the rows of a
@@ -663,10 +663,15 @@ lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_key
 
     // Sorted lists (set B, and set A unless it is unsorted), 2^parts_log2 threads to a list: thread
     // part p takes the entries p, p + P, ..., which descend.
-    const int parts = 1 << parts_log2, part = tid & (parts - 1);
+    const int parts = 1 << parts_log2;
     const int sortedA = A.sorted ? A.n_slabs : 0, n_sorted = sortedA + B.n_slabs;
     // Unsorted lists (set A only): contiguous, taken as one array of 16-byte pieces.
     const int n_pieces = A.sorted ? 0 : A.n_slabs * (A.list_len / 2);
+    // Where they do not fill the threads, the launcher has the lists (the pieces, a line at a time) dealt out to the wavefronts
+    // in turn.
+    auto dealt = [&](int log2_run) { return (((lane >> log2_run) * NWV + w) << log2_run) | (lane & ((1 << log2_run) - 1)); };
+    const int unit_s = deal & 1 ? dealt(parts_log2) : tid, unit_p = deal & 2 ? dealt(3) : tid;
+    const int part = unit_s & (parts - 1);
     const int step_sorted = NT >> parts_log2, step_pieces = NT * kPieces;
 
     int len = 0;
@@ -674,7 +679,7 @@ lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_key
     u64 se[kEager];
     u32x4 up[kPieces];
     auto fetch = [&](int round) {
-        const int L = round * step_sorted + (tid >> parts_log2);
+        const int L = round * step_sorted + (unit_s >> parts_log2);
         const bool inA = L < sortedA;
         lst = (inA ? keysA + (size_t)L * A.key_slab : keysB + (size_t)(L - sortedA) * B.key_slab) + part;
         len = L < n_sorted ? (inA ? A.list_len : B.list_len) - part : 0;       // entries are lst[0], lst[parts], ... below len
@@ -683,7 +688,7 @@ lmhead_merge_kernel(PartialSet A, PartialSet B, ChunkBatch cb, size_t a_pass_key
         if (n_pieces) {
 #pragma unroll
             for (int j = 0; j < kPieces; ++j) {
-                const int q = round * step_pieces + j * NT + tid;
+                const int q = round * step_pieces + j * NT + unit_p;
                 up[j] = u32x4{~0u, ~0u, ~0u, ~0u};
                 if (q < n_pieces) up[j] = *(gvec_ptr)(keysA + 2 * (size_t)q);
             }
@@ -977,6 +982,13 @@ hipError_t launch_merge_batch(const MergeSet& a, size_t a_pass_bytes, const Merg
     const int max_len = A.list_len > B.list_len ? A.list_len : B.list_len;
     int parts_log2 = 0;
     while (n_sorted > 0 && parts_log2 < 4 && (n_sorted << (parts_log2 + 1)) <= nt && (2 << parts_log2) <= max_len) ++parts_log2;
+    // The kernel's bound is the sets-th largest of the wavefronts' q-th largest candidates (see there).  Lists or pieces
+    // that do not fill the threads are dealt out to the wavefronts in turn where each then gets 2 q of them, and where
+    // otherwise not even `sets` wavefronts have q, so that everything would be a candidate (16 lists of 5 9.0 us, 64 of 1
+    // 8.6; dealt out 5.2 and 5.1; 132 lists of 64, where each wavefront gets q of 33: 43 dealt out, 10 not).
+    const int sets = nt / 128, q = (k + sets - 1) / sets;
+    auto deals = [&](int units) { return units < nt && (units >= 2 * q * (nt / 64) || units < 64 * (sets - 1) + q); };
+    const int deal = (deals(n_sorted << parts_log2) ? 1 : 0) | (deals(n_pieces) ? 2 : 0);
     // room for what usually reaches the bound, up to 32 KB (more is handled, slowly), and the running k
     int pend_cap = nt / 64 * k * (max_len > 16 ? max_len : 16);
     pend_cap = ((pend_cap < 4096 ? pend_cap : 4096) + k + 7) & ~7;
@@ -984,7 +996,7 @@ hipError_t launch_merge_batch(const MergeSet& a, size_t a_pass_bytes, const Merg
 #define EVOSPEC_MERGE(NT_)                                                                                  \
     hipLaunchKernelGGL(lmhead_merge_kernel<NT_>, grid, dim3(NT_), (size_t)pend_cap * 8, stream, A, B, cb,    \
                        a_pass_bytes / 8, a_pass_bytes / 8, b_chunk_bytes / 8, b_chunk_bytes / 8, k, parts_log2, \
-                       pend_cap, out_vals, out_ids, out_logz, upd)
+                       deal, pend_cap, out_vals, out_ids, out_logz, upd)
     if (nt == 256) EVOSPEC_MERGE(256);
     else if (nt == 512) EVOSPEC_MERGE(512);
     else EVOSPEC_MERGE(1024);

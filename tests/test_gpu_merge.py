@@ -15,6 +15,11 @@ pytestmark = pytest.mark.gpu
     (10, 3, 10),              # one list that holds exactly k
     (65, 5, 64),              # two lists, k close to everything
     (1000, 2, 1),
+    (1000, 20, 5),            # sixteen lists of 5, dealt out to the wavefronts
+    (4090, 17, 1),            # 64 lists of 1
+    (5900, 33, 64),           # 93 lists of 64: fewer than 2 q for every wavefront
+    (8448, 60, 64),           # 132: not dealt out
+    (900, 140, 10),           # unsorted lists, dealt out a line at a time
     (1024, 7, 33),            # sixteen lists, several threads to a list
     (4100, 2, 63),
     (16400, 3, 11),           # a little more than 256 lists, odd k (lists 8-byte aligned)
