@@ -153,7 +153,8 @@ int evospec_active_lmhead_partials(const void* h, int M, int d, const void* W_ac
     if (use_narrow(M, d)) {
         const NarrowPlan np = make_narrow_plan(M, V_act, k, num_cu);
         hipError_t e = launch_narrow_partials(np, h, M, d, W_act, ids, V_act, k, ws + np.keys_off, ws + np.stats_off,
-                                              static_cast<hipStream_t>(stream), layout == EVOSPEC_PACKED);
+                                              static_cast<hipStream_t>(stream), layout == EVOSPEC_PACKED,
+                                              streams_once((size_t)V_act, d, layout == EVOSPEC_PACKED));
         return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);
     }
     const Plan p = make_plan(M, V_act, d, k, num_cu);
@@ -226,8 +227,12 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
         hipError_t e;
         if (use_narrow(rows, d)) {
             const NarrowPlan np = make_narrow_plan(rows, V_act, k, num_cu);
+            // (the last rows after passes over a row-major matrix, which go through the caches, find part of it there: 65 rows,
+            // 36,864 x 2,048 80.3 us past the caches, 72.6 through them; 100,000 x 2,048, too large for that, 190 and 199)
+            const bool once = (packed || m0 == 0 || matrix_elems((size_t)V_act, d, false) * 2 >= ((size_t)320 << 20)) &&
+                              streams_once((size_t)V_act, d, packed);
             e = launch_narrow_partials(np, hp + (size_t)m0 * d, rows, d, W_act, ids, V_act, k, ws + np.keys_off,
-                                       ws + np.stats_off, st, packed);
+                                       ws + np.stats_off, st, packed, once);
             a = MergeSet{ws + np.keys_off, ws + np.stats_off, np.n_slabs, 0, rows, 0, true};
         } else {
             const Plan p = make_plan(rows, V_act, d, k, num_cu);

@@ -43,9 +43,9 @@ hipError_t launch_partials(const Plan& p, const void* h, int rows, int d, const 
                            const int32_t* ids, int V_act, int k, void* keys, void* stats,
                            hipStream_t stream, bool packed = false);
 // A few draft rows: partials of M <= kNarrowRows rows, row-major: keys u64 [M][n_slabs][k] descending,
-// stats float2 [M][n_slabs].
+// stats float2 [M][n_slabs].  once: the weights are loaded past the caches (see streams_once).
 hipError_t launch_narrow_partials(const NarrowPlan& p, const void* h, int M, int d, const void* W, const int32_t* ids,
-                                  int V_act, int k, void* keys, void* stats, hipStream_t stream, bool packed);
+                                  int V_act, int k, void* keys, void* stats, hipStream_t stream, bool packed, bool once);
 // Large-M path: partials of all M draft rows, row-major: keys u64 [M][ceil(V_act/128)][gemm_list_len(k)]
 // in any order, stats float2 [M][ceil(V_act/128)].
 hipError_t launch_gemm_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act,

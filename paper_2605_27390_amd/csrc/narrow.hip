@@ -251,9 +251,8 @@ hipError_t launch_narrow_ku(const NarrowPlan& p, const void* h, int M, int d, co
 }  // namespace
 
 hipError_t launch_narrow_partials(const NarrowPlan& p, const void* h, int M, int d, const void* W, const int32_t* ids,
-                                  int V_act, int k, void* keys, void* stats, hipStream_t stream, bool packed) {
+                                  int V_act, int k, void* keys, void* stats, hipStream_t stream, bool packed, bool once) {
     if (M < 1 || M > kNarrowRows || d > kNarrowMaxD) return hipErrorInvalidValue;
-    const bool once = streams_once((size_t)V_act, d, packed);
     switch ((packed_d(d) / 64 + kNW - 1) / kNW) {
 #define EVOSPEC_ARGS p, h, M, d, W, ids, V_act, k, keys, stats, stream
 #define EVOSPEC_KU(KU_)                                                                                     \
