@@ -150,7 +150,7 @@ int evospec_active_lmhead_partials(const void* h, int M, int d, const void* W_ac
     rc = device_num_cu(&num_cu);
     if (rc) return rc;
     char* ws = static_cast<char*>(workspace);
-    if (use_narrow(M, d)) {
+    if (use_narrow(M, d, V_act, num_cu)) {
         const NarrowPlan np = make_narrow_plan(M, V_act, k, num_cu);
         hipError_t e = launch_narrow_partials(np, h, M, d, W_act, ids, V_act, k, ws + np.keys_off, ws + np.stats_off,
                                               static_cast<hipStream_t>(stream), layout == EVOSPEC_PACKED,
@@ -177,7 +177,7 @@ int evospec_active_lmhead_merge(int M, int V_act, int d, int k, float* out_vals,
     if (rc) return rc;
     const char* ws = static_cast<const char*>(workspace);
     MergeSet a{}, none{};
-    if (use_narrow(M, d)) {
+    if (use_narrow(M, d, V_act, num_cu)) {
         const NarrowPlan np = make_narrow_plan(M, V_act, k, num_cu);
         a = MergeSet{ws + np.keys_off, ws + np.stats_off, np.n_slabs, 0, M, 0, true};
     } else {
@@ -225,7 +225,7 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
         const int rows = (M - m0) < kMTile ? (M - m0) : kMTile;
         MergeSet a{}, none{};
         hipError_t e;
-        if (use_narrow(rows, d)) {
+        if (use_narrow(rows, d, V_act, num_cu)) {
             const NarrowPlan np = make_narrow_plan(rows, V_act, k, num_cu);
             // (the last rows after passes over a row-major matrix, which go through the caches, find part of it there: 65 rows,
             // 36,864 x 2,048 80.3 us past the caches, 72.6 through them; 100,000 x 2,048, too large for that, 190 and 199)

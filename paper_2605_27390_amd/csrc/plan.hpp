@@ -227,7 +227,18 @@ constexpr int kNarrowWaves = 8;
 constexpr int kNarrowGroup = 8;            // tiles whose partial sums share the LDS
 constexpr int kNarrowMaxTiles = 40;        // tiles of a workgroup (logits in LDS: 16 rows x 640 x 4 bytes)
 constexpr int kNarrowMaxD = 4096;          // h of a wavefront in registers: 16 k-steps
-inline bool use_narrow(int M, int d) { return M <= kNarrowRows && d <= kNarrowMaxD; }
+// Taken for up to 8 rows, one for each wavefront's selection at the end (against the slab kernel at 8 rows: 1,500 to
+// 24,000 rows 1.05 to 1.6 times as fast, 48,000 1.0, 100,000 1.0 to 1.4).  From 9 rows on every wavefront selects twice,
+// which pays only while a workgroup has a single tile, or where the slab kernel needs more than one round of its
+// tallest slabs (16 rows, 768 hidden: 1,500 rows 1.02, 6,000 0.94, 24,000 0.88, 48,000 0.90, 100,000 1.01; 2,048
+// hidden, packed: 1.03, 0.93, 0.97, 0.91, 1.00).  The same between those two for hidden sizes that leave wavefronts without
+// work, once a workgroup has more than some 6 tiles (256 hidden, 8 rows: 12,000 rows 1.10, 24,000 0.98, 48,000 0.86).
+inline bool use_narrow(int M, int d, int V_act, int num_cu) {
+    if (M > kNarrowRows || d > kNarrowMaxD) return false;
+    const int tiles = (V_act + 15) / 16, tallest = 16 * kShapes[kNumShapes - 1].nw;
+    if (tiles <= num_cu || (V_act + tallest - 1) / tallest > num_cu) return true;
+    return M <= kNarrowWaves && (d > 256 || tiles <= 6 * num_cu);
+}
 
 struct NarrowPlan {
     int n_slabs = 0, base_tiles = 0, rem_tiles = 0;

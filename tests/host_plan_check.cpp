@@ -51,6 +51,22 @@ int main() {
             REQUIRE(fine_groups(k, nw) == (k >= 4 * nw), "fine_groups");
             REQUIRE(!fine_groups(k, nw) || group_level_for(k, nw) == 0, "level of pairs");
         }
+    // few draft rows: when, and everything the kernel assumes of its plan
+    REQUIRE(use_narrow(1, 4096, 151936, 256) && use_narrow(16, 4096, 151936, 256) && use_narrow(8, 4096, 18432, 256) && use_narrow(16, 8, 4096, 256), "few rows");
+    REQUIRE(!use_narrow(17, 256, 100, 256) && !use_narrow(1, 4104, 100, 256) && !use_narrow(9, 4096, 18432, 256) && !use_narrow(8, 256, 36864, 256) && use_narrow(8, 256, 24576, 256), "the other kernel");
+    for (int cu : cus)
+        for (int M = 1; M <= kNarrowRows; ++M)
+            for (int k : {1, 10, 17, 64})
+                for (int V_act = k; V_act <= 2000000; V_act = V_act < 300 ? V_act + 1 : V_act + V_act / 7 + 13) {
+                    const NarrowPlan p = make_narrow_plan(M, V_act, k, cu);
+                    const int tiles = (V_act + 15) / 16, most = p.base_tiles + (p.rem_tiles > 0);
+                    REQUIRE(p.n_slabs >= 1 && p.base_tiles >= 1 && p.rem_tiles >= 0 && p.rem_tiles < p.n_slabs, "V_act=%d", V_act);
+                    REQUIRE((long)p.n_slabs * p.base_tiles + p.rem_tiles == tiles, "tiles V_act=%d", V_act);
+                    REQUIRE(most <= kNarrowMaxTiles && p.z_stride >= most * 16 + 4 && p.z_stride % 4 == 0, "most=%d", most);
+                    REQUIRE(p.lds_bytes <= (size_t)kLdsLimit, "lds=%zu", p.lds_bytes);
+                    REQUIRE(p.stats_off >= (size_t)p.n_slabs * M * k * 8 && p.total_bytes >= p.stats_off + (size_t)p.n_slabs * M * 8, "layout");
+                    REQUIRE(p.total_bytes <= workspace_upper_bound(V_act, k), "total=%zu V_act=%d M=%d k=%d", p.total_bytes, V_act, M, k);
+                }
     // packed layout sizes
     REQUIRE(packed_d(4096) == 4096 && packed_d(8) == 256 && packed_d(264) == 512, "packed_d");
     REQUIRE(packed_rows(36864) == 36864 && packed_rows(1) == 16 && packed_rows(17) == 32, "packed_rows");

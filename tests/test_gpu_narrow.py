@@ -24,6 +24,11 @@ pytestmark = pytest.mark.gpu
     (9000, 3000, 15, 20),
     (5000, 4104, 4, 10),      # past it: the other kernel
     (170000, 64, 2, 10),      # more tiles than one round of workgroups takes
+    (4000, 4096, 16, 64),     # all rows, one tile to a workgroup: the largest hidden size, k == 64
+    (4091, 3000, 15, 20),
+    (49169, 264, 16, 64),     # all rows, 12 and 13 tiles to a workgroup: more than a round of slabs
+    (50003, 776, 13, 33),
+    (30000, 256, 8, 10),      # the other kernel: few hidden elements, many tiles
 ])
 def test_few_rows(ev, oracle_mod, layout, V_act, d, M, k):
     import torch
