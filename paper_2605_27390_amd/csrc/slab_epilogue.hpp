@@ -336,9 +336,7 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
             const int i0 = 2 * n16, a0 = 16 * (i0 >> 2) + 4 * g + (i0 & 3);
             const float2 z = *reinterpret_cast<const float2*>(zpark + (r + 16 * g) * 32 + i0);
             const int2 id = *reinterpret_cast<const int2*>(Ids + a0);
-            // (a NaN with its sign set, below -inf in this order, is no survivor above and no candidate here)
-            auto ordered = [](float x) { const uint32_t o = f32_to_ordered(x); return o >= 0x007fffffu ? o : 0u; };
-            const uint32_t o0 = a0 < nvalid ? ordered(z.x) : 0u, o1 = a0 + 1 < nvalid ? ordered(z.y) : 0u;
+            const uint32_t o0 = a0 < nvalid ? f32_to_ordered(z.x) : 0u, o1 = a0 + 1 < nvalid ? f32_to_ordered(z.y) : 0u;
             // a value that at least q and at most `most` of the 128 reach, if there is one; else the largest that
             // q reach (found bit by bit; between 10 and 16 of 128 it takes some 12 of the 32 steps)
             auto kth = [&](uint32_t x0, uint32_t x1, int q, int most) {
@@ -354,7 +352,9 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
                 return t;
             };
             uint32_t th = kth(o0, o1, k, list_len);
-            th = th ? th : 1u;                                     // fewer than k rows: all of them
+            // fewer than k rows: all of them down to -inf (a NaN with its sign set, below that in this order, is no
+            // survivor above and no candidate here)
+            th = th > 0x007fffffu ? th : 0x007fffffu;
             bool in0 = o0 >= th, in1 = o1 >= th;
             if (__popcll(__ballot(in0)) + __popcll(__ballot(in1)) > list_len) {
                 // equal logits at the k-th place: the smallest ids among them
