@@ -279,17 +279,23 @@ inline bool use_gemm(int M, int d) { return M >= kGemmMinRows && d % (2 * kGemmK
 inline int gemm_list_len(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 
 // Tiles of 128 x 128 (tile.hip) instead of 256 x 256 (gemm.hip); same partials.  A round of one workgroup
-// per compute unit costs a large tile kTileCost times what it costs a small one (measured at d = 4,096:
-// 125 us against 38; 512 x 32,768 in one round of large tiles 138 us, in four of small ones 161; 960 x
-// 32,768 251 and 282; 200 x 16,384 130 and 52; 300 x 20,000 x 2,048 223 and 64).
+// per compute unit costs a large tile some 2.7 times what it costs a small one, and 3.4 times where the hidden
+// dimension is short (large and small tiles, measured: 512 x 32,768 x 4,096 in one round of large tiles 138 us, in four
+// of small ones 161; one and three rounds: 256 x 45,000 x 5,120 177 and 201, 1,024 x 10,000 x 4,096 132 and 144, 256 x
+// 36,864 x 2,048 86 and 89, 256 x 45,000 x 1,024 65 and 58; two and five: 512 x 40,000 x 2,560 183 and 155; 200 x 16,384 x
+// 4,096 130 and 52).  A last slab whose rows are too few for the bound (but more than a list holds) sends all its
+// draft rows through the selection one by one, four times as many in a wavefront of large tiles (512 x 20,011 x 2,560 137
+// and 112 at k = 10; at k = 1, where the bound holds, 91 and 100).
 constexpr int kTileRows = 128;
-constexpr double kTileCost = 3.3;
-inline bool use_small_tiles(int M, int V_act, int num_cu) {
+inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu) {
+    const int last = V_act % kGemmSlab;
+    const bool slow_last = last > 16 && last / 4 < k + k / 2;
+    const double tile_cost = d < 2048 || slow_last ? 3.3 : 2.9;
     auto rounds = [&](int v, int m) {
         const long n = (long)((V_act + v - 1) / v) * ((M + m - 1) / m);
         return (n + num_cu - 1) / num_cu;
     };
-    return (double)rounds(kGemmSlab, kTileRows) < kTileCost * (double)rounds(kGemmTile, kGemmTile);
+    return (double)rounds(kGemmSlab, kTileRows) < tile_cost * (double)rounds(kGemmTile, kGemmTile);
 }
 
 struct GemmPlan {

@@ -82,6 +82,10 @@ int main() {
             REQUIRE(g.n_slabs == (V_act + 127) / 128 && g.list_len == 16, "gemm slabs");
             REQUIRE(g.stats_off >= (size_t)g.n_slabs * M * g.list_len * 8 && g.total_bytes >= g.stats_off + (size_t)g.n_slabs * M * 8, "gemm layout");
         }
+    // small tiles: where they take fewer than some three times the rounds of the large ones
+    REQUIRE(use_small_tiles(200, 16384, 4096, 10, 256) && use_small_tiles(129, 1, 64, 1, 256) && use_small_tiles(300, 20000, 2048, 10, 256), "small tiles");
+    REQUIRE(!use_small_tiles(960, 32768, 4096, 10, 256) && !use_small_tiles(512, 32768, 4096, 10, 256) && !use_small_tiles(256, 45000, 5120, 10, 256), "large tiles");
+    REQUIRE(use_small_tiles(256, 45000, 1024, 10, 256) && use_small_tiles(512, 20011, 2560, 10, 256) && !use_small_tiles(512, 20011, 2560, 1, 256), "three rounds");
     REQUIRE(gemm_list_len(16) == 16 && gemm_list_len(17) == 32 && gemm_list_len(64) == 64, "list_len");
     REQUIRE(use_gemm(129, 4096) && !use_gemm(128, 4096) && !use_gemm(960, 4104), "use_gemm");
     std::printf("ok\n");
