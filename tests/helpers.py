@@ -102,3 +102,19 @@ def matrix_bits(Wm, batch=None):
     if hasattr(Wm, "rows"):
         return unpack_bits(bf16_dev_to_bits(Wm.data), Wm.rows, Wm.d, batch=batch)[0]
     return bf16_dev_to_bits(Wm)
+
+
+def plan_route(M, V_act, d, k, cus=256):
+    """How the head of this shape is launched: {"kernel": "narrow" | "slab" | "tile" | "gemm", ...}, from the
+    launch planning itself, compiled with the host compiler."""
+    import os
+    import subprocess
+    import tempfile
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    if not hasattr(plan_route, "exe"):
+        exe = os.path.join(tempfile.mkdtemp(prefix="plan_route"), "plan_route")
+        subprocess.check_call(["g++", "-std=c++17", "-I", os.path.join(root, "paper_2605_27390_amd", "csrc"),
+                               os.path.join(root, "tests", "plan_route.cpp"), "-o", exe])
+        plan_route.exe = exe
+    line = subprocess.check_output([plan_route.exe] + [str(x) for x in (M, V_act, d, k, cus)], text=True)
+    return {a: int(b) if b.isdigit() else b for a, b in (w.split("=") for w in line.split())}

@@ -1,10 +1,11 @@
-"""GPU parity of the large-M path (256 x 256 MFMA tiles, taken from 129 draft rows on when the
-hidden size is a multiple of 64) against the fp64 oracle.  Needs an MI355X: run with `-m gpu`."""
+"""GPU parity of the large-M path (matrix tiles, taken from 129 draft rows on when the hidden size is a multiple of
+64) against the fp64 oracle.  The small problems here go through 128 x 128 tiles; `test_large_tiles*` are large enough
+for the 256 x 256 ones.  Needs an MI355X: run with `-m gpu`."""
 import numpy as np
 import pytest
 
 import evospec_inputs as gi
-from helpers import check_head, to_dev_bf16, to_dev_i32
+from helpers import check_head, new_matrix, plan_route, to_dev_bf16, to_dev_i32
 from test_gpu_parity import ev, problem, run_head  # noqa: F401  (fixture and helpers)
 
 pytestmark = pytest.mark.gpu
@@ -127,3 +128,56 @@ def test_large_m_all_equal_logits(ev):
     want = np.sort(ids)[:10]
     assert np.all(i == want[None, :]) and np.all(v == 0)
     np.testing.assert_allclose(l, np.log(1000.0), rtol=1e-6)
+
+
+def num_cu():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def some_rows(M, step=29):
+    """Draft rows at the edges of the row tiles and their quadrants, and every 29th."""
+    edges = [r + o for r in range(0, M + 1, 128) for o in (-2, -1, 0, 1)]
+    return np.unique([r for r in edges + list(range(0, M, step)) if 0 <= r < M])
+
+
+@pytest.mark.parametrize("layout", ["packed", "row_major"])
+@pytest.mark.parametrize("M,V_act,d,k", [
+    (1999, 6230, 64, 10),      # a single pair of chunks, both sides ragged, an odd number of slabs (a quadrant wholly empty)
+    (2048, 6272, 128, 16),     # whole tiles of rows, whole slabs; k == list length
+    (1990, 6271, 192, 17),     # lists of 32: every row is selected on its own
+    (1985, 6145, 320, 33),     # a last slab of one row; lists of 64
+    (3000, 4100, 64, 64),      # the largest k, a last slab of four rows
+])
+def test_large_tiles(ev, oracle_mod, layout, M, V_act, d, k):
+    import torch
+    assert plan_route(M, V_act, d, k, num_cu())["kernel"] == "gemm"
+    W, h, ids = problem(300 + M + V_act, V_act, d, M)
+    full = np.zeros((int(ids.max()) + 1, d), dtype=np.uint16)
+    full[ids] = W
+    W_act = new_matrix(ev, V_act, d, layout)
+    act_ids = torch.empty(V_act, dtype=torch.int32, device="cuda")
+    ev.active_gather(to_dev_bf16(full), to_dev_i32(ids), None, W_act, act_ids)
+    v, i, l = (x.cpu().numpy() for x in ev.active_lmhead_topk(to_dev_bf16(h), W_act, act_ids, k))
+    r = some_rows(M)
+    check_head(v[r], i[r], l[r], oracle_mod.logits(h[r], W), ids, k, f"{layout} M={M} V_act={V_act} d={d} k={k}")
+
+
+@pytest.mark.parametrize("k", [10, 40])
+def test_large_tiles_equal_logits_and_exact_integers(ev, k):
+    """All logits equal in half of the draft rows (every list overflows, the k smallest ids win), small integers in the
+    others (exact in fp32: the layout of the tiles, bit for bit)."""
+    rng = np.random.default_rng(50 + k)
+    M, V_act, d = 2000, 6200, 128
+    assert plan_route(M, V_act, d, k, num_cu())["kernel"] == "gemm"
+    Wf = rng.integers(-4, 5, size=(V_act, d)).astype(np.float32)
+    hf = rng.integers(-4, 5, size=(M, d)).astype(np.float32)
+    hf[::2] = 0
+    ids = rng.permutation(20000)[:V_act].astype(np.int32)
+    v, i, l = run_head(ev, gi.f32_to_bf16_bits(hf), gi.f32_to_bf16_bits(Wf), ids, k)
+    assert np.all(i[::2] == np.sort(ids)[:k]) and not v[::2].any()
+    np.testing.assert_allclose(l[::2], np.log(V_act), rtol=1e-6)
+    for m in some_rows(M):
+        z = hf[m] @ Wf.T
+        order = np.lexsort((ids, -z))[:k]
+        assert np.array_equal(i[m], ids[order]) and np.array_equal(v[m], z[order]), f"row {m}"

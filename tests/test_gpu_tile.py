@@ -1,10 +1,10 @@
-"""The head for a few hundred draft rows (128 x 128 tiles): both layouts at the edges of tiles, the ring
+"""The head for a few hundred draft rows (128 x 128 tiles): both layouts at the edges of tiles, both ring depths
 and the epilogue's paths.  Needs an MI355X: run with `-m gpu`."""
 import numpy as np
 import pytest
 
 import evospec_inputs as gi
-from helpers import check_head, new_matrix, to_dev_bf16, to_dev_i32
+from helpers import check_head, new_matrix, plan_route, to_dev_bf16, to_dev_i32
 from test_gpu_parity import ev, problem  # noqa: F401  (fixture and helper)
 
 pytestmark = pytest.mark.gpu
@@ -18,9 +18,17 @@ pytestmark = pytest.mark.gpu
     (1000, 320, 257, 16),     # five pairs, three row tiles, lists full
     (700, 576, 131, 33),      # k past the staged lists
     (300, 4096, 140, 64),     # the benchmark's hidden size, largest k
+    # more tiles than compute units: a ring of two stages, two workgroups to a unit
+    (20003, 320, 300, 10),    # five pairs, both sides ragged
+    (17000, 192, 200, 20),    # three pairs, lists of 32
+    (11500, 448, 257, 16),    # seven pairs, a row tile of one row
+    (33000, 256, 140, 10),    # four pairs
+    (33009, 64, 129, 10),     # a single pair
 ])
 def test_few_hundred_rows(ev, oracle_mod, layout, V_act, d, M, k):
     import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert plan_route(M, V_act, d, k, cus) == {"kernel": "tile", "stages": 2 if V_act > 10000 else 4}
     W, h, ids = problem(700 + V_act + d, V_act, d, M, V=V_act + 5)
     full = np.zeros((V_act + 5, d), dtype=np.uint16)
     full[ids] = W
