@@ -213,8 +213,9 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
     const uint16_t* hp = static_cast<const uint16_t*>(h);
     if (use_gemm(M, d)) {                               // bound by the contraction: all rows at once
         const GemmPlan gp = make_gemm_plan(M, V_act, k);
-        auto partials = use_small_tiles(M, V_act, d, k, num_cu) ? launch_tile_partials : launch_gemm_partials;
-        hipError_t e = partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed);
+        hipError_t e = use_small_tiles(M, V_act, d, k, num_cu)
+                           ? launch_tile_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu)
+                           : launch_gemm_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed);
         if (e != hipSuccess) return hip_fail(e);
         MergeSet a{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
         MergeSet none{};
@@ -322,8 +323,9 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     MergeSet core{};
     if (gemm_core) {
         const GemmPlan gp = make_gemm_plan(M, V_core, k);
-        auto partials = use_small_tiles(M, V_core, d, k, num_cu) ? launch_tile_partials : launch_gemm_partials;
-        hipError_t e = partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed);
+        hipError_t e = use_small_tiles(M, V_core, d, k, num_cu)
+                           ? launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu)
+                           : launch_gemm_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed);
         if (e != hipSuccess) return hip_fail(e);
         core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
     } else if (V_core > 0) {

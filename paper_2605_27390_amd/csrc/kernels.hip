@@ -922,8 +922,7 @@ hipError_t launch_partials_batch(const Plan& p, const void* h, const ChunkBatch&
                                  void* stats, hipStream_t stream) {
     if (cb.n < 1 || cb.n > kMaxChunks || bl.chunk_bytes % 8 != 0) return hipErrorInvalidValue;
     switch (p.nw) {
-#define EVOSPEC_SHAPE(TW_, RGW_, RC_, KS4_, KS2_)                                               \
-    static_assert(RGW_ == 1, "the kernel gives a wavefront one tile");                          \
+#define EVOSPEC_SHAPE(TW_, RC_, KS4_, KS2_)                                                     \
     case TW_: return launch_partials_shape<TW_, RC_, KS4_, KS2_>(p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream);
         EVOSPEC_SLAB_SHAPES(EVOSPEC_SHAPE)
 #undef EVOSPEC_SHAPE

@@ -1,7 +1,7 @@
 // Host-side launch planning for the active-vocabulary LM head (no HIP calls here).
 //
 // The restricted projection of Eq. 1 (EvoSpec paper) streams W_act once.  Rows of
-// W_act are cut into slabs of RT = 16 * NW * RGW rows; one workgroup of NW wavefronts
+// W_act are cut into slabs of RT = 16 * NW rows; one workgroup of NW wavefronts
 // handles one slab and leaves, per draft row, a partial (max, sum-exp, k best keys)
 // in the workspace.  This header decides the slab shape for a problem size and lays
 // out the workspace; both halves of the head (partials, merge) derive the same plan
@@ -20,8 +20,8 @@ constexpr int kRowsMinSlab = 64;    // smallest slab any plan uses (workspace up
 constexpr int kLdsLimit = 160 * 1024;
 constexpr int kRoundRows = 37;      // fixed cost of a round of workgroups, in slab rows (see make_plan)
 
-// Slab shapes that have a compiled kernel: X(nw, rgw, rc, ks4, ks2) with nw * rgw tiles of 16 rows per workgroup
-// (RT = 16 * nw * rgw rows per slab) and a W-operand ring of rc chunks of kKC hidden elements per lane.  (Measured
+// Slab shapes that have a compiled kernel: X(nw, rc, ks4, ks2) with nw tiles of 16 rows per workgroup
+// (RT = 16 * nw rows per slab) and a W-operand ring of rc chunks of kKC hidden elements per lane.  (Measured
 // on MI355X: more waves per CU beat a deeper ring per wave.)  ks4 / ks2: wavefronts that may share a tile with
 // four / two blocks of draft rows.  A workgroup with few tiles has too few wavefronts to hide the operand reads
 // and the trips to L2 for h, so several share a tile, up to 16 wavefronts in all (measured at 60 rows, all x
@@ -32,15 +32,15 @@ constexpr int kRoundRows = 37;      // fixed cost of a round of workgroups, in s
 // 24 rows, 51,446 x 512 17.4 -> 14.5; 32 rows, 124,638 x 1,536 72.1 -> 61.3; with four blocks 59,624 x 4,096 119 shared,
 // 124 not).
 #define EVOSPEC_SLAB_SHAPES(X) \
-    X(4, 1, 2, 4, 2) X(5, 1, 2, 2, 2) X(6, 1, 2, 2, 2) X(7, 1, 2, 2, 2) X(8, 1, 2, 2, 2) X(9, 1, 2, 1, 1) X(10, 1, 2, 1, 1) X(12, 1, 2, 1, 1)
-struct SlabShape { int nw; int rgw; int rc; int ks4; int ks2; };
-#define EVOSPEC_SHAPE_ENTRY(NW_, RGW_, RC_, KS4_, KS2_) {NW_, RGW_, RC_, KS4_, KS2_},
+    X(4, 2, 4, 2) X(5, 2, 2, 2) X(6, 2, 2, 2) X(7, 2, 2, 2) X(8, 2, 2, 2) X(9, 2, 1, 1) X(10, 2, 1, 1) X(12, 2, 1, 1)
+struct SlabShape { int nw; int rc; int ks4; int ks2; };
+#define EVOSPEC_SHAPE_ENTRY(NW_, RC_, KS4_, KS2_) {NW_, RC_, KS4_, KS2_},
 constexpr SlabShape kShapes[] = {EVOSPEC_SLAB_SHAPES(EVOSPEC_SHAPE_ENTRY)};
 #undef EVOSPEC_SHAPE_ENTRY
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 constexpr bool shapes_respect_min_slab() {
     for (int i = 0; i < kNumShapes; ++i)
-        if (16 * kShapes[i].nw * kShapes[i].rgw < kRowsMinSlab) return false;
+        if (16 * kShapes[i].nw < kRowsMinSlab) return false;
     return true;
 }
 static_assert(shapes_respect_min_slab(), "workspace_upper_bound assumes no slab below kRowsMinSlab rows");
@@ -76,7 +76,8 @@ inline size_t matrix_elems(size_t rows, int d, bool packed) {
     return packed ? packed_rows(rows) * (size_t)packed_d(d) : rows * (size_t)d;
 }
 
-// Whether a launch loads its weights past the caches (the slab kernel: of packed matrices only).  A set well below the 256 MB memory-side cache is
+// Whether a launch loads its weights past the caches (the slab kernel: of packed matrices whose rows are whole chunks
+// only).  A set well below the 256 MB memory-side cache is
 // still there when a decode loop comes back to it, and non-temporal loads find it more slowly (7,086 x
 // 1,536, 22 MB, 53 rows: 18.0 us with ordinary loads, 18.3 without); a larger one only drags itself through
 // (151,936 x 4,096 at one row 207 against 185 us, 36,864 x 4,096 at 60 rows 60.0 against 54.3, and against
@@ -130,8 +131,7 @@ struct InlineRows {
 };
 
 struct Plan {
-    int nw = 0, rgw = 0;     // tiles per workgroup: nw groups of rgw 16-row tiles
-    int rc = 0;              // chunks in the W-operand ring
+    int nw = 0;              // 16-row tiles per workgroup
     int ks = 1;              // wavefronts that share a tile, each a part of the hidden dimension
     int mb = 0;              // 16-row blocks of draft rows held in accumulators (1, 2 or 4)
     int rt = 0;              // slab rows
@@ -145,7 +145,7 @@ struct Plan {
 inline int mb_for_rows(int rows) { return rows <= 16 ? 1 : (rows <= 32 ? 2 : 4); }
 
 // Granularity of the selection groups in the slab epilogue.  A slab's logits for one draft row
-// sit 4*rgw per lane in 4*nw lanes; level 0 takes each lane as a group, level 1 pairs of lanes,
+// sit 4 per lane in 4*nw lanes; level 0 takes each lane as a group, level 1 pairs of lanes,
 // level 2 whole wavefronts (nw groups).  The k-th largest group maximum is a lower bound of the
 // slab's k-th best logit, so only entries at or above it need exact ranking.  Coarser groups cost
 // less to rank and filter almost as well: take the coarsest level with at least 1.5 k groups.
@@ -168,8 +168,8 @@ constexpr int list_stride(int rt) { return rt + 2; }
 // 13.8 and 13.0 / 12.7).
 constexpr bool fine_groups(int k, int nw) { return k >= 4 * nw; }
 
-inline size_t lds_bytes_for(int nw, int rgw, int mb, int k) {
-    const int rt = 16 * nw * rgw;
+inline size_t lds_bytes_for(int nw, int mb, int k) {
+    const int rt = 16 * nw;
     const int mrows = 16 * mb;
     size_t hs = 2ull * mrows * kHStride * 2;                 // h chunk, double buffered
     size_t list = (size_t)mrows * list_stride(rt) * 8;       // surviving keys per draft row
@@ -196,17 +196,17 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
     long best_cost = -1;
     const int mb = mb_for_rows(rows);
     for (int i = 0; i < kNumShapes; ++i) {
-        const int nw = kShapes[i].nw, rgw = kShapes[i].rgw;
-        const int rt = 16 * nw * rgw;
+        const int nw = kShapes[i].nw;
+        const int rt = 16 * nw;
         const int n_slabs = (V_act + rt - 1) / rt;
-        const size_t lds = lds_bytes_for(nw, rgw, mb, k);
+        const size_t lds = lds_bytes_for(nw, mb, k);
         if (lds > (size_t)kLdsLimit) continue;
         const long rounds = ((long)n_slabs * replicas + num_cu - 1) / num_cu;
         long cost = rounds * (rt + kRoundRows) * 8;
         if (((size_t)rt * (size_t)d * 2) % ((size_t)1 << 20) == 0) cost += cost / 8;
         if (best_cost < 0 || cost < best_cost || (cost == best_cost && rt > best.rt)) {
             best_cost = cost;
-            best.nw = nw; best.rgw = rgw; best.rc = kShapes[i].rc; best.mb = mb;
+            best.nw = nw; best.mb = mb;
             best.ks = !share || mb == 1 || (mb == 2 && rounds > 1) ? 1 : (mb == 2 ? kShapes[i].ks2 : kShapes[i].ks4);
             best.rt = rt; best.n_slabs = n_slabs;
             best.gl = group_level_for(k, nw); best.lds_bytes = lds;

@@ -146,15 +146,13 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
 }
 
 hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
-                                void* stats, hipStream_t stream, bool packed) {
+                                void* stats, hipStream_t stream, bool packed, int num_cu) {
     if (d % 64 != 0 || d < 64) return hipErrorInvalidValue;              // callers route such d elsewhere
     const int v_tiles = (V_act + kTV - 1) / kTV, m_tiles = (M + kTM - 1) / kTM;
     // more tiles than compute units: two workgroups with shallow rings share one, so that one computes while
     // the other starts or ends
-    int dev = 0, num_cu = 0;
+    int dev = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     const bool two = v_tiles * m_tiles > num_cu;
     auto kern = packed ? (two ? lmhead_tile_kernel<true, 2> : lmhead_tile_kernel<true, 4>)

@@ -23,8 +23,8 @@ int main() {
                         if (k > V_act) continue;
                         for (int replicas : {1, 16}) {
                             const Plan p = make_plan(rows, V_act, d, k, cu, replicas);
-                            REQUIRE(p.nw >= 4 && p.nw <= 12 && p.rgw == 1 && p.rc == 2, "shape nw=%d rgw=%d rc=%d", p.nw, p.rgw, p.rc);
-                            REQUIRE(p.rt == 16 * p.nw * p.rgw, "rt=%d", p.rt);
+                            REQUIRE(p.nw >= 4 && p.nw <= 12 && (p.ks == 1 || p.ks == 2 || p.ks == 4) && p.nw * p.ks <= 16 && p.mb % p.ks == 0, "shape nw=%d ks=%d", p.nw, p.ks);
+                            REQUIRE(p.rt == 16 * p.nw, "rt=%d", p.rt);
                             REQUIRE(p.mb == mb_for_rows(rows) && 16 * p.mb >= rows, "mb=%d rows=%d", p.mb, rows);
                             REQUIRE((long)p.n_slabs * p.rt >= V_act && (long)(p.n_slabs - 1) * p.rt < V_act, "slabs=%d rt=%d V_act=%d", p.n_slabs, p.rt, V_act);
                             REQUIRE(p.lds_bytes <= (size_t)kLdsLimit, "lds=%zu", p.lds_bytes);
