@@ -310,7 +310,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     const uint16_t* hp = static_cast<const uint16_t*>(h);
-    const bool gemm_core = V_core > 0 && use_gemm(M, d);
+    const bool gemm_core = V_core > 0 && use_gemm(M, d), one_set = V_core == 0 || V_arc == 0;
     const size_t core_stride = V_core > 0 ? workspace_upper_bound(V_core, k) : 0;
     const size_t arc_stride = V_arc > 0 ? workspace_upper_bound(V_arc, k) : 0;
     char* ws_arc = ws + (V_core > 0 ? core_workspace_bytes(M, d, V_core, k) : 0);
@@ -319,7 +319,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     // passes all use the plan of a full pass, so that one merge launch can address any of them.  Logits of the
     // core and of an extension meet in one result, where equal rows must tie: every kernel here sums the hidden
     // dimension front to back, so no tile is shared (with shared tiles in the extensions: 4 sequences, 197 rows,
-    // 16,384 + 1,000 rows x 4,096 77.4 us instead of 80.8; 16 x 60 rows the same).
+    // 16,384 + 1,000 rows x 4,096 77.4 us instead of 80.8; 16 x 60 rows the same), unless there is only one set.
     MergeSet core{};
     if (gemm_core) {
         const GemmPlan gp = make_gemm_plan(M, V_core, k);
@@ -329,7 +329,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         if (e != hipSuccess) return hip_fail(e);
         core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
     } else if (V_core > 0) {
-        const Plan pc = make_plan(kMTile, V_core, d, k, num_cu, 1, false);
+        const Plan pc = make_plan(kMTile, V_core, d, k, num_cu, 1, one_set);
         for (int m0 = 0, pss = 0; m0 < M; m0 += kMTile, ++pss) {
             const int rows = (M - m0) < kMTile ? (M - m0) : kMTile;
             char* w = ws + (size_t)pss * core_stride;
@@ -351,7 +351,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         for (int i = 0; i < cb.n; ++i) max_rows = cb.rows[i] > max_rows ? cb.rows[i] : max_rows;
         MergeSet arc{};
         if (V_arc > 0) {
-            const Plan pa = make_plan(max_rows, V_arc, d, k, num_cu, cb.n, false);
+            const Plan pa = make_plan(max_rows, V_arc, d, k, num_cu, cb.n, one_set);
             BatchLayout bl;
             bl.seq_rows = V_arc;
             bl.chunk_bytes = arc_stride;
