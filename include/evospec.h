@@ -56,7 +56,7 @@ typedef enum evospec_status {
  * Layouts of a compact active matrix (W_act, W_core, W_arc).  The paper does not say how the
  * restricted projection of Algorithm 1 ("draft restricted to V_t") keeps its weights; the layout
  * is this library's choice and the packed one is the fast one on MI355X (the head streams it with
- * whole-cache-line, fully coalesced loads; 0.70 against 0.64 of the HBM peak at 36,864 x 4,096).
+ * whole-cache-line, fully coalesced loads; 0.69 against 0.55 of the HBM peak at 36,864 x 4,096).
  *   EVOSPEC_ROW_MAJOR  bf16 [rows, d], as W_lm.
  *   EVOSPEC_PACKED     rows padded to a multiple of 16, d padded to dp = a multiple of 256 (pad
  *                      elements are zero).  The 16-byte piece c (elements 8c .. 8c+7) of row r is

@@ -1,17 +1,17 @@
-"""The head for up to 16 draft rows (hidden dimension dealt out to the wavefronts, h in registers): both
-layouts at the edges of tiles, units, rings and groups.  Needs an MI355X: run with `-m gpu`."""
+"""The head for up to 16 draft rows: both layouts at the edges of tiles, units, rings and groups of the few-row kernel
+(hidden dimension dealt out to the wavefronts, h in registers), and on both sides of the line to the slab kernel.
+Needs an MI355X: run with `-m gpu`."""
 import numpy as np
 import pytest
 
 import evospec_inputs as gi
-from helpers import check_head, new_matrix, to_dev_bf16, to_dev_i32
+from helpers import check_head, new_matrix, plan_route, to_dev_bf16, to_dev_i32
 from test_gpu_parity import ev, problem  # noqa: F401  (fixture and helper)
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("layout", ["packed", "row_major"])
-@pytest.mark.parametrize("V_act,d,M,k", [
+CASES = [
     (1, 8, 1, 1),             # one row, one 16-byte piece
     (16, 64, 16, 16),         # exactly one tile, k == rows
     (17, 72, 3, 10),          # a tile and a row; a unit and a piece
@@ -28,8 +28,25 @@ pytestmark = pytest.mark.gpu
     (4091, 3000, 15, 20),
     (49169, 264, 16, 64),     # all rows, 12 and 13 tiles to a workgroup: more than a round of slabs
     (50003, 776, 13, 33),
+    (3000, 2048, 5, 10),      # four, five and seven units to a wavefront
+    (5999, 2504, 8, 7),
+    (8001, 3504, 2, 10),
     (30000, 256, 8, 10),      # the other kernel: few hidden elements, many tiles
-])
+]
+
+
+def test_cases_reach_both_kernels(ev):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    few = [c for c in CASES if plan_route(c[2], c[0], c[1], c[3], cus)["kernel"] == "narrow"]
+    # every number of units per wavefront and ring depth, up to 8 rows and more, one tile to a workgroup and many
+    assert {-(-c[1] // 512) for c in few} >= set(range(1, 9))
+    assert any(c[2] > 8 and c[0] > 16 * cus for c in few) and any(c[2] > 8 and c[0] <= 16 * cus for c in few)
+    assert {c[2] for c in CASES if c not in few} >= {4, 8, 9, 16}
+
+
+@pytest.mark.parametrize("layout", ["packed", "row_major"])
+@pytest.mark.parametrize("V_act,d,M,k", CASES)
 def test_few_rows(ev, oracle_mod, layout, V_act, d, M, k):
     import torch
     W, h, ids = problem(500 + V_act + d, V_act, d, M, V=V_act + 5)
