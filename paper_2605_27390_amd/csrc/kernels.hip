@@ -211,7 +211,7 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 // rows, 32,256 x 2,048 42.9 -> 44.1 us for the head, full vocabulary 275 -> 280, and a set below 256 MB that is read
 // again at once loses what the memory-side cache holds of it, 60,000 x 2,048 59.6 -> 72.0; 24 rows gain, 36,864 x
 // 4,096 72.1 -> 68.0.)
-template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE>
+template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS>
 __global__ void __launch_bounds__(TW * KS * 64)
 lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int seq_rows,
                        size_t chunk_keys, size_t chunk_stats, int d,
@@ -250,7 +250,9 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     constexpr int LS = list_stride(RT);
     constexpr size_t hs_bytes = 2ull * MR * kHStride * 2;
     constexpr size_t list_bytes = (size_t)MR * list_stride(RT) * 8;
-    constexpr size_t u_bytes = align_up(hs_bytes > list_bytes ? hs_bytes : list_bytes, 16);
+    // (with two segments, the sums of the other one behind the h chunks: [NW][MB][64] f32x4)
+    constexpr size_t h_lev_bytes = hs_bytes + slab_level_bytes(NW, MB, SEGS);
+    constexpr size_t u_bytes = align_up(h_lev_bytes > list_bytes ? h_lev_bytes : list_bytes, 16);
     const bool fine = fine_groups(k, TW);                                     // (then GL is 0)
     const int NGS = fine ? 8 * TW : 4 * TW;                                   // row stride of gm
     float* gm = reinterpret_cast<float*>(smem + u_bytes);                     // [MR][NGS] group maxima
@@ -262,7 +264,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = (tid >> 6) / KS, kq = KS > 1 ? (tid >> 6) % KS : 0;          // this wavefront's tile, and its part of the k-steps
-    const int s0 = kq * KSTEPS;                                               // first of its k-steps in a chunk
+    const int s0 = kq * KSTEPS;                                               // first of its k-steps in a chunk of h in LDS
     const int n16 = lane & 15, g = lane >> 4;
     const int row0 = blockIdx.x * RT;
     const int n_valid = min(RT, V_act - row0);
@@ -286,10 +288,12 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Every workgroup takes the chunks in the same order: equal rows of different slabs must tie exactly.
-    // (Start chunks rotated by workgroup spread row-major rows a power of two apart over the memory channels,
-    // 36,864 x 4,096 at 60 rows 68.6 -> 59.1 us, but the order of a logit's sum then depends on its slab.)
+    // Every workgroup adds up a logit in the same order: equal rows of different slabs must tie exactly.  With two segments
+    // (segments_for) the chunks of either (c / 4 even, odd) are summed front to back by themselves and the two sums are added
+    // at the end.  A workgroup with cx = 4 takes the chunks c ^ 4, each four of the other segment first: both sums
+    // and the last addition are the same to the bit, but it is 2 KB away from the others in its rows.
     const int nchunks = (d + KC - 1) / KC;
+    const int cx = !PACKED && SEGS == 2 ? ((int)blockIdx.x & 1) * kSegChunks : 0;
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
     // chunks that h is requested ahead of its use (13 to 16 wavefronts have 128 registers each, which three pieces
     // per thread twice over exceed)
@@ -371,27 +375,27 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         constexpr bool STEADY = decltype(steady)::value;
         const bool pw = STEADY || (c + RC < nchunks);
         const bool ph = STEADY || (c + 1 < nchunks);
-        const int buf = c & 1;
+        const int buf = c & 1, cw = (c + RC) ^ cx;
         constexpr std::bool_constant<FULLK || STEADY> whole{};
         bf16x8 b0[MB], b1[MB];
-        if (STEADY || c + HA < nchunks) load_h(hreg[(SLOT + HA) % HA], c + HA, whole);
+        if (STEADY || c + HA < nchunks) load_h(hreg[(SLOT + HA) % HA], (c + HA) ^ cx, whole);
         load_b(b0, buf, 0);
 #pragma unroll
         for (int s = 0; s < KSTEPS; s += 2) {
             load_b(b1, buf, s + 1);
             __builtin_amdgcn_sched_barrier(0);
             mfma_step(SLOT * KSTEPS + s, b0);
-            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s, c + RC, s, whole);
+            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s, cw, s, whole);
             if (s + 2 < KSTEPS) load_b(b0, buf, s + 2);
             __builtin_amdgcn_sched_barrier(0);
             mfma_step(SLOT * KSTEPS + s + 1, b1);
-            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s + 1, c + RC, s + 1, whole);
+            if (PACKED && pw) load_w_step(SLOT * KSTEPS + s + 1, cw, s + 1, whole);
         }
         if (!PACKED && pw) {
             // row-major rows: the chunk's 8 requests go out together, so that the 512 bytes they
             // take from each row reach the memory side close in time (measured: 3.5 us of 73)
 #pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) load_w_step(SLOT * KSTEPS + s, c + RC, s, whole);
+            for (int s = 0; s < KSTEPS; ++s) load_w_step(SLOT * KSTEPS + s, cw, s, whole);
         }
         if (ph) store_h(hreg[(SLOT + 1) % HA], buf ^ 1);
         lds_barrier();
@@ -409,32 +413,54 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     static_assert(RC >= 1 && RC <= 4, "ring depth");
 
     constexpr std::bool_constant<FULLK> first{};
-    load_h(hreg[0], 0, first);
+    load_h(hreg[0], 0 ^ cx, first);
 #pragma unroll
     for (int i = 0; i < RC; ++i) {
         if (i < nchunks) {
 #pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) load_w_step(i * KSTEPS + s, i, s, first);
+            for (int s = 0; s < KSTEPS; ++s) load_w_step(i * KSTEPS + s, i ^ cx, s, first);
         }
     }
     for (int i = tid; i < MR * NGS; i += NT) gm[i] = -INFINITY;      // padding of the group-maximum rows
     if (tid < RT) Ids[tid] = id_reg;
     store_h(hreg[0], 0);
     if constexpr (HA > 1) {
-        if (nchunks > 1) load_h(hreg[1], 1, first);
+        if (nchunks > 1) load_h(hreg[1], 1 ^ cx, first);
     }
     lds_barrier();
     int c = 0;
     const int nwhole = d / KC;
-    for (; c + 2 * RC <= nwhole; c += RC) chunk_group(c, std::true_type{});      // every prefetch target exists, and whole
-    for (; c < nchunks; c += RC) chunk_group(c, std::false_type{});
+    // between two segments: the sum so far waits behind the h chunks, the other segment's goes on
+    f32x4* lev = reinterpret_cast<f32x4*>(smem + hs_bytes) + (size_t)(tid >> 6) * MB * 64 + lane;
+    auto turn = [&](int done) {
+        if (SEGS == 1 || (done & (kSegChunks - 1)) != 0 || done >= nchunks) return;      // (uniform)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const f32x4 other = done == kSegChunks ? f32x4{0.f, 0.f, 0.f, 0.f} : lev[mb * 64];
+            lev[mb * 64] = acc[mb];
+            acc[mb] = other;
+        }
+    };
+    static_assert(kSegChunks % RC == 0, "segments end with a turn of the ring");
+    for (; c + 2 * RC <= nwhole; c += RC) {                                      // every prefetch target exists, and whole
+        chunk_group(c, std::true_type{});
+        turn(c + RC);
+    }
+    for (; c < nchunks; c += RC) {
+        chunk_group(c, std::false_type{});
+        turn(c + RC);
+    }
+    if constexpr (SEGS == 2) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] += lev[mb * 64];
+    }
     // every wave is past its last read of Hs (the loop ends on a barrier): region U is free
 
     // ---- the wavefronts of a tile add up: wavefront kq keeps the blocks kq * MBW .. + MBW of draft rows, the
     // parts are added in the order of kq
     if constexpr (KS > 1) {
         f32x4* red = reinterpret_cast<f32x4*>(smem);               // [TW][KS][MB][64] (fits region U)
-        static_assert((size_t)TW * KS * MB * 1024 <= u_bytes, "partial sums fit region U");
+        static_assert((size_t)TW * KS * MB * 1024 <= hs_bytes, "partial sums fit the h chunks");
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) red[((size_t)(w * KS + kq) * MB + mb) * 64 + lane] = acc[mb];
         __syncthreads();
@@ -870,11 +896,11 @@ namespace evospec {
 namespace {
 constexpr int kMaxDevices = 64;
 
-template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE>
+template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS>
 hipError_t launch_partials_k(const Plan& p, const void* h, const ChunkBatch& cb, const BatchLayout& bl, int d,
                              const void* W, const int32_t* ids, int V_act, int k, void* keys, void* stats,
                              hipStream_t stream) {
-    auto kern = lmhead_partials_kernel<TW, KS, RC, MB, FULLK, PACKED, ONCE>;
+    auto kern = lmhead_partials_kernel<TW, KS, RC, MB, FULLK, PACKED, ONCE, SEGS>;
     static std::atomic<bool> attr_set[kMaxDevices] = {};      // concurrent first calls may both set the (idempotent) attribute
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -899,19 +925,25 @@ hipError_t launch_partials_shape(const Plan& p, const void* h, const ChunkBatch&
     const bool full = d % kKC == 0;
     const bool once = streams_once((size_t)V_act * (bl.seq_rows ? cb.n : 1), d, bl.packed);
 #define EVOSPEC_ARGS p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream
+#define EVOSPEC_FULL(MB_, KS_, SEGS_)                                                                           \
+    (!bl.packed ? launch_partials_k<TW, KS_, RC, MB_, true, false, false, SEGS_>(EVOSPEC_ARGS)                  \
+     : once     ? launch_partials_k<TW, KS_, RC, MB_, true, true, true, SEGS_>(EVOSPEC_ARGS)                    \
+                : launch_partials_k<TW, KS_, RC, MB_, true, true, false, SEGS_>(EVOSPEC_ARGS))
 #define EVOSPEC_MB(MB_, KS_)                                                                                    \
     if (p.mb == MB_ && p.ks == KS_) {                                                                           \
-        if (bl.packed)                                                                                          \
-            return !full ? launch_partials_k<TW, KS_, RC, MB_, false, true, false>(EVOSPEC_ARGS)               \
-                         : (once ? launch_partials_k<TW, KS_, RC, MB_, true, true, true>(EVOSPEC_ARGS)         \
-                                 : launch_partials_k<TW, KS_, RC, MB_, true, true, false>(EVOSPEC_ARGS));      \
-        return full ? launch_partials_k<TW, KS_, RC, MB_, true, false, false>(EVOSPEC_ARGS)                    \
-                    : launch_partials_k<TW, KS_, RC, MB_, false, false, false>(EVOSPEC_ARGS);                  \
+        if (!full)                                                                                              \
+            return bl.packed ? launch_partials_k<TW, KS_, RC, MB_, false, true, false, 1>(EVOSPEC_ARGS)         \
+                             : launch_partials_k<TW, KS_, RC, MB_, false, false, false, 1>(EVOSPEC_ARGS);       \
+        if constexpr (KS_ <= kSegMaxShare) {                                                                    \
+            if (p.segs == 2) return EVOSPEC_FULL(MB_, KS_, 2);                                                  \
+        }                                                                                                       \
+        return EVOSPEC_FULL(MB_, KS_, 1);                                                                       \
     }
     EVOSPEC_MB(1, 1) EVOSPEC_MB(2, 1) EVOSPEC_MB(4, 1)
     if constexpr (KS2 > 1) { EVOSPEC_MB(2, KS2) }
     if constexpr (KS4 > 1) { EVOSPEC_MB(4, KS4) }
 #undef EVOSPEC_MB
+#undef EVOSPEC_FULL
 #undef EVOSPEC_ARGS
     return hipErrorInvalidValue;
 }

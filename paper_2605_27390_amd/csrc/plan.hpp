@@ -133,6 +133,7 @@ struct InlineRows {
 struct Plan {
     int nw = 0;              // 16-row tiles per workgroup
     int ks = 1;              // wavefronts that share a tile, each a part of the hidden dimension
+    int segs = 1;            // segments of the hidden dimension (see segments_for)
     int mb = 0;              // 16-row blocks of draft rows held in accumulators (1, 2 or 4)
     int rt = 0;              // slab rows
     int n_slabs = 0;
@@ -168,16 +169,37 @@ constexpr int list_stride(int rt) { return rt + 2; }
 // 13.8 and 13.0 / 12.7).
 constexpr bool fine_groups(int k, int nw) { return k >= 4 * nw; }
 
-inline size_t lds_bytes_for(int nw, int mb, int k) {
+// LDS that holds the other segment's sums: an accumulator set of every wavefront.
+constexpr size_t slab_level_bytes(int wavefronts, int mb, int segs) { return segs == 2 ? (size_t)wavefronts * mb * 1024 : 0; }
+
+inline size_t lds_bytes_for(int nw, int mb, int k, int ks = 1, int segs = 1) {
     const int rt = 16 * nw;
     const int mrows = 16 * mb;
-    size_t hs = 2ull * mrows * kHStride * 2;                 // h chunk, double buffered
+    size_t hs = 2ull * mrows * kHStride * 2 + slab_level_bytes(nw * ks, mb, segs);   // h chunk, double buffered; segment sums
     size_t list = (size_t)mrows * list_stride(rt) * 8;       // surviving keys per draft row
     size_t u = hs > list ? hs : list;                        // the two never live together
     size_t gm = (size_t)mrows * (fine_groups(k, nw) ? 8 : 4) * nw * 4;   // group maxima
     size_t wsum = (size_t)nw * mrows * 4;                    // per-wave sum-exp
     size_t small = align_up((size_t)rt * 4, 16) + (size_t)mrows * 3 * 4;   // ids, tau, vmax, counters
     return align_up(u, 16) + gm + wsum + small;
+}
+
+// Segments of the hidden dimension in the slab kernel.  Rows of a row-major matrix that lie a multiple of 4 KB apart meet at
+// the same memory channels while all workgroups are at the same place of their rows; in two segments of alternating
+// 2 KB runs, half of the workgroups can take the other run first without a change of any sum (see the kernel).  Measured,
+// row-major, 60 draft rows unless said, one segment and two: 151,936 x 4,096 275 and 256 us, 36,864 x 4,096 74.6 and 68.2 (24
+// rows 69.0 and 62.7), 32,256 x 2,048 42.8 and 37.2, 60,000 x 2,048 72.8 and 66.1 (12 rows, 48,000 50.4 and 44.4).  Runs
+// of 4 KB or of 1 KB gain next to nothing (274, 259).  A packed matrix is summed alike, so that both layouts give the same bits (36,864 x
+// 4,096 61.2 and 61.4).  Only where the LDS has room for one set of sums, without costing a second workgroup on the
+// compute unit (which four blocks of draft rows have no registers for anyway).  Four wavefronts to a tile gain nothing (8,448 x
+// 4,096 35.1 and 35.2) and lose on a packed matrix (26.9 and 27.5).
+constexpr int kSegChunks = 4;
+constexpr int kSegMaxShare = 2;
+inline int segments_for(int nw, int ks, int mb, int d, int k, long rounds) {
+    if (d % (2 * kSegChunks * kKC) != 0 || ks > kSegMaxShare) return 1;
+    const size_t base = lds_bytes_for(nw, mb, k, ks);
+    const size_t limit = rounds > 1 && mb <= 2 && 2 * base <= (size_t)kLdsLimit ? kLdsLimit / 2 : kLdsLimit;
+    return lds_bytes_for(nw, mb, k, ks, 2) <= limit ? 2 : 1;
 }
 
 // Slab shape for V_act rows of d elements on a device with `num_cu` compute units: the least
@@ -209,7 +231,8 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
             best.nw = nw; best.mb = mb;
             best.ks = !share || mb == 1 || (mb == 2 && rounds > 1) ? 1 : (mb == 2 ? kShapes[i].ks2 : kShapes[i].ks4);
             best.rt = rt; best.n_slabs = n_slabs;
-            best.gl = group_level_for(k, nw); best.lds_bytes = lds;
+            best.segs = share ? segments_for(nw, best.ks, mb, d, k, rounds) : 1;
+            best.gl = group_level_for(k, nw); best.lds_bytes = lds_bytes_for(nw, mb, k, best.ks, best.segs);
         }
     }
     best.keys_off = 0;
