@@ -205,12 +205,10 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 //   part_stats[slab][m] = (max_i z, sum_i exp(z - max))         over the slab's rows
 //   part_keys[slab][m][0..k) = the slab's k best keys, descending (0 = none)
 // Logits never leave the CU.
-// ONCE (packed, see streams_once): the weights bypass the caches, 60.0 -> 54.3 us at 36,864 x 4,096 and 60 rows.  On a
-// row-major matrix a load takes half lines of 16 rows, the other half of which must be found in the caches again.
-// (Whole lines of 8 rows, permuted into operands within 16 lanes, past the caches: as fast or slower at 33 to 64
-// rows, 32,256 x 2,048 42.9 -> 44.1 us for the head, full vocabulary 275 -> 280, and a set below 256 MB that is read
-// again at once loses what the memory-side cache holds of it, 60,000 x 2,048 59.6 -> 72.0; 24 rows gain, 36,864 x
-// 4,096 72.1 -> 68.0.)
+// ONCE (see slab_streams_once): the weights bypass the caches, 60.0 -> 54.3 us at 36,864 x 4,096 and 60 rows.  On a
+// row-major matrix a load otherwise takes half lines of 16 rows, the other half of which must be found in the caches again; past
+// them it takes whole lines of 8 rows, permuted into operands within 16 lanes: full vocabulary 253 -> 244 us.  (Whole lines
+// through the caches gain nothing: 254.5, 32,256 x 2,048 37.0 -> 37.3, 24 rows, 36,864 x 4,096 62.1 -> 64.1.)
 template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS>
 __global__ void __launch_bounds__(TW * KS * 64)
 lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int seq_rows,
@@ -275,11 +273,20 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     int id_reg = 0x7fffffff;
     if (tid < RT && row0 + tid < V_act) id_reg = ids ? ids[row0 + tid] : row0 + tid;
 
-    const uint16_t* wp;
+    // Row-major rows past the caches: a load must take whole 128-byte lines (the other half of a line would be fetched
+    // again).  The first load of two k-steps takes the line of rows 0..7, the second that of rows 8..15, and permutes within
+    // 16 lanes make the operands (see pick_bank).
+    constexpr bool LINES = !PACKED && ONCE;
+    static_assert(!LINES || FULLK, "whole lines");
+    const uint16_t *wp, *wp8 = nullptr;
     if constexpr (PACKED) {
         // the wavefront's tile: 1 KB operand blocks in k-step order, lane l at byte 16 l
         const int tile = min((row0 >> 4) + w, (V_act - 1) >> 4);   // tail slab: a valid tile, masked later
         wp = W + (size_t)tile * kPackRows * dp + lane * 8;
+    } else if constexpr (LINES) {
+        const int row = row0 + w * 16 + (n16 & 7), c = 8 * g, c_hi = n16 & 8 ? 32 : 0;     // (row past the end: see below)
+        wp = W + (size_t)min(row, V_act - 1) * d + c + c_hi;
+        wp8 = W + (size_t)min(row + 8, V_act - 1) * d + c + (32 - c_hi);
     } else {
         wp = W + (size_t)min(row0 + w * 16 + n16, V_act - 1) * d + g * 8;   // tail slab: duplicate a valid row, masked later
     }
@@ -343,6 +350,8 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
         const int koff = c * KC + (s0 + s) * 32;
         if constexpr (PACKED) {
             wr[slot] = load_w((gvec_ptr)wp + (koff / 32) * 64);          // rows are padded to whole chunks
+        } else if constexpr (LINES) {
+            wr[slot] = load_w((gvec_ptr)((s & 1 ? wp8 - 32 : wp) + koff));
         } else {
             if constexpr (decltype(whole)::value) {
                 wr[slot] = load_w((gvec_ptr)(wp + koff));
@@ -359,7 +368,13 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
             b[mb] = *reinterpret_cast<const bf16x8*>(Hs + ((size_t)buf * MR + mb * 16 + n16) * kHStride + (s0 + s) * 32 + g * 8);
     };
     auto mfma_step = [&](int slot, const bf16x8 (&b)[MB]) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, wr[slot]);
+        u32x4 x = wr[slot];
+        if constexpr (LINES) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                x[i] = slot & 1 ? pick_bank_ror8(wr[slot & ~1][i], wr[slot | 1][i]) : pick_bank(wr[slot & ~1][i], wr[slot | 1][i]);
+        }
+        const bf16x8 a = __builtin_bit_cast(bf16x8, x);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[mb], acc[mb], 0, 0, 0);
     };
@@ -923,12 +938,13 @@ hipError_t launch_partials_shape(const Plan& p, const void* h, const ChunkBatch&
                                  const void* W, const int32_t* ids, int V_act, int k, void* keys, void* stats,
                                  hipStream_t stream) {
     const bool full = d % kKC == 0;
-    const bool once = streams_once((size_t)V_act * (bl.seq_rows ? cb.n : 1), d, bl.packed);
+    const bool once = slab_streams_once((size_t)V_act * (bl.seq_rows ? cb.n : 1), d, bl.packed);
 #define EVOSPEC_ARGS p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream
 #define EVOSPEC_FULL(MB_, KS_, SEGS_)                                                                           \
-    (!bl.packed ? launch_partials_k<TW, KS_, RC, MB_, true, false, false, SEGS_>(EVOSPEC_ARGS)                  \
-     : once     ? launch_partials_k<TW, KS_, RC, MB_, true, true, true, SEGS_>(EVOSPEC_ARGS)                    \
-                : launch_partials_k<TW, KS_, RC, MB_, true, true, false, SEGS_>(EVOSPEC_ARGS))
+    (bl.packed ? (once ? launch_partials_k<TW, KS_, RC, MB_, true, true, true, SEGS_>(EVOSPEC_ARGS)             \
+                       : launch_partials_k<TW, KS_, RC, MB_, true, true, false, SEGS_>(EVOSPEC_ARGS))           \
+               : (once ? launch_partials_k<TW, KS_, RC, MB_, true, false, true, SEGS_>(EVOSPEC_ARGS)            \
+                       : launch_partials_k<TW, KS_, RC, MB_, true, false, false, SEGS_>(EVOSPEC_ARGS)))
 #define EVOSPEC_MB(MB_, KS_)                                                                                    \
     if (p.mb == MB_ && p.ks == KS_) {                                                                           \
         if (!full)                                                                                              \

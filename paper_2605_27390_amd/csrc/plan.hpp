@@ -88,6 +88,15 @@ inline bool streams_once(size_t rows, int d, bool packed) {
     return (packed || d % 64 == 0) && matrix_elems(rows, d, packed) * 2 >= ((size_t)128 << 20);
 }
 
+// The slab kernel takes a row-major matrix past the caches only where too little of it is left in the memory-side cache when it is
+// read again (another matrix each time, then the same one again, through the caches and past them, x 4,096 at 60 rows: 151,936 rows
+// 253 and 244 us; 50,000 rows at 128, two passes, 208 and 198 again; 36,864 rows 67.2 and 64.2, again 63.7 and 65.2; 18,432 rows
+// 44.8 and 42.9, again 37.8 and 42.4; 60,000 x 2,048 66.3 and 65.3, again 58.1 and 63.1).
+constexpr size_t kSlabOnceMiB = 320;
+inline bool slab_streams_once(size_t rows, int d, bool packed) {
+    return packed ? streams_once(rows, d, true) : d % kKC == 0 && rows * (size_t)d * 2 >= (kSlabOnceMiB << 20);
+}
+
 // One dynamic-buffer update: n rows W_act[slots[i]] <- W_lm[src_ids[i]], act_ids[slots[i]] <- src_ids[i]
 // (slots == nullptr: slot i).  Device pointers; row_vec = d / 8.  packed: layout of W_act (W_lm is
 // always row-major).
