@@ -214,8 +214,8 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
     if (use_gemm(M, d)) {                               // bound by the contraction: all rows at once
         const GemmPlan gp = make_gemm_plan(M, V_act, k);
         hipError_t e = use_small_tiles(M, V_act, d, k, num_cu)
-                           ? launch_tile_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu)
-                           : launch_gemm_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed);
+                           ? launch_tile_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, {})
+                           : launch_gemm_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, {});
         if (e != hipSuccess) return hip_fail(e);
         MergeSet a{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
         MergeSet none{};
@@ -321,37 +321,58 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     // dimension front to back, so no tile is shared (with shared tiles in the extensions: 4 sequences, 197 rows,
     // 16,384 + 1,000 rows x 4,096 77.4 us instead of 80.8; 16 x 60 rows the same), unless there is only one set.
     MergeSet core{};
-    if (gemm_core) {
-        const GemmPlan gp = make_gemm_plan(M, V_core, k);
-        hipError_t e = use_small_tiles(M, V_core, d, k, num_cu)
-                           ? launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu)
-                           : launch_gemm_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed);
-        if (e != hipSuccess) return hip_fail(e);
-        core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
-    } else if (V_core > 0) {
-        const Plan pc = make_plan(kMTile, V_core, d, k, num_cu, 1, one_set);
-        for (int m0 = 0, pss = 0; m0 < M; m0 += kMTile, ++pss) {
-            const int rows = (M - m0) < kMTile ? (M - m0) : kMTile;
-            char* w = ws + (size_t)pss * core_stride;
-            hipError_t e = launch_partials(pc, hp + (size_t)m0 * d, rows, d, W_core, ids_core, V_core, k,
-                                           w + pc.keys_off, w + pc.stats_off, st, packed);
+    auto launch_core = [&](const RowBound& bound) -> int {
+        if (gemm_core) {
+            const GemmPlan gp = make_gemm_plan(M, V_core, k);
+            hipError_t e = use_small_tiles(M, V_core, d, k, num_cu)
+                               ? launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, bound)
+                               : launch_gemm_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, bound);
             if (e != hipSuccess) return hip_fail(e);
+            core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
+        } else if (V_core > 0) {
+            const Plan pc = make_plan(kMTile, V_core, d, k, num_cu, 1, one_set);
+            for (int m0 = 0, pss = 0; m0 < M; m0 += kMTile, ++pss) {
+                const int rows = (M - m0) < kMTile ? (M - m0) : kMTile;
+                char* w = ws + (size_t)pss * core_stride;
+                hipError_t e = launch_partials(pc, hp + (size_t)m0 * d, rows, d, W_core, ids_core, V_core, k,
+                                               w + pc.keys_off, w + pc.stats_off, st, packed);
+                if (e != hipSuccess) return hip_fail(e);
+            }
+            core = MergeSet{ws + pc.keys_off, ws + pc.stats_off, pc.n_slabs, 0, kMTile};
         }
-        core = MergeSet{ws + pc.keys_off, ws + pc.stats_off, pc.n_slabs, 0, kMTile};
-    }
+        return EVOSPEC_OK;
+    };
 
     // per sequence: its rows against its own extension, then the merge of both partial sets,
     // kMaxChunks chunks per launch.  A chunk has at most 64 rows and, with 64-row core passes,
     // never crosses a pass boundary, so its core partials sit in one pass.
     ChunkBatch cb;
     cb.n = 0;
-    auto flush = [&]() -> int {
+    bool core_done = false;
+    auto flush = [&](bool all) -> int {
         if (cb.n == 0) return EVOSPEC_OK;
         int max_rows = 0;
         for (int i = 0; i < cb.n; ++i) max_rows = cb.rows[i] > max_rows ? cb.rows[i] : max_rows;
+        const Plan pa = V_arc > 0 ? make_plan(max_rows, V_arc, d, k, num_cu, cb.n, one_set) : Plan{};
+        // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there.
+        RowBound bound;
+        if (V_arc > 0 && gemm_core && all) {
+            choose_bound(&bound, pa.n_slabs, k);
+            if (bound.q > 0) {
+                bound.keys = reinterpret_cast<const unsigned long long*>(ws_arc + pa.keys_off);
+                bound.chunk_keys = arc_stride / 8;
+                bound.n_chunks = cb.n;
+                for (int i = 0; i < cb.n; ++i) bound.m0[i] = cb.m0[i];
+            }
+        }
+        const bool arc_first = bound.n_chunks > 0;
+        if (!arc_first && !core_done) {
+            const int rc2 = launch_core(bound);
+            if (rc2) return rc2;
+            core_done = true;
+        }
         MergeSet arc{};
         if (V_arc > 0) {
-            const Plan pa = make_plan(max_rows, V_arc, d, k, num_cu, cb.n, one_set);
             BatchLayout bl;
             bl.seq_rows = V_arc;
             bl.chunk_bytes = arc_stride;
@@ -361,15 +382,26 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
             if (e != hipSuccess) return hip_fail(e);
             arc = MergeSet{ws_arc + pa.keys_off, ws_arc + pa.stats_off, pa.n_slabs, 0, kMTile};
         }
+        if (arc_first) {
+            const int rc2 = launch_core(bound);
+            if (rc2) return rc2;
+            core_done = true;
+        }
         hipError_t e = launch_merge_batch(core, core_stride, arc, arc_stride, cb, k, out_vals, out_ids, out_logz, st);
         if (e != hipSuccess) return hip_fail(e);
         cb.n = 0;
         return EVOSPEC_OK;
     };
+    bool flushed = false;
     for (int s = 0; s < S; ++s) {
         int m0 = row_off[s];
         const int m_end = row_off[s + 1];
         while (m0 < m_end) {
+            if (cb.n == kMaxChunks) {
+                const int rc2 = flush(false);
+                if (rc2) return rc2;
+                flushed = true;
+            }
             const int pass = m0 / kMTile;
             const int piece_end = gemm_core ? m0 + kMTile : (pass + 1) * kMTile;
             const int rows = (m_end < piece_end ? m_end : piece_end) - m0;
@@ -377,14 +409,10 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
             cb.m0[i] = m0; cb.rows[i] = rows; cb.seq[i] = s;
             cb.a_pass[i] = gemm_core ? 0 : pass;
             cb.a_slot[i] = gemm_core ? m0 : m0 - pass * kMTile;
-            if (cb.n == kMaxChunks) {
-                const int rc2 = flush();
-                if (rc2) return rc2;
-            }
             m0 += rows;
         }
     }
-    return flush();
+    return flush(!flushed);
 }
 
 int evospec_kl_gate_workspace_bytes(int E, int V, size_t* out_bytes) {

@@ -35,8 +35,10 @@ constexpr int kGStageBytes = 2 * kGOperandBytes;              // W_act rows, the
 constexpr size_t kGLds = (size_t)kGStages * kGStageBytes;     // 128 KB
 constexpr size_t kGLdsTotal = kGLds > 4ull * epi_bytes(8) ? kGLds : 4ull * epi_bytes(8);
 
+constexpr size_t kGLdsAll = kGLdsTotal + kGemmTile * 4;       // and the draft rows' bounds
+
 static_assert(kGLds <= (size_t)kLdsLimit, "operand ring exceeds the LDS of a compute unit");
-static_assert(kGLdsTotal <= (size_t)kLdsLimit, "epilogue lists exceed the LDS of a compute unit");
+static_assert(kGLdsAll <= (size_t)kLdsLimit, "epilogue lists exceed the LDS of a compute unit");
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
@@ -59,7 +61,7 @@ template <bool PACKED>
 __global__ void __launch_bounds__(256, 1)
 lmhead_gemm_kernel(const uint16_t* __restrict__ h, int M, int d,
                    const uint16_t* __restrict__ W, const int32_t* __restrict__ ids, int V_act, int k, int list_len,
-                   int m_tiles, u64* __restrict__ part_keys, float2* __restrict__ part_stats) {
+                   int m_tiles, u64* __restrict__ part_keys, float2* __restrict__ part_stats, RowBound bound) {
     extern __shared__ __align__(16) unsigned char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -162,6 +164,9 @@ lmhead_gemm_kernel(const uint16_t* __restrict__ h, int M, int d,
     for (int p = 0; p < 2; ++p)
 #pragma unroll
         for (int j = 0; j < 16; ++j) issue_one(p, j);
+    // the draft rows' bounds, if there are any, while these loads are under way
+    float* bnd = reinterpret_cast<float*>(smem + kGLdsTotal);
+    if (bound.n_chunks) bnd[tid] = row_bound(bound, m0 + tid, M);
     // pair 0 must have landed before its operands are read
     asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
 #pragma unroll
@@ -181,11 +186,12 @@ lmhead_gemm_kernel(const uint16_t* __restrict__ h, int M, int d,
     const int vrow0 = v0 + wv * kGemmSlab;
     if (vrow0 >= V_act) return;                                    // quadrant wholly past the active set
     slab_epilogue<8>(acc, smem + (size_t)w * epi_bytes(8), vrow0, m0 + wm * 128, M, V_act, ids, k, list_len,
-                     tile_v * (kGemmTile / kGemmSlab) + wv, (V_act + kGemmSlab - 1) / kGemmSlab, part_keys, part_stats);
+                     tile_v * (kGemmTile / kGemmSlab) + wv, (V_act + kGemmSlab - 1) / kGemmSlab,
+                     bound.n_chunks ? bnd + wm * 128 : nullptr, part_keys, part_stats);
 }
 
 hipError_t launch_gemm_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act,
-                                int k, void* keys, void* stats, hipStream_t stream, bool packed) {
+                                int k, void* keys, void* stats, hipStream_t stream, bool packed, const RowBound& bound) {
     const int v_tiles = (V_act + kGemmTile - 1) / kGemmTile;
     const int m_tiles = (M + kGemmTile - 1) / kGemmTile;
     if (d % (2 * kGK) != 0 || d < 2 * kGK) return hipErrorInvalidValue;      // callers route such d elsewhere
@@ -198,14 +204,14 @@ hipError_t launch_gemm_partials(const void* h, int M, int d, const void* W, cons
     if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
         for (auto kf : {lmhead_gemm_kernel<true>, lmhead_gemm_kernel<false>}) {
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(kf),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGLdsTotal);
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGLdsAll);
             if (e != hipSuccess) return e;
         }
         if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(v_tiles * m_tiles), dim3(256), kGLdsTotal, stream,
+    hipLaunchKernelGGL(kern, dim3(v_tiles * m_tiles), dim3(256), kGLdsAll, stream,
                        static_cast<const uint16_t*>(h), M, d, static_cast<const uint16_t*>(W), ids, V_act, k, gemm_list_len(k),
-                       m_tiles, static_cast<u64*>(keys), static_cast<float2*>(stats));
+                       m_tiles, static_cast<u64*>(keys), static_cast<float2*>(stats), bound);
     return hipGetLastError();
 }
 

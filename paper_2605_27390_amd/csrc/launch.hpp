@@ -49,10 +49,10 @@ hipError_t launch_narrow_partials(const NarrowPlan& p, const void* h, int M, int
 // Large-M path: partials of all M draft rows, row-major: keys u64 [M][ceil(V_act/128)][gemm_list_len(k)]
 // in any order, stats float2 [M][ceil(V_act/128)].
 hipError_t launch_gemm_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act,
-                                int k, void* keys, void* stats, hipStream_t stream, bool packed = false);
+                                int k, void* keys, void* stats, hipStream_t stream, bool packed, const RowBound& bound);
 // The same partials from 128 x 128 tiles, on num_cu compute units.
 hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
-                                void* stats, hipStream_t stream, bool packed, int num_cu);
+                                void* stats, hipStream_t stream, bool packed, int num_cu, const RowBound& bound);
 hipError_t launch_merge(const MergeSet& a, const MergeSet& b, int k, float* out_vals, int32_t* out_ids,
                         float* out_logz, int out_row0, int nrows, hipStream_t stream,
                         const GatherArgs* update = nullptr);

@@ -330,6 +330,34 @@ inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu) {
     return (double)rounds(kGemmSlab, kTileRows) < tile_cost * (double)rounds(kGemmTile, kGemmTile);
 }
 
+// A bound of every draft row for the matrix-tile kernels, from sorted lists of other candidates of the row that
+// are there already (the extensions of the batched head): every list's q-th best is reached by q logits, so the
+// `sets`-th largest of them is reached by k when q * sets >= k, and no core logit below it can be among the row's k
+// best.  The lists of a row lie as the slab kernel leaves them, per chunk of draft rows.
+constexpr int kBoundLists = 16;          // lists that are looked at (all lists' bound is hardly better)
+struct RowBound {
+    const unsigned long long* keys = nullptr;
+    size_t chunk_keys = 0;               // keys between two chunks
+    int n_lists = 0, q = 0, sets = 0, k = 0;
+    int n_chunks = 0;                    // 0: no bound
+    int m0[kMaxChunks];                  // first draft row of each chunk
+};
+// q and sets for n_lists lists, or q = 0 where the bound would be hardly better than the one that a slab finds by itself (reached by some
+// 11 of its 128 logits).  With 3 sets to 4 lists of R rows each about 1.4 / R of all logits reach the bound for q = 1, twice
+// as many for q = 2.  Without and with the bound, us for the call: 16 x 60 rows, 32,768 + 2,048 rows x 4,096, k = 10 (15 lists) 304
+// and 297; 800 rows, 32,768 + 700, k = 4 (10 lists) 269 and 258; 197 rows, 16,384 + 1,000 (16) 77.8 and 77.4; 300 rows,
+// 8,192 + 512 x 2,048 (8 lists, q = 2) 45.7 and 44.9; 300 rows, 20,000 + 2,048, k = 16 (15 lists, q = 2) 157 and 115,
+// since a slab's own bound leaves more than a list of 16 holds.  Past k = 16 the lists are longer than the tiles stage.
+inline void choose_bound(RowBound* b, int n_lists, int k) {
+    b->n_lists = n_lists < kBoundLists ? n_lists : kBoundLists;
+    b->k = k;
+    b->q = 0;
+    for (int q = 1; q <= 2 && k <= 16; ++q) {
+        const int sets = (k + q - 1) / q;
+        if (4 * sets <= 3 * b->n_lists) { b->q = q; b->sets = sets; return; }
+    }
+}
+
 struct GemmPlan {
     int n_slabs = 0;
     int list_len = 0;

@@ -13,10 +13,12 @@ namespace evospec {
 
 constexpr int kGFastLen = 16;                 // list length the staged common path of the epilogue handles
 // LDS per wavefront: the staged lists and spare slots of the common path, or a block's parked logits; then ids
-constexpr int epi_bytes(int nmb) {
+constexpr int epi_lists(int nmb) {
     const int common = nmb * 16 * kGFastLen * 8 + 64 * 8, rare = 64 * 32 * 4;
-    return (common > rare ? common : rare) + kGemmSlab * 4;
+    return common > rare ? common : rare;
 }
+// and the logits of a block, where survivors are picked one by one
+constexpr int epi_bytes(int nmb) { return epi_lists(nmb) + 64 * 32 * 4 + kGemmSlab * 4; }
 
 // Accumulators are pinned to the accumulation registers: the register allocator must
 // not be left to shuffle them through the other file or among themselves.  (The compiler does not see that
@@ -83,12 +85,42 @@ __device__ __forceinline__ void quad_all(uint32_t x, uint32_t (&q)[4]) {
     q[0] = e[0]; q[1] = o[0]; q[2] = e[1]; q[3] = o[1];
 }
 
+// The bound of draft row `row` (-inf: none; +inf for rows past the last): see RowBound.
+__device__ __forceinline__ float row_bound(const RowBound& b, int row, int M) {
+    if (row >= M) return INFINITY;
+    int c = 0, first = 0;
+    for (int i = 1; i < b.n_chunks; ++i)
+        if (b.m0[i] <= row) { c = i; first = b.m0[i]; }
+    const u64* p = b.keys + (size_t)c * b.chunk_keys + (size_t)(row - first) * b.k + (b.q - 1);
+    uint32_t v[kBoundLists];
+#pragma unroll
+    for (int i = 0; i < kBoundLists; ++i) v[i] = i < b.n_lists ? (uint32_t)(p[(size_t)i * kMTile * b.k] >> 32) : 0u;
+    // Batcher's odd-even merge sort, descending
+#pragma unroll
+    for (int n = 1; n < kBoundLists; n *= 2)
+#pragma unroll
+        for (int m = n; m >= 1; m /= 2)
+#pragma unroll
+            for (int x = 0; x + m < kBoundLists; ++x)
+                if (x >= m % n && ((x - m % n) / m) % 2 == 0 && x / (2 * n) == (x + m) / (2 * n)) {
+                    const uint32_t hi = v[x] > v[x + m] ? v[x] : v[x + m];
+                    v[x + m] = v[x] > v[x + m] ? v[x + m] : v[x];
+                    v[x] = hi;
+                }
+    uint32_t t = 0;
+#pragma unroll
+    for (int i = 0; i < kBoundLists; ++i) t = i == b.sets - 1 ? v[i] : t;
+    // (0: fewer lists hold q keys; above infinity: NaN, which bounds nothing)
+    return t != 0u && t <= 0xff800000u ? ordered_to_f32(t) : -INFINITY;
+}
+
 // acc[rg][mb]: lane (n16, g) holds the logits of the active rows vrow0 + 16 rg + 4 g + 0..3 and draft row
 // mbase + 16 mb + n16.  `my`: epi_bytes(NMB) of LDS of this wavefront alone.  Lists are laid out [draft
-// row][slab][slot].  NMB <= 8.
+// row][slab][slot].  NMB <= 8.  bnd (or null): in LDS, for each of the draft rows a value that k logits elsewhere reach, so
+// that none below it can be among the row's k best; few enough reach it that the slab needs no bound of its own.
 template <int NMB>
 __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned char* my, int vrow0, int mbase, int M, int V_act,
-                                              const int32_t* __restrict__ ids, int k, int list_len, int slab, int n_slabs,
+                                              const int32_t* __restrict__ ids, int k, int list_len, int slab, int n_slabs, const float* bnd,
                                               u64* __restrict__ part_keys, float2* __restrict__ part_stats) {
     const int lane = threadIdx.x & 63, n16 = lane & 15, g = lane >> 4;
     const int nvalid = min(kGemmSlab, V_act - vrow0);
@@ -166,11 +198,15 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
     // -- phase 2: lower bound of every row's k-th best logit.  Each lane sorts its 8 group maxima;
     // k rounds then take the largest head of the row's 4 lanes and pop it wherever it is the head:
     // at least k group maxima, hence k logits, reach the last value taken.  With more than 32
-    // wanted, or fewer groups than k, the bound stays at -inf and every valid entry is kept.
+    // wanted, or fewer groups than k, the bound stays at -inf and every valid entry is kept.  A bound from elsewhere is
+    // tighter than that and costs nothing here.
     float tau[NMB];
 #pragma unroll
     for (int mb = 0; mb < NMB; ++mb) tau[mb] = -INFINITY;
-    if (k <= 32) {
+    if (bnd) {                                                     // (uniform)
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) tau[mb] = bnd[16 * mb + n16];
+    } else if (k <= 32) {
 #define EVOSPEC_CE(I, J) { float hi[NMB]; EVOSPEC_MB(hi[mb] = fmaxf(t[mb][I], t[mb][J])) \
                            EVOSPEC_MB(t[mb][J] = fminf(t[mb][I], t[mb][J])) EVOSPEC_MB(t[mb][I] = hi[mb]) }
         EVOSPEC_CE(0, 1) EVOSPEC_CE(2, 3) EVOSPEC_CE(4, 5) EVOSPEC_CE(6, 7)
@@ -257,12 +293,6 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
     bool rare = false;
 
     repin();
-    int32_t idv[32];                                               // full-vocabulary ids of the lane's entries
-#pragma unroll
-    for (int rg = 0; rg < 8; ++rg) {
-        const int4 q = *reinterpret_cast<const int4*>(Ids + rg * 16 + 4 * g);
-        idv[4 * rg + 0] = q.x; idv[4 * rg + 1] = q.y; idv[4 * rg + 2] = q.z; idv[4 * rg + 3] = q.w;
-    }
     // -- phase 4: the survivors of every row, as (logit, id) pairs in no particular order, are
     // gathered into the row's 16-slot list in LDS (empty slots: all ones) and the lists copied to the
     // workspace a full line at a time; the merge ranks.  No branch or compare per entry: an entry
@@ -284,17 +314,47 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
             rel[mb] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u64*)(flist + (mb * 16 + n16) * kGFastLen + base) - spare_a;
         }
         EVOSPEC_FENCE();
+        if (bnd) {
+            // Few survivors (about one to a row): block by block the logits are laid out in LDS, where each lane picks
+            // its own survivors one after the other.  (Both this and the bound: 16 x 60 rows over 32,768 + 2,048 rows x 4,096
+            // 304 -> 297 us for the call.)
+            unsigned char* zl = my + epi_lists(NMB) + lane * 16;       // [8][64] f32x4
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            uint32_t at[NMB], sel[NMB];
-            EVOSPEC_MB(at[mb] = mk[mb] & ((1u << i) - 1u))
-            EVOSPEC_MB(at[mb] = __popc(at[mb]))
-            EVOSPEC_MB(sel[mb] = (uint32_t)__builtin_amdgcn_sbfe((int)mk[mb], i, 1))
-            EVOSPEC_MB(at[mb] = rel[mb] + 8u * at[mb])
-            EVOSPEC_MB(at[mb] &= sel[mb])
-            EVOSPEC_MB(at[mb] += spare_a)
-            EVOSPEC_MB(*(__attribute__((address_space(3))) u64*)(uintptr_t)at[mb] =
-                           ((u64)__float_as_uint(acc[i >> 2][mb][i & 3]) << 32) | (uint32_t)idv[i])
+            for (int mb = 0; mb < NMB; ++mb) {
+#pragma unroll
+                for (int rg = 0; rg < 8; ++rg) *reinterpret_cast<f32x4*>(zl + rg * 1024) = acc[rg][mb];
+                uint32_t m = mk[mb], at = spare_a + rel[mb];
+                while (__ballot(m != 0u) != 0) {
+                    if (m != 0u) {
+                        const int i = __builtin_ctz(m);
+                        m &= m - 1;
+                        const uint32_t z = *reinterpret_cast<const uint32_t*>(zl + (i >> 2) * 1024 + (i & 3) * 4);
+                        const uint32_t id = (uint32_t)Ids[16 * (i >> 2) + 4 * g + (i & 3)];
+                        *(__attribute__((address_space(3))) u64*)(uintptr_t)at = ((u64)z << 32) | id;
+                        at += 8;
+                    }
+                }
+            }
+        } else {
+            int32_t idv[32];                                               // full-vocabulary ids of the lane's entries
+#pragma unroll
+            for (int rg = 0; rg < 8; ++rg) {
+                const int4 q = *reinterpret_cast<const int4*>(Ids + rg * 16 + 4 * g);
+                idv[4 * rg + 0] = q.x; idv[4 * rg + 1] = q.y; idv[4 * rg + 2] = q.z; idv[4 * rg + 3] = q.w;
+            }
+            repin();                                               // (or the logits are read out of their registers for both branches at once, and spilled)
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {
+                uint32_t at[NMB], sel[NMB];
+                EVOSPEC_MB(at[mb] = mk[mb] & ((1u << i) - 1u))
+                EVOSPEC_MB(at[mb] = __popc(at[mb]))
+                EVOSPEC_MB(sel[mb] = (uint32_t)__builtin_amdgcn_sbfe((int)mk[mb], i, 1))
+                EVOSPEC_MB(at[mb] = rel[mb] + 8u * at[mb])
+                EVOSPEC_MB(at[mb] &= sel[mb])
+                EVOSPEC_MB(at[mb] += spare_a)
+                EVOSPEC_MB(*(__attribute__((address_space(3))) u64*)(uintptr_t)at[mb] =
+                               ((u64)__float_as_uint(acc[i >> 2][mb][i & 3]) << 32) | (uint32_t)idv[i])
+            }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         // piece p = 64 it + lane of the staged lists: block p / 128, row (p / 8) % 16, 16 bytes p % 8

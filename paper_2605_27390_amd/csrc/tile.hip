@@ -31,7 +31,7 @@ constexpr int kTOperand = 128 * 128;                           // bytes of one o
 constexpr int kTStage = 2 * kTOperand;
 constexpr size_t tile_lds(int stages) {
     const size_t ring = (size_t)stages * kTStage, epi = 4ull * epi_bytes(2);
-    return ring > epi ? ring : epi;
+    return (ring > epi ? ring : epi) + kTM * 4;                // and the draft rows' bounds
 }
 static_assert(kTV == 128 && kTM == 128, "the load and operand offsets below assume it");
 static_assert(tile_lds(4) <= (size_t)kLdsLimit && 2 * tile_lds(2) <= (size_t)kLdsLimit, "one deep or two shallow rings per compute unit");
@@ -48,7 +48,7 @@ template <bool PACKED, int S>
 __global__ void __launch_bounds__(256, S > 2 ? 1 : 2)
 lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t* __restrict__ W,
                    const int32_t* __restrict__ ids, int V_act, int k, int list_len, int m_tiles,
-                   u64* __restrict__ part_keys, float2* __restrict__ part_stats) {
+                   u64* __restrict__ part_keys, float2* __restrict__ part_stats, RowBound bound) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -126,6 +126,9 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
     for (int p = 0; p < S; ++p)
 #pragma unroll
         for (int j = 0; j < 8; ++j) issue(p, j);
+    // the draft rows' bounds, if there are any, while these loads are under way
+    float* bnd = reinterpret_cast<float*>(smem + tile_lds(S) - kTM * 4);
+    if (bound.n_chunks && tid < kTM) bnd[tid] = row_bound(bound, m0 + tid, M);
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(8 * (S - 1)) : "memory");      // pair 0 has landed, for every wavefront
 #pragma unroll
     for (int i = 0; i < 2; ++i) read_b(S0{}, 0, i);
@@ -142,11 +145,11 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
     // the last MFMAs drain before the accumulators are read; the ring is dead once the trailing loads have landed and every wavefront is here
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     slab_epilogue<2>(acc, smem + (size_t)w * epi_bytes(2), v0, m0 + w * 32, M, V_act, ids, k, list_len, tile_v,
-                     (V_act + kGemmSlab - 1) / kGemmSlab, part_keys, part_stats);
+                     (V_act + kGemmSlab - 1) / kGemmSlab, bound.n_chunks ? bnd + w * 32 : nullptr, part_keys, part_stats);
 }
 
 hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
-                                void* stats, hipStream_t stream, bool packed, int num_cu) {
+                                void* stats, hipStream_t stream, bool packed, int num_cu, const RowBound& bound) {
     if (d % 64 != 0 || d < 64) return hipErrorInvalidValue;              // callers route such d elsewhere
     const int v_tiles = (V_act + kTV - 1) / kTV, m_tiles = (M + kTM - 1) / kTM;
     // more tiles than compute units: two workgroups with shallow rings share one, so that one computes while
@@ -168,7 +171,7 @@ hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, cons
     }
     hipLaunchKernelGGL(kern, dim3(v_tiles * m_tiles), dim3(256), tile_lds(two ? 2 : 4), stream, static_cast<const uint16_t*>(h), M, d,
                        static_cast<const uint16_t*>(W), ids, V_act, k, gemm_list_len(k), m_tiles, static_cast<u64*>(keys),
-                       static_cast<float2*>(stats));
+                       static_cast<float2*>(stats), bound);
     return hipGetLastError();
 }
 
