@@ -300,7 +300,11 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int se
     // at the end.  A workgroup with cx = 4 takes the chunks c ^ 4, each four of the other segment first: both sums
     // and the last addition are the same to the bit, but it is 2 KB away from the others in its rows.
     const int nchunks = (d + KC - 1) / KC;
-    const int cx = !PACKED && SEGS == 2 ? ((int)blockIdx.x & 1) * kSegChunks : 0;
+    // (Every other workgroup; every other pair where slabs are a power of two high, whose places in memory alternate by themselves:
+    // 32,256 x 2,048 in slabs of 128 rows 38.3 to 40.9 us by where the matrix lies, by pairs 38.1; 24,000 x 2,048 in slabs of 96
+    // 31.5, by pairs 32.9.)
+    constexpr int kTurnBit = (TW & (TW - 1)) == 0 ? 1 : 0;
+    const int cx = !PACKED && SEGS == 2 ? ((int)(blockIdx.x >> kTurnBit) & 1) * kSegChunks : 0;
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
     // chunks that h is requested ahead of its use (13 to 16 wavefronts have 128 registers each, which three pieces
     // per thread twice over exceed)
