@@ -353,7 +353,8 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         if (cb.n == 0) return EVOSPEC_OK;
         int max_rows = 0;
         for (int i = 0; i < cb.n; ++i) max_rows = cb.rows[i] > max_rows ? cb.rows[i] : max_rows;
-        const Plan pa = V_arc > 0 ? make_plan(max_rows, V_arc, d, k, num_cu, cb.n, one_set) : Plan{};
+        const bool split = V_arc > 0 && !one_set && split_rows(max_rows, V_arc, d, k, num_cu, cb.n);
+        const Plan pa = V_arc > 0 ? make_plan(split ? kSplitRows : max_rows, V_arc, d, k, num_cu, split ? 2 * cb.n : cb.n, one_set) : Plan{};
         // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there.
         RowBound bound;
         if (V_arc > 0 && gemm_core && all) {
@@ -377,6 +378,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
             bl.seq_rows = V_arc;
             bl.chunk_bytes = arc_stride;
             bl.packed = packed;
+            bl.split = split;
             hipError_t e = launch_partials_batch(pa, h, cb, bl, d, W_arc, ids_arc, V_arc, k,
                                                  ws_arc + pa.keys_off, ws_arc + pa.stats_off, st);
             if (e != hipSuccess) return hip_fail(e);

@@ -211,24 +211,30 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 // through the caches gain nothing: 254.5, 32,256 x 2,048 37.0 -> 37.3, 24 rows, 36,864 x 4,096 62.1 -> 64.1.)
 template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS>
 __global__ void __launch_bounds__(TW * KS * 64)
-lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int seq_rows,
+lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, int split, int seq_rows,
                        size_t chunk_keys, size_t chunk_stats, int d,
                        const uint16_t* __restrict__ W_all, const int32_t* __restrict__ ids_all,
                        int V_act, int k, int GL,
                        u64* __restrict__ keys_all, float2* __restrict__ stats_all) {
     // this workgroup's problem: chunk blockIdx.y of the batch (its draft rows, its sequence's
     // rows of a per-sequence matrix, its own piece of the partials)
-    const int ci = blockIdx.y;
-    const int rows = cb.rows[ci];
+    // (split = 1: its draft rows go to two workgroups, the first kSplitRows and the others)
+    constexpr bool kMaySplit = MB == mb_for_rows(kSplitRows) && KS == 1;
+    const int ci = kMaySplit ? blockIdx.y >> split : blockIdx.y, row_first = kMaySplit ? (blockIdx.y & split) * kSplitRows : 0;
+    int rows = cb.rows[ci];
+    if constexpr (kMaySplit) {
+        if (split) rows = min(rows - row_first, kSplitRows);
+        if (rows <= 0) return;                                                // (uniform)
+    }
     const size_t seq_row0 = (size_t)cb.seq[ci] * seq_rows;
-    const uint16_t* __restrict__ h = h_all + (size_t)cb.m0[ci] * d;
+    const uint16_t* __restrict__ h = h_all + (size_t)(cb.m0[ci] + row_first) * d;
     // (a packed matrix pads every sequence's rows to whole tiles and its rows to whole chunks)
     const int dp = packed_d(d);
     const uint16_t* __restrict__ W = PACKED ? W_all + (size_t)cb.seq[ci] * packed_rows(seq_rows) * dp
                                             : W_all + seq_row0 * d;
     const int32_t* __restrict__ ids = ids_all ? ids_all + seq_row0 : nullptr;
-    u64* __restrict__ part_keys = keys_all + (size_t)ci * chunk_keys;
-    float2* __restrict__ part_stats = stats_all + (size_t)ci * chunk_stats;
+    u64* __restrict__ part_keys = keys_all + (size_t)ci * chunk_keys + row_first * k;
+    float2* __restrict__ part_stats = stats_all + (size_t)ci * chunk_stats + row_first;
     constexpr int NW = TW * KS;                    // wavefronts: KS of them share a tile, each a part of every chunk's k-steps
     constexpr int NT = NW * 64;
     constexpr int RT = 16 * TW;
@@ -930,8 +936,8 @@ hipError_t launch_partials_k(const Plan& p, const void* h, const ChunkBatch& cb,
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(p.n_slabs, cb.n), dim3(TW * KS * 64), p.lds_bytes, stream,
-                       static_cast<const uint16_t*>(h), cb, bl.seq_rows, bl.chunk_bytes / 8, bl.chunk_bytes / 8, d,
+    hipLaunchKernelGGL(kern, dim3(p.n_slabs, bl.split ? 2 * cb.n : cb.n), dim3(TW * KS * 64), p.lds_bytes, stream,
+                       static_cast<const uint16_t*>(h), cb, bl.split ? 1 : 0, bl.seq_rows, bl.chunk_bytes / 8, bl.chunk_bytes / 8, d,
                        static_cast<const uint16_t*>(W), ids,
                        V_act, k, p.gl, static_cast<u64*>(keys), static_cast<float2*>(stats));
     return hipGetLastError();
@@ -973,6 +979,7 @@ hipError_t launch_partials_batch(const Plan& p, const void* h, const ChunkBatch&
                                  int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
                                  void* stats, hipStream_t stream) {
     if (cb.n < 1 || cb.n > kMaxChunks || bl.chunk_bytes % 8 != 0) return hipErrorInvalidValue;
+    if (bl.split && (p.mb != mb_for_rows(kSplitRows) || p.ks != 1)) return hipErrorInvalidValue;      // (the kernels that know it)
     switch (p.nw) {
 #define EVOSPEC_SHAPE(TW_, RC_, KS4_, KS2_)                                                     \
     case TW_: return launch_partials_shape<TW_, RC_, KS4_, KS2_>(p, h, cb, bl, d, W, ids, V_act, k, keys, stats, stream);

@@ -26,6 +26,7 @@ struct MergeSet {
 struct BatchLayout {
     int seq_rows = 0;
     size_t chunk_bytes = 0;
+    bool split = false;             // the draft rows of a chunk go to two workgroups (the plan is one of kSplitRows rows)
     bool packed = false;            // the matrix is in operand-tile layout (plan.hpp), one padded matrix per sequence
 };
 

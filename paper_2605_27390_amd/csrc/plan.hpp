@@ -152,7 +152,7 @@ struct Plan {
     size_t keys_off = 0, stats_off = 0, total_bytes = 0;
 };
 
-inline int mb_for_rows(int rows) { return rows <= 16 ? 1 : (rows <= 32 ? 2 : 4); }
+constexpr int mb_for_rows(int rows) { return rows <= 16 ? 1 : (rows <= 32 ? 2 : 4); }
 
 // Granularity of the selection groups in the slab epilogue.  A slab's logits for one draft row
 // sit 4 per lane in 4*nw lanes; level 0 takes each lane as a group, level 1 pairs of lanes,
@@ -248,6 +248,17 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
     best.stats_off = align_up((size_t)best.n_slabs * kMTile * k * 8, 256);
     best.total_bytes = best.stats_off + align_up((size_t)best.n_slabs * kMTile * 8, 256);
     return best;
+}
+
+// Whether a batch of chunks gives the draft rows of every chunk to two workgroups, kSplitRows at most to each: where even
+// then a compute unit has no more than one.  Both read the weights (the second out of a cache, mostly), but with half the
+// draft rows a wavefront has half the operand reads and matrix instructions behind every piece of them.  us for the call, without
+// and with it: 4 sequences with 197 rows over 16,384 + 1,000 rows x 4,096 77.0 and 71.3 (the extensions alone 25 and 19.4),
+// 150 rows over 8,192 + 256 60.3 and 54.1, 160 rows over 4,096 + 128 x 2,048 44.0 and 39.6.  Two to a compute unit gain no more, and
+// lose on long lists (16 x 60 rows 303 and 340).
+constexpr int kSplitRows = 32;
+inline bool split_rows(int max_rows, int V_act, int d, int k, int num_cu, int chunks) {
+    return max_rows > kSplitRows && (long)make_plan(kSplitRows, V_act, d, k, num_cu, 2 * chunks, false).n_slabs * 2 * chunks <= num_cu;
 }
 
 // Few draft rows (narrow.hip): workgroups of kNarrowWaves wavefronts, each a run of 16-row tiles, one

@@ -1,0 +1,40 @@
+"""Few extensions of the batched head: the draft rows of a chunk go to two workgroups.  Chunks of 1, 32, 33 and 64 rows beside each
+other, an empty sequence, more than a chunk to a sequence, a core of slabs and of tiles.  Needs an MI355X: run with `-m gpu`."""
+import numpy as np
+import pytest
+
+import evospec_inputs as gi
+from helpers import check_head, new_matrix, to_dev_bf16, to_dev_i32
+from test_gpu_parity import ev  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("layout", ["packed", "row_major"])
+@pytest.mark.parametrize("V_core,V_arc,d,lens,k", [
+    (500, 130, 264, [32, 33, 0, 1], 10),          # core in slabs; a slab of two rows
+    (500, 128, 256, [33, 31], 17),
+    (700, 700, 2048, [64, 1, 70, 33], 10),        # core in tiles
+    (700, 90, 512, [150], 64),                    # three chunks of one sequence
+    (700, 2000, 256, [40, 64, 33], 24),           # pairs of logits as groups
+])
+def test_split_rows(ev, oracle_mod, layout, V_core, V_arc, d, lens, k):
+    import torch
+    S, M, V = len(lens), sum(lens), V_core + len(lens) * V_arc
+    ids = np.random.default_rng(V + M).permutation(V).astype(np.int32)
+    W, h = gi.gen_normal_bf16(V, d, 51, 0.05), gi.gen_h(M, d, 52)
+    dW, dids, row = to_dev_bf16(W), to_dev_i32(ids), np.arange(V, dtype=np.int32)
+    W_core, W_arc = new_matrix(ev, V_core, d, layout), new_matrix(ev, V_arc, d, layout, batch=S)
+    scratch = torch.empty(max(V_core, V_arc), dtype=torch.int32, device="cuda")
+    ev.active_gather(dW, to_dev_i32(row[:V_core]), None, W_core, scratch[:V_core])
+    for s in range(S):
+        lo = V_core + s * V_arc
+        ev.active_gather(dW, to_dev_i32(row[lo:lo + V_arc]), None, W_arc.sub(s) if layout == "packed" else W_arc[s], scratch[:V_arc])
+    row_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    v, i, l = (x.cpu().numpy() for x in ev.active_lmhead_topk_segmented(
+        to_dev_bf16(h), W_core, dids[:V_core].clone(), W_arc, dids[V_core:].reshape(S, V_arc).contiguous(), row_off, k))
+    for s in range(S):
+        a, b, lo = row_off[s], row_off[s + 1], V_core + s * V_arc
+        if a < b:
+            sel = np.concatenate([row[:V_core], row[lo:lo + V_arc]])
+            check_head(v[a:b], i[a:b], l[a:b], oracle_mod.logits(h[a:b], W[sel]), ids[sel], k, f"{layout} {V_core} {V_arc} {lens} k={k} sequence {s}")
