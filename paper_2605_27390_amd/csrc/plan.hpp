@@ -330,9 +330,12 @@ inline int gemm_list_len(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 // draft rows through the selection one by one, four times as many in a wavefront of large tiles (512 x 20,011 x 2,560 137
 // and 112 at k = 10; at k = 1, where the bound holds, 91 and 100).
 constexpr int kTileRows = 128;
-inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu) {
+inline bool slow_last_slab(int V_act, int k) {
     const int last = V_act % kGemmSlab;
-    const bool slow_last = last > 16 && last / 4 < k + k / 2;
+    return last > 16 && last / 4 < k + k / 2;
+}
+inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu) {
+    const bool slow_last = slow_last_slab(V_act, k);
     const double tile_cost = d < 2048 || slow_last ? 3.3 : 2.9;
     auto rounds = [&](int v, int m) {
         const long n = (long)((V_act + v - 1) / v) * ((M + m - 1) / m);
@@ -387,6 +390,22 @@ inline GemmPlan make_gemm_plan(int M, int V_act, int k) {
 inline size_t workspace_upper_bound(int V_act, int k) {
     const size_t n_slabs = ((size_t)V_act + kRowsMinSlab - 1) / kRowsMinSlab;
     return align_up(n_slabs * kMTile * k * 8, 256) + align_up(n_slabs * kMTile * 8, 256);
+}
+
+// Heads of 65 to 128 draft rows: the small tiles read the matrix once where passes of 64 rows read it twice.  Only where their
+// lists fit the scratch: of one pass for a head (M <= 8 k), of two for the core of the batched call (from k = 8 on).
+// Passes and tiles, us: 36,864 x 4,096 at 80 rows, k = 10, 118 and 86; 18,432 x 4,096 at 66 73 and 49; 4,096 x 1,024 at 70 27 and 22; 1,024 x 256
+// at 70 23 and 17; 16,384 x 4,096 at 96, k = 12, 74 and 57; full vocabulary row-major at 72 441 and 275; batched, 66 rows, 32,768 + 2,048 121 and
+// 83, 128 rows, 4,096 + 128 x 2,048 49 and 39.  From k = 13 on too many rows have more survivors than a list of 16 holds, and past 16
+// every row is selected by itself (16,384 x 4,096 at 128 rows, k = 16, 82 and 88; 2,048 x 256 at 80, k = 20, 30 and 45; 16,384 x 2,048 at
+// 100, k = 32, 63 and 74; 20,096 x 1,024 at 80, k = 40, 69 and 44).  A last slab that does the same costs more than a second
+// pass over a small matrix (4,000 x 1,024 at 70 28 and 38) and less over a large one (36,896 x 2,048 at 72 74 and 63; 30,000 x 4,096 at 66
+// 102 and 60; batched, 120 rows, 30,000 + 1,500 122 and 84).
+constexpr size_t kSlowLastMiB = 96;
+inline bool use_tiles_early(int M, int V_act, int d, int k, size_t scratch) {
+    return M > kMTile && M < kGemmMinRows && d % (2 * kGemmKChunk) == 0 && k <= 12 &&
+           (!slow_last_slab(V_act, k) || matrix_elems((size_t)V_act, d, false) * 2 >= (kSlowLastMiB << 20)) &&
+           make_gemm_plan(M, V_act, k).total_bytes <= scratch;
 }
 
 }  // namespace evospec
