@@ -196,10 +196,10 @@ inline size_t lds_bytes_for(int nw, int mb, int k, int ks = 1, int segs = 1) {
 // Segments of the hidden dimension in the slab kernel.  Rows of a row-major matrix that lie a multiple of 4 KB apart meet at
 // the same memory channels while all workgroups are at the same place of their rows; in two segments of alternating
 // 2 KB runs, half of the workgroups can take the other run first without a change of any sum (see the kernel).  Measured,
-// row-major, 60 draft rows unless said, one segment and two: 151,936 x 4,096 275 and 256 us, 36,864 x 4,096 74.6 and 68.2 (24
-// rows 69.0 and 62.7), 32,256 x 2,048 42.8 and 37.2, 60,000 x 2,048 72.8 and 66.1 (12 rows, 48,000 50.4 and 44.4).  Runs
+// row-major, 60 draft rows unless said, one segment and two: 151,936 x 4,096 275 and 252 us, 36,864 x 4,096 75.2 and 67.2 (24
+// rows 69.0 and 62.5), 32,256 x 2,048 42.6 and 38.0, 60,000 x 2,048 73.4 and 66.3 (12 rows, 48,000 51.5 and 44.4).  Runs
 // of 4 KB or of 1 KB gain next to nothing (274, 259).  A packed matrix is summed alike, so that both layouts give the same bits (36,864 x
-// 4,096 61.2 and 61.4).  Only where the LDS has room for one set of sums, without costing a second workgroup on the
+// 4,096 61.0 and 61.1).  Only where the LDS has room for one set of sums, without costing a second workgroup on the
 // compute unit (which four blocks of draft rows have no registers for anyway).  Four wavefronts to a tile gain nothing (8,448 x
 // 4,096 35.1 and 35.2) and lose on a packed matrix (26.9 and 27.5).
 constexpr int kSegChunks = 4;

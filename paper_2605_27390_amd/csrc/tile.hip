@@ -10,6 +10,7 @@
 // 84 us against 91 with one).  Bound by LDS: per pair of chunks 32 KB go in and 80 KB come out, 875 cycles at
 // 128 bytes per cycle against 512 of the matrix cores.  200 rows x 16,384 x 4,096: 43 us, 52 with the merge;
 // the 64 tiles of 256 x 256 of this shape took 120 (130).
+// Heads of 65 to 128 rows come here as well where use_tiles_early says so.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
