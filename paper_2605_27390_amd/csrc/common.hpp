@@ -111,14 +111,13 @@ __device__ __forceinline__ float wave_sum(float x, int lane) {
     return x;
 }
 
-// A lower bound of the q-th largest (counting repeats, 1 <= q <= 64) of the 64 values of a wavefront: the
-// largest t, of those whose low 12 bits are zero, that at least q values reach, found bit by bit.  (For logits, in their
-// order as integers: within 2^-11 of the q-th largest, which admits next to no more candidates; all 32 bits take 12 steps
-// more of a compare and dependent scalar work.)  With 8 wavefronts per SIMD this costs a fifth of sorting the 64 values.
-__device__ __forceinline__ uint32_t wave_kth_bound(uint32_t v, int q) {
+// The q-th largest (counting repeats, 1 <= q <= 64) of the 64 values of a wavefront: the largest t
+// that at least q values reach, found bit by bit.  One vector compare per bit, the rest is scalar:
+// with 8 wavefronts per SIMD this costs a fifth of sorting the 64 values.
+__device__ __forceinline__ uint32_t wave_kth_largest(uint32_t v, int q) {
     uint32_t t = 0;
 #pragma unroll
-    for (int bit = 31; bit >= 12; --bit) {
+    for (int bit = 31; bit >= 0; --bit) {
         const uint32_t c = t | (1u << bit);
         if (__popcll(__ballot(v >= c)) >= q) t = c;              // (uniform)
     }

@@ -147,7 +147,7 @@ __device__ __forceinline__ T wg_sort_desc(T x, T* buf) {
 __device__ __forceinline__ uint32_t kth_bound_1024(uint32_t v, int K, uint32_t* wave_q /*LDS [16]*/) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int q = (K + 15) >> 4;                               // K <= 1024
-    const uint32_t s = wave_kth_bound(v, q);
+    const uint32_t s = wave_kth_largest(v, q);
     if (lane == 0) wave_q[w] = s;
     __syncthreads();
     uint32_t t = wave_q[0];

@@ -198,7 +198,7 @@ lmhead_narrow_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_
         se = wave_sum(se, lane);
         if (lane == 0) part_stats[(size_t)m * n_wg + b] = make_float2(vm, se);
         // the k-th largest of the 64 lane maxima is reached by k logits: what reaches it is ranked by counting
-        const uint32_t th = wave_kth_bound(lane < n_valid ? f32_to_ordered(lane_max) : 0u, k);
+        const uint32_t th = wave_kth_largest(lane < n_valid ? f32_to_ordered(lane_max) : 0u, k);
         u64* lst = list + (size_t)w * z_stride;
         int n = 0;
 #pragma unroll

@@ -110,3 +110,31 @@ def test_full_size(ev):
     for e in range(E):                                            # properties on all events
         assert len(set(got[0][e].tolist())) == 256 and np.all(np.diff(got[1][e]) <= 0)
         assert got[1][e][-1] >= np.partition(z[e], -256)[-256]
+
+
+@pytest.mark.parametrize("V,K,finite", [
+    (5000, 256, "few"),            # one slice; two 16-byte loads per thread
+    (5000, 8, "few"),
+    (30001, 256, "few"),           # the looping sweep
+    (151936, 256, "few"),          # eight slices: fewer finite logits than K in each
+    (151936, 8, "few"),
+    (32770, 256, "few"),
+    (151936, 256, "front"),        # the last slices are masked as a whole
+    (151936, 8, "front"),
+    (40001, 100, "front"),
+    (5000, 256, "run"),            # all finite logits with the threads of one or two wavefronts
+    (151936, 256, "run"),
+])
+def test_masked_logits(ev, V, K, finite):
+    """Masked tokens have logits of -inf.  Where a wavefront sees fewer finite logits than the bound of its slice asks of
+    it, the bound is -inf, which everything reaches."""
+    from oracle import kl_gate
+    d, E = 64, 2
+    rng = np.random.default_rng(V + K)
+    W, h = gi.gen_normal_bf16(V, d, 17, 0.05), gi.gen_h(E, d, 18)
+    z = np.full((E, V), -np.inf, dtype=np.float32)
+    for e in range(E):
+        ids = {"few": lambda: rng.choice(V, K + 3 * e, replace=False), "front": lambda: np.arange(V // 2 + 1000 * e),
+               "run": lambda: np.arange(700, 700 + K + 40 * e)}[finite]()
+        z[e, ids] = rng.standard_normal(len(ids)).astype(np.float32) * 2.5 + 100 * e
+    check(run(ev, z, h, W, K, 1.0), kl_gate(z, h, W, K, 1.0), f"V={V} K={K} {finite}")
