@@ -208,7 +208,8 @@ int evospec_active_lmhead_topk_then_update(const void *h, int M, int d, void *W_
  *   W_lm      dev bf16 [V, d], 16-B aligned, d % 8 == 0, d <= 24,576
  *   out_support dev int32 [E, K]; out_target_logits, out_draft_logits dev fp32 [E, K]; out_kl dev fp32 [E]
  *   workspace dev, 16-B aligned, at least evospec_kl_gate_workspace_bytes(E, V) bytes, scratch
- * T > 0.  No synchronisation; E == 0 is a no-op.
+ * T > 0.  No synchronisation; E == 0 is a no-op.  An event of which fewer than K target logits are numbers (the others NaN)
+ * fills its support up with ids -1 and logits NaN; its divergence is NaN.
  */
 #define EVOSPEC_KL_K_MAX 256
 int evospec_kl_gate_workspace_bytes(int E, int V, size_t *out_bytes /*host*/);

@@ -457,7 +457,10 @@ kl_draft_logits_kernel(const uint16_t* __restrict__ h_draft, int d, const uint16
     const int32_t* sup = support + (size_t)e * K;
     const uint16_t* row[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) row[u] = W_lm + (size_t)sup[r0 + u < K ? r0 + u : K - 1] * d;   // past the end: a valid row again
+    for (int u = 0; u < 4; ++u) {
+        const int32_t id = sup[r0 + u < K ? r0 + u : K - 1];        // past the end: a valid row again
+        row[u] = W_lm + (size_t)(id < 0 ? 0 : id) * d;              // (-1: fewer than K of the event's logits are numbers)
+    }
     for (int i = tid; i < d / 8; i += 256)
         reinterpret_cast<u32x4*>(hs)[i] = *(gvec_ptr)(h_draft + (size_t)e * d + 8 * i);
     __syncthreads();

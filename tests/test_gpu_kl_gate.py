@@ -138,3 +138,22 @@ def test_masked_logits(ev, V, K, finite):
                "run": lambda: np.arange(700, 700 + K + 40 * e)}[finite]()
         z[e, ids] = rng.standard_normal(len(ids)).astype(np.float32) * 2.5 + 100 * e
     check(run(ev, z, h, W, K, 1.0), kl_gate(z, h, W, K, 1.0), f"V={V} K={K} {finite}")
+
+
+@pytest.mark.parametrize("V,numbers", [(5000, 0), (5000, 100), (151936, 0), (40001, 255)])
+def test_an_event_of_nans_leaves_the_others_alone(ev, V, numbers):
+    """Fewer than K logits that are numbers: the support ends with ids -1, whose rows of W_lm nobody may read."""
+    from oracle import kl_gate
+    d, E, K = 64, 3, 256
+    rng = np.random.default_rng(V + numbers)
+    W, h = gi.gen_normal_bf16(V, d, 19, 0.05), gi.gen_h(E, d, 20)
+    z = (rng.standard_normal((E, V)) * 2.5).astype(np.float32)
+    ids = rng.choice(V, numbers, replace=False)
+    row = np.full(V, np.nan, dtype=np.float32)
+    row[ids] = z[1, ids]
+    z[1] = row
+    s, zt, zq, kl = run(ev, z, h, W, K, 1.0)
+    good = [0, 2]
+    check((s[good], zt[good], zq[good], kl[good]), kl_gate(z[good], h[good], W, K, 1.0), f"V={V} numbers={numbers}")
+    assert s[1, :numbers].tolist() == ids[np.lexsort((ids, -row[ids]))].tolist()
+    assert (s[1, numbers:] == -1).all() and np.isnan(zt[1, numbers:]).all() and np.isnan(kl[1])
