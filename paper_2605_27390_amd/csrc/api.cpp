@@ -211,11 +211,11 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     const uint16_t* hp = static_cast<const uint16_t*>(h);
-    const bool early = use_tiles_early(M, V_act, d, k, workspace_upper_bound(V_act, k));
+    const bool early = use_tiles_early(M, V_act, d, k, true, workspace_upper_bound(V_act, k));
     if (use_gemm(M, d) || early) {                      // bound by the contraction: all rows at once
         const GemmPlan gp = make_gemm_plan(M, V_act, k);
         hipError_t e = early || use_small_tiles(M, V_act, d, k, num_cu)
-                           ? launch_tile_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, {})
+                           ? launch_tile_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, early, {})
                            : launch_gemm_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, {});
         if (e != hipSuccess) return hip_fail(e);
         MergeSet a{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
@@ -311,8 +311,9 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     const uint16_t* hp = static_cast<const uint16_t*>(h);
-    const bool early_core = V_core > 0 && use_tiles_early(M, V_core, d, k, core_workspace_bytes(M, d, V_core, k));
-    const bool gemm_core = early_core || (V_core > 0 && use_gemm(M, d)), one_set = V_core == 0 || V_arc == 0;
+    const bool one_set = V_core == 0 || V_arc == 0;
+    const bool early_core = V_core > 0 && use_tiles_early(M, V_core, d, k, one_set, core_workspace_bytes(M, d, V_core, k));
+    const bool gemm_core = early_core || (V_core > 0 && use_gemm(M, d));
     const size_t core_stride = V_core > 0 ? workspace_upper_bound(V_core, k) : 0;
     const size_t arc_stride = V_arc > 0 ? workspace_upper_bound(V_arc, k) : 0;
     char* ws_arc = ws + (V_core > 0 ? core_workspace_bytes(M, d, V_core, k) : 0);
@@ -327,7 +328,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         if (gemm_core) {
             const GemmPlan gp = make_gemm_plan(M, V_core, k);
             hipError_t e = early_core || use_small_tiles(M, V_core, d, k, num_cu)
-                               ? launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, bound)
+                               ? launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, early_core && one_set, bound)
                                : launch_gemm_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, bound);
             if (e != hipSuccess) return hip_fail(e);
             core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};

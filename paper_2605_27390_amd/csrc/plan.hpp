@@ -394,16 +394,24 @@ inline size_t workspace_upper_bound(int V_act, int k) {
 
 // Heads of 65 to 128 draft rows: the small tiles read the matrix once where passes of 64 rows read it twice.  Only where their
 // lists fit the scratch: of one pass for a head (M <= 8 k), of two for the core of the batched call (from k = 8 on).
-// Passes and tiles, us: 36,864 x 4,096 at 80 rows, k = 10, 118 and 86; 18,432 x 4,096 at 66 73 and 49; 4,096 x 1,024 at 70 27 and 22; 1,024 x 256
-// at 70 23 and 17; 16,384 x 4,096 at 96, k = 12, 74 and 57; full vocabulary row-major at 72 441 and 275; batched, 66 rows, 32,768 + 2,048 121 and
+// Passes and tiles, us: 36,864 x 4,096 at 80 rows, k = 10, 118 and 86; 18,432 x 4,096 at 66 72 and 51; 20,000 x 4,096 at 80 77 and 60; 4,096 x
+// 1,024 at 70 28 and 25; 16,384 x 4,096 at 96, k = 12, 74 and 58; full vocabulary row-major at 72 441 and 280; batched, 66 rows, 32,768 + 2,048 121 and
 // 83, 128 rows, 4,096 + 128 x 2,048 49 and 39.  From k = 13 on too many rows have more survivors than a list of 16 holds, and past 16
 // every row is selected by itself (16,384 x 4,096 at 128 rows, k = 16, 82 and 88; 2,048 x 256 at 80, k = 20, 30 and 45; 16,384 x 2,048 at
 // 100, k = 32, 63 and 74; 20,096 x 1,024 at 80, k = 40, 69 and 44).  A last slab that does the same costs more than a second
-// pass over a small matrix (4,000 x 1,024 at 70 28 and 38) and less over a large one (36,896 x 2,048 at 72 74 and 63; 30,000 x 4,096 at 66
+// pass over a small matrix (4,000 x 1,024 at 70 28 and 38) and less over a large one (36,896 x 2,048 at 72 75 and 66; 30,000 x 4,096 at 66
 // 102 and 60; batched, 120 rows, 30,000 + 1,500 122 and 84).
+// parts: the passes would sum the hidden dimension in parts (up to four wavefronts to a tile, eight in the few-row kernel), so the tiles
+// sum it in kTileParts parts as well, a few more if d / 64 is no multiple of them.  Relative error of a call's logits against 64 bits in
+// passes, in a single chain and in parts, 1e-8: 8,448 x 4,096 at 66 rows 9.9, 34 and 7.2; 20,000 x 4,096 at 80 23, 36 and 7.3;
+// 18,432 x 2,048 at 80 16, 24 and 5.9; 4,096 x 1,024 at 70 5.8, 16 and 5.4; 8,192 x 512 at 72 5.0, 12 and 5.2, so that hidden
+// sizes below 1,024 stay with the passes.  (Of a call's rows the up to 16 last ones that the few-row kernel would take, in 16 chains, are 7.5
+// instead of 5.9 off at 8,448 x 4,096, the first 64 7.3 instead of 10.)
 constexpr size_t kSlowLastMiB = 96;
-inline bool use_tiles_early(int M, int V_act, int d, int k, size_t scratch) {
-    return M > kMTile && M < kGemmMinRows && d % (2 * kGemmKChunk) == 0 && k <= 12 &&
+constexpr int kTileParts = 8;
+constexpr int kTilePartsMinD = 1024;
+inline bool use_tiles_early(int M, int V_act, int d, int k, bool parts, size_t scratch) {
+    return M > kMTile && M < kGemmMinRows && d % (2 * kGemmKChunk) == 0 && (!parts || d >= kTilePartsMinD) && k <= 12 &&
            (!slow_last_slab(V_act, k) || matrix_elems((size_t)V_act, d, false) * 2 >= (kSlowLastMiB << 20)) &&
            make_gemm_plan(M, V_act, k).total_bytes <= scratch;
 }

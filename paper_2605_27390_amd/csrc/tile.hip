@@ -10,7 +10,10 @@
 // 84 us against 91 with one).  Bound by LDS: per pair of chunks 32 KB go in and 80 KB come out, 875 cycles at
 // 128 bytes per cycle against 512 of the matrix cores.  200 rows x 16,384 x 4,096: 43 us, 52 with the merge;
 // the 64 tiles of 256 x 256 of this shape took 120 (130).
-// Heads of 65 to 128 rows come here as well where use_tiles_early says so.
+// Heads of 65 to 128 rows come here as well where use_tiles_early says so.  PARTS: the hidden dimension is summed in kTileParts parts,
+// one after the other, whose total waits in registers of its own (use_tiles_early has the errors).  A turn of parts costs 900 cycles
+// with one workgroup to a compute unit (20,000 x 4,096 at 80 rows 57.7 -> 60.1 us, 4,096 x 1,024 at 70 22.5 -> 25.0) and is hidden by
+// the other one with two (36,864 x 4,096 85.7 -> 86.1).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -35,17 +38,23 @@ constexpr size_t tile_lds(int stages) {
     return (ring > epi ? ring : epi) + kTM * 4;                // and the draft rows' bounds
 }
 static_assert(kTV == 128 && kTM == 128, "the load and operand offsets below assume it");
+static_assert(kTilePartsMinD >= kTileParts * 64, "a pair of chunks to every part");
 static_assert(tile_lds(4) <= (size_t)kLdsLimit && 2 * tile_lds(2) <= (size_t)kLdsLimit, "one deep or two shallow rings per compute unit");
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
+
+// (the same with the accumulators in ordinary registers)
+__device__ __forceinline__ void mfma_vec(f32x4& c, const bf16x8& a, const bf16x8& b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
 
 // Where piece p (16 bytes of a 64-byte chunk row) of a row sits in the row's four slots: see gemm.hip.
 __device__ __forceinline__ int swz(int row) { return (((row & 15) >> 1) + ((row & 15) >> 3)) & 3; }
 
 }  // namespace
 
-template <bool PACKED, int S>
+template <bool PACKED, int S, bool PARTS>
 __global__ void __launch_bounds__(256, S > 2 ? 1 : 2)
 lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t* __restrict__ W,
                    const int32_t* __restrict__ ids, int V_act, int k, int list_len, int m_tiles,
@@ -86,6 +95,12 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
         __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)dst, 16, 0, 0);
     };
 
+    // the sum of a part is read out again and again: in ordinary registers, where there are enough of them
+    constexpr bool VEC = PARTS && S > 2;
+    auto pin = [](f32x4& c) {
+        if constexpr (VEC) asm volatile("" : "+v"(c));
+        else asm volatile("" : "+a"(c));
+    };
     f32x4 acc[8][2];
 #pragma unroll
     for (int rg = 0; rg < 8; ++rg)
@@ -113,7 +128,10 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
 #pragma unroll
         for (int rg = 0; rg < 8; ++rg) {
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb) mfma_acc(acc[rg][mb], opa[P][rg], opb[P][mb]);
+            for (int mb = 0; mb < 2; ++mb) {
+                if constexpr (VEC) mfma_vec(acc[rg][mb], opa[P][rg], opb[P][mb]);
+                else mfma_acc(acc[rg][mb], opa[P][rg], opb[P][mb]);
+            }
             if (rg < 2) read_b(NXT{}, c + 1, rg);
             read_a(NXT{}, c + 1, rg);
             if (load) issue(p, rg);
@@ -136,7 +154,30 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
 #pragma unroll
     for (int i = 0; i < 8; ++i) read_a(S0{}, 0, i);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 7" ::: "memory");
+    f32x4 total[8][2];                                           // (PARTS) the sum of the parts so far
+    if constexpr (PARTS) {
+#pragma unroll
+        for (int rg = 0; rg < 8; ++rg)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) total[rg][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    int turn = npairs / kTileParts;                              // (PARTS: at least 1)
     for (int p = 0; p < npairs; ++p) {
+        if (PARTS && p == turn) {                                // (uniform)
+            turn += npairs / kTileParts;
+            // (the compiler does not see that these are results of matrix instructions: wait them out, and the zeros in)
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+            for (int rg = 0; rg < 8; ++rg)
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb) {
+                    pin(acc[rg][mb]);
+                    total[rg][mb] += acc[rg][mb];
+                    acc[rg][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    pin(acc[rg][mb]);
+                }
+            asm volatile("s_nop 7" ::: "memory");
+        }
         step(S0{}, 2 * p, false, 0);
         // odd chunk: pair p + 1 must have landed (the S - 2 pairs after it may be under way), and every
         // wavefront must be through with its reads of pair p, whose stage is filled again
@@ -145,13 +186,22 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
     }
     // the last MFMAs drain before the accumulators are read; the ring is dead once the trailing loads have landed and every wavefront is here
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if constexpr (PARTS) {
+#pragma unroll
+        for (int rg = 0; rg < 8; ++rg)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                pin(acc[rg][mb]);
+                acc[rg][mb] += total[rg][mb];
+            }
+    }
     slab_epilogue<2>(acc, smem + (size_t)w * epi_bytes(2), v0, m0 + w * 32, M, V_act, ids, k, list_len, tile_v,
                      (V_act + kGemmSlab - 1) / kGemmSlab, bound.n_chunks ? bnd + w * 32 : nullptr, part_keys, part_stats);
 }
 
 hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
-                                void* stats, hipStream_t stream, bool packed, int num_cu, const RowBound& bound) {
-    if (d % 64 != 0 || d < 64) return hipErrorInvalidValue;              // callers route such d elsewhere
+                                void* stats, hipStream_t stream, bool packed, int num_cu, bool parts, const RowBound& bound) {
+    if (d % 64 != 0 || d < (parts ? kTilePartsMinD : 64)) return hipErrorInvalidValue;              // callers route such d elsewhere
     const int v_tiles = (V_act + kTV - 1) / kTV, m_tiles = (M + kTM - 1) / kTM;
     // more tiles than compute units: two workgroups with shallow rings share one, so that one computes while
     // the other starts or ends
@@ -159,12 +209,16 @@ hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, cons
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const bool two = v_tiles * m_tiles > num_cu;
-    auto kern = packed ? (two ? lmhead_tile_kernel<true, 2> : lmhead_tile_kernel<true, 4>)
-                       : (two ? lmhead_tile_kernel<false, 2> : lmhead_tile_kernel<false, 4>);
+    auto kern = packed ? (two ? lmhead_tile_kernel<true, 2, false> : lmhead_tile_kernel<true, 4, false>)
+                       : (two ? lmhead_tile_kernel<false, 2, false> : lmhead_tile_kernel<false, 4, false>);
+    if (parts)
+        kern = packed ? (two ? lmhead_tile_kernel<true, 2, true> : lmhead_tile_kernel<true, 4, true>)
+                      : (two ? lmhead_tile_kernel<false, 2, true> : lmhead_tile_kernel<false, 4, true>);
     constexpr int kMaxDevices = 64;
     static std::atomic<bool> attr_set[kMaxDevices] = {};      // concurrent first calls may both set the (idempotent) attribute
     if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-        for (auto kf : {lmhead_tile_kernel<true, 2>, lmhead_tile_kernel<true, 4>, lmhead_tile_kernel<false, 2>, lmhead_tile_kernel<false, 4>}) {
+        for (auto kf : {lmhead_tile_kernel<true, 2, false>, lmhead_tile_kernel<true, 4, false>, lmhead_tile_kernel<false, 2, false>, lmhead_tile_kernel<false, 4, false>,
+                        lmhead_tile_kernel<true, 2, true>, lmhead_tile_kernel<true, 4, true>, lmhead_tile_kernel<false, 2, true>, lmhead_tile_kernel<false, 4, true>}) {
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile_lds(4));
             if (e != hipSuccess) return e;
         }
