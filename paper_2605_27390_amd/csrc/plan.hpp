@@ -407,11 +407,15 @@ inline size_t workspace_upper_bound(int V_act, int k) {
 // 18,432 x 2,048 at 80 16, 24 and 5.9; 4,096 x 1,024 at 70 5.8, 16 and 5.4; 8,192 x 512 at 72 5.0, 12 and 5.2, so that hidden
 // sizes below 1,024 stay with the passes.  (Of a call's rows the up to 16 last ones that the few-row kernel would take, in 16 chains, are 7.5
 // instead of 5.9 off at 8,448 x 4,096, the first 64 7.3 instead of 10.)
+// In parts a tile's chain over a large hidden dimension takes longer than a second pass over a small matrix, above all where that pass
+// has only a few rows (passes and tiles at 66 rows, k = 10: x 4,096 1,024 rows 36 and 40, 5,000 40 and 41, 6,144 47 and 45, 8,192 52 and 47; x
+// 3,072 500 rows 33 and 35, 4,096 35 and 36, row-major 40 and 36; x 2,048 1,024 rows 29 and 30, 2,048 30 and 30, 3,200 31 and 30; x 1,536 and below
+// the tiles from the smallest set on, 128 x 1,024 at 70 27 and 24).  Two sets gain at any size (128 + 200 rows x 4,096 at 66 67 and 51).
 constexpr size_t kSlowLastMiB = 96;
 constexpr int kTileParts = 8;
 constexpr int kTilePartsMinD = 1024;
 inline bool use_tiles_early(int M, int V_act, int d, int k, bool parts, size_t scratch) {
-    return M > kMTile && M < kGemmMinRows && d % (2 * kGemmKChunk) == 0 && (!parts || d >= kTilePartsMinD) && k <= 12 &&
+    return M > kMTile && M < kGemmMinRows && d % (2 * kGemmKChunk) == 0 && (!parts || (d >= kTilePartsMinD && V_act >= 2 * (d - kTilePartsMinD))) && k <= 12 &&
            (!slow_last_slab(V_act, k) || matrix_elems((size_t)V_act, d, false) * 2 >= (kSlowLastMiB << 20)) &&
            make_gemm_plan(M, V_act, k).total_bytes <= scratch;
 }

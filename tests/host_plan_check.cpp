@@ -86,6 +86,10 @@ int main() {
     REQUIRE(use_small_tiles(200, 16384, 4096, 10, 256) && use_small_tiles(129, 1, 64, 1, 256) && use_small_tiles(300, 20000, 2048, 10, 256), "small tiles");
     REQUIRE(!use_small_tiles(960, 32768, 4096, 10, 256) && !use_small_tiles(512, 32768, 4096, 10, 256) && !use_small_tiles(256, 45000, 5120, 10, 256), "large tiles");
     REQUIRE(use_small_tiles(256, 45000, 1024, 10, 256) && use_small_tiles(512, 20011, 2560, 10, 256) && !use_small_tiles(512, 20011, 2560, 1, 256), "three rounds");
+    // 65 to 128 rows: one set in parts from 1,024 hidden elements on, where the matrix is large enough for them; two sets always
+    const size_t any = ~(size_t)0;
+    REQUIRE(use_tiles_early(66, 128, 1024, 10, true, any) && !use_tiles_early(66, 8448, 960, 10, true, any) && use_tiles_early(66, 8448, 960, 10, false, any), "hidden size");
+    REQUIRE(use_tiles_early(66, 6144, 4096, 10, true, any) && !use_tiles_early(66, 6016, 4096, 10, true, any) && use_tiles_early(66, 128, 4096, 10, false, any), "small sets");
     REQUIRE(gemm_list_len(16) == 16 && gemm_list_len(17) == 32 && gemm_list_len(64) == 64, "list_len");
     REQUIRE(use_gemm(129, 4096) && !use_gemm(128, 4096) && !use_gemm(960, 4104), "use_gemm");
     std::printf("ok\n");
