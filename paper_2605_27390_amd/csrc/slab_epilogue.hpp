@@ -117,7 +117,7 @@ __device__ __forceinline__ float row_bound(const RowBound& b, int row, int M) {
 // acc[rg][mb]: lane (n16, g) holds the logits of the active rows vrow0 + 16 rg + 4 g + 0..3 and draft row
 // mbase + 16 mb + n16.  `my`: epi_bytes(NMB) of LDS of this wavefront alone.  Lists are laid out [draft
 // row][slab][slot].  NMB <= 8.  bnd (or null): in LDS, for each of the draft rows a value that k logits elsewhere reach, so
-// that none below it can be among the row's k best; few enough reach it that the slab needs no bound of its own.
+// that none below it can be among the row's k best.
 template <int NMB>
 __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned char* my, int vrow0, int mbase, int M, int V_act,
                                               const int32_t* __restrict__ ids, int k, int list_len, int slab, int n_slabs, const float* bnd,
@@ -195,46 +195,8 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
         quad_max(vm);
     }
 
-    // -- phase 2: lower bound of every row's k-th best logit.  Each lane sorts its 8 group maxima;
-    // k rounds then take the largest head of the row's 4 lanes and pop it wherever it is the head:
-    // at least k group maxima, hence k logits, reach the last value taken.  With more than 32
-    // wanted, or fewer groups than k, the bound stays at -inf and every valid entry is kept.  A bound from elsewhere is
-    // tighter than that and costs nothing here.
-    float tau[NMB];
-#pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) tau[mb] = -INFINITY;
-    if (bnd) {                                                     // (uniform)
-#pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) tau[mb] = bnd[16 * mb + n16];
-    } else if (k <= 32) {
-#define EVOSPEC_CE(I, J) { float hi[NMB]; EVOSPEC_MB(hi[mb] = fmaxf(t[mb][I], t[mb][J])) \
-                           EVOSPEC_MB(t[mb][J] = fminf(t[mb][I], t[mb][J])) EVOSPEC_MB(t[mb][I] = hi[mb]) }
-        EVOSPEC_CE(0, 1) EVOSPEC_CE(2, 3) EVOSPEC_CE(4, 5) EVOSPEC_CE(6, 7)
-        EVOSPEC_CE(0, 2) EVOSPEC_CE(1, 3) EVOSPEC_CE(4, 6) EVOSPEC_CE(5, 7)
-        EVOSPEC_CE(1, 2) EVOSPEC_CE(5, 6) EVOSPEC_CE(0, 4) EVOSPEC_CE(3, 7)
-        EVOSPEC_CE(1, 5) EVOSPEC_CE(2, 6)
-        EVOSPEC_CE(1, 4) EVOSPEC_CE(3, 6)
-        EVOSPEC_CE(2, 4) EVOSPEC_CE(3, 5)
-        EVOSPEC_CE(3, 4)
-#undef EVOSPEC_CE
-        for (int r = 0; r < k; ++r) {
-            EVOSPEC_MB(tau[mb] = t[mb][0])
-            quad_max(tau);
-            // pop the head where it is the value just taken: all ones / zero select, no compare chain
-            uint32_t pop[NMB];
-            EVOSPEC_MB(pop[mb] = t[mb][0] == tau[mb] ? ~0u : 0u)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                EVOSPEC_MB(const uint32_t cur = __float_as_uint(t[mb][i]);
-                           const uint32_t nxt = i < 7 ? __float_as_uint(t[mb][i + 1]) : 0xff800000u;
-                           t[mb][i] = __uint_as_float((pop[mb] & nxt) | (~pop[mb] & cur)))
-            }
-        }
-    }
-
     repin();
-    // -- phase 3: sum of exponentials, exp(z - vm) = 2^(z log2(e) - vm log2(e)), two running sums per block
-    uint32_t mask[NMB];
+    // -- phase 2: sum of exponentials, exp(z - vm) = 2^(z log2(e) - vm log2(e)), two running sums per block
     float se[NMB];
     {
         float nvm[NMB], s0[NMB], s1[NMB];
@@ -252,44 +214,99 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
         EVOSPEC_MB(se[mb] = s0[mb] + s1[mb])
         quad_sum(se);
     }
-    repin();
-    // -- phase 3b: survivor masks without a compare per entry: the sign of (logit - bound) is
-    // shifted in, last entry first, so that entry i ends up as bit i ("below the bound")
-    {
-        uint32_t below[NMB];
-        EVOSPEC_MB(below[mb] = 0u)
-#pragma unroll
-        for (int i = 31; i >= 0; --i) {
-            float df[NMB];
-            EVOSPEC_MB(df[mb] = acc[i >> 2][mb][i & 3] - tau[mb])
-            EVOSPEC_MB(below[mb] = __builtin_amdgcn_alignbit(below[mb], __float_as_uint(df[mb]), 31))
-        }
-        EVOSPEC_MB(mask[mb] = ~below[mb] & vmask)
-    }
     const int mrow0 = mbase + n16;                                 // draft row of block 0
 #pragma unroll
     for (int mb = 0; mb < NMB; ++mb)
         if (g == 0 && mrow0 + 16 * mb < M) part_stats[(size_t)(mrow0 + 16 * mb) * n_slabs + slab] = make_float2(vm[mb], se[mb]);
 
-    // survivors per lane (<= 32), four blocks to a register; from the 4 lanes of a row: the offset
-    // of this lane's survivors in the row's list and the list length L (<= 128), still packed
-    constexpr int NPK = (NMB + 3) / 4;
-    uint32_t basep[NPK], Lp[NPK];
-#pragma unroll
-    for (int hf = 0; hf < NPK; ++hf) {
-        uint32_t pk = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (4 * hf + q < NMB) pk |= (uint32_t)__popc(mask[4 * hf + q]) << (8 * q);
-        uint32_t q[4];
-        quad_all(pk, q);
-        basep[hf] = (g > 0 ? q[0] : 0u) + (g > 1 ? q[1] : 0u) + (g > 2 ? q[2] : 0u);
-        Lp[hf] = q[0] + q[1] + q[2] + q[3];
-    }
     // rows whose survivors fit a list go straight out.  The staged lists have kGFastLen slots: where those of the
     // workspace are longer (k > 16) no row may take that way, one without survivors neither (its 16 empty slots
     // would land in the list of another row, and its own would keep what the workspace held before).
     const int cap = list_len == kGFastLen ? kGFastLen : -1;
+    // -- phase 3: a lower bound of every row's k-th best logit, and what reaches it.  The slab's own bound: each lane sorts
+    // its 8 group maxima; k rounds then take the largest head of the row's 4 lanes and pop it wherever it is the head:
+    // at least k group maxima, hence k logits, reach the last value taken.  With more than 32
+    // wanted, or fewer groups than k, the bound stays at -inf and every valid entry is kept.  A bound from elsewhere (bnd) is
+    // tried first.  It costs nothing here, and about one logit of a row reaches it if the logits here and there are alike.
+    // If they are larger here, most may: where more reach it than a list holds, in any row of the wavefront, the own bound
+    // joins it (16 x 60 rows over 32,768 + 2,048 x 4,096, us for the call without bnd, with it alone and with both: 305, 296
+    // and 295; extensions of half the size 305, 368 and 311; of a hundredth 306, 491 and 312).
+    float tau[NMB];
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb) tau[mb] = -INFINITY;
+    if (bnd) {                                                     // (uniform)
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) tau[mb] = bnd[16 * mb + n16];
+    }
+    uint32_t mask[NMB];
+    // survivors per lane (<= 32), four blocks to a register; from the 4 lanes of a row: the offset
+    // of this lane's survivors in the row's list and the list length L (<= 128), still packed
+    constexpr int NPK = (NMB + 3) / 4;
+    uint32_t basep[NPK], Lp[NPK];
+    for (bool few = bnd != nullptr;; few = false) {                // (uniform)
+        if (!few && k <= 32) {
+            float own[NMB];
+#pragma unroll
+            for (int mb = 0; mb < NMB; ++mb) own[mb] = -INFINITY;
+#define EVOSPEC_CE(I, J) { float hi[NMB]; EVOSPEC_MB(hi[mb] = fmaxf(t[mb][I], t[mb][J])) \
+                           EVOSPEC_MB(t[mb][J] = fminf(t[mb][I], t[mb][J])) EVOSPEC_MB(t[mb][I] = hi[mb]) }
+            EVOSPEC_CE(0, 1) EVOSPEC_CE(2, 3) EVOSPEC_CE(4, 5) EVOSPEC_CE(6, 7)
+            EVOSPEC_CE(0, 2) EVOSPEC_CE(1, 3) EVOSPEC_CE(4, 6) EVOSPEC_CE(5, 7)
+            EVOSPEC_CE(1, 2) EVOSPEC_CE(5, 6) EVOSPEC_CE(0, 4) EVOSPEC_CE(3, 7)
+            EVOSPEC_CE(1, 5) EVOSPEC_CE(2, 6)
+            EVOSPEC_CE(1, 4) EVOSPEC_CE(3, 6)
+            EVOSPEC_CE(2, 4) EVOSPEC_CE(3, 5)
+            EVOSPEC_CE(3, 4)
+#undef EVOSPEC_CE
+            for (int r = 0; r < k; ++r) {
+                EVOSPEC_MB(own[mb] = t[mb][0])
+                quad_max(own);
+                // pop the head where it is the value just taken: all ones / zero select, no compare chain
+                uint32_t pop[NMB];
+                EVOSPEC_MB(pop[mb] = t[mb][0] == own[mb] ? ~0u : 0u)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    EVOSPEC_MB(const uint32_t cur = __float_as_uint(t[mb][i]);
+                               const uint32_t nxt = i < 7 ? __float_as_uint(t[mb][i + 1]) : 0xff800000u;
+                               t[mb][i] = __uint_as_float((pop[mb] & nxt) | (~pop[mb] & cur)))
+                }
+            }
+            EVOSPEC_MB(tau[mb] = fmaxf(tau[mb], own[mb]))
+        }
+        repin();
+        // survivor masks without a compare per entry: the sign of (logit - bound) is
+        // shifted in, last entry first, so that entry i ends up as bit i ("below the bound")
+        {
+            uint32_t below[NMB];
+            EVOSPEC_MB(below[mb] = 0u)
+#pragma unroll
+            for (int i = 31; i >= 0; --i) {
+                float df[NMB];
+                EVOSPEC_MB(df[mb] = acc[i >> 2][mb][i & 3] - tau[mb])
+                EVOSPEC_MB(below[mb] = __builtin_amdgcn_alignbit(below[mb], __float_as_uint(df[mb]), 31))
+            }
+            EVOSPEC_MB(mask[mb] = ~below[mb] & vmask)
+        }
+#pragma unroll
+        for (int hf = 0; hf < NPK; ++hf) {
+            uint32_t pk = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (4 * hf + q < NMB) pk |= (uint32_t)__popc(mask[4 * hf + q]) << (8 * q);
+            uint32_t q[4];
+            quad_all(pk, q);
+            basep[hf] = (g > 0 ? q[0] : 0u) + (g > 1 ? q[1] : 0u) + (g > 2 ? q[2] : 0u);
+            Lp[hf] = q[0] + q[1] + q[2] + q[3];
+        }
+        if (!few) {
+            bnd = nullptr;
+            break;
+        }
+        bool over = false;
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) over = over || (int)((Lp[mb >> 2] >> (8 * (mb & 3))) & 0xff) > cap;
+        if (__ballot(over) == 0) break;
+    }
     bool rare = false;
 
     repin();
@@ -315,7 +332,7 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
         }
         EVOSPEC_FENCE();
         if (bnd) {
-            // Few survivors (about one to a row): block by block the logits are laid out in LDS, where each lane picks
+            // Few survivors (a list's at most, mostly about one to a row): block by block the logits are laid out in LDS, where each lane picks
             // its own survivors one after the other.  (Both this and the bound: 16 x 60 rows over 32,768 + 2,048 rows x 4,096
             // 304 -> 297 us for the call.)
             unsigned char* zl = my + epi_lists(NMB) + lane * 16;       // [8][64] f32x4

@@ -50,3 +50,35 @@ def test_bound_from_extensions(ev, oracle_mod, layout, V_core, V_arc, d, lens, k
         a, b, lo = row_off[s], row_off[s + 1], V_core + s * V_arc
         sel = np.concatenate([row[:V_core], row[lo:lo + V_arc]])
         check_head(v[a:b], i[a:b], l[a:b], oracle_mod.logits(h[a:b], W[sel]), ids[sel], k, f"{layout} {V_core} {V_arc} {lens} k={k} sequence {s}")
+
+
+@pytest.mark.parametrize("layout", ["packed", "row_major"])
+@pytest.mark.parametrize("V_core,V_arc,d,lens,k", [
+    (1000, 1000, 256, [60, 1, 70, 3], 10),       # 128 x 128 tiles
+    (1000, 1000, 256, [64, 65, 1], 16),
+    (1003, 500, 128, [40, 40, 60], 5),           # a last slab of 107 rows
+    (21700, 1500, 64, [60] * 12, 10),            # 256 x 256 tiles
+])
+def test_bound_loose_for_some_rows(ev, oracle_mod, layout, V_core, V_arc, d, lens, k):
+    """Extensions that live in the first half of the hidden dimension, and draft rows that live in either half: where it is
+    the second, the extensions' logits are 0 and half of the core's reach the bound; beside them rows that it serves well."""
+    import torch
+    S, M, V = len(lens), sum(lens), V_core + len(lens) * V_arc
+    W, h = gi.gen_normal_bf16(V, d, 43, 0.05), gi.gen_h(M, d, 44)
+    W[V_core:, d // 2:] = 0
+    h[::3, :d // 2] = 0                                          # (every third draft row; the others see both halves)
+    ids = np.random.default_rng(V + M).permutation(V).astype(np.int32)
+    dW, dids, row = to_dev_bf16(W), to_dev_i32(ids), np.arange(V, dtype=np.int32)
+    W_core, W_arc = new_matrix(ev, V_core, d, layout), new_matrix(ev, V_arc, d, layout, batch=S)
+    scratch = torch.empty(max(V_core, V_arc), dtype=torch.int32, device="cuda")
+    ev.active_gather(dW, to_dev_i32(row[:V_core]), None, W_core, scratch[:V_core])
+    for s in range(S):
+        lo = V_core + s * V_arc
+        ev.active_gather(dW, to_dev_i32(row[lo:lo + V_arc]), None, W_arc.sub(s) if layout == "packed" else W_arc[s], scratch[:V_arc])
+    row_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    v, i, l = (x.cpu().numpy() for x in ev.active_lmhead_topk_segmented(
+        to_dev_bf16(h), W_core, dids[:V_core].clone(), W_arc, dids[V_core:].reshape(S, V_arc).contiguous(), row_off, k))
+    for s in range(S):
+        a, b, lo = row_off[s], row_off[s + 1], V_core + s * V_arc
+        sel = np.concatenate([row[:V_core], row[lo:lo + V_arc]])
+        check_head(v[a:b], i[a:b], l[a:b], oracle_mod.logits(h[a:b], W[sel]), ids[sel], k, f"{layout} {V_core} {V_arc} {lens} k={k} sequence {s}")
