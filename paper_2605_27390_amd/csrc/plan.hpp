@@ -251,14 +251,20 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
 }
 
 // Whether a batch of chunks gives the draft rows of every chunk to two workgroups, kSplitRows at most to each: where even
-// then a compute unit has no more than one.  Both read the weights (the second out of a cache, mostly), but with half the
+// then a compute unit has no more than one, and its slabs are hardly taller for it.  Both read the weights, but with half the
 // draft rows a wavefront has half the operand reads and matrix instructions behind every piece of them.  us for the call, without
-// and with it: 4 sequences with 197 rows over 16,384 + 1,000 rows x 4,096 77.0 and 71.3 (the extensions alone 25 and 19.4),
-// 150 rows over 8,192 + 256 60.3 and 54.1, 160 rows over 4,096 + 128 x 2,048 44.0 and 39.6.  Two to a compute unit gain no more, and
-// lose on long lists (16 x 60 rows 303 and 340).
+// and with it, core of 16,384: 4 sequences with 197 rows over 1,000 rows x 4,096 77.5 and 72.0, 8 with 480 over 500 112.6 and 107.5, over 1,000
+// 115.1 and 110.0; slabs of 64 and 80 rows: over 1,250 117.6 and 113.0, row-major x 2,048 67.7 and 66.9, 2 with 128 over 5,000 86.0 and
+// 86.9.  Taller than that, the extensions filled half of the chip and more by themselves, and the slower streams cost more than that:
+// 64 and 96 rows, 2 with 256 over 5,500 95 and 118, 8 with 480 over 1,400 x 2,048 65.0 and 68.9 (4 with 240 over 3,000 90.4 and 84.7,
+// row-major 95.0 and 96.1); 64 and 128, 8 with 480 over 2,048 119 and 132.  Two to a compute unit gain no more, and
+// lose on long lists (16 x 60 rows 303 and 340).  (Weights past the caches for both, where slab_streams_once says so: 4 with 240 over 2,048
+// x 8,192 112.2 us, through them 120.6.)
 constexpr int kSplitRows = 32;
 inline bool split_rows(int max_rows, int V_act, int d, int k, int num_cu, int chunks) {
-    return max_rows > kSplitRows && (long)make_plan(kSplitRows, V_act, d, k, num_cu, 2 * chunks, false).n_slabs * 2 * chunks <= num_cu;
+    if (max_rows <= kSplitRows) return false;
+    const Plan whole = make_plan(max_rows, V_act, d, k, num_cu, chunks, false), half = make_plan(kSplitRows, V_act, d, k, num_cu, 2 * chunks, false);
+    return (long)half.n_slabs * 2 * chunks <= num_cu && 4 * half.rt <= 5 * whole.rt;
 }
 
 // Few draft rows (narrow.hip): workgroups of kNarrowWaves wavefronts, each a run of 16-row tiles, one

@@ -90,6 +90,10 @@ int main() {
     const size_t any = ~(size_t)0;
     REQUIRE(use_tiles_early(66, 128, 1024, 10, true, any) && !use_tiles_early(66, 8448, 960, 10, true, any) && use_tiles_early(66, 8448, 960, 10, false, any), "hidden size");
     REQUIRE(use_tiles_early(66, 6144, 4096, 10, true, any) && !use_tiles_early(66, 6016, 4096, 10, true, any) && use_tiles_early(66, 128, 4096, 10, false, any), "small sets");
+    // draft rows of few extensions shared out: not where the slabs get taller than by a quarter, or a compute unit two workgroups
+    REQUIRE(split_rows(60, 1000, 4096, 10, 256, 4) && split_rows(60, 1024, 4096, 10, 256, 8) && split_rows(33, 1250, 2048, 10, 256, 8), "shared out");
+    REQUIRE(!split_rows(32, 1000, 4096, 10, 256, 4) && !split_rows(60, 2048, 4096, 10, 256, 8) && !split_rows(64, 5500, 4096, 10, 256, 4) && !split_rows(60, 1400, 2048, 10, 256, 8) &&
+            !split_rows(60, 2048, 4096, 10, 256, 16), "not shared out");
     REQUIRE(gemm_list_len(16) == 16 && gemm_list_len(17) == 32 && gemm_list_len(64) == 64, "list_len");
     REQUIRE(use_gemm(129, 4096) && !use_gemm(128, 4096) && !use_gemm(960, 4104), "use_gemm");
     std::printf("ok\n");
