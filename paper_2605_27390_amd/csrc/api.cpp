@@ -48,14 +48,6 @@ int check_head_args(const void* h, int M, int d, const void* W, int V_act, int k
     return EVOSPEC_OK;
 }
 
-// Scratch for the shared core of the segmented head: one set of partials per 64-row pass, or
-// the large-M layout from kGemmMinRows rows on.
-size_t core_workspace_bytes(int M, int d, int V_core, int k) {
-    if (evospec::use_gemm(M, d)) return evospec::make_gemm_plan(M, V_core, k).total_bytes;
-    const size_t passes = ((size_t)M + evospec::kMTile - 1) / evospec::kMTile;
-    return passes * evospec::workspace_upper_bound(V_core, k);
-}
-
 // Chunks (pieces of at most 64 rows of one sequence) whose extension partials one launch keeps.
 size_t arc_chunks(int M, int S) {
     const size_t n = (size_t)S + (size_t)M / evospec::kMTile + 1;
@@ -191,6 +183,14 @@ int evospec_active_lmhead_merge(int M, int V_act, int d, int k, float* out_vals,
 }  // extern "C"
 
 namespace evospec {
+namespace {
+hipError_t launch_tiles(const TileRoute& r, const GemmPlan& gp, const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k,
+                        char* ws, hipStream_t st, bool packed, int num_cu, const RowBound& bound) {
+    return r.small ? launch_tile_partials(h, M, d, W, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, r.parts, bound)
+                   : launch_gemm_partials(h, M, d, W, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, bound);
+}
+}  // namespace
+
 // The head, with an optional update that rides on its last merge launch.
 int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids,
               int V_act, int layout, int k, float* out_vals, int32_t* out_ids, float* out_logz,
@@ -211,12 +211,10 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     const uint16_t* hp = static_cast<const uint16_t*>(h);
-    const bool early = use_tiles_early(M, V_act, d, k, true, workspace_upper_bound(V_act, k));
-    if (use_gemm(M, d) || early) {                      // bound by the contraction: all rows at once
+    const TileRoute route = tile_route(M, V_act, d, k, num_cu, true, workspace_upper_bound(V_act, k));
+    if (route.tiles) {                                  // bound by the contraction: all rows at once
         const GemmPlan gp = make_gemm_plan(M, V_act, k);
-        hipError_t e = early || use_small_tiles(M, V_act, d, k, num_cu)
-                           ? launch_tile_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, early, {})
-                           : launch_gemm_partials(h, M, d, W_act, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, {});
+        hipError_t e = launch_tiles(route, gp, h, M, d, W_act, ids, V_act, k, ws, st, packed, num_cu, {});
         if (e != hipSuccess) return hip_fail(e);
         MergeSet a{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
         MergeSet none{};
@@ -231,7 +229,7 @@ int head_impl(const void* h, int M, int d, const void* W_act, const int32_t* ids
             const NarrowPlan np = make_narrow_plan(rows, V_act, k, num_cu);
             // (the last rows after passes over a row-major matrix, which go through the caches, find part of it there: 65 rows,
             // 36,864 x 2,048 80.3 us past the caches, 72.6 through them; 100,000 x 2,048, too large for that, 190 and 199)
-            const bool once = (packed || m0 == 0 || matrix_elems((size_t)V_act, d, false) * 2 >= ((size_t)320 << 20)) &&
+            const bool once = (packed || m0 == 0 || matrix_elems((size_t)V_act, d, false) * 2 >= (kSlabOnceMiB << 20)) &&
                               streams_once((size_t)V_act, d, packed);
             e = launch_narrow_partials(np, hp + (size_t)m0 * d, rows, d, W_act, ids, V_act, k, ws + np.keys_off,
                                        ws + np.stats_off, st, packed, once);
@@ -312,8 +310,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     char* ws = static_cast<char*>(workspace);
     const uint16_t* hp = static_cast<const uint16_t*>(h);
     const bool one_set = V_core == 0 || V_arc == 0;
-    const bool early_core = V_core > 0 && use_tiles_early(M, V_core, d, k, one_set, core_workspace_bytes(M, d, V_core, k));
-    const bool gemm_core = early_core || (V_core > 0 && use_gemm(M, d));
+    const TileRoute route = V_core > 0 ? tile_route(M, V_core, d, k, num_cu, one_set, core_workspace_bytes(M, d, V_core, k)) : TileRoute{};
     const size_t core_stride = V_core > 0 ? workspace_upper_bound(V_core, k) : 0;
     const size_t arc_stride = V_arc > 0 ? workspace_upper_bound(V_arc, k) : 0;
     char* ws_arc = ws + (V_core > 0 ? core_workspace_bytes(M, d, V_core, k) : 0);
@@ -325,11 +322,9 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     // 16,384 + 1,000 rows x 4,096 77.4 us instead of 80.8; 16 x 60 rows the same), unless there is only one set.
     MergeSet core{};
     auto launch_core = [&](const RowBound& bound) -> int {
-        if (gemm_core) {
+        if (route.tiles) {
             const GemmPlan gp = make_gemm_plan(M, V_core, k);
-            hipError_t e = early_core || use_small_tiles(M, V_core, d, k, num_cu)
-                               ? launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, early_core && one_set, bound)
-                               : launch_gemm_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, bound);
+            hipError_t e = launch_tiles(route, gp, h, M, d, W_core, ids_core, V_core, k, ws, st, packed, num_cu, bound);
             if (e != hipSuccess) return hip_fail(e);
             core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
         } else if (V_core > 0) {
@@ -360,7 +355,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         const Plan pa = V_arc > 0 ? make_plan(split ? kSplitRows : max_rows, V_arc, d, k, num_cu, split ? 2 * cb.n : cb.n, one_set) : Plan{};
         // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there.
         RowBound bound;
-        if (V_arc > 0 && gemm_core && all) {
+        if (V_arc > 0 && route.tiles && all) {
             choose_bound(&bound, pa.n_slabs, k);
             if (bound.q > 0) {
                 bound.keys = reinterpret_cast<const unsigned long long*>(ws_arc + pa.keys_off);
@@ -408,12 +403,12 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
                 flushed = true;
             }
             const int pass = m0 / kMTile;
-            const int piece_end = gemm_core ? m0 + kMTile : (pass + 1) * kMTile;
+            const int piece_end = route.tiles ? m0 + kMTile : (pass + 1) * kMTile;
             const int rows = (m_end < piece_end ? m_end : piece_end) - m0;
             const int i = cb.n++;
             cb.m0[i] = m0; cb.rows[i] = rows; cb.seq[i] = s;
-            cb.a_pass[i] = gemm_core ? 0 : pass;
-            cb.a_slot[i] = gemm_core ? m0 : m0 - pass * kMTile;
+            cb.a_pass[i] = route.tiles ? 0 : pass;
+            cb.a_slot[i] = route.tiles ? m0 : m0 - pass * kMTile;
             m0 += rows;
         }
     }

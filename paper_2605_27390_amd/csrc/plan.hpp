@@ -426,4 +426,23 @@ inline bool use_tiles_early(int M, int V_act, int d, int k, bool parts, size_t s
            make_gemm_plan(M, V_act, k).total_bytes <= scratch;
 }
 
+// How M draft rows take a matrix in matrix tiles, if they do.  one_set: no other partial set meets this one in a result.
+struct TileRoute {
+    bool tiles = false;      // all rows in one launch of matrix tiles
+    bool small = false;      // of 128 x 128
+    bool parts = false;      // which sum the hidden dimension in parts
+};
+inline TileRoute tile_route(int M, int V_act, int d, int k, int num_cu, bool one_set, size_t scratch) {
+    const bool early = use_tiles_early(M, V_act, d, k, one_set, scratch), tiles = early || use_gemm(M, d);
+    return TileRoute{tiles, early || (tiles && use_small_tiles(M, V_act, d, k, num_cu)), early && one_set};
+}
+
+// Scratch for the shared core of the segmented head: one set of partials per 64-row pass, or
+// the large-M layout from kGemmMinRows rows on.
+inline size_t core_workspace_bytes(int M, int d, int V_core, int k) {
+    if (use_gemm(M, d)) return make_gemm_plan(M, V_core, k).total_bytes;
+    const size_t passes = ((size_t)M + kMTile - 1) / kMTile;
+    return passes * workspace_upper_bound(V_core, k);
+}
+
 }  // namespace evospec

@@ -107,6 +107,15 @@ def matrix_bits(Wm, batch=None):
 def plan_route(M, V_act, d, k, cus=256):
     """How the head of this shape is launched: {"kernel": "narrow" | "slab" | "tile" | "gemm", ...}, from the
     launch planning itself, compiled with the host compiler."""
+    return _plan_route(M, V_act, d, k, cus)
+
+
+def plan_route_batched(V_core, V_arc, d, k, lens, cus=256):
+    """The same for the batched head with lens[s] draft rows in sequence s: the core's launch, and the extensions'."""
+    return _plan_route("batched", V_core, V_arc, d, k, cus, *lens)
+
+
+def _plan_route(*args):
     import os
     import subprocess
     import tempfile
@@ -116,5 +125,5 @@ def plan_route(M, V_act, d, k, cus=256):
         subprocess.check_call(["g++", "-std=c++17", "-I", os.path.join(root, "paper_2605_27390_amd", "csrc"),
                                os.path.join(root, "tests", "plan_route.cpp"), "-o", exe])
         plan_route.exe = exe
-    line = subprocess.check_output([plan_route.exe] + [str(x) for x in (M, V_act, d, k, cus)], text=True)
+    line = subprocess.check_output([plan_route.exe] + [str(x) for x in args], text=True)
     return {a: int(b) if b.isdigit() else b for a, b in (w.split("=") for w in line.split())}
