@@ -29,6 +29,17 @@ int main() {
                             REQUIRE((long)p.n_slabs * p.rt >= V_act && (long)(p.n_slabs - 1) * p.rt < V_act, "slabs=%d rt=%d V_act=%d", p.n_slabs, p.rt, V_act);
                             REQUIRE(p.lds_bytes <= (size_t)kLdsLimit, "lds=%zu", p.lds_bytes);
                             REQUIRE(p.gl >= 0 && p.gl <= 2, "gl=%d", p.gl);
+                            REQUIRE(p.segs == 1 || (p.segs == 2 && d % 2048 == 0 && p.ks <= 2), "segments=%d d=%d ks=%d", p.segs, d, p.ks);
+                            // (partial sums of a shared tile, and of the other segment, behind one another)
+                            REQUIRE(p.lds_bytes >= 2ull * 16 * p.mb * kHStride * 2 + slab_level_bytes(p.nw * p.ks, p.mb, p.segs), "lds=%zu segments=%d", p.lds_bytes, p.segs);
+                            // without sharing, as where two sets meet: a logit's sum runs front to back
+                            const Plan q = make_plan(rows, V_act, d, k, cu, replicas, false);
+                            REQUIRE(q.ks == 1 && q.segs == 1 && q.rt == p.rt, "two sets ks=%d segments=%d", q.ks, q.segs);
+                            for (int chunks : {1, 4, 16})
+                                if (split_rows(rows, V_act, d, k, cu, chunks)) {
+                                    const Plan s = make_plan(kSplitRows, V_act, d, k, cu, 2 * chunks, false);
+                                    REQUIRE(rows > kSplitRows && s.mb == mb_for_rows(kSplitRows) && s.ks == 1 && (long)s.n_slabs * 2 * chunks <= cu, "shared out rows=%d V_act=%d chunks=%d", rows, V_act, chunks);
+                                }
                             // the workspace the ABI asks callers for covers the plan's own layout
                             REQUIRE(p.stats_off >= (size_t)p.n_slabs * kMTile * k * 8, "stats_off");
                             REQUIRE(p.total_bytes <= workspace_upper_bound(V_act, k), "total=%zu bound=%zu V_act=%d k=%d nw=%d", p.total_bytes,
@@ -86,6 +97,29 @@ int main() {
     REQUIRE(use_small_tiles(200, 16384, 4096, 10, 256) && use_small_tiles(129, 1, 64, 1, 256) && use_small_tiles(300, 20000, 2048, 10, 256), "small tiles");
     REQUIRE(!use_small_tiles(960, 32768, 4096, 10, 256) && !use_small_tiles(512, 32768, 4096, 10, 256) && !use_small_tiles(256, 45000, 5120, 10, 256), "large tiles");
     REQUIRE(use_small_tiles(256, 45000, 1024, 10, 256) && use_small_tiles(512, 20011, 2560, 10, 256) && !use_small_tiles(512, 20011, 2560, 1, 256), "three rounds");
+    // a bound from other lists: q of each of `sets` lists are k logits, of lists that are there and entries that they have
+    for (int k = 1; k <= kKMax; ++k)
+        for (int n = 1; n <= 300; ++n) {
+            RowBound b;
+            choose_bound(&b, n, k);
+            REQUIRE(b.k == k && b.n_lists <= n && b.n_lists <= kBoundLists && b.q <= 2 && (b.q == 0 || k <= 16), "k=%d lists=%d", k, n);
+            REQUIRE(b.q == 0 || (b.q <= k && b.sets >= 1 && b.sets <= b.n_lists && b.q * b.sets >= k), "k=%d lists=%d q=%d sets=%d", k, n, b.q, b.sets);
+        }
+    // 65 to 128 rows in tiles: the lists fit the scratch, whatever the caller's is
+    for (int M = 1; M <= 300; ++M)
+        for (int k : {1, 4, 7, 8, 10, 12, 13, 16, 17, 64})
+            for (int d : {64, 264, 512, 1024, 1088, 4096})
+                for (int V_act = k; V_act <= 200000; V_act += V_act / 3 + 7) {
+                    const size_t head = workspace_upper_bound(V_act, k), core = core_workspace_bytes(M, d, V_act, k);
+                    const TileRoute r = tile_route(M, V_act, d, k, 256, true, head), two = tile_route(M, V_act, d, k, 256, false, core);
+                    REQUIRE(r.tiles == two.tiles || (M > kMTile && M < kGemmMinRows), "M=%d", M);
+                    if (M <= kMTile) REQUIRE(!r.tiles && !two.tiles, "M=%d", M);
+                    REQUIRE(!r.parts || (r.tiles && r.small && M < kGemmMinRows && d >= kTilePartsMinD && k <= 12), "parts M=%d d=%d k=%d", M, d, k);
+                    REQUIRE(!two.parts && (!r.tiles || d % 64 == 0) && (!two.tiles || d % 64 == 0), "two sets M=%d d=%d", M, d);
+                    const size_t need = make_gemm_plan(M, V_act, k).total_bytes;
+                    if (r.tiles && M < kGemmMinRows) REQUIRE(need <= head, "M=%d V_act=%d k=%d", M, V_act, k);
+                    if (two.tiles) REQUIRE(need <= core, "M=%d V_act=%d k=%d", M, V_act, k);
+                }
     // 65 to 128 rows: one set in parts from 1,024 hidden elements on, where the matrix is large enough for them; two sets always
     const size_t any = ~(size_t)0;
     REQUIRE(use_tiles_early(66, 128, 1024, 10, true, any) && !use_tiles_early(66, 8448, 960, 10, true, any) && use_tiles_early(66, 8448, 960, 10, false, any), "hidden size");

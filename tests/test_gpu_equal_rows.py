@@ -4,7 +4,7 @@ not on their order.  Needs an MI355X: run with `-m gpu`."""
 import numpy as np
 import pytest
 
-from helpers import new_matrix, to_dev_i32
+from helpers import new_matrix, plan_route_batched, to_dev_i32
 from test_gpu_parity import ev  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
@@ -45,6 +45,7 @@ def check_equal_rows(vals, out_ids, ids, group, where):
     (9000, 4096, 40, 10),
     (9000, 3000, 40, 10),      # no whole number of chunks
     (5000, 1024, 100, 10),     # two passes over the matrix
+    (5000, 1024, 80, 10),      # 128 x 128 tiles, in parts
     (3000, 1024, 200, 10),     # 128 x 128 tiles
 ])
 def test_equal_rows_and_order(ev, layout, V_act, d, M, k):
@@ -70,16 +71,20 @@ def test_equal_rows_and_order(ev, layout, V_act, d, M, k):
 
 
 @pytest.mark.parametrize("layout", ["packed", "row_major"])
-@pytest.mark.parametrize("V_core,V_arc,d,lens", [
-    (16000, 400, 512, [20, 1, 40]),          # core in one pass of slabs of 4 tiles
-    (36864, 900, 1024, [33, 64, 10]),        # core of 9 tiles, extensions of 4
-    (2000, 2000, 2048, [60, 17, 60, 8]),     # 128 x 128 tiles and slabs
-    (300, 17000, 256, [64]),
+@pytest.mark.parametrize("V_core,V_arc,d,lens,k,core", [
+    (16000, 400, 512, [20, 1, 40], 12, "slab"),          # core in one pass of slabs of 4 tiles
+    (36864, 900, 1024, [33, 64, 10], 12, "tile"),        # 107 rows: 128 x 128 tiles in a single chain, extensions of 4 tiles
+    (36864, 900, 1024, [33, 64, 10], 13, "slab"),        # core of 9 tiles in two passes, extensions of 4
+    (36864, 900, 2048, [33, 64, 10], 13, "slab"),        # a hidden dimension that a call with one set takes in two segments
+    (2000, 2000, 2048, [60, 17, 60, 8], 12, "tile"),     # 128 x 128 tiles and slabs
+    (300, 17000, 256, [64], 12, "slab"),
 ])
-def test_equal_rows_in_core_and_extension(ev, layout, V_core, V_arc, d, lens):
+def test_equal_rows_in_core_and_extension(ev, layout, V_core, V_arc, d, lens, k, core):
     """Copies of one row in the shared core and in an extension tie as well."""
     import torch
-    S, M, k = len(lens), sum(lens), 12
+    S, M = len(lens), sum(lens)
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count)
+    assert r["kernel"] == core and "parts" not in r and r.get("segments", 1) == 1
     W, group = scattered_copies(V_core + V_arc, 4, d, V_core + d)
     rng = np.random.default_rng(d)
     ids = rng.permutation(2 * (V_core + V_arc)).astype(np.int32)

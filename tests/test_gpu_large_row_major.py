@@ -20,6 +20,7 @@ def test_past_the_caches(ev, V_act, d, M, k, shared):
     import torch
     r = plan_route(M, V_act, d, k, torch.cuda.get_device_properties(0).multi_processor_count)
     assert r["kernel"] == "slab" and shared in (None, r["shared"]) and V_act * d * 2 >= 320 << 20
+    assert r["segments"] == (2 if d % 2048 == 0 else 1)
     g = torch.Generator(device="cuda").manual_seed(V_act)
     W = torch.empty((V_act, d), dtype=torch.bfloat16, device="cuda").normal_(0, 0.05, generator=g)
     h = torch.empty((M, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import evospec_inputs as gi
-from helpers import check_head, new_matrix, to_dev_bf16, to_dev_i32
+from helpers import check_head, new_matrix, plan_route_batched, to_dev_bf16, to_dev_i32
 from test_gpu_parity import ev  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
@@ -26,6 +26,9 @@ pytestmark = pytest.mark.gpu
 ])
 def test_bound_from_extensions(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, arc_scale):
     import torch
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count)
+    assert r["kernel"] == ("gemm" if V_core > 20000 else "tile")
+    assert r["bound"] == {300: 0, 500: 2}.get(V_arc, 2 if k == 16 else 1)
     S, M = len(lens), sum(lens)
     rng = np.random.default_rng(V_core + V_arc + M + k)
     V = V_core + S * V_arc

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("V_act,d,M,k,tiles,blocks,shared", [
-    (4200, 2048, 60, 10, 4, 4, 4),       # two segments of four chunks; the last slab is ragged
+    (4200, 2048, 60, 10, 4, 4, 4),       # four wavefronts to a tile: one segment; the last slab is ragged
+    (4200, 2048, 20, 10, 4, 2, 2),       # two segments of four chunks
     (4200, 4096, 20, 10, 4, 2, 2),       # of eight chunks, taken four at a time
     (18000, 2048, 40, 40, 5, 4, 2),      # pairs of logits as groups: more LDS
     (18000, 2048, 12, 10, 5, 1, 1),
@@ -20,12 +21,16 @@ pytestmark = pytest.mark.gpu
     (33001, 2048, 64, 33, 9, 4, 1),      # one wavefront per tile
     (45000, 2048, 33, 10, 12, 4, 1),     # tallest slabs
     (131080, 2048, 17, 10, 12, 2, 1),    # several rounds, two workgroups on a compute unit
-    (5000, 6144, 33, 10, 4, 4, 4),       # three turns of eight chunks
+    (5000, 6144, 33, 10, 4, 4, 4),       # one segment
+    (18000, 6144, 33, 10, 5, 4, 2),      # three turns of eight chunks: an odd number
+    (4200, 6144, 20, 10, 4, 2, 2),
+    (4200, 10240, 17, 10, 4, 2, 2),      # five
 ])
 def test_two_segments(ev, oracle_mod, V_act, d, M, k, tiles, blocks, shared):
     import torch
     r = plan_route(M, V_act, d, k, torch.cuda.get_device_properties(0).multi_processor_count)
     assert (r["kernel"], r["tiles"], r["blocks"], r["shared"]) == ("slab", tiles, blocks, shared)
+    assert r["segments"] == (1 if shared == 4 else 2)
     rng = np.random.default_rng(V_act + d)
     g = torch.Generator(device="cuda").manual_seed(V_act + M)
     base = torch.empty((V_act // 4 + 1, d), dtype=torch.bfloat16, device="cuda").normal_(0, 0.05, generator=g)

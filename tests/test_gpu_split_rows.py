@@ -4,22 +4,26 @@ import numpy as np
 import pytest
 
 import evospec_inputs as gi
-from helpers import check_head, new_matrix, to_dev_bf16, to_dev_i32
+from helpers import check_head, new_matrix, plan_route_batched, to_dev_bf16, to_dev_i32
 from test_gpu_parity import ev  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("layout", ["packed", "row_major"])
-@pytest.mark.parametrize("V_core,V_arc,d,lens,k", [
-    (500, 130, 264, [32, 33, 0, 1], 10),          # core in slabs; a slab of two rows
-    (500, 128, 256, [33, 31], 17),
-    (700, 700, 2048, [64, 1, 70, 33], 10),        # core in tiles
-    (700, 90, 512, [150], 64),                    # three chunks of one sequence
-    (700, 2000, 256, [40, 64, 33], 24),           # pairs of logits as groups
+@pytest.mark.parametrize("V_core,V_arc,d,lens,k,core,tiles", [
+    (500, 130, 264, [32, 33, 0, 1], 10, "slab", None),      # the pass cuts the longest chunk to 32 rows: not shared out
+    (500, 130, 264, [33, 31, 0, 2], 10, "slab", 4),         # a slab of two rows
+    (500, 128, 256, [33, 31], 17, "slab", 4),
+    (700, 700, 2048, [64, 1, 70, 33], 10, "tile", 4),
+    (700, 90, 512, [150], 64, "tile", 4),                   # three chunks of one sequence
+    (700, 2000, 256, [40, 64, 33], 24, "tile", 4),          # pairs of logits as groups
+    (700, 1250, 256, [40] * 8, 10, "tile", 5),              # taller slabs than without
 ])
-def test_split_rows(ev, oracle_mod, layout, V_core, V_arc, d, lens, k):
+def test_split_rows(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, core, tiles):
     import torch
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count)
+    assert r["kernel"] == core and r["split"] == (tiles is not None) and tiles in (None, r["arc_tiles"])
     S, M, V = len(lens), sum(lens), V_core + len(lens) * V_arc
     ids = np.random.default_rng(V + M).permutation(V).astype(np.int32)
     W, h = gi.gen_normal_bf16(V, d, 51, 0.05), gi.gen_h(M, d, 52)
