@@ -23,6 +23,7 @@ pytestmark = pytest.mark.gpu
     (1000, 1000, 256, [33, 64, 64], 10, 0.0),        # every logit of the extensions is 0
     (21700, 1500, 64, [60] * 12, 10, 1.0),           # 256 x 256 tiles
     (21700, 1500, 64, [64] * 12, 7, 0.05),
+    (1000, 700, 64, [3] * 64, 2, 1.0),               # as many chunks as one launch takes
 ])
 def test_bound_from_extensions(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, arc_scale):
     import torch
