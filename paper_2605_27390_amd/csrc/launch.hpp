@@ -51,7 +51,7 @@ hipError_t launch_narrow_partials(const NarrowPlan& p, const void* h, int M, int
 // in any order, stats float2 [M][ceil(V_act/128)].
 hipError_t launch_gemm_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act,
                                 int k, void* keys, void* stats, hipStream_t stream, bool packed, const RowBound& bound);
-// The same partials from 128 x 128 tiles, on num_cu compute units; parts: the hidden dimension (kTileParts * 64 and more) in parts.
+// The same partials from 128 x 128 tiles, on num_cu compute units; parts: the hidden dimension (kTilePartsMinD and more) in parts.
 hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
                                 void* stats, hipStream_t stream, bool packed, int num_cu, bool parts, const RowBound& bound);
 hipError_t launch_merge(const MergeSet& a, const MergeSet& b, int k, float* out_vals, int32_t* out_ids,
