@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libevospec.so")
 SOURCES = ["kernels.hip", "gemm.hip", "tile.hip", "narrow.hip", "klgate.hip", "noalloc.hip", "api.cpp", "arc.cpp", "path_a.cpp"]
-HEADERS = ["plan.hpp", "launch.hpp", "common.hpp", "slab_epilogue.hpp", os.path.join(ROOT, "include", "evospec.h"),
+HEADERS = ["plan.hpp", "launch.hpp", "common.hpp", "slab.hpp", "slab_epilogue.hpp", os.path.join(ROOT, "include", "evospec.h"),
            os.path.join(ROOT, "include", "evospec_arc.h")]
 
 HIPCC_FLAGS = [

@@ -351,6 +351,28 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         if (cb.n == 0) return EVOSPEC_OK;
         int max_rows = 0;
         for (int i = 0; i < cb.n; ++i) max_rows = cb.rows[i] > max_rows ? cb.rows[i] : max_rows;
+        BatchLayout bl;
+        bl.seq_rows = V_arc;
+        bl.chunk_bytes = arc_stride;
+        bl.packed = packed;
+        if (!route.tiles && !one_set && !core_done) {   // slabs of both sets in one launch
+            const JointPlan jp = make_joint_plan(M, V_core, V_arc, cb.n, d, k, num_cu);
+            CoreSet cs;
+            cs.W = W_core; cs.ids = ids_core; cs.V = V_core; cs.M = M;
+            cs.keys = ws + jp.core.keys_off; cs.stats = ws + jp.core.stats_off;
+            cs.pass_keys = cs.pass_stats = core_stride / 8;
+            cs.n_slabs = jp.core.n_slabs; cs.chunk_slabs = jp.arc.n_slabs;
+            cs.blocks = jp.core.n_slabs * ((M + kMTile - 1) / kMTile);
+            hipError_t e = launch_partials_batch(jp.arc, h, cb, cs, bl, d, W_arc, ids_arc, V_arc, k,
+                                                 ws_arc + jp.arc.keys_off, ws_arc + jp.arc.stats_off, st);
+            if (e != hipSuccess) return hip_fail(e);
+            core = MergeSet{ws + jp.core.keys_off, ws + jp.core.stats_off, jp.core.n_slabs, 0, kMTile};
+            core_done = true;
+            const MergeSet arc{ws_arc + jp.arc.keys_off, ws_arc + jp.arc.stats_off, jp.arc.n_slabs, 0, kMTile};
+            e = launch_merge_batch(core, core_stride, arc, arc_stride, cb, k, out_vals, out_ids, out_logz, st);
+            cb.n = 0;
+            return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);
+        }
         const bool split = V_arc > 0 && !one_set && split_rows(max_rows, V_arc, d, k, num_cu, cb.n);
         const Plan pa = V_arc > 0 ? make_plan(split ? kSplitRows : max_rows, V_arc, d, k, num_cu, split ? 2 * cb.n : cb.n, one_set) : Plan{};
         // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there.
@@ -372,12 +394,8 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         }
         MergeSet arc{};
         if (V_arc > 0) {
-            BatchLayout bl;
-            bl.seq_rows = V_arc;
-            bl.chunk_bytes = arc_stride;
-            bl.packed = packed;
             bl.split = split;
-            hipError_t e = launch_partials_batch(pa, h, cb, bl, d, W_arc, ids_arc, V_arc, k,
+            hipError_t e = launch_partials_batch(pa, h, cb, CoreSet{}, bl, d, W_arc, ids_arc, V_arc, k,
                                                  ws_arc + pa.keys_off, ws_arc + pa.stats_off, st);
             if (e != hipSuccess) return hip_fail(e);
             arc = MergeSet{ws_arc + pa.keys_off, ws_arc + pa.stats_off, pa.n_slabs, 0, kMTile};

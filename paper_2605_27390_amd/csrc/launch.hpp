@@ -30,7 +30,8 @@ struct BatchLayout {
     bool packed = false;            // the matrix is in operand-tile layout (plan.hpp), one padded matrix per sequence
 };
 
-hipError_t launch_partials_batch(const Plan& p, const void* h, const ChunkBatch& cb, const BatchLayout& bl,
+// core.blocks > 0: the core of the batch in the same launch, of a plan of make_joint_plan.
+hipError_t launch_partials_batch(const Plan& p, const void* h, const ChunkBatch& cb, const CoreSet& core, const BatchLayout& bl,
                                  int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
                                  void* stats, hipStream_t stream);
 // One launch merges every chunk of the batch: row r of chunk i takes slot a_slot[i] + r of the first

@@ -58,6 +58,20 @@ struct ChunkBatch {
     int a_slot[kMaxChunks];
 };
 
+// The shared core of a batch, where it rides in the launch of the extensions' slabs: its passes of kMTile draft rows, one after the
+// other, `blocks` workgroups in all.
+struct CoreSet {
+    const void* W = nullptr;
+    const int32_t* ids = nullptr;
+    void* keys = nullptr;
+    void* stats = nullptr;
+    size_t pass_keys = 0, pass_stats = 0;     // u64 and float2 between two passes' partials
+    int V = 0, M = 0;                         // its rows, and all draft rows
+    int n_slabs = 0;                          // slabs of a pass
+    int blocks = 0;                           // 0: no core in this launch
+    int chunk_slabs = 0;                      // slabs of an extension
+};
+
 constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Operand-tile ("packed") layout of a compact matrix.  The slab kernel hands a wavefront 16 rows and
@@ -221,6 +235,15 @@ inline int segments_for(int nw, int ks, int mb, int d, int k, long rounds) {
 // share: several wavefronts may share a tile.  Their parts of a logit's sum are added at the end, another order
 // than one wavefront's, so launches whose logits meet in one result must not differ in it: the calls that merge
 // two partial sets (a core and an extension) go without.
+inline void lay_out(Plan* p, int k) {
+    p->keys_off = 0;
+    p->stats_off = align_up((size_t)p->n_slabs * kMTile * k * 8, 256);
+    p->total_bytes = p->stats_off + align_up((size_t)p->n_slabs * kMTile * 8, 256);
+}
+inline long round_cost(long rounds, int rt, int d) {
+    const long cost = rounds * (rt + kRoundRows) * 8;
+    return ((size_t)rt * (size_t)d * 2) % ((size_t)1 << 20) == 0 ? cost + cost / 8 : cost;
+}
 inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, int d, int k, int num_cu,
                       int replicas = 1 /*chunks that share the launch*/, bool share = true) {
     Plan best;
@@ -233,8 +256,7 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
         const size_t lds = lds_bytes_for(nw, mb, k);
         if (lds > (size_t)kLdsLimit) continue;
         const long rounds = ((long)n_slabs * replicas + num_cu - 1) / num_cu;
-        long cost = rounds * (rt + kRoundRows) * 8;
-        if (((size_t)rt * (size_t)d * 2) % ((size_t)1 << 20) == 0) cost += cost / 8;
+        const long cost = round_cost(rounds, rt, d);
         if (best_cost < 0 || cost < best_cost || (cost == best_cost && rt > best.rt)) {
             best_cost = cost;
             best.nw = nw; best.mb = mb;
@@ -244,9 +266,41 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
             best.gl = group_level_for(k, nw); best.lds_bytes = lds_bytes_for(nw, mb, k, best.ks, best.segs);
         }
     }
-    best.keys_off = 0;
-    best.stats_off = align_up((size_t)best.n_slabs * kMTile * k * 8, 256);
-    best.total_bytes = best.stats_off + align_up((size_t)best.n_slabs * kMTile * 8, 256);
+    lay_out(&best, k);
+    return best;
+}
+
+// The plans of a core of V_core rows (M draft rows in passes of kMTile) and of `chunks` extensions of V_arc rows that share one
+// launch: one slab shape for both, chosen by the same costs over all their slabs.  No tile is shared and no row in segments (see make_plan).
+// A launch of a few slabs is a chain of chunks that leaves the chip idle (4 extensions of 226 rows x 4,096: 16 workgroups, 19 us, row-major
+// 38), and so is each pass of a small core: side by side they cost what the longest of them does.  One launch after the other and all
+// in one, us for the call: packed, 11,986 + 226 x 4,096, 60 rows of 4 sequences 58 and 39; 32,768 + 2,048, 60 rows of 2 72.6 and 61.7; 5,000 + 200 x
+// 2,048, 24 rows of 2 26.1 and 16.4; 30,000 + 1,500 x 2,048, 60 rows of 7 55 and 42; two passes, 20,000 + 1,000, 120 rows of 5, k = 20 115 and 78;
+// row-major, 69 rows of 4 over 11,986 + 226, k = 45 136 and 72; 40 rows of 2 over 32,768 + 2,048 97.6 and 75.6.
+struct JointPlan { Plan core, arc; };
+inline JointPlan make_joint_plan(int M, int V_core, int V_arc, int chunks, int d, int k, int num_cu) {
+    JointPlan best;
+    long best_cost = -1;
+    const int mb = mb_for_rows(M < kMTile ? M : kMTile), passes = (M + kMTile - 1) / kMTile;
+    for (int i = 0; i < kNumShapes; ++i) {
+        Plan c;
+        c.nw = kShapes[i].nw; c.mb = mb; c.rt = 16 * c.nw;
+        c.gl = group_level_for(k, c.nw);
+        c.lds_bytes = lds_bytes_for(c.nw, mb, k);
+        if (c.lds_bytes > (size_t)kLdsLimit) continue;
+        Plan a = c;
+        c.n_slabs = (V_core + c.rt - 1) / c.rt;
+        a.n_slabs = (V_arc + a.rt - 1) / a.rt;
+        const long rounds = ((long)c.n_slabs * passes + (long)a.n_slabs * chunks + num_cu - 1) / num_cu;
+        const long cost = round_cost(rounds, c.rt, d);
+        if (best_cost < 0 || cost < best_cost || (cost == best_cost && c.rt > best.core.rt)) {
+            best_cost = cost;
+            lay_out(&c, k);
+            lay_out(&a, k);
+            best.core = c;
+            best.arc = a;
+        }
+    }
     return best;
 }
 

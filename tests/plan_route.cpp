@@ -43,6 +43,10 @@ static int batched(int n, char** a) {
         if (r.tiles) choose_bound(&b, p.n_slabs, k);
         std::printf(" chunks=%d split=%d arc_tiles=%d arc_blocks=%d bound=%d", chunks, split ? 1 : 0, p.nw, p.mb, b.q);
     }
+    if (!r.tiles && !one_set) {                                // both sets in one launch
+        const JointPlan j = make_joint_plan(M, V_core, V_arc, chunks, d, k, cus);
+        std::printf(" joint_tiles=%d joint_blocks=%d joint_slabs=%d", j.core.nw, j.core.mb, j.core.n_slabs);
+    }
     std::printf("\n");
     return 0;
 }
