@@ -15,7 +15,7 @@ namespace evospec {
 constexpr int kMTile = 64;          // draft rows per pass over W_act
 constexpr int kKMax = 64;           // largest supported k
 constexpr int kKC = 256;            // hidden-dimension chunk staged in LDS per step
-constexpr int kHStride = kKC + 8;   // LDS row stride of the h chunk (bf16 elements, +16 B pad)
+constexpr int kHStride = kKC;       // LDS row stride of the h chunk (bf16 elements; its pieces are permuted, see slab.hpp)
 constexpr int kRowsMinSlab = 64;    // smallest slab any plan uses (workspace upper bound)
 constexpr int kLdsLimit = 160 * 1024;
 constexpr int kRoundRows = 37;      // fixed cost of a round of workgroups, in slab rows (see make_plan)

@@ -136,7 +136,7 @@ __device__ __forceinline__ void slab_partials(const SlabProblem& pr, int slab, i
         const int m = idc / (KC / 8), c8 = idc % (KC / 8);
         hcol[p] = c8 * 8;
         hsrc[p] = (gvec_ptr)(h + (size_t)min(m, rows - 1) * d + c8 * 8);
-        hdst[p] = m * kHStride + c8 * 8;
+        hdst[p] = m * kHStride + (c8 ^ (m & 15)) * 8;
     }
 
     // Loads past the end of a row (only in the last chunk when d is not a multiple of KC: `whole` says that
@@ -178,10 +178,17 @@ __device__ __forceinline__ void slab_partials(const SlabProblem& pr, int slab, i
             }
         }
     };
-    auto load_b = [&](bf16x8 (&b)[MB], int buf, int s) {
+    // h in LDS: piece c (16 bytes) of draft row m sits in place c ^ (m mod 16) of its row.  A 128-bit read takes the 64 lanes in four turns
+    // of 16, {0-3, 12-15, 20-27} the first, which holds every draft row of the block once: 16 different 16-byte columns of 256 bytes, no
+    // bank twice.  (Rows padded by 16 bytes had one conflict in every turn, which doubled its time.)
+    const uint16_t* brow = Hs + n16 * kHStride;
+    int bcol[4];                                   // this lane's piece of k-steps 0..3 (4..7: 128 elements on), relative to its row
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-            b[mb] = *reinterpret_cast<const bf16x8*>(Hs + ((size_t)buf * MR + mb * 16 + n16) * kHStride + (s0 + s) * 32 + g * 8);
+    for (int s = 0; s < 4; ++s) bcol[s] = ((4 * (((KS > 1 ? s0 : 0) + s) & 3) + g) ^ n16) * 8;
+    auto load_b = [&](bf16x8 (&b)[MB], int buf, int s) {
+        const int at = bcol[s & 3] + ((KS > 1 ? s0 : 0) + s) / 4 * 128;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) b[mb] = *reinterpret_cast<const bf16x8*>(brow + ((size_t)buf * MR + mb * 16) * kHStride + at);
     };
     auto mfma_step = [&](int slot, const bf16x8 (&b)[MB]) {
         u32x4 x = wr[slot];
