@@ -186,7 +186,7 @@ namespace evospec {
 namespace {
 hipError_t launch_tiles(const TileRoute& r, const GemmPlan& gp, const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k,
                         char* ws, hipStream_t st, bool packed, int num_cu, const RowBound& bound) {
-    return r.small ? launch_tile_partials(h, M, d, W, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, r.parts, bound)
+    return r.small ? launch_tile_partials(h, M, d, W, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, r.parts, bound, nullptr)
                    : launch_gemm_partials(h, M, d, W, ids, V_act, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, bound);
 }
 }  // namespace
@@ -369,6 +369,21 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
             core = MergeSet{ws + jp.core.keys_off, ws + jp.core.stats_off, jp.core.n_slabs, 0, kMTile};
             core_done = true;
             const MergeSet arc{ws_arc + jp.arc.keys_off, ws_arc + jp.arc.stats_off, jp.arc.n_slabs, 0, kMTile};
+            e = launch_merge_batch(core, core_stride, arc, arc_stride, cb, k, out_vals, out_ids, out_logz, st);
+            cb.n = 0;
+            return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);
+        }
+        const Plan pt = make_tile_batch_plan(max_rows, V_arc, k);
+        if (route.tiles && route.small && !one_set && !core_done && joint_tiles(M, V_core, d, num_cu, packed, pt.n_slabs, cb.n)) {
+            // tiles of the core and slabs of the extensions in one launch
+            const GemmPlan gp = make_gemm_plan(M, V_core, k);
+            const Plan& pa = pt;
+            const TileBatch tb{&pa, &cb, W_arc, ids_arc, V_arc, arc_stride, ws_arc + pa.keys_off, ws_arc + pa.stats_off};
+            hipError_t e = launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, false, RowBound{}, &tb);
+            if (e != hipSuccess) return hip_fail(e);
+            core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
+            core_done = true;
+            const MergeSet arc{ws_arc + pa.keys_off, ws_arc + pa.stats_off, pa.n_slabs, 0, kMTile};
             e = launch_merge_batch(core, core_stride, arc, arc_stride, cb, k, out_vals, out_ids, out_logz, st);
             cb.n = 0;
             return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);

@@ -52,9 +52,20 @@ hipError_t launch_narrow_partials(const NarrowPlan& p, const void* h, int M, int
 // in any order, stats float2 [M][ceil(V_act/128)].
 hipError_t launch_gemm_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act,
                                 int k, void* keys, void* stats, hipStream_t stream, bool packed, const RowBound& bound);
+// The extensions of a batch whose slabs ride in the launch of the core's small tiles.
+struct TileBatch {
+    const Plan* plan;               // of the extensions (4 tiles to a slab, no shared tiles, one segment)
+    const ChunkBatch* cb;
+    const void* W;
+    const int32_t* ids;
+    int seq_rows;
+    size_t chunk_bytes;
+    void* keys;
+    void* stats;
+};
 // The same partials from 128 x 128 tiles, on num_cu compute units; parts: the hidden dimension (kTilePartsMinD and more) in parts.
 hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
-                                void* stats, hipStream_t stream, bool packed, int num_cu, bool parts, const RowBound& bound);
+                                void* stats, hipStream_t stream, bool packed, int num_cu, bool parts, const RowBound& bound, const TileBatch* tb);
 hipError_t launch_merge(const MergeSet& a, const MergeSet& b, int k, float* out_vals, int32_t* out_ids,
                         float* out_logz, int out_row0, int nrows, hipStream_t stream,
                         const GatherArgs* update = nullptr);

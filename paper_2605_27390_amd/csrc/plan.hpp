@@ -304,6 +304,28 @@ inline JointPlan make_joint_plan(int M, int V_core, int V_arc, int chunks, int d
     return best;
 }
 
+// The plan of extensions that share a launch with small tiles, whose workgroups have four wavefronts.
+inline Plan make_tile_batch_plan(int max_rows, int V_arc, int k) {
+    Plan p;
+    p.nw = 4; p.mb = mb_for_rows(max_rows); p.rt = 16 * p.nw;
+    p.n_slabs = (V_arc + p.rt - 1) / p.rt;
+    p.gl = group_level_for(k, p.nw);
+    p.lds_bytes = lds_bytes_for(p.nw, p.mb, k);
+    lay_out(&p, k);
+    return p;
+}
+
+// Whether the extensions' slabs (of make_tile_batch_plan) ride in the launch of the core's small tiles.  Without and with it, us for the call, k = 10:
+// packed, 5,225 + 151 x 4,096, 220 rows of 11 52 and 35; 9,276 + 522 x 2,048, 363 of 16 47.6 and 37.5; 14,416 + 332 x 4,096, 477 of 13
+// 106 and 93; 16,384 + 1,000 x 4,096, 197 of 4 72 and 69.5; 4,000 + 2,000 x 4,096, 400 of 16 98 and 84.  Row-major slabs are slower, and tiles that share a
+// compute unit have a ring of two stages: where both fit the chip once (5,225 + 151 62 and 39), where the tiles take more than
+// a round anyway (14,416 + 332 117 and 104), or beside a few slabs with short rows (16,384 + 1,000 x 2,048, 250 of 5 54 and
+// 51; x 4,096, 197 of 4 82 and 86; 4,906 + 1,764 x 4,096, 293 of 7, 117 tiles and 196 slabs, 79 and 91).
+inline bool joint_tiles(int M, int V_core, int d, int num_cu, bool packed, int arc_slabs, int chunks) {
+    const int tiles = ((V_core + 127) / 128) * ((M + 127) / 128);
+    return packed || tiles > num_cu || tiles + arc_slabs * chunks <= num_cu || (d <= 2048 && 2 * arc_slabs * chunks <= tiles);
+}
+
 // Whether a batch of chunks gives the draft rows of every chunk to two workgroups, kSplitRows at most to each: where even
 // then a compute unit has no more than one, and its slabs are hardly taller for it.  Both read the weights, but with half the
 // draft rows a wavefront has half the operand reads and matrix instructions behind every piece of them.  us for the call, without
@@ -388,20 +410,24 @@ inline int gemm_list_len(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 // 36,864 x 2,048 86 and 89, 256 x 45,000 x 1,024 65 and 58; two and five: 512 x 40,000 x 2,560 183 and 155; 200 x 16,384 x
 // 4,096 130 and 52).  A last slab whose rows are too few for the bound (but more than a list holds) sends all its
 // draft rows through the selection one by one, four times as many in a wavefront of large tiles (512 x 20,011 x 2,560 137
-// and 112 at k = 10; at k = 1, where the bound holds, 91 and 100).
+// and 112 at k = 10; at k = 1, where the bound holds, 91 and 100).  From k = 13 on most rows have more survivors than a list, which large tiles
+// select one by one and small ones by halves: 65,536 x 4,096 at 500 rows, k = 13 336 and 298, k = 16 516 and 304, k = 32 553 and 370;
+// 32,768 x 4,096 at 960, k = 64 486 and 368; 32,768 x 1,024 at 512, k = 20 169 and 74.
 constexpr int kTileRows = 128;
+constexpr int kTileMaxD = 1 << 23;         // (rows of a tile within 32-bit offsets)
 inline bool slow_last_slab(int V_act, int k) {
     const int last = V_act % kGemmSlab;
     return last > 16 && last / 4 < k + k / 2;
 }
 inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu) {
     const bool slow_last = slow_last_slab(V_act, k);
+    if (k > 12 && d >= 1024) return d <= kTileMaxD;
     const double tile_cost = d < 2048 || slow_last ? 3.3 : 2.9;
     auto rounds = [&](int v, int m) {
         const long n = (long)((V_act + v - 1) / v) * ((M + m - 1) / m);
         return (n + num_cu - 1) / num_cu;
     };
-    return (double)rounds(kGemmSlab, kTileRows) < tile_cost * (double)rounds(kGemmTile, kGemmTile);
+    return d <= kTileMaxD && (double)rounds(kGemmSlab, kTileRows) < tile_cost * (double)rounds(kGemmTile, kGemmTile);
 }
 
 // A bound of every draft row for the matrix-tile kernels, from sorted lists of other candidates of the row that
@@ -475,7 +501,7 @@ constexpr size_t kSlowLastMiB = 96;
 constexpr int kTileParts = 8;
 constexpr int kTilePartsMinD = 1024;
 inline bool use_tiles_early(int M, int V_act, int d, int k, bool parts, size_t scratch) {
-    return M > kMTile && M < kGemmMinRows && d % (2 * kGemmKChunk) == 0 && (!parts || (d >= kTilePartsMinD && V_act >= 2 * (d - kTilePartsMinD))) && k <= 12 &&
+    return M > kMTile && M < kGemmMinRows && d % (2 * kGemmKChunk) == 0 && d <= kTileMaxD && (!parts || (d >= kTilePartsMinD && V_act >= 2 * (d - kTilePartsMinD))) && k <= 12 &&
            (!slow_last_slab(V_act, k) || matrix_elems((size_t)V_act, d, false) * 2 >= (kSlowLastMiB << 20)) &&
            make_gemm_plan(M, V_act, k).total_bytes <= scratch;
 }

@@ -11,6 +11,7 @@
 
 namespace evospec {
 
+constexpr int kOwnBoundK = 12;                // largest k whose bound of 32 group maxima leaves a list of 16 some room
 constexpr int kGFastLen = 16;                 // list length the staged common path of the epilogue handles
 // LDS per wavefront: the staged lists and spare slots of the common path, or a block's parked logits; then ids
 constexpr int epi_lists(int nmb) {
@@ -118,7 +119,8 @@ __device__ __forceinline__ float row_bound(const RowBound& b, int row, int M) {
 // mbase + 16 mb + n16.  `my`: epi_bytes(NMB) of LDS of this wavefront alone.  Lists are laid out [draft
 // row][slab][slot].  NMB <= 8.  bnd (or null): in LDS, for each of the draft rows a value that k logits elsewhere reach, so
 // that none below it can be among the row's k best.
-template <int NMB>
+// ACC: the accumulators sit in the accumulation registers.  HAS_BND: bnd may be given.
+template <int NMB, bool ACC = true, bool HAS_BND = true>
 __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned char* my, int vrow0, int mbase, int M, int V_act,
                                               const int32_t* __restrict__ ids, int k, int list_len, int slab, int n_slabs, const float* bnd,
                                               u64* __restrict__ part_keys, float2* __restrict__ part_stats) {
@@ -165,7 +167,10 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
 #pragma unroll
         for (int rg = 0; rg < 8; ++rg)
 #pragma unroll
-            for (int mb = 0; mb < NMB; ++mb) asm volatile("" : "+a"(acc[rg][mb]));
+            for (int mb = 0; mb < NMB; ++mb) {
+                if constexpr (ACC) asm volatile("" : "+a"(acc[rg][mb]));
+                else asm volatile("" : "+v"(acc[rg][mb]));
+            }
     };
     repin();
     // Dependent vector instructions of one wavefront issue many cycles apart, so each phase is
@@ -219,22 +224,25 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
     for (int mb = 0; mb < NMB; ++mb)
         if (g == 0 && mrow0 + 16 * mb < M) part_stats[(size_t)(mrow0 + 16 * mb) * n_slabs + slab] = make_float2(vm[mb], se[mb]);
 
-    // rows whose survivors fit a list go straight out.  The staged lists have kGFastLen slots: where those of the
-    // workspace are longer (k > 16) no row may take that way, one without survivors neither (its 16 empty slots
-    // would land in the list of another row, and its own would keep what the workspace held before).
-    const int cap = list_len == kGFastLen ? kGFastLen : -1;
-    // -- phase 3: a lower bound of every row's k-th best logit, and what reaches it.  The slab's own bound: each lane sorts
-    // its 8 group maxima; k rounds then take the largest head of the row's 4 lanes and pop it wherever it is the head:
-    // at least k group maxima, hence k logits, reach the last value taken.  With more than 32
-    // wanted, or fewer groups than k, the bound stays at -inf and every valid entry is kept.  A bound from elsewhere (bnd) is
-    // tried first.  It costs nothing here, and about one logit of a row reaches it if the logits here and there are alike.
-    // If they are larger here, most may: where more reach it than a list holds, in any row of the wavefront, the own bound
-    // joins it (16 x 60 rows over 32,768 + 2,048 x 4,096, us for the call without bnd, with it alone and with both: 305, 296
-    // and 295; extensions of half the size 305, 368 and 311; of a hundredth 306, 491 and 312).
+    // -- phase 3: a lower bound of every row's k-th best logit, and what reaches it: at most a list's length.  Three ways to
+    // a bound, each tried on all rows of the wavefront where the one before leaves any row more than that:
+    // (0) from elsewhere (bnd).  It costs nothing here, and about one logit of a row reaches it if the logits here and there are alike.
+    // If they are larger here, most may (16 x 60 rows over 32,768 + 2,048 x 4,096, us for the call without bnd, with it alone and with
+    // the next: 305, 296 and 295; extensions of half the size 305, 368 and 311; of a hundredth 306, 491 and 312).
+    // (1) The slab's own, up to k = kOwnBoundK: each lane sorts its 8 group maxima; k rounds then take the largest head of the row's 4 lanes and
+    // pop it wherever it is the head: at least k group maxima, hence k logits, reach the last value taken.
+    // (2) By halving the interval between a value that too many reach and the row's maximum, until between k and a list's length do,
+    // some 4 to 8 times: a ragged last slab with too few groups for (1), k past it.  (One row after the other, as all such rows used to
+    // go, and by halves, us: 20,000 x 2,048 at 256 rows, k = 16 90 and 53, k = 30 93 and 56, k = 60 126 and 69; 14,877 x 1,024 at
+    // 200, a last slab of 29 rows, 39 and 24.)
+    // (Blocks of 128 draft rows to a wavefront have no registers for (2), nor for the longer lists below: such rows go one by one.)
+    constexpr bool kRoom = NMB <= 2;
+    const int cap = list_len == kGFastLen ? kGFastLen : (kRoom ? list_len : -1);
+    constexpr int kHalvings = 20;                                  // (what is left then has equal logits, or next to equal ones)
     float tau[NMB];
 #pragma unroll
     for (int mb = 0; mb < NMB; ++mb) tau[mb] = -INFINITY;
-    if (bnd) {                                                     // (uniform)
+    if (HAS_BND && bnd) {                                          // (uniform)
 #pragma unroll
         for (int mb = 0; mb < NMB; ++mb) tau[mb] = bnd[16 * mb + n16];
     }
@@ -243,8 +251,42 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
     // of this lane's survivors in the row's list and the list length L (<= 128), still packed
     constexpr int NPK = (NMB + 3) / 4;
     uint32_t basep[NPK], Lp[NPK];
-    for (bool few = bnd != nullptr;; few = false) {                // (uniform)
-        if (!few && k <= 32) {
+    auto length = [&](int mb) { return (int)((Lp[mb >> 2] >> (8 * (mb & 3))) & 0xff); };
+    // what reaches x: mask, basep and Lp
+    auto reach = [&](const float (&x)[NMB]) {
+        // survivor masks without a compare per entry: the sign of (logit - bound) is
+        // shifted in, last entry first, so that entry i ends up as bit i ("below the bound")
+        uint32_t below[NMB];
+        EVOSPEC_MB(below[mb] = 0u)
+#pragma unroll
+        for (int i = 31; i >= 0; --i) {
+            float df[NMB];
+            EVOSPEC_MB(df[mb] = acc[i >> 2][mb][i & 3] - x[mb])
+            EVOSPEC_MB(below[mb] = __builtin_amdgcn_alignbit(below[mb], __float_as_uint(df[mb]), 31))
+        }
+        EVOSPEC_MB(mask[mb] = ~below[mb] & vmask)
+#pragma unroll
+        for (int hf = 0; hf < NPK; ++hf) {
+            uint32_t pk = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (4 * hf + q < NMB) pk |= (uint32_t)__popc(mask[4 * hf + q]) << (8 * q);
+            uint32_t q[4];
+            quad_all(pk, q);
+            basep[hf] = (g > 0 ? q[0] : 0u) + (g > 1 ? q[1] : 0u) + (g > 2 ? q[2] : 0u);
+            Lp[hf] = q[0] + q[1] + q[2] + q[3];
+        }
+    };
+    auto any_over = [&]() {
+        bool over = false;
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) over = over || length(mb) > cap;
+        return __ballot(over) != 0;
+    };
+    float lo[NMB], hi[NMB];                                        // (2) the interval of an open row
+    uint32_t fixed = 0;                                            // bit mb: the row's bound stands
+    for (int it = HAS_BND && bnd ? -1 : 0;; ++it) {                // (uniform)
+        if (it == 0 && k <= (kRoom ? kOwnBoundK : 32)) {
             float own[NMB];
 #pragma unroll
             for (int mb = 0; mb < NMB; ++mb) own[mb] = -INFINITY;
@@ -274,47 +316,46 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
             EVOSPEC_MB(tau[mb] = fmaxf(tau[mb], own[mb]))
         }
         repin();
-        // survivor masks without a compare per entry: the sign of (logit - bound) is
-        // shifted in, last entry first, so that entry i ends up as bit i ("below the bound")
-        {
-            uint32_t below[NMB];
-            EVOSPEC_MB(below[mb] = 0u)
-#pragma unroll
-            for (int i = 31; i >= 0; --i) {
-                float df[NMB];
-                EVOSPEC_MB(df[mb] = acc[i >> 2][mb][i & 3] - tau[mb])
-                EVOSPEC_MB(below[mb] = __builtin_amdgcn_alignbit(below[mb], __float_as_uint(df[mb]), 31))
-            }
-            EVOSPEC_MB(mask[mb] = ~below[mb] & vmask)
-        }
-#pragma unroll
-        for (int hf = 0; hf < NPK; ++hf) {
-            uint32_t pk = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (4 * hf + q < NMB) pk |= (uint32_t)__popc(mask[4 * hf + q]) << (8 * q);
-            uint32_t q[4];
-            quad_all(pk, q);
-            basep[hf] = (g > 0 ? q[0] : 0u) + (g > 1 ? q[1] : 0u) + (g > 2 ? q[2] : 0u);
-            Lp[hf] = q[0] + q[1] + q[2] + q[3];
-        }
-        if (!few) {
+        reach(tau);
+        if (it >= 0) {
             bnd = nullptr;
-            break;
+            if (!kRoom) break;
         }
-        bool over = false;
+        if (it <= 0) {
+            if (!any_over()) break;
+            if (it < 0) continue;
+        }
+        if constexpr (kRoom) {
+            if (it == 0) {
+                // the least logit of the row, where nothing better is known
+                float least[NMB];
+                EVOSPEC_MB(least[mb] = -INFINITY)
 #pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) over = over || (int)((Lp[mb >> 2] >> (8 * (mb & 3))) & 0xff) > cap;
-        if (__ballot(over) == 0) break;
+                for (int i = 0; i < 32; ++i) { EVOSPEC_MB(least[mb] = fmaxf(least[mb], (vmask >> i) & 1u ? -acc[i >> 2][mb][i & 3] : -INFINITY)) }
+                quad_max(least);
+                EVOSPEC_MB(lo[mb] = fmaxf(tau[mb], -least[mb]); hi[mb] = vm[mb]; fixed |= length(mb) <= cap ? 1u << mb : 0u)
+            } else {
+#pragma unroll
+                for (int mb = 0; mb < NMB; ++mb) {
+                    const bool open = !((fixed >> mb) & 1u), enough = length(mb) >= k;
+                    lo[mb] = open && enough ? tau[mb] : lo[mb];
+                    hi[mb] = open && !enough ? tau[mb] : hi[mb];
+                    fixed |= enough && length(mb) <= cap ? 1u << mb : 0u;
+                }
+            }
+            // (after the last halving a look at the lower end, which enough reach)
+            if (__ballot(fixed != (1u << NMB) - 1u) == 0 || it > kHalvings) break;
+            EVOSPEC_MB(tau[mb] = (fixed >> mb) & 1u ? tau[mb] : (it == kHalvings ? lo[mb] : 0.5f * lo[mb] + 0.5f * hi[mb]))
+        }
     }
     bool rare = false;
 
     repin();
-    // -- phase 4: the survivors of every row, as (logit, id) pairs in no particular order, are
+    // -- phase 4: the survivors of every row, as (logit, id) pairs in no particular order.  Up to k = 16 they are
     // gathered into the row's 16-slot list in LDS (empty slots: all ones) and the lists copied to the
     // workspace a full line at a time; the merge ranks.  No branch or compare per entry: an entry
     // that is not a survivor goes to the lane's spare slot.
-    {
+    if (!kRoom || list_len == kGFastLen) {
         const u32x4 ones = {~0u, ~0u, ~0u, ~0u};
 #pragma unroll
         for (int it = 0; it < NMB * 16 * kGFastLen * 8 / 1024; ++it)
@@ -325,13 +366,13 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
 #pragma unroll
         for (int mb = 0; mb < NMB; ++mb) {
             const int base = (basep[mb >> 2] >> (8 * (mb & 3))) & 0xff;
-            const int L = (Lp[mb >> 2] >> (8 * (mb & 3))) & 0xff;
+            const int L = length(mb);
             rare = rare || L > cap;
             mk[mb] = L <= cap ? mask[mb] : 0u;
             rel[mb] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u64*)(flist + (mb * 16 + n16) * kGFastLen + base) - spare_a;
         }
         EVOSPEC_FENCE();
-        if (bnd) {
+        if (HAS_BND && bnd) {
             // Few survivors (a list's at most, mostly about one to a row): block by block the logits are laid out in LDS, where each lane picks
             // its own survivors one after the other.  (Both this and the bound: 16 x 60 rows over 32,768 + 2,048 rows x 4,096
             // 304 -> 297 us for the call.)
@@ -384,19 +425,44 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
             if (L <= cap && m < M)
                 *reinterpret_cast<u32x4*>(part_keys + ((size_t)m * n_slabs + slab) * kGFastLen + 2 * (lane & 7)) = q;
         }
+    } else if constexpr (kRoom) {
+        // Longer lists: block by block the logits are laid out in LDS, each lane takes its own survivors to their places one after the
+        // other (some k / 4 of them), the four lanes of a row fill the rest of its list.
+        unsigned char* zl = my + lane * 16;                            // [8][64] f32x4
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) {
+#pragma unroll
+            for (int rg = 0; rg < 8; ++rg) *reinterpret_cast<f32x4*>(zl + rg * 1024) = acc[rg][mb];
+            const int L = length(mb), m = mrow0 + 16 * mb;
+            rare = rare || L > cap;
+            const bool out = L <= cap && m < M;
+            u64* dst = part_keys + ((size_t)(out ? m : 0) * n_slabs + slab) * list_len;
+            uint32_t mk = out ? mask[mb] : 0u;
+            int at = (basep[mb >> 2] >> (8 * (mb & 3))) & 0xff;
+            while (__ballot(mk != 0u) != 0) {
+                if (mk != 0u) {
+                    const int i = __builtin_ctz(mk);
+                    mk &= mk - 1;
+                    const uint32_t z = *reinterpret_cast<const uint32_t*>(zl + (i >> 2) * 1024 + (i & 3) * 4);
+                    const uint32_t id = (uint32_t)Ids[16 * (i >> 2) + 4 * g + (i & 3)];
+                    dst[at++] = ((u64)z << 32) | id;
+                }
+            }
+            if (out)
+                for (int e = L + g; e < list_len; e += 4) dst[e] = ~0ull;
+        }
     }
 #undef EVOSPEC_MB
 #undef EVOSPEC_FENCE
     if (__ballot(rare) == 0) return;
     repin();
 
-    // -- rows with more survivors than a list holds (one row in a few hundred at k = 10; many equal logits; k past
-    // what the bound above handles), one after the other: the whole wavefront takes the row, two logits to a
+    // -- rows with more survivors than a list holds whatever the bound (equal logits, infinities), one after the other: the whole wavefront takes the row, two logits to a
     // lane, finds its k-th largest bit by bit and keeps what reaches it.  The block's logits are parked in LDS.
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the staged lists have been read
     float* zbuf = zpark + lane * 32;
     for (int mbr = 0; mbr < NMB; ++mbr) {
-        const int L = (Lp[mbr >> 2] >> (8 * (mbr & 3))) & 0xff;
+        const int L = (Lp[mbr >> 2] >> (8 * (mbr & 3))) & 0xff;    // (mbr is no constant)
         uint32_t todo = (uint32_t)__ballot(mrow0 + 16 * mbr < M && L > cap) & 0xffffu;       // (the 4 lanes of a row agree)
         if (todo == 0) continue;
 #pragma unroll

@@ -43,6 +43,8 @@ static int batched(int n, char** a) {
         if (r.tiles) choose_bound(&b, p.n_slabs, k);
         std::printf(" chunks=%d split=%d arc_tiles=%d arc_blocks=%d bound=%d", chunks, split ? 1 : 0, p.nw, p.mb, b.q);
     }
+    if (r.tiles && r.small && !one_set)
+        std::printf(" joint=%d", joint_tiles(M, V_core, d, cus, true, make_tile_batch_plan(max_rows, V_arc, k).n_slabs, chunks) ? 1 : 0);
     if (!r.tiles && !one_set) {                                // both sets in one launch
         const JointPlan j = make_joint_plan(M, V_core, V_arc, chunks, d, k, cus);
         std::printf(" joint_tiles=%d joint_blocks=%d joint_slabs=%d", j.core.nw, j.core.mb, j.core.n_slabs);
