@@ -3,6 +3,8 @@
 // Declared in include/evospec_arc.h.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cstdint>
 #include <vector>
 
@@ -14,6 +16,57 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr int kMaxCandidates = 4096;
+
+// Where the search leaves its ids for the host: places in one page of pinned memory, which the merge kernel writes itself.  (A copy of 40
+// bytes to pageable memory and the wait for it took some 25 us more.)  One page per process, given back when it ends; a call holds a place
+// while it runs, whatever its thread, stream or device, and one that finds none copies.
+class IdPlaces {
+public:
+    static constexpr int kPlaces = 16;
+    int32_t* take(int* place) {
+        if (!base_.load(std::memory_order_acquire)) {
+            void* p = nullptr;
+            if (hipHostMalloc(&p, kPlaces * EVOSPEC_K_MAX * sizeof(int32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+                (void)hipGetLastError();                 // (the copy will do)
+                return nullptr;
+            }
+            int32_t* none = nullptr;
+            if (!base_.compare_exchange_strong(none, static_cast<int32_t*>(p), std::memory_order_acq_rel)) (void)hipHostFree(p);
+        }
+        for (int i = 0; i < kPlaces; ++i)
+            if (!(taken_.fetch_or(1u << i, std::memory_order_acquire) & (1u << i))) {
+                *place = i;
+                return base_.load(std::memory_order_acquire) + i * EVOSPEC_K_MAX;
+            }
+        return nullptr;
+    }
+    void give(int place) { taken_.fetch_and(~(1u << place), std::memory_order_release); }
+    ~IdPlaces() {
+        if (int32_t* p = base_.load()) (void)hipHostFree(p);
+    }
+
+private:
+    std::atomic<int32_t*> base_{nullptr};
+    std::atomic<uint32_t> taken_{0};
+};
+IdPlaces g_places;
+
+constexpr int32_t kNotYet = INT32_MIN;           // no id, and not "none" (-1) either
+constexpr auto kSpin = std::chrono::milliseconds(2);
+
+// Waits until the n ids are there: looks for them for a while, then waits for the stream.
+hipError_t wait_for_ids(const int32_t* ids, int n, hipStream_t st) {
+    const auto* seen = reinterpret_cast<const std::atomic<int32_t>*>(ids);
+    static_assert(sizeof(std::atomic<int32_t>) == sizeof(int32_t), "a plain word");
+    const auto give_up = std::chrono::steady_clock::now() + kSpin;
+    int i = 0;
+    for (unsigned spins = 0;; ++spins) {
+        while (i < n && seen[i].load(std::memory_order_acquire) != kNotYet) ++i;
+        if (i == n) return hipSuccess;
+        __builtin_ia32_pause();
+        if ((spins & 63) == 63 && std::chrono::steady_clock::now() > give_up) return hipStreamSynchronize(st);
+    }
+}
 }  // namespace
 
 extern "C" {
@@ -64,13 +117,30 @@ int evospec_path_a_event(evospec_arc* arc, const void* h_target, int d, const vo
     hipStream_t st = static_cast<hipStream_t>(stream);
 
     // 1. exact search over the full vocabulary (identity ids), ids to the host
-    rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, top_vals, top_ids, top_logz,
-                                    workspace, head, stream);
-    if (rc) return rc;
     int32_t mips[EVOSPEC_K_MAX];
-    if (hipMemcpyAsync(mips, top_ids, (size_t)n_mips * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return EVOSPEC_HIP_ERROR;
+    int place = -1;
+    int32_t* host_ids = g_places.take(&place);
+    if (host_ids) {
+        for (int i = 0; i < n_mips; ++i) host_ids[i] = kNotYet;
+        rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, top_vals, host_ids, top_logz,
+                                        workspace, head, stream);
+        // (after an error something may still write to the place: it is not used again)
+        if (rc) return rc;
+        const hipError_t e = wait_for_ids(host_ids, n_mips, st);
+        if (e != hipSuccess) return evospec::record_hip_error(e);
+        for (int i = 0; i < n_mips; ++i) {
+            mips[i] = host_ids[i];
+            if (mips[i] == kNotYet) return EVOSPEC_HIP_ERROR;
+        }
+        g_places.give(place);
+    } else {
+        rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, top_vals, top_ids, top_logz,
+                                        workspace, head, stream);
+        if (rc) return rc;
+        if (hipMemcpyAsync(mips, top_ids, (size_t)n_mips * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return EVOSPEC_HIP_ERROR;
+    }
     // 2. candidates, 3. admission
     std::vector<int32_t> cand((size_t)kMaxCandidates);
     int n_cand = 0;
