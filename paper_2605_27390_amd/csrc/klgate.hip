@@ -140,6 +140,13 @@ __device__ __forceinline__ T wg_sort_desc(T x, T* buf) {
     return x;
 }
 
+// Four logits from a 4-byte aligned place.
+__device__ __forceinline__ float4 load4(const float* p) {
+    typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+    const f32x4_u v = *reinterpret_cast<const f32x4_u*>(p);
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // A lower bound of the K-th largest (counting repeats) of the 1024 values v, one per thread, without
 // a selection over the workgroup: with q = ceil(K / 16), each of the 16 wavefronts holds q values at or
 // above its own q-th largest, so K values reach the smallest of the 16.  (Looser than the exact K-th
@@ -161,10 +168,11 @@ __device__ __forceinline__ uint32_t kth_bound_1024(uint32_t v, int K, uint32_t* 
 // slice that can still be among the event's K largest go to the workspace, unranked:
 // ws_keys[(e * G + g) * kKlCand + ...], their number to ws_cnt[e * G + g].
 //
-// NL > 0: the slice fits NL 16-byte loads per thread (and the logits are 16-byte aligned).  All of
+// NL > 0: the slice fits NL 16-byte loads per thread (aligned or not: a row of V logits starts anywhere, and a 16-byte load needs 4-byte
+// alignment only; the last one to three logits of a V that is no multiple of 4 are loaded by themselves).  All of
 // them are issued before the first is used and the values stay in registers for the second sweep:
 // the kernel is bound by memory latency, and a loop of dependent load-then-compare iterations pays
-// that latency once per iteration.  NL == 0: any size and alignment, two sweeps over memory.
+// that latency once per iteration.  NL == 0: any size, two sweeps over memory.
 // (Two workgroups per compute unit, so that the 8 x E workgroups of 60 events run as one round: the
 // second launch-bounds figure caps the registers at 64 per lane; the radix path below may spill.)
 template <int NL>
@@ -193,17 +201,21 @@ kl_select_slices_kernel(const float* __restrict__ z_target, int V, int K, int G,
     float mx = -INFINITY;
     bool any = false;
     float4 q[NL > 0 ? NL : 1];
-    const bool vec = NL > 0 || ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(z_target) & 15) == 0);
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(z_target) & 15) == 0;
+    const int hi4 = lo + ((hi - lo) & ~3), tail = hi - hi4;        // whole loads end here (the last slice only may have a tail)
+    float zt = -INFINITY;                                          // this thread's logit of the tail
     if constexpr (NL > 0) {
-        // (the launcher picks NL > 0 only for aligned logits and a slice that NL loads per thread cover)
+        // (the launcher picks NL > 0 only for a slice that NL loads per thread cover, and of four logits at least)
+        if (tail > 0 && tid < tail) zt = z[hi4 + tid];
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
             const int i = lo + 4 * (tid + j * kKlThreads);
-            q[j] = *reinterpret_cast<const float4*>(z + (i < hi ? i : lo));     // past the end: a valid address, masked below
+            q[j] = load4(z + (i < hi4 ? i : lo));                  // past the end: a valid address, masked below
         }
+        if (tail > 0 && tid < tail) { mx = fmaxf(mx, zt); any = true; }
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            const bool in = lo + 4 * (tid + j * kKlThreads) < hi;
+            const bool in = lo + 4 * (tid + j * kKlThreads) < hi4;
             if (!in) q[j] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
             mx = fmaxf(fmaxf(mx, fmaxf(q[j].x, q[j].y)), fmaxf(q[j].z, q[j].w));
             any = any || in;
@@ -233,8 +245,9 @@ kl_select_slices_kernel(const float* __restrict__ z_target, int V, int K, int G,
         uint32_t pass = 0;                                       // (4 NL <= 32 bits) bit 4 j + c: component c of load j reaches the bound
 #pragma unroll
         for (int x = 0; x < 4 * NL; ++x)
-            if (lo + 4 * (tid + (x >> 2) * kKlThreads) < hi && qf[x] >= tau0) pass |= 1u << x;
-        const int mine = __popc(pass);
+            if (lo + 4 * (tid + (x >> 2) * kKlThreads) < hi4 && qf[x] >= tau0) pass |= 1u << x;
+        const bool tail_in = tid < tail && zt >= tau0;
+        const int mine = __popc(pass) + (tail_in ? 1 : 0);
         int before = 0, total = 0;
 #pragma unroll
         for (int bit = 0; bit < 6; ++bit) {
@@ -256,6 +269,7 @@ kl_select_slices_kernel(const float* __restrict__ z_target, int V, int K, int G,
                 ++p;
             }
         }
+        if (tail_in && p < kKlCand) cand[p] = make_key(zt, hi4 + tid);
     } else if (vec) {
         for (int i = lo + 4 * tid; i < hi; i += 4 * kKlThreads) {
             const float4 v = *reinterpret_cast<const float4*>(z + i);
@@ -530,8 +544,10 @@ hipError_t launch_kl_gate(const float* z_target, int E, int V, const void* h_dra
     const int slice = ((V + G - 1) / G + 3) / 4 * 4;
     u64* ws_keys = static_cast<u64*>(workspace);
     int* ws_cnt = reinterpret_cast<int*>(ws_keys + (size_t)E * G * kKlCand);
-    // 16-byte loads per thread that cover a slice, when the logits allow them
-    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(z_target) & 15) == 0;
+    // 16-byte loads per thread that cover a slice, which has one at least.  (For a V that is no multiple of 4, or logits that are not 16-byte aligned,
+    // against two sweeps of single loads, us for the call: 60 events, V = 100,003 x 4,096 53.2 and 48.9; 51, 110,729 x 512 30.2 and 27.1; 20,
+    // 151,935 x 2,048, K = 100 27.4 and 22.1.)
+    const bool vec = V >= 4;
     const int per_thread = (slice / 4 + kKlThreads - 1) / kKlThreads;
     auto slices = kl_select_slices_kernel<0>;
     if (vec && per_thread <= 2) slices = kl_select_slices_kernel<2>;
