@@ -4,7 +4,7 @@
 // the temperature T_KD turn both into distributions p, q on that support; the event is admitted
 // when D_KL(p || q) exceeds the gate.
 //
-// Four launches:
+// Three launches, or four where the events are many (2 and 3 apart):
 //  1. kl_select_slices_kernel, one workgroup of 16 wavefronts per (eighth of the vocabulary, event),
 //     two of them per compute unit: every thread loads its share of the slice once (all requests in
 //     flight together, the values stay in registers) and takes its maximum; a value that K of these
@@ -36,6 +36,7 @@ constexpr int kKlThreads = 1024;
 constexpr int kKlMaxK = 256;
 constexpr int kKlBits = 11;
 constexpr int kKlBins = 1 << kKlBits;
+constexpr int kJointGroups = 256;             // workgroups up to which stages 2 and 3 share a launch
 constexpr int kKlCand = 2048;                 // candidates the common path can rank
 
 __device__ __forceinline__ float wave_sum(float x) { return evospec::wave_sum(x, (int)(threadIdx.x & 63)); }
@@ -335,14 +336,18 @@ kl_select_slices_kernel(const float* __restrict__ z_target, int V, int K, int G,
 // Stage 2, one workgroup per event: the K largest of the slices' candidates, by decreasing key.
 // The same bound (K-th largest of the per-thread maxima, here over at most 16 candidates per
 // thread) leaves at most 16 K keys, which are ranked by counting.
-__global__ void __launch_bounds__(kKlThreads)
-kl_select_final_kernel(const u64* __restrict__ ws_keys, const int* __restrict__ ws_cnt, int G, int K,
-                       int32_t* __restrict__ out_support, float* __restrict__ out_zt) {
-    __shared__ __align__(16) u64 surv[16 * kKlMaxK];
-    __shared__ u64 sorted[kKlMaxK];
-    __shared__ u64 tau_s;
-    __shared__ int nsurv;
-    const int tid = threadIdx.x, e = blockIdx.x;
+struct FinalShared {
+    __align__(16) u64 surv[16 * kKlMaxK];
+    u64 sorted[kKlMaxK];                                         // the answer
+    u64 tau_s;
+    int nsurv;
+};
+__device__ __forceinline__ void select_final(FinalShared& sh, const u64* __restrict__ ws_keys, const int* __restrict__ ws_cnt, int e, int G, int K) {
+    u64* surv = sh.surv;
+    u64* sorted = sh.sorted;
+    u64& tau_s = sh.tau_s;
+    int& nsurv = sh.nsurv;
+    const int tid = threadIdx.x;
     if (tid == 0) nsurv = 0;
     // The slices' lists, taken as one sequence, are dealt out to the threads, wavefronts first
     // (entry i to lane (i / 16) % 64 of wavefront i % 16, at most 16 per thread), so that every
@@ -450,34 +455,37 @@ kl_select_final_kernel(const u64* __restrict__ ws_keys, const int* __restrict__ 
         }
     }
     __syncthreads();
-    for (int r = tid; r < K; r += kKlThreads) {
-        out_support[(size_t)e * K + r] = key_id(sorted[r]);
-        out_zt[(size_t)e * K + r] = key_value(sorted[r]);
+}
+__device__ __forceinline__ void store_support(const FinalShared& sh, int e, int K, int32_t* __restrict__ out_support, float* __restrict__ out_zt) {
+    for (int r = threadIdx.x; r < K; r += kKlThreads) {
+        out_support[(size_t)e * K + r] = key_id(sh.sorted[r]);
+        out_zt[(size_t)e * K + r] = key_value(sh.sorted[r]);
     }
+}
+__global__ void __launch_bounds__(kKlThreads)
+kl_select_final_kernel(const u64* __restrict__ ws_keys, const int* __restrict__ ws_cnt, int G, int K,
+                       int32_t* __restrict__ out_support, float* __restrict__ out_zt) {
+    __shared__ FinalShared sh;
+    select_final(sh, ws_keys, ws_cnt, blockIdx.x, G, K);
+    store_support(sh, blockIdx.x, K, out_support, out_zt);
 }
 
 // Draft logits z_q[e][r] = h_draft[e] . W_lm[support[e][r]] for the 16 rows r = 16 blockIdx.x + ...
 // The rows come through the caches: events share support rows, within a call and from call to call (whole call,
 // 60 events, V = 151,936, d = 4,096, new events on one W_lm: 47.6 us, and past the caches 47.5; supports mostly the same
 // tokens 38.2 and 47.2; the same events again 44.5 and 46.8; only with another W_lm at every call 49.6 and 47.6).
-__global__ void __launch_bounds__(256)
-kl_draft_logits_kernel(const uint16_t* __restrict__ h_draft, int d, const uint16_t* __restrict__ W_lm, int K,
-                       const int32_t* __restrict__ support, float* __restrict__ out_zq) {
-    extern __shared__ __align__(16) unsigned char kl_smem[];
-    uint16_t* hs = reinterpret_cast<uint16_t*>(kl_smem);            // [d] draft hidden state of the event
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int e = blockIdx.y;
-    const int r0 = 16 * blockIdx.x + 4 * w;                         // this wavefront's 4 rows
-    const int32_t* sup = support + (size_t)e * K;
+//
+// One wavefront, the four rows from r0 on (r_end or less); hs: the event's draft hidden state in LDS.
+template <typename IdOf>
+__device__ __forceinline__ void draft_rows(const uint16_t* hs, int d, const uint16_t* __restrict__ W_lm, int r0, int r_end, IdOf id_of,
+                                           float* __restrict__ zq) {
+    const int lane = threadIdx.x & 63;
     const uint16_t* row[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int32_t id = sup[r0 + u < K ? r0 + u : K - 1];        // past the end: a valid row again
+        const int32_t id = id_of(r0 + u < r_end ? r0 + u : r_end - 1);      // past the end: a valid row again
         row[u] = W_lm + (size_t)(id < 0 ? 0 : id) * d;              // (-1: fewer than K of the event's logits are numbers)
     }
-    for (int i = tid; i < d / 8; i += 256)
-        reinterpret_cast<u32x4*>(hs)[i] = *(gvec_ptr)(h_draft + (size_t)e * d + 8 * i);
-    __syncthreads();
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int p0 = 0; p0 < d / 8; p0 += 64) {
         const int p = p0 + lane < d / 8 ? p0 + lane : d / 8 - 1;      // ragged end: clamp, then weigh by zero
@@ -499,8 +507,41 @@ kl_draft_logits_kernel(const uint16_t* __restrict__ h_draft, int d, const uint16
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const float t = wave_sum(acc[u]);
-        if (lane == 0 && r0 + u < K) out_zq[(size_t)e * K + r0 + u] = t;
+        if (lane == 0 && r0 + u < r_end) zq[r0 + u] = t;
     }
+}
+__global__ void __launch_bounds__(256)
+kl_draft_logits_kernel(const uint16_t* __restrict__ h_draft, int d, const uint16_t* __restrict__ W_lm, int K,
+                       const int32_t* __restrict__ support, float* __restrict__ out_zq) {
+    extern __shared__ __align__(16) unsigned char kl_smem[];
+    uint16_t* hs = reinterpret_cast<uint16_t*>(kl_smem);            // [d] draft hidden state of the event
+    const int tid = threadIdx.x, e = blockIdx.y;
+    const int32_t* sup = support + (size_t)e * K;
+    for (int i = tid; i < d / 8; i += 256)
+        reinterpret_cast<u32x4*>(hs)[i] = *(gvec_ptr)(h_draft + (size_t)e * d + 8 * i);
+    __syncthreads();
+    const int r0 = 16 * blockIdx.x + 4 * (tid >> 6);                // this wavefront's 4 rows
+    if (r0 < K) draft_rows(hs, d, W_lm, r0, K, [&](int r) { return sup[r]; }, out_zq + (size_t)e * K);
+}
+
+// Stages 2 and 3 in one launch, as long as its workgroups of 16 wavefronts fit the chip once: each selects the event's support by itself (the lists are
+// in L2 by then) and takes 16 to 64 rows of the answer, which saves a launch and the trip of the ids through memory.  us for the call, in
+// two launches and in one: 60 events, V = 151,936 x 4,096 49.9 and 47.8; 60, 100,003 x 4,096 48.9 and 46.5; 10, 57,159 x 512,
+// K = 45 17.8 and 16.1; 1, 33,141 x 1,024, K = 154 18.8 and 16.9.
+__global__ void __launch_bounds__(kKlThreads)
+kl_final_logits_kernel(const u64* __restrict__ ws_keys, const int* __restrict__ ws_cnt, int G, int K, int rows_per,
+                       const uint16_t* __restrict__ h_draft, int d, const uint16_t* __restrict__ W_lm,
+                       int32_t* __restrict__ out_support, float* __restrict__ out_zt, float* __restrict__ out_zq) {
+    extern __shared__ __align__(16) unsigned char kl_smem[];
+    __shared__ FinalShared sh;
+    uint16_t* hs = reinterpret_cast<uint16_t*>(kl_smem);            // [d]
+    const int e = blockIdx.y, first = blockIdx.x * rows_per, end = min(K, first + rows_per);
+    for (int i = threadIdx.x; i < d / 8; i += kKlThreads)
+        reinterpret_cast<u32x4*>(hs)[i] = *(gvec_ptr)(h_draft + (size_t)e * d + 8 * i);
+    select_final(sh, ws_keys, ws_cnt, e, G, K);                     // (ends on a barrier)
+    if (blockIdx.x == 0) store_support(sh, e, K, out_support, out_zt);
+    const int r0 = first + 4 * (int)(threadIdx.x >> 6);
+    if (r0 < end) draft_rows(hs, d, W_lm, r0, end, [&](int r) { return key_id(sh.sorted[r]); }, out_zq + (size_t)e * K);
 }
 
 // KL = sum_i p_i (a_i - b_i) - logZ_a + logZ_b with a = z_t / T, b = z_q / T; one wavefront per event.
@@ -554,6 +595,16 @@ hipError_t launch_kl_gate(const float* z_target, int E, int V, const void* h_dra
     else if (vec && per_thread <= 5) slices = kl_select_slices_kernel<5>;
     else if (vec && per_thread <= 8) slices = kl_select_slices_kernel<8>;
     hipLaunchKernelGGL(slices, dim3(G, E), dim3(kKlThreads), 0, stream, z_target, V, K, G, slice, ws_keys, ws_cnt);
+    // Workgroups to an event of the joint stages: 16 to 64 rows each, some 256 in all.
+    const int least = (K + 63) / 64, most = (K + 15) / 16, want = kJointGroups / E;
+    const int parts = want < least ? least : (want > most ? most : want);
+    if ((long)E * least <= kJointGroups && (size_t)d * 2 + sizeof(FinalShared) <= 64 * 1024) {
+        const int rows_per = ((K + parts - 1) / parts + 3) / 4 * 4;
+        hipLaunchKernelGGL(kl_final_logits_kernel, dim3((K + rows_per - 1) / rows_per, E), dim3(kKlThreads), (size_t)d * 2, stream, ws_keys, ws_cnt, G, K,
+                           rows_per, static_cast<const uint16_t*>(h_draft), d, static_cast<const uint16_t*>(W_lm), out_support, out_zt, out_zq);
+        hipLaunchKernelGGL(kl_divergence_kernel, dim3(E), dim3(64), 0, stream, out_zt, out_zq, K, 1.0f / T, out_kl);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(kl_select_final_kernel, dim3(E), dim3(kKlThreads), 0, stream, ws_keys, ws_cnt, G, K,
                        out_support, out_zt);
     hipLaunchKernelGGL(kl_draft_logits_kernel, dim3((K + 15) / 16, E), dim3(256), (size_t)d * 2, stream,
