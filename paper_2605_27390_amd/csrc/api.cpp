@@ -355,7 +355,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         bl.seq_rows = V_arc;
         bl.chunk_bytes = arc_stride;
         bl.packed = packed;
-        if (!route.tiles && !one_set && !core_done) {   // slabs of both sets in one launch
+        if (!route.tiles && !one_set && !core_done && joint_slabs(M, V_core, V_arc, cb.n)) {    // slabs of both sets in one launch
             const JointPlan jp = make_joint_plan(M, V_core, V_arc, cb.n, d, k, num_cu);
             CoreSet cs;
             cs.W = W_core; cs.ids = ids_core; cs.V = V_core; cs.M = M;
@@ -377,13 +377,12 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         if (route.tiles && route.small && !one_set && !core_done && joint_tiles(M, V_core, d, num_cu, packed, pt.n_slabs, cb.n)) {
             // tiles of the core and slabs of the extensions in one launch
             const GemmPlan gp = make_gemm_plan(M, V_core, k);
-            const Plan& pa = pt;
-            const TileBatch tb{&pa, &cb, W_arc, ids_arc, V_arc, arc_stride, ws_arc + pa.keys_off, ws_arc + pa.stats_off};
+            const TileBatch tb{&pt, &cb, W_arc, ids_arc, V_arc, arc_stride, ws_arc + pt.keys_off, ws_arc + pt.stats_off};
             hipError_t e = launch_tile_partials(h, M, d, W_core, ids_core, V_core, k, ws + gp.keys_off, ws + gp.stats_off, st, packed, num_cu, false, RowBound{}, &tb);
             if (e != hipSuccess) return hip_fail(e);
             core = MergeSet{ws + gp.keys_off, ws + gp.stats_off, gp.n_slabs, 0, M, gp.list_len, true};
             core_done = true;
-            const MergeSet arc{ws_arc + pa.keys_off, ws_arc + pa.stats_off, pa.n_slabs, 0, kMTile};
+            const MergeSet arc{ws_arc + pt.keys_off, ws_arc + pt.stats_off, pt.n_slabs, 0, kMTile};
             e = launch_merge_batch(core, core_stride, arc, arc_stride, cb, k, out_vals, out_ids, out_logz, st);
             cb.n = 0;
             return e == hipSuccess ? EVOSPEC_OK : hip_fail(e);
@@ -408,8 +407,8 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
             core_done = true;
         }
         MergeSet arc{};
+        bl.split = split;
         if (V_arc > 0) {
-            bl.split = split;
             hipError_t e = launch_partials_batch(pa, h, cb, CoreSet{}, bl, d, W_arc, ids_arc, V_arc, k,
                                                  ws_arc + pa.keys_off, ws_arc + pa.stats_off, st);
             if (e != hipSuccess) return hip_fail(e);

@@ -277,6 +277,11 @@ inline Plan make_plan(int rows /*draft rows in this pass, 1..64*/, int V_act, in
 // in one, us for the call: packed, 11,986 + 226 x 4,096, 60 rows of 4 sequences 58 and 39; 32,768 + 2,048, 60 rows of 2 72.6 and 61.7; 5,000 + 200 x
 // 2,048, 24 rows of 2 26.1 and 16.4; 30,000 + 1,500 x 2,048, 60 rows of 7 55 and 42; two passes, 20,000 + 1,000, 120 rows of 5, k = 20 115 and 78;
 // row-major, 69 rows of 4 over 11,986 + 226, k = 45 136 and 72; 40 rows of 2 over 32,768 + 2,048 97.6 and 75.6.
+// (joint_slabs: the threads of a launch are counted in 32 bits.)
+constexpr long kJointWorkgroups = 1l << 22;
+inline bool joint_slabs(int M, int V_core, int V_arc, int chunks) {
+    return ((long)(M + kMTile - 1) / kMTile) * ((V_core + kRowsMinSlab - 1) / kRowsMinSlab) + (long)chunks * ((V_arc + kRowsMinSlab - 1) / kRowsMinSlab) <= kJointWorkgroups;
+}
 struct JointPlan { Plan core, arc; };
 inline JointPlan make_joint_plan(int M, int V_core, int V_arc, int chunks, int d, int k, int num_cu) {
     JointPlan best;
@@ -322,7 +327,8 @@ inline Plan make_tile_batch_plan(int max_rows, int V_arc, int k) {
 // a round anyway (14,416 + 332 117 and 104), or beside a few slabs with short rows (16,384 + 1,000 x 2,048, 250 of 5 54 and
 // 51; x 4,096, 197 of 4 82 and 86; 4,906 + 1,764 x 4,096, 293 of 7, 117 tiles and 196 slabs, 79 and 91).
 inline bool joint_tiles(int M, int V_core, int d, int num_cu, bool packed, int arc_slabs, int chunks) {
-    const int tiles = ((V_core + 127) / 128) * ((M + 127) / 128);
+    const long tiles = ((V_core + 127l) / 128) * ((M + 127l) / 128);
+    if (tiles + (long)arc_slabs * chunks > kJointWorkgroups) return false;
     return packed || tiles > num_cu || tiles + arc_slabs * chunks <= num_cu || (d <= 2048 && 2 * arc_slabs * chunks <= tiles);
 }
 
