@@ -17,16 +17,18 @@ constexpr size_t kAlign = 256;
 size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr int kMaxCandidates = 4096;
 
-// Where the search leaves its ids for the host: places in one page of pinned memory, which the merge kernel writes itself.  (A copy of 40
-// bytes to pageable memory and the wait for it took some 25 us more.)  One page per process, given back when it ends; a call holds a place
+// Where the search leaves its ids for the host: places in a block of pinned memory, which the merge kernel writes itself.  (A copy of 40
+// bytes to pageable memory and the wait for it took 10 to 14 us more.)  The values and the log-normaliser, which nobody reads, go there too, behind the
+// ids: the host may see the ids before the last of them is stored, and the workspace is the caller's again when the call returns.  One block per process, given back when it ends; a call holds a place
 // while it runs, whatever its thread, stream or device, and one that finds none copies.
 class IdPlaces {
 public:
     static constexpr int kPlaces = 16;
+    static constexpr int kWords = 2 * EVOSPEC_K_MAX + 16;      // ids, values, log-normaliser
     int32_t* take(int* place) {
         if (!base_.load(std::memory_order_acquire)) {
             void* p = nullptr;
-            if (hipHostMalloc(&p, kPlaces * EVOSPEC_K_MAX * sizeof(int32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            if (hipHostMalloc(&p, kPlaces * kWords * sizeof(int32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
                 (void)hipGetLastError();                 // (the copy will do)
                 return nullptr;
             }
@@ -36,7 +38,7 @@ public:
         for (int i = 0; i < kPlaces; ++i)
             if (!(taken_.fetch_or(1u << i, std::memory_order_acquire) & (1u << i))) {
                 *place = i;
-                return base_.load(std::memory_order_acquire) + i * EVOSPEC_K_MAX;
+                return base_.load(std::memory_order_acquire) + i * kWords;
             }
         return nullptr;
     }
@@ -122,7 +124,8 @@ int evospec_path_a_event(evospec_arc* arc, const void* h_target, int d, const vo
     int32_t* host_ids = g_places.take(&place);
     if (host_ids) {
         for (int i = 0; i < n_mips; ++i) host_ids[i] = kNotYet;
-        rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, top_vals, host_ids, top_logz,
+        float* rest = reinterpret_cast<float*>(host_ids + EVOSPEC_K_MAX);
+        rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, rest, host_ids, rest + EVOSPEC_K_MAX,
                                         workspace, head, stream);
         // (after an error something may still write to the place: it is not used again)
         if (rc) return rc;
