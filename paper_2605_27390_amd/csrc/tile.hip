@@ -404,6 +404,22 @@ lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const ui
                      (V_act + kGemmSlab - 1) / kGemmSlab, nullptr, part_keys, part_stats);
 }
 
+namespace {
+// Lets a kernel have all the LDS of a compute unit, once per device (concurrent first calls may both set the idempotent attribute).
+template <auto KERN>
+hipError_t allow_lds() {
+    static std::atomic<uint64_t> set{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (bit && (set.load(std::memory_order_acquire) & bit)) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
+    if (e == hipSuccess) set.fetch_or(bit, std::memory_order_release);
+    return e;
+}
+}  // namespace
+
 hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, const int32_t* ids, int V_act, int k, void* keys,
                                 void* stats, hipStream_t stream, bool packed, int num_cu, bool parts, const RowBound& bound, const TileBatch* tb) {
     if (d % 64 != 0 || d < (parts ? kTilePartsMinD : 64) || d > kTileMaxD) return hipErrorInvalidValue;              // callers route such d elsewhere
@@ -427,40 +443,34 @@ hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, cons
     const bool bounded = bound.n_chunks > 0, own = packed && !parts && (tb || two);
     const size_t need = own ? kPackedTileLds : tile_lds(two ? 2 : 4), lds = need > xlds ? need : xlds;
     hipError_t e = hipSuccess;
-    auto go = [&](auto kern) {
-        static std::atomic<uint64_t> attr_set{0};               // devices (concurrent first calls may both set the idempotent attribute)
-        int dev = 0;
-        e = hipGetDevice(&dev);
+    auto go = [&](hipError_t allowed, auto kern) {
+        e = allowed;
         if (e != hipSuccess) return;
-        const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
-        if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
-            if (e != hipSuccess) return;
-            attr_set.fetch_or(bit, std::memory_order_release);
-        }
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, stream, static_cast<const uint16_t*>(h), M, d, static_cast<const uint16_t*>(W), ids,
                            V_act, k, gemm_list_len(k), m_tiles, n_tiles, static_cast<u64*>(keys), static_cast<float2*>(stats), cb, ext, bound);
         e = hipGetLastError();
     };
+#define EVOSPEC_GO(...) go(allow_lds<__VA_ARGS__>(), __VA_ARGS__)
     auto go_packed = [&](auto XMB) {
-        if (d % kKC == 0) go(lmhead_packed_tile_kernel<decltype(XMB)::value, true>);
-        else go(lmhead_packed_tile_kernel<decltype(XMB)::value, false>);
+        if (d % kKC == 0) EVOSPEC_GO(lmhead_packed_tile_kernel<decltype(XMB)::value, true>);
+        else EVOSPEC_GO(lmhead_packed_tile_kernel<decltype(XMB)::value, false>);
     };
     auto go_rows = [&](auto ST, auto XMB) {
-        if (d % kKC == 0) go(lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, true>);
-        else go(lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, false>);
+        if (d % kKC == 0) EVOSPEC_GO(lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, true>);
+        else EVOSPEC_GO(lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, false>);
     };
     using C1 = std::integral_constant<int, 1>;
     using C2 = std::integral_constant<int, 2>;
     using C4 = std::integral_constant<int, 4>;
-    if (parts && packed) two ? go(lmhead_tile_kernel<true, 2, true, 0, true>) : go(lmhead_tile_kernel<true, 4, true, 0, true>);
-    else if (parts) two ? go(lmhead_tile_kernel<false, 2, true, 0, true>) : go(lmhead_tile_kernel<false, 4, true, 0, true>);
-    else if (bounded && !packed) two ? go(lmhead_tile_kernel<false, 2, false, -1, true>) : go(lmhead_tile_kernel<false, 4, false, -1, true>);
-    else if (packed && !own) go(lmhead_tile_kernel<true, 4, false, 0, true>);
-    else if (packed) xmb == 0 ? go(lmhead_packed_tile_kernel<0, true>) : xmb == 1 ? go_packed(C1{}) : xmb == 2 ? go_packed(C2{}) : go_packed(C4{});
-    else if (xmb == 0) two ? go(lmhead_tile_kernel<false, 2, false, 0, true>) : go(lmhead_tile_kernel<false, 4, false, 0, true>);
+    if (parts && packed) two ? EVOSPEC_GO(lmhead_tile_kernel<true, 2, true, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<true, 4, true, 0, true>);
+    else if (parts) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, true, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, true, 0, true>);
+    else if (bounded && !packed) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, false, -1, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, false, -1, true>);
+    else if (packed && !own) EVOSPEC_GO(lmhead_tile_kernel<true, 4, false, 0, true>);
+    else if (packed) xmb == 0 ? EVOSPEC_GO(lmhead_packed_tile_kernel<0, true>) : xmb == 1 ? go_packed(C1{}) : xmb == 2 ? go_packed(C2{}) : go_packed(C4{});
+    else if (xmb == 0) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, false, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, false, 0, true>);
     else if (two) xmb == 1 ? go_rows(C2{}, C1{}) : xmb == 2 ? go_rows(C2{}, C2{}) : go_rows(C2{}, C4{});
     else xmb == 1 ? go_rows(C4{}, C1{}) : xmb == 2 ? go_rows(C4{}, C2{}) : go_rows(C4{}, C4{});
+#undef EVOSPEC_GO
     return e;
 }
 
