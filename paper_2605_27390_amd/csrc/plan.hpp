@@ -436,6 +436,14 @@ inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu) {
     return d <= kTileMaxD && (double)rounds(kGemmSlab, kTileRows) < tile_cost * (double)rounds(kGemmTile, kGemmTile);
 }
 
+// The ring of the packed tile kernel (tile.hip): kPRing pairs of k-steps on the way.  A pair is kRingH loads of h to LDS and twice kRingW of W to
+// registers, requested in this order; pair p requests half of pair p + S of W in its first k-step, waits for h of pair p + 1, and requests h
+// of pair p + S and the other half in its second.  A wait names the loads of a wavefront that may still be under way: those behind
+// h of pair 0 at the start, and behind h of pair p + 1 later on, when that was requested by pair p + 1 - S (at the start there are 2 * kRingW more behind it).
+constexpr int kPRing = 4, kRingH = 4, kRingW = 2;
+constexpr int ring_first_wait(int S) { return 2 * kRingW + (S - 1) * (kRingH + 2 * kRingW); }
+constexpr int ring_wait(int S) { return kRingW + (S - 2) * (kRingH + 2 * kRingW) + kRingW; }
+
 // A bound of every draft row for the matrix-tile kernels, from sorted lists of other candidates of the row that
 // are there already (the extensions of the batched head): every list's q-th best is reached by q logits, so the
 // `sets`-th largest of them is reached by k when q * sets >= k, and no core logit below it can be among the row's k

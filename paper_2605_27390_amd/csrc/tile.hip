@@ -49,13 +49,10 @@ static_assert(tile_lds(4) <= (size_t)kLdsLimit && 2 * tile_lds(2) <= (size_t)kLd
 
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-constexpr int kPRing = 4;                                      // packed tiles: pairs of k-steps of W and of h on the way
 constexpr size_t kPackedTileLds = 4ull * epi_bytes(2) > (size_t)kPRing * kTOperand ? 4ull * epi_bytes(2) : (size_t)kPRing * kTOperand;
 static_assert(kPackedTileLds >= 64 * 1024 && 2 * kPackedTileLds <= (size_t)kLdsLimit, "the logits of a tile; two workgroups per compute unit");
 // operand of s_waitcnt: so many loads, and LDS (or scalar) accesses, may be under way
 constexpr int wait_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm << 8) | (vm >> 4 << 14); }
-// Loads of a wavefront behind the pair of h that a barrier waits for: two of W, eight to every pair in between (four of h, four of W), two of W.
-constexpr int ring_younger(int S) { return 2 + (S - 2) * 8 + 2; }
 
 constexpr int kRsrcFlags = 0x00020000;                         // raw buffer of 32-bit offsets
 // Bytes of the rows of a tile (below 4 GB: the offsets are 32 bits).
@@ -293,7 +290,8 @@ lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const ui
     const int tile_v = logical / m_tiles, tile_m = logical - tile_v * m_tiles;
     const int v0 = tile_v * kTV, m0 = tile_m * kTM;
 
-    // W: this wavefront's 32 rows, two operand blocks of 1 KB to a k-step, straight into registers through a ring of kPRing pairs
+    // W: this wavefront's 32 rows, two operand blocks of 1 KB to a k-step, straight into registers through a ring of kPRing pairs (the loads
+    // under way at each barrier: plan.hpp)
     const uint16_t* wsrc[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)                                  // (tiles past the end repeat the last)
@@ -330,29 +328,37 @@ lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const ui
     };
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
-    // One k-step: 16 MFMAs on ring slot SLOT and operand set S, the operand reads of the next k-step between them.
-    auto step = [&](auto SLOT, auto PAR, int p) {
+    // One k-step: 16 MFMAs on ring slot SLOT and operand set S, the operand reads of the next k-step between them; with LOAD, the pair p + S is
+    // requested.
+    auto step = [&](auto SLOT, auto PAR, int p, auto LOAD) {
         constexpr int s = decltype(PAR)::value, slot = decltype(SLOT)::value;
+        constexpr bool load = decltype(LOAD)::value;
         using NXT = std::integral_constant<int, 1 - s>;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
 #pragma unroll
             for (int t = 0; t < 2; ++t) acc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[slot][t]), opb[s][i], acc[t][i], 0, 0, 0);
             read_b(NXT{}, s ? p + 1 : p, 1 - s, i);              // (past the end: stale operands, never used)
-            if (s == 1 && i < 4) issue_h(p + S, i);
+            if (load && s == 1 && i < 4) issue_h(p + S, i);
             __builtin_amdgcn_sched_barrier(0);
         }
-        load_w(SLOT, p + S, s);
+        if constexpr (load) load_w(SLOT, p + S, s);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto pair = [&](auto R, int p) {
         constexpr int r = decltype(R)::value;
-        step(std::integral_constant<int, 2 * r>{}, S0{}, p);
-        // pair p + 1 of h must have landed for every wavefront (of the loads behind it, 4 of h and 2 of W to a pair or more are
-        // younger: ring_younger(S)), and every wavefront must be through with its reads of pair p, whose stage is filled again
-        __builtin_amdgcn_s_waitcnt(wait_imm(ring_younger(S), 0));
+        step(std::integral_constant<int, 2 * r>{}, S0{}, p, std::true_type{});
+        // pair p + 1 of h must have landed for every wavefront, and every wavefront must be through with its reads of pair p, whose
+        // stage is filled again
+        __builtin_amdgcn_s_waitcnt(wait_imm(ring_wait(S), 0));
         asm volatile("s_barrier" ::: "memory");
-        step(std::integral_constant<int, 2 * r + 1>{}, S1{}, p);
+        step(std::integral_constant<int, 2 * r + 1>{}, S1{}, p, std::true_type{});
+    };
+    // (a pair whose successors have landed, all of them)
+    auto last_pair = [&](auto R, int p) {
+        constexpr int r = decltype(R)::value;
+        step(std::integral_constant<int, 2 * r>{}, S0{}, p, std::false_type{});
+        step(std::integral_constant<int, 2 * r + 1>{}, S1{}, p, std::false_type{});
     };
 
     auto prologue = [&](auto R) {
@@ -368,8 +374,10 @@ lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const ui
 #define EVOSPEC_X(I) prologue(std::integral_constant<int, I>{});
     EVOSPEC_RING(EVOSPEC_X)
 #undef EVOSPEC_X
-    __builtin_amdgcn_s_waitcnt(wait_imm(8 * S - 4, 15));
-    asm volatile("s_barrier" ::: "memory");                      // pair 0 has landed, for every wavefront
+    // pair 0 has landed, for every wavefront.  (Fewer pairs than stages: nothing reads the last ones' W, whose loads need not be there to be counted.)
+    if (npairs >= S) __builtin_amdgcn_s_waitcnt(wait_imm(ring_first_wait(S), 15));
+    else __builtin_amdgcn_s_waitcnt(wait_imm(0, 15));
+    asm volatile("s_barrier" ::: "memory");
 #pragma unroll
     for (int i = 0; i < 8; ++i) read_b(S0{}, 0, 0, i);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 7" ::: "memory");
@@ -379,13 +387,17 @@ lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const ui
         EVOSPEC_RING(EVOSPEC_X)
 #undef EVOSPEC_X
     }
-    // (the ring's first places once more)
-#define EVOSPEC_X(I) if constexpr (I + 1 < S) { if (p + I < npairs) pair(std::integral_constant<int, I>{}, p + I); }
+    // The last pairs, fewer than the ring has: all of them are on their way, nothing more is requested, and they are waited for together.  (Every
+    // register of the ring is read here, so that the loads that the waits above count are there in the last turn of the loop too.)
+#pragma unroll
+    for (int i = 0; i < 2 * S; ++i) asm volatile("" : "+v"(wr[i][0]), "+v"(wr[i][1]));
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+#define EVOSPEC_X(I) if constexpr (I + 1 < S) { if (p + I < npairs) last_pair(std::integral_constant<int, I>{}, p + I); }
     EVOSPEC_RING(EVOSPEC_X)
 #undef EVOSPEC_X
 #undef EVOSPEC_RING
-    // the ring is dead once the trailing loads have landed and every wavefront is here
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // the ring is dead once every wavefront is here
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     // The logits change hands through LDS: from here on a wavefront has all 128 active rows for 32 draft rows.  (Blocks of 16 x 16, which keep
     // their lanes.)
     unsigned char* z = smem + lane * 16;

@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <initializer_list>
+#include <vector>
 
 #include "plan.hpp"
 
@@ -128,6 +129,32 @@ int main() {
     REQUIRE(split_rows(60, 1000, 4096, 10, 256, 4) && split_rows(60, 1024, 4096, 10, 256, 8) && split_rows(33, 1250, 2048, 10, 256, 8), "shared out");
     REQUIRE(!split_rows(32, 1000, 4096, 10, 256, 4) && !split_rows(60, 2048, 4096, 10, 256, 8) && !split_rows(64, 5500, 4096, 10, 256, 4) && !split_rows(60, 1400, 2048, 10, 256, 8) &&
             !split_rows(60, 2048, 4096, 10, 256, 16), "not shared out");
+    // the packed tiles' ring: every wait covers the pair of h that is read behind it, whatever the number of pairs
+    for (int pairs = 1; pairs <= 40; ++pairs) {
+        std::vector<int> flight;                                   // a wavefront's loads in the order of their requests: pair of h, or -1 for W
+        std::vector<bool> landed(pairs + 2 * kPRing, false);
+        auto request = [&](int what, int n) { flight.insert(flight.end(), n, what); };
+        auto wait = [&](int n) {
+            while ((int)flight.size() > n) {
+                if (flight.front() >= 0) landed[flight.front()] = true;
+                flight.erase(flight.begin());
+            }
+        };
+        for (int p = 0; p < kPRing; ++p) { request(p, kRingH); request(-1, p < pairs ? 2 * kRingW : 0); }      // (at least: what nobody reads may not be requested)
+        wait(pairs >= kPRing ? ring_first_wait(kPRing) : 0);
+        REQUIRE(landed[0], "pairs=%d", pairs);
+        int p = 0;
+        for (; p < pairs / kPRing * kPRing; ++p) {                 // (whole turns of the ring)
+            request(-1, kRingW);
+            wait(ring_wait(kPRing));
+            REQUIRE(landed[p + 1] || p + 1 >= pairs, "pair %d of %d", p + 1, pairs);
+            request(p + kPRing, kRingH);
+            request(-1, kRingW);
+        }
+        wait(0);                                                   // the last pairs request nothing
+        for (; p < pairs; ++p) REQUIRE(landed[p], "pair %d of %d", p, pairs);
+    }
+    REQUIRE(ring_first_wait(kPRing) < 64 && ring_wait(kPRing) < 64, "a wait counts to 63");
     REQUIRE(gemm_list_len(16) == 16 && gemm_list_len(17) == 32 && gemm_list_len(64) == 64, "list_len");
     REQUIRE(use_gemm(129, 4096) && !use_gemm(128, 4096) && !use_gemm(960, 4104), "use_gemm");
     std::printf("ok\n");

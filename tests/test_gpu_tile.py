@@ -24,6 +24,8 @@ pytestmark = pytest.mark.gpu
     (11500, 448, 257, 16),    # seven pairs, a row tile of one row
     (33000, 256, 140, 10),    # four pairs
     (33009, 64, 129, 10),     # a single pair
+    (18011, 128, 150, 10),    # two
+    (16500, 384, 129, 20),    # six: two after the ring's only turn
 ])
 def test_few_hundred_rows(ev, oracle_mod, layout, V_act, d, M, k):
     import torch
