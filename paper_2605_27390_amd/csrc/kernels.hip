@@ -199,55 +199,56 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 
 // ---------------------------------------------------------------------------------------
 // Pass 1 of the restricted head, one slab to a workgroup (slab.hpp).  Grid: (slabs, chunks of the batch, twice as many where
-// their draft rows are split); with a core beside the extensions (core.blocks > 0, always front to back: KS and SEGS 1), one
-// dimension: the core's slabs pass by pass, then the chunks'.
-template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS>
+// their draft rows are split).  CORE: with a core beside the extensions (always front to back: KS and SEGS 1), one
+// dimension: the core's slabs pass by pass, then the chunks'.  (Kernels of their own: as a case of one kernel, whose other launches then carried
+// the core's arguments too, these lost up to 0.4 us: row-major 12,000 x 768 at 12 rows 15.9 and 16.3, packed 26,044 x 1,024 at 14 19.1 and 19.2.)
+template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS, bool CORE>
 __global__ void __launch_bounds__(TW * KS * 64)
-lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, CoreSet core, int split, int seq_rows,
+lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, std::conditional_t<CORE, CoreSet, int> core_or_split, int seq_rows,
                        size_t chunk_keys, size_t chunk_stats, int d,
                        const uint16_t* __restrict__ W_all, const int32_t* __restrict__ ids_all,
                        int V_act, int k, int GL,
                        u64* __restrict__ keys_all, float2* __restrict__ stats_all) {
+    static_assert(!CORE || (KS == 1 && SEGS == 1), "two sets: every logit's sum front to back");
     extern __shared__ __align__(16) unsigned char smem[];
-    // this workgroup's problem: chunk blockIdx.y of the batch (its draft rows, its sequence's
-    // rows of a per-sequence matrix, its own piece of the partials)
+    // this workgroup's problem: chunk `ci` of the batch (its draft rows, its sequence's
+    // rows of a per-sequence matrix, its own piece of the partials), or a pass of the core
     // (split = 1: its draft rows go to two workgroups, the first kSplitRows and the others)
-    constexpr bool kMaySplit = MB == mb_for_rows(kSplitRows) && KS == 1;
-    int slab = blockIdx.x, ci = kMaySplit ? blockIdx.y >> split : blockIdx.y;
-    const int row_first = kMaySplit ? (blockIdx.y & split) * kSplitRows : 0;
-    SlabProblem pr;
+    constexpr bool kMaySplit = !CORE && MB == mb_for_rows(kSplitRows) && KS == 1;
+    int slab = blockIdx.x, ci = blockIdx.y, row_first = 0;
     bool of_core = false;
-    int c_rows = cb.rows[ci], c_m0 = cb.m0[ci], c_seq = cb.seq[ci];
-    if constexpr (KS == 1 && SEGS == 1) {
-        // (requested together with the other arguments, not after the branch: 26,044 x 1,024 at 14 rows 19.5 us, so 19.3)
-        asm volatile("" : "+s"(c_rows), "+s"(c_m0), "+s"(c_seq));
-        if (core.blocks > 0) {
-            of_core = slab < core.blocks;
-            slab = of_core ? slab : slab - core.blocks;
-            const int n = of_core ? core.n_slabs : core.chunk_slabs;
-            ci = slab / n;                                                    // pass of the core, or chunk
-            slab -= ci * n;
-            if (!of_core) { c_rows = cb.rows[ci]; c_m0 = cb.m0[ci]; c_seq = cb.seq[ci]; }
-        }
+    if constexpr (CORE) {
+        of_core = slab < core_or_split.blocks;
+        slab = of_core ? slab : slab - core_or_split.blocks;
+        const int n = of_core ? core_or_split.n_slabs : core_or_split.chunk_slabs;
+        ci = slab / n;
+        slab -= ci * n;
+    } else if constexpr (kMaySplit) {
+        ci = blockIdx.y >> core_or_split;
+        row_first = (blockIdx.y & core_or_split) * kSplitRows;
     }
-    if (of_core) {
-        pr.rows = min(core.M - ci * kMTile, kMTile);
-        pr.h = h_all + (size_t)ci * kMTile * d;
-        pr.W = static_cast<const uint16_t*>(core.W);
-        pr.ids = core.ids;
-        pr.V_act = core.V;
-        pr.keys = static_cast<u64*>(core.keys) + ci * core.pass_keys;
-        pr.stats = static_cast<float2*>(core.stats) + ci * core.pass_stats;
+    SlabProblem pr;
+    if (CORE && of_core) {
+        if constexpr (CORE) {
+            const CoreSet& core = core_or_split;
+            pr.rows = min(core.M - ci * kMTile, kMTile);
+            pr.h = h_all + (size_t)ci * kMTile * d;
+            pr.W = static_cast<const uint16_t*>(core.W);
+            pr.ids = core.ids;
+            pr.V_act = core.V;
+            pr.keys = static_cast<u64*>(core.keys) + ci * core.pass_keys;
+            pr.stats = static_cast<float2*>(core.stats) + ci * core.pass_stats;
+        }
     } else {
-        pr.rows = c_rows;
+        pr.rows = cb.rows[ci];
         if constexpr (kMaySplit) {
-            if (split) pr.rows = min(pr.rows - row_first, kSplitRows);
+            if (core_or_split) pr.rows = min(pr.rows - row_first, kSplitRows);
             if (pr.rows <= 0) return;                                         // (uniform)
         }
-        const size_t seq_row0 = (size_t)c_seq * seq_rows;
-        pr.h = h_all + (size_t)(c_m0 + row_first) * d;
+        const size_t seq_row0 = (size_t)cb.seq[ci] * seq_rows;
+        pr.h = h_all + (size_t)(cb.m0[ci] + row_first) * d;
         // (a packed matrix pads every sequence's rows to whole tiles and its rows to whole chunks)
-        pr.W = W_all + (PACKED ? (size_t)c_seq * packed_rows(seq_rows) * packed_d(d) : seq_row0 * d);
+        pr.W = W_all + (PACKED ? (size_t)cb.seq[ci] * packed_rows(seq_rows) * packed_d(d) : seq_row0 * d);
         pr.ids = ids_all ? ids_all + seq_row0 : nullptr;
         pr.V_act = V_act;
         pr.keys = keys_all + (size_t)ci * chunk_keys + row_first * k;
@@ -548,11 +549,11 @@ namespace evospec {
 namespace {
 constexpr int kMaxDevices = 64;
 
-template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS>
+template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS, bool CORE>
 hipError_t launch_partials_k(const Plan& p, const void* h, const ChunkBatch& cb, const CoreSet& core, const BatchLayout& bl, int d,
                              const void* W, const int32_t* ids, int V_act, int k, void* keys, void* stats,
                              hipStream_t stream) {
-    auto kern = lmhead_partials_kernel<TW, KS, RC, MB, FULLK, PACKED, ONCE, SEGS>;
+    auto kern = lmhead_partials_kernel<TW, KS, RC, MB, FULLK, PACKED, ONCE, SEGS, CORE>;
     static std::atomic<bool> attr_set[kMaxDevices] = {};      // concurrent first calls may both set the (idempotent) attribute
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -563,9 +564,12 @@ hipError_t launch_partials_k(const Plan& p, const void* h, const ChunkBatch& cb,
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
     }
-    const dim3 grid = core.blocks > 0 ? dim3(core.blocks + p.n_slabs * cb.n) : dim3(p.n_slabs, bl.split ? 2 * cb.n : cb.n);
+    const dim3 grid = CORE ? dim3(core.blocks + p.n_slabs * cb.n) : dim3(p.n_slabs, bl.split ? 2 * cb.n : cb.n);
+    std::conditional_t<CORE, CoreSet, int> core_or_split;
+    if constexpr (CORE) core_or_split = core;
+    else core_or_split = bl.split ? 1 : 0;
     hipLaunchKernelGGL(kern, grid, dim3(TW * KS * 64), p.lds_bytes, stream,
-                       static_cast<const uint16_t*>(h), cb, core, bl.split ? 1 : 0, bl.seq_rows, bl.chunk_bytes / 8, bl.chunk_bytes / 8, d,
+                       static_cast<const uint16_t*>(h), cb, core_or_split, bl.seq_rows, bl.chunk_bytes / 8, bl.chunk_bytes / 8, d,
                        static_cast<const uint16_t*>(W), ids,
                        V_act, k, p.gl, static_cast<u64*>(keys), static_cast<float2*>(stats));
     return hipGetLastError();
@@ -580,24 +584,25 @@ hipError_t launch_partials_shape(const Plan& p, const void* h, const ChunkBatch&
     const bool once = core.blocks > core.n_slabs ? false
                                                  : slab_streams_once((size_t)V_act * (bl.seq_rows ? cb.n : 1) + (core.blocks > 0 ? core.V : 0), d, bl.packed);
 #define EVOSPEC_ARGS p, h, cb, core, bl, d, W, ids, V_act, k, keys, stats, stream
-#define EVOSPEC_FULL(MB_, KS_, SEGS_)                                                                           \
-    (bl.packed ? (once ? launch_partials_k<TW, KS_, RC, MB_, true, true, true, SEGS_>(EVOSPEC_ARGS)             \
-                       : launch_partials_k<TW, KS_, RC, MB_, true, true, false, SEGS_>(EVOSPEC_ARGS))           \
-               : (once ? launch_partials_k<TW, KS_, RC, MB_, true, false, true, SEGS_>(EVOSPEC_ARGS)            \
-                       : launch_partials_k<TW, KS_, RC, MB_, true, false, false, SEGS_>(EVOSPEC_ARGS)))
-#define EVOSPEC_MB(MB_, KS_)                                                                                    \
-    if (p.mb == MB_ && p.ks == KS_) {                                                                           \
+#define EVOSPEC_FULL(MB_, KS_, SEGS_, CORE_)                                                                    \
+    (bl.packed ? (once ? launch_partials_k<TW, KS_, RC, MB_, true, true, true, SEGS_, CORE_>(EVOSPEC_ARGS)      \
+                       : launch_partials_k<TW, KS_, RC, MB_, true, true, false, SEGS_, CORE_>(EVOSPEC_ARGS))    \
+               : (once ? launch_partials_k<TW, KS_, RC, MB_, true, false, true, SEGS_, CORE_>(EVOSPEC_ARGS)     \
+                       : launch_partials_k<TW, KS_, RC, MB_, true, false, false, SEGS_, CORE_>(EVOSPEC_ARGS)))
+#define EVOSPEC_MB(MB_, KS_, CORE_)                                                                             \
+    if (p.mb == MB_ && p.ks == KS_ && CORE_ == (core.blocks > 0)) {                                             \
         if (!full)                                                                                              \
-            return bl.packed ? launch_partials_k<TW, KS_, RC, MB_, false, true, false, 1>(EVOSPEC_ARGS)         \
-                             : launch_partials_k<TW, KS_, RC, MB_, false, false, false, 1>(EVOSPEC_ARGS);       \
-        if constexpr (KS_ <= kSegMaxShare) {                                                                    \
-            if (p.segs == 2) return EVOSPEC_FULL(MB_, KS_, 2);                                                  \
+            return bl.packed ? launch_partials_k<TW, KS_, RC, MB_, false, true, false, 1, CORE_>(EVOSPEC_ARGS)  \
+                             : launch_partials_k<TW, KS_, RC, MB_, false, false, false, 1, CORE_>(EVOSPEC_ARGS); \
+        if constexpr (KS_ <= kSegMaxShare && !CORE_) {                                                          \
+            if (p.segs == 2) return EVOSPEC_FULL(MB_, KS_, 2, CORE_);                                           \
         }                                                                                                       \
-        return EVOSPEC_FULL(MB_, KS_, 1);                                                                       \
+        return EVOSPEC_FULL(MB_, KS_, 1, CORE_);                                                                \
     }
-    EVOSPEC_MB(1, 1) EVOSPEC_MB(2, 1) EVOSPEC_MB(4, 1)
-    if constexpr (KS2 > 1) { EVOSPEC_MB(2, KS2) }
-    if constexpr (KS4 > 1) { EVOSPEC_MB(4, KS4) }
+    EVOSPEC_MB(1, 1, false) EVOSPEC_MB(2, 1, false) EVOSPEC_MB(4, 1, false)
+    EVOSPEC_MB(1, 1, true) EVOSPEC_MB(2, 1, true) EVOSPEC_MB(4, 1, true)
+    if constexpr (KS2 > 1) { EVOSPEC_MB(2, KS2, false) }
+    if constexpr (KS4 > 1) { EVOSPEC_MB(4, KS4, false) }
 #undef EVOSPEC_MB
 #undef EVOSPEC_FULL
 #undef EVOSPEC_ARGS

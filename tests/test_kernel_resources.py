@@ -1,0 +1,38 @@
+"""What the slab kernels of the built library ask of a compute unit, from the metadata that the compiler leaves beside them: arguments and
+registers decide how soon a workgroup starts and how many share a unit, and nothing else here would notice a change."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2605_27390_amd", "libevospec.so")
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.fixture(scope="module")
+def slab_kernels(tmp_path_factory):
+    """{(tiles, wavefronts to a tile, ring, blocks, whole chunks, packed, past the caches, segments, core): its metadata}"""
+    if not os.path.exists(LIB) or not os.path.exists(os.path.join(LLVM, "llvm-objdump")):
+        pytest.skip("no built library, or no tools to read it")
+    tmp = tmp_path_factory.mktemp("lib")
+    shutil.copy(LIB, tmp / "lib.so")
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", "lib.so"], cwd=tmp, check=True, capture_output=True)
+    out = {}
+    for f in tmp.glob("lib.so.*gfx950*"):
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", f.name], cwd=tmp, check=True, capture_output=True, text=True).stdout
+        for k in notes.split("- .agpr_count")[1:]:
+            m = re.search(r"\.name:\s+\S*lmhead_partials_kernelI((?:L[ib]\d+E)+)E", k)
+            if m:
+                out[tuple(int(x) for x in re.findall(r"L[ib](\d+)E", m.group(1)))] = {
+                    x: int(re.search(r"\.%s:\s+(\d+)" % x, k).group(1)) for x in ("vgpr_count", "kernarg_segment_size")}
+    assert out
+    return out
+
+
+def test_only_joint_launches_carry_a_core(slab_kernels):
+    alone = {v["kernarg_segment_size"] for k, v in slab_kernels.items() if not k[8]}
+    core = {v["kernarg_segment_size"] for k, v in slab_kernels.items() if k[8]}
+    assert len(alone) == 1 and len(core) == 1 and core.pop() >= alone.pop() + 64
