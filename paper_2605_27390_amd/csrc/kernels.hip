@@ -198,12 +198,20 @@ validate_ids_kernel(const int32_t* __restrict__ ids, int n, int V, int* flag) {
 }
 
 // ---------------------------------------------------------------------------------------
+// Wavefronts to a SIMD that the slab kernel's registers must leave room for: those of two workgroups to a compute unit, which launches of several rounds
+// want, where 128 registers are nearly enough anyway (seven wavefronts of 132 cost the second one: packed, 24 rows, 51,446 x 512 26.7 us instead of
+// 23.9, x 2,048 48.8 instead of 45.6.  One block of draft rows does without: nine wavefronts held to 96 70,000 x 5,120 at 8 rows 119.9, otherwise 117.5).
+constexpr int slab_waves(int tw, int ks, int mb, bool packed, int segs) {
+    if (ks == 1 && mb == 2 && (tw == 7 || tw == 8) && (packed || segs == 2)) return 4;
+    return (tw * ks + 3) / 4;                          // (one workgroup)
+}
+
 // Pass 1 of the restricted head, one slab to a workgroup (slab.hpp).  Grid: (slabs, chunks of the batch, twice as many where
 // their draft rows are split).  CORE: with a core beside the extensions (always front to back: KS and SEGS 1), one
 // dimension: the core's slabs pass by pass, then the chunks'.  (Kernels of their own: as a case of one kernel, whose other launches then carried
 // the core's arguments too, these lost up to 0.4 us: row-major 12,000 x 768 at 12 rows 15.9 and 16.3, packed 26,044 x 1,024 at 14 19.1 and 19.2.)
 template <int TW, int KS, int RC, int MB, bool FULLK, bool PACKED, bool ONCE, int SEGS, bool CORE>
-__global__ void __launch_bounds__(TW * KS * 64)
+__global__ void __launch_bounds__(TW * KS * 64, slab_waves(TW, KS, MB, PACKED, SEGS))
 lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, std::conditional_t<CORE, CoreSet, int> core_or_split, int seq_rows,
                        size_t chunk_keys, size_t chunk_stats, int d,
                        const uint16_t* __restrict__ W_all, const int32_t* __restrict__ ids_all,

@@ -36,3 +36,9 @@ def test_only_joint_launches_carry_a_core(slab_kernels):
     alone = {v["kernarg_segment_size"] for k, v in slab_kernels.items() if not k[8]}
     core = {v["kernarg_segment_size"] for k, v in slab_kernels.items() if k[8]}
     assert len(alone) == 1 and len(core) == 1 and core.pop() >= alone.pop() + 64
+
+
+def test_two_workgroups_of_seven_or_eight_wavefronts(slab_kernels):
+    """Two blocks of draft rows on a matrix of several rounds: 14 to 16 wavefronts, four to a SIMD of 512 registers."""
+    two = {k: v["vgpr_count"] for k, v in slab_kernels.items() if k[:2] in ((7, 1), (8, 1)) and k[3] == 2 and (k[5] or k[7] == 2)}
+    assert two and all(v <= 128 for v in two.values()), two
