@@ -310,7 +310,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     char* ws = static_cast<char*>(workspace);
     const uint16_t* hp = static_cast<const uint16_t*>(h);
     const bool one_set = V_core == 0 || V_arc == 0;
-    const TileRoute route = V_core > 0 ? tile_route(M, V_core, d, k, num_cu, one_set, core_workspace_bytes(M, d, V_core, k)) : TileRoute{};
+    const TileRoute route = batch_route(row_off, S, V_core, V_arc, d, k, num_cu, packed, core_workspace_bytes(M, d, V_core, k));
     const size_t core_stride = V_core > 0 ? workspace_upper_bound(V_core, k) : 0;
     const size_t arc_stride = V_arc > 0 ? workspace_upper_bound(V_arc, k) : 0;
     char* ws_arc = ws + (V_core > 0 ? core_workspace_bytes(M, d, V_core, k) : 0);
@@ -389,9 +389,10 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         }
         const bool split = V_arc > 0 && !one_set && split_rows(max_rows, V_arc, d, k, num_cu, cb.n);
         const Plan pa = V_arc > 0 ? make_plan(split ? kSplitRows : max_rows, V_arc, d, k, num_cu, split ? 2 * cb.n : cb.n, one_set) : Plan{};
-        // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there.
+        // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there (small tiles of a packed
+        // matrix have no kernel for it).
         RowBound bound;
-        if (V_arc > 0 && route.tiles && all) {
+        if (V_arc > 0 && route.tiles && !(route.small && packed) && all) {
             choose_bound(&bound, pa.n_slabs, k);
             if (bound.q > 0) {
                 bound.keys = reinterpret_cast<const unsigned long long*>(ws_arc + pa.keys_off);

@@ -418,17 +418,22 @@ inline int gemm_list_len(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 // draft rows through the selection one by one, four times as many in a wavefront of large tiles (512 x 20,011 x 2,560 137
 // and 112 at k = 10; at k = 1, where the bound holds, 91 and 100).  From k = 13 on most rows have more survivors than a list, which large tiles
 // select one by one and small ones by halves: 65,536 x 4,096 at 500 rows, k = 13 336 and 298, k = 16 516 and 304, k = 32 553 and 370;
-// 32,768 x 4,096 at 960, k = 64 486 and 368; 32,768 x 1,024 at 512, k = 20 169 and 74.
+// 32,768 x 4,096 at 960, k = 64 486 and 368; 32,768 x 1,024 at 512, k = 20 169 and 74; 32,768 x 4,096 at 4,000, k = 16 1,960 and 1,223, x 1,024 1,422 and 472.
+// bounded: beside extensions whose lists bound the rows (choose_bound), so that few have.  There the rounds decide again, with more for the small tiles of a packed matrix,
+// which share their launch with the extensions (32,768 + 2,048 x 4,096, k = 16, large tiles and small ones: packed, 960 rows of 16, two rounds and eight, 301 and
+// 336; 480 of 8, one and four, 177 and 184; 300 of 5, one and three, 160 and 147; 640 of 11, two and five, 282 and 236; row-major 319 and 365, 186
+// and 208, 165 and 175, 291 and 259; x 2,048, 24,000 + 1,024, 500 of 16, one and three, 112 and 108).
+constexpr int kOwnBoundK = 12;             // largest k whose bound of 32 group maxima (slab_epilogue.hpp) leaves a list of 16 some room
 constexpr int kTileRows = 128;
 constexpr int kTileMaxD = 1 << 23;         // (rows of a tile within 32-bit offsets)
 inline bool slow_last_slab(int V_act, int k) {
     const int last = V_act % kGemmSlab;
     return last > 16 && last / 4 < k + k / 2;
 }
-inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu) {
+inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu, bool bounded = false, bool packed = false) {
     const bool slow_last = slow_last_slab(V_act, k);
-    if (k > 12 && d >= 1024) return d <= kTileMaxD;
-    const double tile_cost = d < 2048 || slow_last ? 3.3 : 2.9;
+    if (k > kOwnBoundK && d >= 1024 && !bounded) return d <= kTileMaxD;
+    const double tile_cost = d < 2048 || slow_last || (bounded && (packed || d <= 2048)) ? 3.3 : 2.9;
     auto rounds = [&](int v, int m) {
         const long n = (long)((V_act + v - 1) / v) * ((M + m - 1) / m);
         return (n + num_cu - 1) / num_cu;
@@ -449,6 +454,7 @@ constexpr int ring_wait(int S) { return kRingW + (S - 2) * (kRingH + 2 * kRingW)
 // `sets`-th largest of them is reached by k when q * sets >= k, and no core logit below it can be among the row's k
 // best.  The lists of a row lie as the slab kernel leaves them, per chunk of draft rows.
 constexpr int kBoundLists = 16;          // lists that are looked at (all lists' bound is hardly better)
+constexpr int kBoundK = 16;              // largest k with a bound: longer lists than 16 are more than the tiles stage
 struct RowBound {
     const unsigned long long* keys = nullptr;
     size_t chunk_keys = 0;               // keys between two chunks
@@ -466,10 +472,19 @@ inline void choose_bound(RowBound* b, int n_lists, int k) {
     b->n_lists = n_lists < kBoundLists ? n_lists : kBoundLists;
     b->k = k;
     b->q = 0;
-    for (int q = 1; q <= 2 && k <= 16; ++q) {
+    for (int q = 1; q <= 2 && k <= kBoundK; ++q) {
         const int sets = (k + q - 1) / q;
         if (4 * sets <= 3 * b->n_lists) { b->q = q; b->sets = sets; return; }
     }
+}
+
+// Whether the lists of a batch's extensions bound its draft rows: `chunks` of at most max_rows rows in one launch.
+inline bool lists_bound(int max_rows, int V_arc, int d, int k, int num_cu, int chunks) {
+    if (V_arc <= 0 || chunks < 1 || chunks > kMaxChunks) return false;
+    const bool split = split_rows(max_rows, V_arc, d, k, num_cu, chunks);
+    RowBound b;
+    choose_bound(&b, make_plan(split ? kSplitRows : max_rows, V_arc, d, k, num_cu, split ? 2 * chunks : chunks, false).n_slabs, k);
+    return b.q > 0;
 }
 
 struct GemmPlan {
@@ -529,6 +544,30 @@ struct TileRoute {
 inline TileRoute tile_route(int M, int V_act, int d, int k, int num_cu, bool one_set, size_t scratch) {
     const bool early = use_tiles_early(M, V_act, d, k, one_set, scratch), tiles = early || use_gemm(M, d);
     return TileRoute{tiles, early || (tiles && use_small_tiles(M, V_act, d, k, num_cu)), early && one_set};
+}
+
+// The same for the core of a batch (row_off: the first draft row of every sequence, and M).  Chunks are pieces of at most kMTile rows of one sequence, which
+// without tiles end where a pass over the core does.
+struct ChunkCount { int n = 0, max_rows = 0; };
+inline ChunkCount count_chunks(const int32_t* row_off, int S, bool tiles) {
+    ChunkCount c;
+    for (int s = 0; s < S; ++s)
+        for (int m0 = row_off[s], end = row_off[s + 1]; m0 < end; ++c.n) {
+            const int limit = tiles ? m0 + kMTile : (m0 / kMTile + 1) * kMTile, to = end < limit ? end : limit;
+            if (to - m0 > c.max_rows) c.max_rows = to - m0;
+            m0 = to;
+        }
+    return c;
+}
+inline TileRoute batch_route(const int32_t* row_off, int S, int V_core, int V_arc, int d, int k, int num_cu, bool packed, size_t scratch) {
+    const int M = row_off[S];
+    if (V_core == 0) return TileRoute{};
+    TileRoute r = tile_route(M, V_core, d, k, num_cu, V_arc == 0, scratch);
+    if (V_arc > 0 && use_gemm(M, d) && k > kOwnBoundK && k <= kBoundK) {
+        const ChunkCount c = count_chunks(row_off, S, true);
+        if (lists_bound(c.max_rows, V_arc, d, k, num_cu, c.n)) r.small = use_small_tiles(M, V_core, d, k, num_cu, true, packed);
+    }
+    return r;
 }
 
 // Scratch for the shared core of the segmented head: one set of partials per 64-row pass, or

@@ -11,7 +11,6 @@
 
 namespace evospec {
 
-constexpr int kOwnBoundK = 12;                // largest k whose bound of 32 group maxima leaves a list of 16 some room
 constexpr int kGFastLen = 16;                 // list length the staged common path of the epilogue handles
 // LDS per wavefront: the staged lists and spare slots of the common path, or a block's parked logits; then ids
 constexpr int epi_lists(int nmb) {

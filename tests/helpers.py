@@ -110,9 +110,9 @@ def plan_route(M, V_act, d, k, cus=256):
     return _plan_route(M, V_act, d, k, cus)
 
 
-def plan_route_batched(V_core, V_arc, d, k, lens, cus=256):
-    """The same for the batched head with lens[s] draft rows in sequence s: the core's launch, and the extensions'."""
-    return _plan_route("batched", V_core, V_arc, d, k, cus, *lens)
+def plan_route_batched(V_core, V_arc, d, k, lens, cus=256, layout="packed"):
+    """The same for the batched head with lens[s] draft rows in sequence s: the core's launch, and the extensions', alone or in one ("joint")."""
+    return _plan_route("batched", layout, V_core, V_arc, d, k, cus, *lens)
 
 
 def _plan_route(*args):

@@ -106,6 +106,14 @@ int main() {
             REQUIRE(b.k == k && b.n_lists <= n && b.n_lists <= kBoundLists && b.q <= 2 && (b.q == 0 || k <= 16), "k=%d lists=%d", k, n);
             REQUIRE(b.q == 0 || (b.q <= k && b.sets >= 1 && b.sets <= b.n_lists && b.q * b.sets >= k), "k=%d lists=%d q=%d sets=%d", k, n, b.q, b.sets);
         }
+    // k past the slabs' own bound: small tiles, but large ones beside extensions that bound the rows, where these take far fewer rounds
+    const int32_t full[] = {0, 60, 120, 180, 240, 300, 360, 420, 480, 540, 600, 660, 720, 780, 840, 900, 960};
+    for (int packed = 0; packed < 2; ++packed) {
+        REQUIRE(tile_route(960, 32768, 4096, 16, 256, true, 0).small && !batch_route(full, 16, 32768, 2048, 4096, 16, 256, packed, 0).small, "16 x 60");
+        REQUIRE(batch_route(full, 16, 32768, 2048, 4096, 17, 256, packed, 0).small && batch_route(full, 16, 32768, 300, 4096, 16, 256, packed, 0).small, "no bound");
+        REQUIRE(batch_route(full, 5, 32768, 2048, 4096, 16, 256, packed, 0).small == (packed != 0) && batch_route(full, 5, 32768, 2048, 2048, 13, 256, packed, 0).small, "5 x 60");
+        REQUIRE(batch_route(full, 16, 8192, 2048, 4096, 16, 256, packed, 0).small, "two rounds");
+    }
     // 65 to 128 rows in tiles: the lists fit the scratch, whatever the caller's is
     for (int M = 1; M <= 300; ++M)
         for (int k : {1, 4, 7, 8, 10, 12, 13, 16, 17, 64})

@@ -50,7 +50,8 @@ def test_head_of_65_to_128_rows(ev, oracle_mod, layout, V_act, d, M, k, route):
 
 @pytest.mark.parametrize("layout", ["packed", "row_major"])
 @pytest.mark.parametrize("V_core,V_arc,d,lens,k,route,bound", [
-    (1000, 700, 256, [64, 1], 10, "tile", 2),                # a bound from the extensions' lists
+    (1000, 700, 256, [64, 1], 10, "tile", 0),                # one launch with the extensions
+    (20096, 2048, 64, [30, 30, 30, 20], 10, "tile", 1),      # (row-major: a bound from the extensions' lists)
     (5000, 90, 1024, [60, 40, 28], 10, "tile", 0),           # none: too few lists
     (1000, 20, 192, [50, 78], 8, "tile", 0),                 # the lists just fit the core's scratch
     (1000, 20, 192, [50, 60], 8, "tile", 0),
@@ -59,8 +60,8 @@ def test_head_of_65_to_128_rows(ev, oracle_mod, layout, V_act, d, M, k, route):
 ])
 def test_core_of_65_to_128_rows(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, route, bound):
     import torch
-    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count)
-    assert r["kernel"] == route and r["bound"] == bound and "parts" not in r
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count, layout)
+    assert r["kernel"] == route and r["bound"] == (bound if layout == "row_major" else 0) and "parts" not in r
     S, M, V = len(lens), sum(lens), V_core + len(lens) * V_arc
     ids = np.random.default_rng(V + M).permutation(V).astype(np.int32)
     W, h = gi.gen_normal_bf16(V, d, 61, 0.05), gi.gen_h(M, d, 62)

@@ -74,16 +74,17 @@ def test_equal_rows_and_order(ev, layout, V_act, d, M, k):
 @pytest.mark.parametrize("V_core,V_arc,d,lens,k,core", [
     (16000, 400, 512, [20, 1, 40], 12, "slab"),          # core in one pass of slabs of 4 tiles
     (36864, 900, 1024, [33, 64, 10], 12, "tile"),        # 107 rows: 128 x 128 tiles in a single chain, extensions of 4 tiles
-    (36864, 900, 1024, [33, 64, 10], 13, "slab"),        # core of 9 tiles in two passes, extensions of 4
+    (36864, 900, 1024, [33, 64, 10], 13, "slab"),        # core in two passes
     (36864, 900, 2048, [33, 64, 10], 13, "slab"),        # a hidden dimension that a call with one set takes in two segments
     (2000, 2000, 2048, [60, 17, 60, 8], 12, "tile"),     # 128 x 128 tiles and slabs
+    (10300, 2048, 256, [50, 33, 64], 12, "tile"),        # (row-major: in two launches, rows of the extensions shared out, a bound from their lists)
     (300, 17000, 256, [64], 12, "slab"),
 ])
 def test_equal_rows_in_core_and_extension(ev, layout, V_core, V_arc, d, lens, k, core):
     """Copies of one row in the shared core and in an extension tie as well."""
     import torch
     S, M = len(lens), sum(lens)
-    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count)
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count, layout)
     assert r["kernel"] == core and "parts" not in r and r.get("segments", 1) == 1
     W, group = scattered_copies(V_core + V_arc, 4, d, V_core + d)
     rng = np.random.default_rng(d)

@@ -45,8 +45,8 @@ def check_batch(ev, oracle_mod, layout, V_core, V_arc, d, lens, k):
 ])
 def test_joint_launch(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, blocks):
     import torch
-    chunks = plan_route_batched(V_core, V_arc, d, k, lens[:64], torch.cuda.get_device_properties(0).multi_processor_count)
-    assert chunks["kernel"] == "slab" and chunks["joint_blocks"] == blocks
+    r = plan_route_batched(V_core, V_arc, d, k, lens[:64], torch.cuda.get_device_properties(0).multi_processor_count, layout)
+    assert r["kernel"] == "slab" and r["joint"] == 1 and r["arc_blocks"] == blocks
     check_batch(ev, oracle_mod, layout, V_core, V_arc, d, lens, k)
 
 
@@ -63,7 +63,7 @@ def test_joint_launch(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, blocks)
 ])
 def test_joint_tiles(ev, oracle_mod, layout, V_core, V_arc, d, lens, k):
     import torch
-    r = plan_route_batched(V_core, V_arc, d, k, lens if len(lens) <= 64 else [sum(lens) // 7] * 7, torch.cuda.get_device_properties(0).multi_processor_count)
+    r = plan_route_batched(V_core, V_arc, d, k, lens if len(lens) <= 64 else [sum(lens) // 7] * 7, torch.cuda.get_device_properties(0).multi_processor_count, layout)
     assert r["kernel"] == "tile" and r["joint"] == 1
     check_batch(ev, oracle_mod, layout, V_core, V_arc, d, lens, k)
 

@@ -13,23 +13,53 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("layout", ["packed", "row_major"])
 @pytest.mark.parametrize("V_core,V_arc,d,lens,k,arc_scale", [
-    (1000, 1000, 256, [60, 1, 70, 3], 10, 1.0),      # 128 x 128 tiles, the first best of 16 lists, a chunk of a single row
-    (1000, 1000, 256, [64, 65, 1], 16, 1.0),         # the second best of 16
-    (1100, 500, 128, [40, 40, 60], 10, 1.0),         # of 8 lists
-    (1000, 300, 64, [130], 10, 1.0),                 # too few lists: a slab's own bound
-    (1000, 1000, 256, [33, 64, 64], 10, 0.01),       # nothing of the extension is among the best: more survivors than a list holds
+    (1000, 1000, 256, [60, 1, 70, 3], 10, 1.0),      # 128 x 128 tiles in one launch with the extensions: a slab's own bound, a chunk of a single row
+    (1000, 1000, 256, [64, 65, 1], 16, 1.0),         # by halves
+    (1100, 500, 128, [40, 40, 60], 10, 1.0),
+    (1000, 300, 64, [130], 10, 1.0),
+    (1000, 1000, 256, [33, 64, 64], 10, 0.01),       # nothing of the extension is among the best
     (1000, 1000, 256, [33, 64, 64], 10, 40.0),       # nothing of the core is
     (1000, 1000, 256, [33, 64, 64], 1, 1.0),
     (1000, 1000, 256, [33, 64, 64], 10, 0.0),        # every logit of the extensions is 0
-    (21700, 1500, 64, [60] * 12, 10, 1.0),           # 256 x 256 tiles
+    (21700, 1500, 64, [60] * 12, 10, 1.0),           # 256 x 256 tiles: the first best of 16 lists
     (21700, 1500, 64, [64] * 12, 7, 0.05),
+    (32700, 2048, 64, [60] * 8, 16, 1.0),            # lists as long as k: the second best
+    (32700, 2048, 64, [60] * 8, 16, 0.05),
+    (32700, 500, 128, [60] * 8, 10, 1.0),            # of 8 lists
     (1000, 700, 64, [3] * 64, 2, 1.0),               # as many chunks as one launch takes
 ])
 def test_bound_from_extensions(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, arc_scale):
     import torch
-    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count)
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count, layout)
     assert r["kernel"] == ("gemm" if V_core > 20000 else "tile")
-    assert r["bound"] == {300: 0, 500: 2}.get(V_arc, 2 if k == 16 else 1)
+    if V_core > 20000:
+        assert r["bound"] == (2 if k == 16 or V_arc == 500 else 1)
+    else:
+        assert r["joint"] == (V_arc != 700 or layout == "packed") and r["bound"] == 1 - r["joint"]
+    check_bound(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, arc_scale)
+
+
+@pytest.mark.parametrize("V_core,V_arc,d,lens,k,arc_scale,bound", [
+    (10300, 2048, 128, [60, 1, 70, 3], 10, 1.0, 1),          # 128 x 128 tiles, the first best of 16 lists, a chunk of a single row
+    (10300, 2048, 64, [64, 65, 1], 16, 1.0, 2),              # the second best of 16
+    (8300, 300, 64, [5] * 26, 8, 1.0, 0),                    # too few lists: a slab's own bound
+    (8300, 500, 64, [9] * 16, 10, 1.0, 2),                   # of 8 lists
+    (10300, 2048, 64, [33, 64, 64], 10, 0.01, 1),            # nothing of the extension is among the best: more survivors than a list holds
+    (10300, 2048, 64, [33, 64, 64], 10, 40.0, 1),            # nothing of the core is
+    (10300, 2048, 64, [33, 64, 64], 1, 1.0, 1),
+    (10300, 2048, 64, [33, 64, 64], 10, 0.0, 1),             # every logit of the extensions is 0
+    (10307, 2048, 64, [33, 64, 64], 13, 0.05, 2),            # a ragged last slab
+])
+def test_bound_from_extensions_of_small_tiles(ev, oracle_mod, V_core, V_arc, d, lens, k, arc_scale, bound):
+    """Row-major small tiles that the extensions do not ride with."""
+    import torch
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count, "row_major")
+    assert r["kernel"] == "tile" and r["joint"] == 0 and r["bound"] == bound
+    check_bound(ev, oracle_mod, "row_major", V_core, V_arc, d, lens, k, arc_scale)
+
+
+def check_bound(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, arc_scale):
+    import torch
     S, M = len(lens), sum(lens)
     rng = np.random.default_rng(V_core + V_arc + M + k)
     V = V_core + S * V_arc
@@ -61,6 +91,8 @@ def test_bound_from_extensions(ev, oracle_mod, layout, V_core, V_arc, d, lens, k
     (1000, 1000, 256, [60, 1, 70, 3], 10),       # 128 x 128 tiles
     (1000, 1000, 256, [64, 65, 1], 16),
     (1003, 500, 128, [40, 40, 60], 5),           # a last slab of 107 rows
+    (10300, 2048, 64, [60, 1, 70, 3], 10),       # (row-major: these by themselves and bounded, those above beside the extensions)
+    (10300, 2048, 64, [64, 65, 1], 16),
     (21700, 1500, 64, [60] * 12, 10),            # 256 x 256 tiles
 ])
 def test_bound_loose_for_some_rows(ev, oracle_mod, layout, V_core, V_arc, d, lens, k):
