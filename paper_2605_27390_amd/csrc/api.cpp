@@ -389,10 +389,11 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
         }
         const bool split = V_arc > 0 && !one_set && split_rows(max_rows, V_arc, d, k, num_cu, cb.n);
         const Plan pa = V_arc > 0 ? make_plan(split ? kSplitRows : max_rows, V_arc, d, k, num_cu, split ? 2 * cb.n : cb.n, one_set) : Plan{};
-        // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there (small tiles of a packed
-        // matrix have no kernel for it).
+        // The matrix tiles of the core can take over a bound from the extensions' lists, when those of all draft rows are there.  (The tiles of a packed
+        // matrix that have no use for it still go second: 31,859 + 1,936 x 4,096, 138 rows of 12 127.1 us for the call, so 121.8; 32,000 + 1,024, 140 of 3 106.3 and
+        // 100.8; 28,000 + 2,048, 150 of 3 99.4 and 100.3.)
         RowBound bound;
-        if (V_arc > 0 && route.tiles && !(route.small && packed) && all) {
+        if (V_arc > 0 && route.tiles && all) {
             choose_bound(&bound, pa.n_slabs, k);
             if (bound.q > 0) {
                 bound.keys = reinterpret_cast<const unsigned long long*>(ws_arc + pa.keys_off);

@@ -320,16 +320,27 @@ inline Plan make_tile_batch_plan(int max_rows, int V_arc, int k) {
     return p;
 }
 
+constexpr int kTileRows = 128;           // (tile.hip)
+
 // Whether the extensions' slabs (of make_tile_batch_plan) ride in the launch of the core's small tiles.  Without and with it, us for the call, k = 10:
 // packed, 5,225 + 151 x 4,096, 220 rows of 11 52 and 35; 9,276 + 522 x 2,048, 363 of 16 47.6 and 37.5; 14,416 + 332 x 4,096, 477 of 13
-// 106 and 93; 16,384 + 1,000 x 4,096, 197 of 4 72 and 69.5; 4,000 + 2,000 x 4,096, 400 of 16 98 and 84.  Row-major slabs are slower, and tiles that share a
-// compute unit have a ring of two stages: where both fit the chip once (5,225 + 151 62 and 39), where the tiles take more than
-// a round anyway (14,416 + 332 117 and 104), or beside a few slabs with short rows (16,384 + 1,000 x 2,048, 250 of 5 54 and
-// 51; x 4,096, 197 of 4 82 and 86; 4,906 + 1,764 x 4,096, 293 of 7, 117 tiles and 196 slabs, 79 and 91).
+// 106 and 93; 16,384 + 1,000 x 4,096, 197 of 4 72 and 69.5; 4,000 + 2,000 x 4,096, 400 of 16 98 and 84.
+// More tiles than compute units sit there in twos, in as many places as twice the units; slabs that find none wait for tiles to end, and by themselves they
+// would have their rows shared out (split_rows) and leave a bound.  512 places, row-major, whose tiles take over a bound: 440 tiles and 128 slabs 114 and 100; 399 and
+// 135 112 and 96; 372 and 400 x 2,048 84 and 76; 1,280 and 352 277 and 259; but 512 and 40 118.6 and 127.9; 512 and 128 118 and 131; 435 and 200 115
+// and 122; 483 and 108 x 2,048 68.6 and 70.1; 471 and 256 125 and 127.  Packed, where most tiles do not: 408 and 96 104 and 83; 483 and 108 65 and 61; 512 and 128 109 and 102; 471 and
+// 256 117 and 108; 512 and 512 152 and 144; only with little in the second row of tiles and a large hidden dimension not, x 4,096, 150 rows of 3: 470 and 96
+// 101.3 and 107.3; 438 and 96 99.5 and 105.4; 512 and 96 104.8 and 111; 138 rows of 12, 498 and 372 122 and 133; 180 of 3, 512 and 96 109 and 109; x 2,048, 150 of 3, 438 and 96 64 and 59.
+// Row-major tiles that have a compute unit each have a ring of four stages by themselves and of two beside slabs: all on the chip once (5,225 +
+// 151 62 and 39), or beside a few slabs with short rows (16,384 + 1,000 x 2,048, 250 of 5 54 and 51; x 4,096, 197 of 4 82 and 86; 4,906 + 1,764 x 4,096, 293 of 7,
+// 117 tiles and 196 slabs, 79 and 91).
 inline bool joint_tiles(int M, int V_core, int d, int num_cu, bool packed, int arc_slabs, int chunks) {
-    const long tiles = ((V_core + 127l) / 128) * ((M + 127l) / 128);
-    if (tiles + (long)arc_slabs * chunks > kJointWorkgroups) return false;
-    return packed || tiles > num_cu || tiles + arc_slabs * chunks <= num_cu || (d <= 2048 && 2 * arc_slabs * chunks <= tiles);
+    const long tiles = ((V_core + 127l) / 128) * ((M + 127l) / 128), slabs = (long)arc_slabs * chunks;
+    if (tiles + slabs > kJointWorkgroups) return false;
+    const long places = 2l * num_cu, free = (tiles + places - 1) / places * places - tiles;      // beside the last round of tiles
+    if (packed) return d <= 2048 || M > kTileRows + 32 || slabs <= free;         // (few rows in the second row of tiles)
+    if (tiles > num_cu) return slabs <= 2 * free || 4 * free >= places;
+    return tiles + slabs <= num_cu || (d <= 2048 && 2 * slabs <= tiles);
 }
 
 // Whether a batch of chunks gives the draft rows of every chunk to two workgroups, kSplitRows at most to each: where even
@@ -424,7 +435,6 @@ inline int gemm_list_len(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 // 336; 480 of 8, one and four, 177 and 184; 300 of 5, one and three, 160 and 147; 640 of 11, two and five, 282 and 236; row-major 319 and 365, 186
 // and 208, 165 and 175, 291 and 259; x 2,048, 24,000 + 1,024, 500 of 16, one and three, 112 and 108).
 constexpr int kOwnBoundK = 12;             // largest k whose bound of 32 group maxima (slab_epilogue.hpp) leaves a list of 16 some room
-constexpr int kTileRows = 128;
 constexpr int kTileMaxD = 1 << 23;         // (rows of a tile within 32-bit offsets)
 inline bool slow_last_slab(int V_act, int k) {
     const int last = V_act % kGemmSlab;

@@ -114,6 +114,11 @@ int main() {
         REQUIRE(batch_route(full, 5, 32768, 2048, 4096, 16, 256, packed, 0).small == (packed != 0) && batch_route(full, 5, 32768, 2048, 2048, 13, 256, packed, 0).small, "5 x 60");
         REQUIRE(batch_route(full, 16, 8192, 2048, 4096, 16, 256, packed, 0).small, "two rounds");
     }
+    // the extensions beside small tiles in twos: where they find places
+    REQUIRE(joint_tiles(150, 26000, 4096, 256, true, 32, 3) && !joint_tiles(150, 30000, 4096, 256, true, 32, 3) && joint_tiles(180, 32768, 4096, 256, true, 32, 3), "packed");
+    REQUIRE(joint_tiles(480, 14000, 4096, 256, false, 16, 8) && !joint_tiles(480, 16384, 4096, 256, false, 16, 8) && !joint_tiles(480, 16384, 4096, 256, false, 5, 8) &&
+            joint_tiles(367, 15792, 2048, 256, false, 25, 16) && joint_tiles(640, 32768, 4096, 256, false, 32, 11), "row-major");
+    REQUIRE(joint_tiles(220, 5225, 4096, 256, false, 3, 11) && joint_tiles(250, 16384, 2048, 256, false, 16, 5) && !joint_tiles(197, 16384, 4096, 256, false, 16, 4), "a compute unit each");
     // 65 to 128 rows in tiles: the lists fit the scratch, whatever the caller's is
     for (int M = 1; M <= 300; ++M)
         for (int k : {1, 4, 7, 8, 10, 12, 13, 16, 17, 64})

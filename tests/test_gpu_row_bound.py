@@ -49,6 +49,8 @@ def test_bound_from_extensions(ev, oracle_mod, layout, V_core, V_arc, d, lens, k
     (10300, 2048, 64, [33, 64, 64], 1, 1.0, 1),
     (10300, 2048, 64, [33, 64, 64], 10, 0.0, 1),             # every logit of the extensions is 0
     (10307, 2048, 64, [33, 64, 64], 13, 0.05, 2),            # a ragged last slab
+    (30000, 2048, 64, [50] * 3, 10, 1.0, 1),                 # more tiles than compute units: rings of two stages
+    (16300, 1000, 128, [60] * 8, 16, 0.3, 2),
 ])
 def test_bound_from_extensions_of_small_tiles(ev, oracle_mod, V_core, V_arc, d, lens, k, arc_scale, bound):
     """Row-major small tiles that the extensions do not ride with."""

@@ -35,6 +35,7 @@ def test_split_rows(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, core, til
     (10300, 2048, 264, [50, 33, 64], 10, 0),                # d no multiple of 64: slabs, in one launch
     (10300, 2048, 256, [50, 33, 64], 10, 1),                # small tiles, one to a compute unit, that take over a bound
     (10300, 2048, 320, [50, 33, 64], 20, 0),                # none
+    (30000, 2048, 64, [50] * 3, 10, 1),                     # in twos, and too few places beside them
 ])
 def test_beside_small_tiles(ev, oracle_mod, V_core, V_arc, d, lens, k, bound):
     import torch
