@@ -451,6 +451,18 @@ inline bool use_small_tiles(int M, int V_act, int d, int k, int num_cu, bool bou
     return d <= kTileMaxD && (double)rounds(kGemmSlab, kTileRows) < tile_cost * (double)rounds(kGemmTile, kGemmTile);
 }
 
+// Whether small tiles of a packed matrix that sit in twos on the compute units keep W in registers (lmhead_packed_tile_kernel) or send it through LDS as
+// well.  Registers gain 2 to 13 % (x 4,096, us: 28,000 at 150 rows 82.1 and 77.6; 11,000 at 300 68.0 and 60.2; 16,384 at 512 90.4 and 86.1; 32,768 at 250 96.2 and 94.1;
+// x 2,048, 28,000 at 200 53.9 and 51.1), but not where only some units have two tiles and the hidden dimension is of the middle (x 2,048, 16,500 at 200 rows
+// 38.5 and 40.4, 17,000 at 150 38.6 and 40.3, 8,300 at 512 39.0 and 40.0, 20,000 at 200 42.4 and 42.9; x 1,024 17,000 at 150 28.8 and 29.0; x 4,096 18,000 at 200 77.8 and 76.6),
+// nor where all have two, the second row of tiles holds little and the hidden dimension is large (32,768 x 4,096 at 135 rows 88.5 and 92.9, at 170 88.7 and
+// 92.0, at 200 90.1 and 88.9; x 8,192 at 150 156 and 168; x 3,072 at 140 72.3 and 74.6; x 2,048 at 135 53.7 and 50.8; 32,400 x 4,096 at 150 88.2 and 88.3).
+inline bool w_in_registers(int M, int V_act, int d, int num_cu) {
+    const long tiles = ((V_act + kTileRows - 1l) / kTileRows) * ((M + kTileRows - 1l) / kTileRows);
+    if (4 * tiles <= 5l * num_cu && d > 1024 && d < 4096) return false;
+    return !(tiles > 2l * num_cu - num_cu / 32 && tiles <= 2l * num_cu && M <= kTileRows + 48 && d >= 3072);
+}
+
 // The ring of the packed tile kernel (tile.hip): kPRing pairs of k-steps on the way.  A pair is kRingH loads of h to LDS and twice kRingW of W to
 // registers, requested in this order; pair p requests half of pair p + S of W in its first k-step, waits for h of pair p + 1, and requests h
 // of pair p + S and the other half in its second.  A wait names the loads of a wavefront that may still be under way: those behind

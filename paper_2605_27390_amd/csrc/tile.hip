@@ -452,7 +452,7 @@ hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, cons
     }
     // more workgroups than compute units: two with shallow rings share one, so that one computes while the other starts or ends
     const bool two = blocks > num_cu;
-    const bool bounded = bound.n_chunks > 0, own = packed && !parts && (tb || two);
+    const bool bounded = bound.n_chunks > 0, own = packed && !parts && (tb || (two && w_in_registers(M, V_act, d, num_cu)));
     const size_t need = own ? kPackedTileLds : tile_lds(two ? 2 : 4), lds = need > xlds ? need : xlds;
     hipError_t e = hipSuccess;
     auto go = [&](hipError_t allowed, auto kern) {
@@ -477,7 +477,8 @@ hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, cons
     if (parts && packed) two ? EVOSPEC_GO(lmhead_tile_kernel<true, 2, true, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<true, 4, true, 0, true>);
     else if (parts) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, true, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, true, 0, true>);
     else if (bounded && !packed) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, false, -1, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, false, -1, true>);
-    else if (packed && !own) EVOSPEC_GO(lmhead_tile_kernel<true, 4, false, 0, true>);
+    else if (packed && !own && two && bounded) EVOSPEC_GO(lmhead_tile_kernel<true, 2, false, -1, true>);
+    else if (packed && !own) two ? EVOSPEC_GO(lmhead_tile_kernel<true, 2, false, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<true, 4, false, 0, true>);
     else if (packed) xmb == 0 ? EVOSPEC_GO(lmhead_packed_tile_kernel<0, true>) : xmb == 1 ? go_packed(C1{}) : xmb == 2 ? go_packed(C2{}) : go_packed(C4{});
     else if (xmb == 0) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, false, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, false, 0, true>);
     else if (two) xmb == 1 ? go_rows(C2{}, C1{}) : xmb == 2 ? go_rows(C2{}, C2{}) : go_rows(C2{}, C4{});

@@ -115,6 +115,8 @@ int main() {
         REQUIRE(batch_route(full, 16, 8192, 2048, 4096, 16, 256, packed, 0).small, "two rounds");
     }
     // the extensions beside small tiles in twos: where they find places
+    REQUIRE(w_in_registers(150, 28000, 4096, 256) && !w_in_registers(200, 16500, 2048, 256) && w_in_registers(200, 22000, 2048, 256) && w_in_registers(200, 17000, 1024, 256), "few with two");
+    REQUIRE(!w_in_registers(150, 32768, 4096, 256) && w_in_registers(200, 32768, 4096, 256) && w_in_registers(150, 32768, 2048, 256) && w_in_registers(150, 33000, 4096, 256), "all with two");
     REQUIRE(joint_tiles(150, 26000, 4096, 256, true, 32, 3) && !joint_tiles(150, 30000, 4096, 256, true, 32, 3) && joint_tiles(180, 32768, 4096, 256, true, 32, 3), "packed");
     REQUIRE(joint_tiles(480, 14000, 4096, 256, false, 16, 8) && !joint_tiles(480, 16384, 4096, 256, false, 16, 8) && !joint_tiles(480, 16384, 4096, 256, false, 5, 8) &&
             joint_tiles(367, 15792, 2048, 256, false, 25, 16) && joint_tiles(640, 32768, 4096, 256, false, 32, 11), "row-major");

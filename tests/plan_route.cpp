@@ -44,7 +44,9 @@ static int batched(int n, char** a) {
         const Plan p = joint ? (r.tiles ? make_tile_batch_plan(c.max_rows, V_arc, k) : j.arc)
                              : make_plan(split ? kSplitRows : c.max_rows, V_arc, d, k, cus, split ? 2 * c.n : c.n, one_set);
         RowBound b;
-        if (r.tiles && !joint && !(r.small && packed)) choose_bound(&b, p.n_slabs, k);
+        const long tiles = ((V_core + 127l) / 128) * ((M + 127l) / 128);
+        const bool takes = !r.small || !packed || (tiles > cus && !w_in_registers(M, V_core, d, cus));      // a kernel for it
+        if (r.tiles && !joint && takes) choose_bound(&b, p.n_slabs, k);
         std::printf(" split=%d arc_tiles=%d arc_blocks=%d arc_slabs=%d bound=%d", split ? 1 : 0, p.nw, p.mb, p.n_slabs, b.q);
     }
     std::printf("\n");

@@ -39,6 +39,15 @@ def test_bound_from_extensions(ev, oracle_mod, layout, V_core, V_arc, d, lens, k
     check_bound(ev, oracle_mod, layout, V_core, V_arc, d, lens, k, arc_scale)
 
 
+def test_bound_from_extensions_of_packed_small_tiles(ev, oracle_mod):
+    """Two tiles on every compute unit and little in the second row of them: W through LDS, and a bound."""
+    import torch
+    V_core, V_arc, d, lens, k = 32700, 1000, 3072, [50, 31, 50], 10
+    r = plan_route_batched(V_core, V_arc, d, k, lens, torch.cuda.get_device_properties(0).multi_processor_count, "packed")
+    assert r["kernel"] == "tile" and r["joint"] == 0 and r["bound"] == 1 and r["split"] == 1
+    check_bound(ev, oracle_mod, "packed", V_core, V_arc, d, lens, k, 1.0)
+
+
 @pytest.mark.parametrize("V_core,V_arc,d,lens,k,arc_scale,bound", [
     (10300, 2048, 128, [60, 1, 70, 3], 10, 1.0, 1),          # 128 x 128 tiles, the first best of 16 lists, a chunk of a single row
     (10300, 2048, 64, [64, 65, 1], 16, 1.0, 2),              # the second best of 16

@@ -26,6 +26,7 @@ pytestmark = pytest.mark.gpu
     (33009, 64, 129, 10),     # a single pair
     (18011, 128, 150, 10),    # two
     (16500, 384, 129, 20),    # six: two after the ring's only turn
+    (16500, 2048, 150, 10),   # a few compute units with two tiles
 ])
 def test_few_hundred_rows(ev, oracle_mod, layout, V_act, d, M, k):
     import torch
