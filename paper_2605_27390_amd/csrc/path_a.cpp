@@ -21,15 +21,20 @@ constexpr int kMaxCandidates = 4096;
 // bytes to pageable memory and the wait for it took 10 to 14 us more.)  The values and the log-normaliser, which nobody reads, go there too, behind the
 // ids: the host may see the ids before the last of them is stored, and the workspace is the caller's again when the call returns.  One block per process, given back when it ends; a call holds a place
 // while it runs, whatever its thread, stream or device, and one that finds none copies.
+constexpr int kPlaces = 16;
+constexpr int kWords = 2 * EVOSPEC_K_MAX + 16;                 // ids, values, log-normaliser
 class IdPlaces {
 public:
-    static constexpr int kPlaces = 16;
-    static constexpr int kWords = 2 * EVOSPEC_K_MAX + 16;      // ids, values, log-normaliser
     int32_t* take(int* place) {
         if (!base_.load(std::memory_order_acquire)) {
+            // (an allocation that this call is alone with: another thread may be recording a graph in the mode that forbids it to all)
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
             void* p = nullptr;
-            if (hipHostMalloc(&p, kPlaces * kWords * sizeof(int32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-                (void)hipGetLastError();                 // (the copy will do)
+            const hipError_t e = hipHostMalloc(&p, kPlaces * kWords * sizeof(int32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();                       // (the copy will do)
                 return nullptr;
             }
             int32_t* none = nullptr;
@@ -52,6 +57,29 @@ private:
     std::atomic<uint32_t> taken_{0};
 };
 IdPlaces g_places;
+
+// The place of one call.  It goes back when all ids were seen: nothing behind the ids is read, and nothing else is stored there.  A call that does not get that far first
+// waits for what it put on the stream; where even that fails, something may still write to the place, and nobody has it again.
+class HeldPlace {
+public:
+    explicit HeldPlace(hipStream_t st) : st_(st) {
+        // (a stream that records a graph takes the copy, which the graph refuses: the places are for work that runs now)
+        hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &recording) != hipSuccess) (void)hipGetLastError();
+        else if (recording == hipStreamCaptureStatusNone) ids = g_places.take(&place_);
+    }
+    HeldPlace(const HeldPlace&) = delete;
+    ~HeldPlace() {
+        if (ids && (seen_ || hipStreamSynchronize(st_) == hipSuccess)) g_places.give(place_);
+    }
+    void all_seen() { seen_ = true; }
+    int32_t* ids = nullptr;                                    // null: none free
+
+private:
+    hipStream_t st_;
+    int place_ = -1;
+    bool seen_ = false;
+};
 
 constexpr int32_t kNotYet = INT32_MIN;           // no id, and not "none" (-1) either
 constexpr auto kSpin = std::chrono::milliseconds(2);
@@ -120,29 +148,29 @@ int evospec_path_a_event(evospec_arc* arc, const void* h_target, int d, const vo
 
     // 1. exact search over the full vocabulary (identity ids), ids to the host
     int32_t mips[EVOSPEC_K_MAX];
-    int place = -1;
-    int32_t* host_ids = g_places.take(&place);
-    if (host_ids) {
-        for (int i = 0; i < n_mips; ++i) host_ids[i] = kNotYet;
-        float* rest = reinterpret_cast<float*>(host_ids + EVOSPEC_K_MAX);
-        rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, rest, host_ids, rest + EVOSPEC_K_MAX,
-                                        workspace, head, stream);
-        // (after an error something may still write to the place: it is not used again)
-        if (rc) return rc;
-        const hipError_t e = wait_for_ids(host_ids, n_mips, st);
-        if (e != hipSuccess) return evospec::record_hip_error(e);
-        for (int i = 0; i < n_mips; ++i) {
-            mips[i] = host_ids[i];
-            if (mips[i] == kNotYet) return EVOSPEC_HIP_ERROR;
+    {
+        HeldPlace place(st);
+        if (place.ids) {
+            for (int i = 0; i < n_mips; ++i) place.ids[i] = kNotYet;
+            float* rest = reinterpret_cast<float*>(place.ids + EVOSPEC_K_MAX);
+            rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, rest, place.ids, rest + EVOSPEC_K_MAX,
+                                            workspace, head, stream);
+            if (rc) return rc;
+            const hipError_t e = wait_for_ids(place.ids, n_mips, st);
+            if (e != hipSuccess) return evospec::record_hip_error(e);
+            for (int i = 0; i < n_mips; ++i) {
+                mips[i] = place.ids[i];
+                if (mips[i] == kNotYet) return EVOSPEC_HIP_ERROR;
+            }
+            place.all_seen();
+        } else {
+            rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, top_vals, top_ids, top_logz,
+                                            workspace, head, stream);
+            if (rc) return rc;
+            if (hipMemcpyAsync(mips, top_ids, (size_t)n_mips * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipStreamSynchronize(st) != hipSuccess)
+                return EVOSPEC_HIP_ERROR;
         }
-        g_places.give(place);
-    } else {
-        rc = evospec_active_lmhead_topk(h_target, 1, d, W_lm, nullptr, V, EVOSPEC_ROW_MAJOR, n_mips, top_vals, top_ids, top_logz,
-                                        workspace, head, stream);
-        if (rc) return rc;
-        if (hipMemcpyAsync(mips, top_ids, (size_t)n_mips * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return EVOSPEC_HIP_ERROR;
     }
     // 2. candidates, 3. admission
     std::vector<int32_t> cand((size_t)kMaxCandidates);
