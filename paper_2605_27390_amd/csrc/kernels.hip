@@ -235,6 +235,7 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, std::c
         ci = blockIdx.y >> core_or_split;
         row_first = (blockIdx.y & core_or_split) * kSplitRows;
     }
+    const int c_rows = cb.rows[of_core ? 0 : ci], c_m0 = cb.m0[of_core ? 0 : ci], c_seq = cb.seq[of_core ? 0 : ci];      // (asked for together)
     SlabProblem pr;
     if (CORE && of_core) {
         if constexpr (CORE) {
@@ -248,15 +249,15 @@ lmhead_partials_kernel(const uint16_t* __restrict__ h_all, ChunkBatch cb, std::c
             pr.stats = static_cast<float2*>(core.stats) + ci * core.pass_stats;
         }
     } else {
-        pr.rows = cb.rows[ci];
+        pr.rows = c_rows;
         if constexpr (kMaySplit) {
             if (core_or_split) pr.rows = min(pr.rows - row_first, kSplitRows);
             if (pr.rows <= 0) return;                                         // (uniform)
         }
-        const size_t seq_row0 = (size_t)cb.seq[ci] * seq_rows;
-        pr.h = h_all + (size_t)(cb.m0[ci] + row_first) * d;
+        const size_t seq_row0 = (size_t)c_seq * seq_rows;
+        pr.h = h_all + (size_t)(c_m0 + row_first) * d;
         // (a packed matrix pads every sequence's rows to whole tiles and its rows to whole chunks)
-        pr.W = W_all + (PACKED ? (size_t)cb.seq[ci] * packed_rows(seq_rows) * packed_d(d) : seq_row0 * d);
+        pr.W = W_all + (PACKED ? (size_t)c_seq * packed_rows(seq_rows) * packed_d(d) : seq_row0 * d);
         pr.ids = ids_all ? ids_all + seq_row0 : nullptr;
         pr.V_act = V_act;
         pr.keys = keys_all + (size_t)ci * chunk_keys + row_first * k;

@@ -181,12 +181,19 @@ __device__ __forceinline__ void slab_partials(const SlabProblem& pr, int slab, i
     // h in LDS: piece c (16 bytes) of draft row m sits in place c ^ (m mod 16) of its row.  A 128-bit read takes the 64 lanes in four turns
     // of 16, {0-3, 12-15, 20-27} the first, which holds every draft row of the block once: 16 different 16-byte columns of 256 bytes, no
     // bank twice.  (Rows padded by 16 bytes had one conflict in every turn, which doubled its time.)
-    // (The piece of this wavefront's k-step s is that of its first with 4 s flipped in; from the fifth on, 128 elements away.)
-    static_assert(KSTEPS == 8 || KSTEPS == 4 || KSTEPS == 2, "its first k-step, modulo 4, is 0, or 2 of two");
-    const uint16_t* brow = Hs + n16 * kHStride + s0 / 4 * 128;
-    const int bcol = ((4 * (s0 & 3) + g) ^ n16) * 8;
-    auto load_b = [&](bf16x8 (&b)[MB], int col, int buf, int s) {
-        const int at = (col ^ (s & 3) * 32) + s / 4 * 128;
+    // ANEW: the places of four k-steps are found in every chunk.  Kept over the chunks they are registers that seven and eight wavefronts with two blocks of draft
+    // rows have no room for beside a second workgroup (packed 51,446 x 2,048 at 24 rows 45.6 us, kept 48.8), nor shared tiles in one segment, which
+    // spill (row-major 28,000 x 1,024 at 60 26.0 and 27.7); elsewhere they cost nothing and save the flips (full vocabulary row-major 243.2, kept 241.2).
+    constexpr bool ANEW = (KS == 1 && MB == 2 && (TW == 7 || TW == 8)) || (KS == 2 && MB == 4 && SEGS == 1);
+    const uint16_t* brow = Hs + n16 * kHStride;
+    int bcol[4];                                   // this lane's piece of k-steps 0..3 (4..7: 128 elements on), relative to its row
+#pragma unroll
+    for (int s = 0; s < 4; ++s) bcol[s] = ((4 * (((KS > 1 ? s0 : 0) + s) & 3) + g) ^ n16) * 8;
+    // (k-step 0 of this wavefront is k-step 0, or 2 where it has two, of a group of four: the piece of the s-th has 4 s flipped)
+    static_assert(KSTEPS == 8 || KSTEPS == 4 || KSTEPS == 2, "groups of four k-steps");
+    int flip0 = bcol[0] + s0 / 4 * 128;            // (ANEW)
+    auto load_b = [&](bf16x8 (&b)[MB], int buf, int s) {
+        const int at = ANEW ? (flip0 ^ (s & 3) * 32) + s / 4 * 128 : bcol[s & 3] + ((KS > 1 ? s0 : 0) + s) / 4 * 128;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) b[mb] = *reinterpret_cast<const bf16x8*>(brow + ((size_t)buf * MR + mb * 16) * kHStride + at);
     };
@@ -216,19 +223,16 @@ __device__ __forceinline__ void slab_partials(const SlabProblem& pr, int slab, i
         const int buf = c & 1, cw = (c + RC) ^ cx;
         constexpr std::bool_constant<FULLK || STEADY> whole{};
         bf16x8 b0[MB], b1[MB];
-        // (anew in every chunk: kept over the chunks, the places of four k-steps are registers that the second workgroup of a compute unit, or a
-        // tile that is shared, has no room for: row-major 28,000 x 1,024 at 60 rows 26.0 us, with them 27.7; packed 51,446 x 2,048 at 24 45.6 and 48.8)
-        int col = bcol;
-        asm volatile("" : "+v"(col));
+        if constexpr (ANEW) asm volatile("" : "+v"(flip0));
         if (STEADY || c + HA < nchunks) load_h(hreg[(SLOT + HA) % HA], (c + HA) ^ cx, whole);
-        load_b(b0, col, buf, 0);
+        load_b(b0, buf, 0);
 #pragma unroll
         for (int s = 0; s < KSTEPS; s += 2) {
-            load_b(b1, col, buf, s + 1);
+            load_b(b1, buf, s + 1);
             __builtin_amdgcn_sched_barrier(0);
             mfma_step(SLOT * KSTEPS + s, b0);
             if (PACKED && pw) load_w_step(SLOT * KSTEPS + s, cw, s, whole);
-            if (s + 2 < KSTEPS) load_b(b0, col, buf, s + 2);
+            if (s + 2 < KSTEPS) load_b(b0, buf, s + 2);
             __builtin_amdgcn_sched_barrier(0);
             mfma_step(SLOT * KSTEPS + s + 1, b1);
             if (PACKED && pw) load_w_step(SLOT * KSTEPS + s + 1, cw, s + 1, whole);
