@@ -234,9 +234,12 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
     // some 4 to 8 times: a ragged last slab with too few groups for (1), k past it.  (One row after the other, as all such rows used to
     // go, and by halves, us: 20,000 x 2,048 at 256 rows, k = 16 90 and 53, k = 30 93 and 56, k = 60 126 and 69; 14,877 x 1,024 at
     // 200, a last slab of 29 rows, 39 and 24.)
+    // Up to kFewOver such rows in a wavefront go one after the other all the same, which is sooner done: with a bound of (1) one row in a few hundred is left, and
+    // halving was 1 us more on a small launch (5,000 x 768 at 400 rows 22.4 us, by halves 23.5; 8,192 x 1,024 at 256 23.7 and 24.7).
     // (Blocks of 128 draft rows to a wavefront have no registers for (2), nor for the longer lists below: such rows go one by one.)
     constexpr bool kRoom = NMB <= 2;
     const int cap = list_len == kGFastLen ? kGFastLen : (kRoom ? list_len : -1);
+    constexpr int kFewOver = 3;
     constexpr int kHalvings = 20;                                  // (what is left then has equal logits, or next to equal ones)
     float tau[NMB];
 #pragma unroll
@@ -276,11 +279,11 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
             Lp[hf] = q[0] + q[1] + q[2] + q[3];
         }
     };
-    auto any_over = [&]() {
-        bool over = false;
+    auto over = [&]() {                                            // rows with more than that (the 4 lanes of a row agree)
+        int n = 0;
 #pragma unroll
-        for (int mb = 0; mb < NMB; ++mb) over = over || length(mb) > cap;
-        return __ballot(over) != 0;
+        for (int mb = 0; mb < NMB; ++mb) n += __popcll(__ballot(length(mb) > cap));
+        return n / 4;
     };
     float lo[NMB], hi[NMB];                                        // (2) the interval of an open row
     uint32_t fixed = 0;                                            // bit mb: the row's bound stands
@@ -321,7 +324,8 @@ __device__ __forceinline__ void slab_epilogue(f32x4 (&acc)[8][NMB], unsigned cha
             if (!kRoom) break;
         }
         if (it <= 0) {
-            if (!any_over()) break;
+            const int n = over();
+            if (n == 0 || (it == 0 && n <= kFewOver)) break;
             if (it < 0) continue;
         }
         if constexpr (kRoom) {

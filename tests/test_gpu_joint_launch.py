@@ -88,3 +88,16 @@ def test_bounds_at_every_scale(ev, oracle_mod, V_act, k):
         assert np.all(np.abs(v[m] - best) <= err), f"row {m}"
         slot = np.argsort(ids)[i[m]]
         assert len(set(i[m].tolist())) == k and np.all(np.abs(z[m][slot] - v[m]) <= err), f"row {m}"
+
+
+@pytest.mark.parametrize("V_act,M,k,zeros", [(5000, 160, 10, 1), (5000, 160, 10, 3), (5000, 160, 10, 4), (4000, 140, 5, 2), (3000, 140, 33, 3)])
+def test_few_rows_past_their_lists(ev, oracle_mod, V_act, M, k, zeros):
+    """Rows whose logits are all equal, some of the 32 that a wavefront has: up to three go one after the other, more by halves first."""
+    d = 128
+    W, h = gi.gen_normal_bf16(V_act, d, 65, 0.05), gi.gen_h(M, d, 66)
+    empty = np.arange(M) % 32 >= 32 - zeros
+    h[empty] = 0
+    ids = np.random.default_rng(V_act + zeros).permutation(V_act).astype(np.int32)
+    v, i, l = (x.cpu().numpy() for x in ev.active_lmhead_topk(to_dev_bf16(h), to_dev_bf16(W), to_dev_i32(ids), k))
+    assert np.all(i[empty] == np.arange(k)) and not v[empty].any()
+    check_head(v[~empty], i[~empty], l[~empty], oracle_mod.logits(h[~empty], W), ids, k, f"V_act={V_act} k={k} zeros={zeros}")
