@@ -47,6 +47,7 @@ static_assert(kTV == 128 && kTM == 128, "the load and operand offsets below assu
 static_assert(kTilePartsMinD >= kTileParts * 64, "a pair of chunks to every part");
 static_assert(tile_lds(4) <= (size_t)kLdsLimit && 2 * tile_lds(2) <= (size_t)kLdsLimit, "one deep or two shallow rings per compute unit");
 
+typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 constexpr size_t kPackedTileLds = 4ull * epi_bytes(2) > (size_t)kPRing * kTOperand ? 4ull * epi_bytes(2) : (size_t)kPRing * kTOperand;
@@ -56,9 +57,7 @@ constexpr int wait_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm <
 
 constexpr int kRsrcFlags = 0x00020000;                         // raw buffer of 32-bit offsets
 // Bytes of the rows of a tile (below 4 GB: the offsets are 32 bits).
-__device__ __forceinline__ int tile_bytes(int rows, int d, bool packed) {
-    return (int)((unsigned)(packed ? (int)packed_rows(rows) : rows) * (unsigned)(packed ? packed_d(d) : d) * 2u);
-}
+__device__ __forceinline__ int tile_bytes(int rows, int d) { return (int)((unsigned)rows * (unsigned)d * 2u); }
 
 // (the same with the accumulators in ordinary registers)
 __device__ __forceinline__ void mfma_vec(f32x4& c, const bf16x8& a, const bf16x8& b) {
@@ -119,11 +118,10 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
     // A wave-level load fills one 1 KB block of a pair-stage: 8 rows x 128 bytes of h or of a row-major W, piece p of row r in
     // place p ^ (r / 2 mod 8) of its eight; or one k-step of 16 rows of a packed W.  Each wavefront: 4 blocks of W, 4 of h.
     // (A 128-bit read takes its 16 rows' pieces in four turns of 16 lanes, {0-3, 12-15, 20-27} the first: each turn meets 16 different
-    // 16-byte columns of 256 bytes, so no bank twice.  Buffer loads: after global_load_lds, which the compiler takes for
-    // an access to either memory, it waits for all of both.)
-    const auto wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W + (size_t)v0 * (PACKED ? packed_d(d) : d)), 0,
-                                                         tile_bytes(min(V_act - v0, kTV), d, PACKED), kRsrcFlags);
-    const auto hrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(h + (size_t)m0 * d), 0, tile_bytes(min(M - m0, kTM), d, false), kRsrcFlags);
+    // 16-byte columns of 256 bytes, so no bank twice.  Global loads: buffer loads cost row-major tiles of five rounds 5 to 7 % (512 rows, 40,000 x 2,560 169.3 us, so 181.8;
+    // x 1,536 112.1 and 117.0), one round up to 1.5 % (5,000 x 2,048 at 400 28.9 and 29.3).)
+    const char* wbase = reinterpret_cast<const char*>(W + (size_t)v0 * (PACKED ? packed_d(d) : d));
+    const char* hbase = reinterpret_cast<const char*>(h + (size_t)m0 * d);
     unsigned aoff[4], boff[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -139,10 +137,10 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
     const int npairs = d / 64;
     // load j (0..7) of pair p; pairs past the end repeat the last into a stage that nobody reads again
     auto issue = [&](int p, int j) {
-        const int at = min(p, npairs - 1) * 128;
+        const size_t at = (size_t)min(p, npairs - 1) * 128;
         const auto dst = (lptr_t)(smem + (p & (S - 1)) * kTStage + (j & 1) * kTOperand + (4 * w + (j >> 1)) * 1024);
-        if (j & 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(hrsrc, dst, 16, (int)boff[j >> 1], at, 0, 0);
-        else __builtin_amdgcn_raw_ptr_buffer_load_lds(wrsrc, dst, 16, (int)aoff[j >> 1], PACKED ? at * 16 : at, 0, 0);
+        const char* src = j & 1 ? hbase + boff[j >> 1] + at : wbase + aoff[j >> 1] + (PACKED ? at * 16 : at);
+        __builtin_amdgcn_global_load_lds((gptr_t)src, dst, 16, 0, 0);
     };
 
     // the sum of a part is read out again and again: in ordinary registers, where there are enough of them
@@ -297,7 +295,7 @@ lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const ui
     for (int t = 0; t < 2; ++t)                                  // (tiles past the end repeat the last)
         wsrc[t] = W + (size_t)min((v0 >> 4) + 2 * w + t, (V_act - 1) >> 4) * kPackRows * packed_d(d) + lane * 8;
     // h: a wave-level load fills one 1 KB block of a pair-stage: 8 rows x 128 bytes, as in the kernel above
-    const auto hrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(h + (size_t)m0 * d), 0, tile_bytes(min(M - m0, kTM), d, false), kRsrcFlags);
+    const auto hrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(h + (size_t)m0 * d), 0, tile_bytes(min(M - m0, kTM), d), kRsrcFlags);
     unsigned hoff[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
