@@ -7,7 +7,7 @@
 // with direct-to-LDS loads in pairs of 32-element chunks through a ring of S stages: four stages when there
 // is one workgroup per compute unit (a tile this small is through with a stage long before a load comes back),
 // two stages and two workgroups per compute unit otherwise.  lmhead_packed_tile_kernel, for packed matrices with two workgroups per compute
-// unit: only h goes through LDS, W straight into registers (30,000 x 2,048 at 256 rows 63 -> 60 us; with one workgroup per compute unit
+// unit where w_in_registers says so: only h goes through LDS, W straight into registers (30,000 x 2,048 at 256 rows 63 -> 60 us; with one workgroup per compute unit
 // 14,848 x 4,096 at 200 51 -> 54).
 // Bound by what a compute unit is sent: 32 KB per pair of chunks, 0.3 us with few of them at work and 0.6 with all (54 GB/s each).
 // Neither LDS, free of bank conflicts or not, nor a ring twice as deep, nor draft rows of zeros make a difference;
@@ -78,12 +78,20 @@ struct TileExtensions {
     float2* stats = nullptr;
 };
 
+// What a launch brings beside the tiles' own arguments, and nothing that it does not: 1.7 KB of them cost a launch some 0.3 us.
+struct ExtensionArgs {
+    ChunkBatch cb;
+    TileExtensions ext;
+};
+template <int XMB>
+using BesideArgs = std::conditional_t<(XMB > 0), ExtensionArgs, std::conditional_t<(XMB < 0), RowBound, int>>;
+
 // XMB: 16-row blocks of an extension's draft rows (0: no extensions in this launch, -1: but a bound from their lists); XFULL: d is a multiple of kKC.
 template <bool PACKED, int S, bool PARTS, int XMB, bool XFULL>
 __global__ void __launch_bounds__(256, S > 2 ? 1 : 2)
 lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t* __restrict__ W,
                    const int32_t* __restrict__ ids, int V_act, int k, int list_len, int m_tiles, int n_tiles,
-                   u64* __restrict__ part_keys, float2* __restrict__ part_stats, ChunkBatch cb, TileExtensions ext, RowBound bound) {
+                   u64* __restrict__ part_keys, float2* __restrict__ part_stats, BesideArgs<XMB> beside) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -91,6 +99,8 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
 
     if constexpr (XMB > 0) {
         if ((int)blockIdx.x >= n_tiles) {
+            const ChunkBatch& cb = beside.cb;
+            const TileExtensions& ext = beside.ext;
             int slab = (int)blockIdx.x - n_tiles;
             const int ci = slab / ext.n_slabs;
             slab -= ci * ext.n_slabs;
@@ -195,7 +205,7 @@ lmhead_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t*
     // the draft rows' bounds, if there are any, while these loads are under way
     float* bnd = reinterpret_cast<float*>(smem + tile_lds(S) - kTM * 4);
     if constexpr (XMB < 0) {
-        if (tid < kTM) bnd[tid] = row_bound(bound, m0 + tid, M);
+        if (tid < kTM) bnd[tid] = row_bound(beside, m0 + tid, M);
     }
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(8 * (S - 1)) : "memory");      // pair 0 has landed, for every wavefront
 #pragma unroll
@@ -255,7 +265,7 @@ template <int XMB, bool XFULL>
 __global__ void __launch_bounds__(256, 2)
 lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const uint16_t* W,
                    const int32_t* __restrict__ ids, int V_act, int k, int list_len, int m_tiles, int n_tiles,
-                   u64* __restrict__ part_keys, float2* __restrict__ part_stats, ChunkBatch cb, TileExtensions ext, RowBound) {
+                   u64* __restrict__ part_keys, float2* __restrict__ part_stats, BesideArgs<XMB> beside) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int S = kPRing;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -264,6 +274,8 @@ lmhead_packed_tile_kernel(const uint16_t* __restrict__ h, int M, int d, const ui
 
     if constexpr (XMB > 0) {
         if ((int)blockIdx.x >= n_tiles) {
+            const ChunkBatch& cb = beside.cb;
+            const TileExtensions& ext = beside.ext;
             int slab = (int)blockIdx.x - n_tiles;
             const int ci = slab / ext.n_slabs;
             slab -= ci * ext.n_slabs;
@@ -434,8 +446,9 @@ hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, cons
                                 void* stats, hipStream_t stream, bool packed, int num_cu, bool parts, const RowBound& bound, const TileBatch* tb) {
     if (d % 64 != 0 || d < (parts ? kTilePartsMinD : 64) || d > kTileMaxD) return hipErrorInvalidValue;              // callers route such d elsewhere
     const int v_tiles = (V_act + kTV - 1) / kTV, m_tiles = (M + kTM - 1) / kTM, n_tiles = v_tiles * m_tiles;
-    ChunkBatch cb;
-    TileExtensions ext;
+    ExtensionArgs x;
+    ChunkBatch& cb = x.cb;
+    TileExtensions& ext = x.ext;
     int blocks = n_tiles, xmb = 0;
     size_t xlds = 0;
     if (tb) {
@@ -453,32 +466,37 @@ hipError_t launch_tile_partials(const void* h, int M, int d, const void* W, cons
     const bool bounded = bound.n_chunks > 0, own = packed && !parts && (tb || (two && w_in_registers(M, V_act, d, num_cu)));
     const size_t need = own ? kPackedTileLds : tile_lds(two ? 2 : 4), lds = need > xlds ? need : xlds;
     hipError_t e = hipSuccess;
-    auto go = [&](hipError_t allowed, auto kern) {
+    auto go = [&](hipError_t allowed, auto kern, const auto& beside) {
         e = allowed;
         if (e != hipSuccess) return;
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, stream, static_cast<const uint16_t*>(h), M, d, static_cast<const uint16_t*>(W), ids,
-                           V_act, k, gemm_list_len(k), m_tiles, n_tiles, static_cast<u64*>(keys), static_cast<float2*>(stats), cb, ext, bound);
+                           V_act, k, gemm_list_len(k), m_tiles, n_tiles, static_cast<u64*>(keys), static_cast<float2*>(stats), beside);
         e = hipGetLastError();
     };
-#define EVOSPEC_GO(...) go(allow_lds<__VA_ARGS__>(), __VA_ARGS__)
+    auto args_of = [&](auto XMB) -> const auto& {
+        if constexpr (decltype(XMB)::value > 0) return x;
+        else if constexpr (decltype(XMB)::value < 0) return bound;
+        else return blocks;                                        // (nothing)
+    };
+#define EVOSPEC_GO(X, ...) go(allow_lds<__VA_ARGS__>(), __VA_ARGS__, args_of(std::integral_constant<int, X>{}))
     auto go_packed = [&](auto XMB) {
-        if (d % kKC == 0) EVOSPEC_GO(lmhead_packed_tile_kernel<decltype(XMB)::value, true>);
-        else EVOSPEC_GO(lmhead_packed_tile_kernel<decltype(XMB)::value, false>);
+        if (d % kKC == 0) EVOSPEC_GO(decltype(XMB)::value, lmhead_packed_tile_kernel<decltype(XMB)::value, true>);
+        else EVOSPEC_GO(decltype(XMB)::value, lmhead_packed_tile_kernel<decltype(XMB)::value, false>);
     };
     auto go_rows = [&](auto ST, auto XMB) {
-        if (d % kKC == 0) EVOSPEC_GO(lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, true>);
-        else EVOSPEC_GO(lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, false>);
+        if (d % kKC == 0) EVOSPEC_GO(decltype(XMB)::value, lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, true>);
+        else EVOSPEC_GO(decltype(XMB)::value, lmhead_tile_kernel<false, decltype(ST)::value, false, decltype(XMB)::value, false>);
     };
     using C1 = std::integral_constant<int, 1>;
     using C2 = std::integral_constant<int, 2>;
     using C4 = std::integral_constant<int, 4>;
-    if (parts && packed) two ? EVOSPEC_GO(lmhead_tile_kernel<true, 2, true, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<true, 4, true, 0, true>);
-    else if (parts) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, true, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, true, 0, true>);
-    else if (bounded && !packed) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, false, -1, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, false, -1, true>);
-    else if (packed && !own && two && bounded) EVOSPEC_GO(lmhead_tile_kernel<true, 2, false, -1, true>);
-    else if (packed && !own) two ? EVOSPEC_GO(lmhead_tile_kernel<true, 2, false, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<true, 4, false, 0, true>);
-    else if (packed) xmb == 0 ? EVOSPEC_GO(lmhead_packed_tile_kernel<0, true>) : xmb == 1 ? go_packed(C1{}) : xmb == 2 ? go_packed(C2{}) : go_packed(C4{});
-    else if (xmb == 0) two ? EVOSPEC_GO(lmhead_tile_kernel<false, 2, false, 0, true>) : EVOSPEC_GO(lmhead_tile_kernel<false, 4, false, 0, true>);
+    if (parts && packed) two ? EVOSPEC_GO(0, lmhead_tile_kernel<true, 2, true, 0, true>) : EVOSPEC_GO(0, lmhead_tile_kernel<true, 4, true, 0, true>);
+    else if (parts) two ? EVOSPEC_GO(0, lmhead_tile_kernel<false, 2, true, 0, true>) : EVOSPEC_GO(0, lmhead_tile_kernel<false, 4, true, 0, true>);
+    else if (bounded && !packed) two ? EVOSPEC_GO(-1, lmhead_tile_kernel<false, 2, false, -1, true>) : EVOSPEC_GO(-1, lmhead_tile_kernel<false, 4, false, -1, true>);
+    else if (packed && !own && two && bounded) EVOSPEC_GO(-1, lmhead_tile_kernel<true, 2, false, -1, true>);
+    else if (packed && !own) two ? EVOSPEC_GO(0, lmhead_tile_kernel<true, 2, false, 0, true>) : EVOSPEC_GO(0, lmhead_tile_kernel<true, 4, false, 0, true>);
+    else if (packed) xmb == 0 ? EVOSPEC_GO(0, lmhead_packed_tile_kernel<0, true>) : xmb == 1 ? go_packed(C1{}) : xmb == 2 ? go_packed(C2{}) : go_packed(C4{});
+    else if (xmb == 0) two ? EVOSPEC_GO(0, lmhead_tile_kernel<false, 2, false, 0, true>) : EVOSPEC_GO(0, lmhead_tile_kernel<false, 4, false, 0, true>);
     else if (two) xmb == 1 ? go_rows(C2{}, C1{}) : xmb == 2 ? go_rows(C2{}, C2{}) : go_rows(C2{}, C4{});
     else xmb == 1 ? go_rows(C4{}, C1{}) : xmb == 2 ? go_rows(C4{}, C2{}) : go_rows(C4{}, C4{});
 #undef EVOSPEC_GO
