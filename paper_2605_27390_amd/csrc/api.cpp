@@ -318,8 +318,7 @@ int evospec_active_lmhead_topk_segmented(const void* h, int M, int d, const void
     // shared core: every draft row against W_core, partials kept for all rows.  The 64-row
     // passes all use the plan of a full pass, so that one merge launch can address any of them.  Logits of the
     // core and of an extension meet in one result, where equal rows must tie: every kernel here sums the hidden
-    // dimension front to back, so no tile is shared (with shared tiles in the extensions: 4 sequences, 197 rows,
-    // 16,384 + 1,000 rows x 4,096 77.4 us instead of 80.8; 16 x 60 rows the same), unless there is only one set.
+    // dimension front to back, so no tile is shared, unless there is only one set.
     MergeSet core{};
     auto launch_core = [&](const RowBound& bound) -> int {
         if (route.tiles) {

@@ -44,11 +44,10 @@ typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // A row of a chunk holds 32 hidden elements = four 16-byte pieces, rows are stored in blocks of 8
-// (see the kernel).  Piece p of row r sits in slot p ^ swz(r).  The 16 lanes of an MFMA operand
-// read take one piece of 16 consecutive rows: with this swizzle any 8 consecutive rows fall into 8 different 16-byte columns of a 128-byte
-// bank window and any 16 into 16 different columns of a 256-byte window, so the read is free of
-// bank conflicts for either bank count (consecutive rows are 64 bytes apart inside a block, blocks
-// 1 KB apart).  The direct-to-LDS load writes lane L of a wavefront to byte 16 L of a 1 KB block, so
+// (see the kernel).  Piece p of row r sits in slot p ^ swz(r), which gives the same piece of 16 consecutive rows 16 different 16-byte
+// columns of 256 bytes.  (A 128-bit read takes 16 lanes at a time from two pieces, {0-3, 12-15, 20-27} the first, and meets 12 columns with
+// them, four twice.  An order that meets 16 gained nothing here, where the matrix cores are the bound.)  Consecutive rows are 64 bytes
+// apart inside a block, blocks 1 KB.  The direct-to-LDS load writes lane L of a wavefront to byte 16 L of a 1 KB block, so
 // the swizzle is applied on the source side: the lane that fills (row, slot) fetches piece
 // slot ^ swz(row).
 __device__ __forceinline__ int swz(int row) { return (((row & 15) >> 1) + ((row & 15) >> 3)) & 3; }

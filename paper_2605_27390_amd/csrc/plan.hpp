@@ -346,13 +346,12 @@ inline bool joint_tiles(int M, int V_core, int d, int num_cu, bool packed, int a
 // Whether a batch of chunks gives the draft rows of every chunk to two workgroups, kSplitRows at most to each: where even
 // then a compute unit has no more than one, and its slabs are hardly taller for it.  Both read the weights, but with half the
 // draft rows a wavefront has half the operand reads and matrix instructions behind every piece of them.  us for the call, without
-// and with it, core of 16,384: 4 sequences with 197 rows over 1,000 rows x 4,096 77.5 and 72.0, 8 with 480 over 500 112.6 and 107.5, over 1,000
-// 115.1 and 110.0; slabs of 64 and 80 rows: over 1,250 117.6 and 113.0, row-major x 2,048 67.7 and 66.9, 2 with 128 over 5,000 86.0 and
-// 86.9.  Taller than that, the extensions filled half of the chip and more by themselves, and the slower streams cost more than that:
-// 64 and 96 rows, 2 with 256 over 5,500 95 and 118, 8 with 480 over 1,400 x 2,048 65.0 and 68.9 (4 with 240 over 3,000 90.4 and 84.7,
-// row-major 95.0 and 96.1); 64 and 128, 8 with 480 over 2,048 119 and 132.  Two to a compute unit gain no more, and
-// lose on long lists (16 x 60 rows 303 and 340).  (Weights past the caches for both, where slab_streams_once says so: 4 with 240 over 2,048
-// x 8,192 112.2 us, through them 120.6.)
+// and with it (only extensions with a launch of their own: beside large tiles, and beside small ones where joint_tiles says no): row-major, core of 16,384, 4 sequences with 197 rows over 1,000 rows x 4,096 84.7
+// and 79.4, 8 with 480 over 500 121.3 and 115.5, over 1,000 123.4 and 117.9, 4 with 240 over 2,048 x 8,192 150 and 141; packed, core of 32,768, 8 with 480 over 500 161.4 and 154.9, over
+// 1,000 160.9 and 155.9; core of 30,000, 3 with 150 over 2,048 103.5 and 98.5.  Slabs of 64 and 80 rows: packed, 8 with 480 over 1,250 162.9 and 159.3; row-major 124.2 and 123.9, x 2,048
+// 76.8 and 75.7, 2 with 128 over 5,000 93.3 and 95.1.  Taller than that, the extensions filled half of the chip and more by themselves, and the slower streams cost more than that:
+// 64 and 96 rows, 2 with 256 over 5,500 95 and 118, 8 with 480 over 1,400 x 2,048 65.0 and 68.9; 64 and 128, 8 with 480 over 2,048 119 and 132.  Two to a compute unit gain no more, and
+// lose on long lists (16 x 60 rows 303 and 340).
 constexpr int kSplitRows = 32;
 inline bool split_rows(int max_rows, int V_act, int d, int k, int num_cu, int chunks) {
     if (max_rows <= kSplitRows) return false;
@@ -426,10 +425,13 @@ inline int gemm_list_len(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 // of small ones 161; one and three rounds: 256 x 45,000 x 5,120 177 and 201, 1,024 x 10,000 x 4,096 132 and 144, 256 x
 // 36,864 x 2,048 86 and 89, 256 x 45,000 x 1,024 65 and 58; two and five: 512 x 40,000 x 2,560 183 and 155; 200 x 16,384 x
 // 4,096 130 and 52).  A last slab whose rows are too few for the bound (but more than a list holds) sends all its
-// draft rows through the selection one by one, four times as many in a wavefront of large tiles (512 x 20,011 x 2,560 137
-// and 112 at k = 10; at k = 1, where the bound holds, 91 and 100).  From k = 13 on most rows have more survivors than a list, which large tiles
+// draft rows through the selection one by one in large tiles, by halves in small ones (512 x 20,011 x 2,560 138
+// and 84 at k = 10; at k = 1, where the bound holds, 90 and 81; 256 x 45,011 x 4,096 145 and 130; 512 x 65,547 x 4,096 378 and 325: the 3.3 is
+// from when small tiles selected them one by one as well, and more of these calls would gain).  From k = 13 on most rows have more survivors than a list, which large tiles
 // select one by one and small ones by halves: 65,536 x 4,096 at 500 rows, k = 13 336 and 298, k = 16 516 and 304, k = 32 553 and 370;
 // 32,768 x 4,096 at 960, k = 64 486 and 368; 32,768 x 1,024 at 512, k = 20 169 and 74; 32,768 x 4,096 at 4,000, k = 16 1,960 and 1,223, x 1,024 1,422 and 472.
+// (Below 1,024 hidden elements the rounds decide for these as well, although the small tiles are the faster ones there too: 512 rows, 65,536 x 512, k = 20 320
+// and 115, x 960, k = 13 191 and 112.)
 // bounded: beside extensions whose lists bound the rows (choose_bound), so that few have.  There the rounds decide again, with more for the small tiles of a packed matrix,
 // which share their launch with the extensions (32,768 + 2,048 x 4,096, k = 16, large tiles and small ones: packed, 960 rows of 16, two rounds and eight, 301 and
 // 336; 480 of 8, one and four, 177 and 184; 300 of 5, one and three, 160 and 147; 640 of 11, two and five, 282 and 236; row-major 319 and 365, 186
@@ -486,9 +488,9 @@ struct RowBound {
 };
 // q and sets for n_lists lists, or q = 0 where the bound would be hardly better than the one that a slab finds by itself (reached by some
 // 11 of its 128 logits).  With 3 sets to 4 lists of R rows each about 1.4 / R of all logits reach the bound for q = 1, twice
-// as many for q = 2.  Without and with the bound, us for the call: 16 x 60 rows, 32,768 + 2,048 rows x 4,096, k = 10 (15 lists) 304
-// and 297; 800 rows, 32,768 + 700, k = 4 (10 lists) 269 and 258; 197 rows, 16,384 + 1,000 (16) 77.8 and 77.4; 300 rows,
-// 8,192 + 512 x 2,048 (8 lists, q = 2) 45.7 and 44.9; 300 rows, 20,000 + 2,048, k = 16 (15 lists, q = 2) 157 and 115,
+// as many for q = 2.  Without and with the bound, us for the call: 16 x 60 rows, 32,768 + 2,048 rows x 4,096, k = 10 (15 lists) 308
+// and 296, k = 16 (q = 2) 333 and 302; 800 rows, 32,768 + 700, k = 4 (11 lists) 267 and 254; row-major small tiles, 197 rows, 16,384 + 1,000 (16) 80.7 and 80.0; 480 rows,
+// 16,384 + 512 x 2,048 (8 lists, q = 2) 70.2 and 68.5; 300 rows, 20,000 + 2,048 (16 lists), k = 10 124.6 and 123.4, k = 16 (q = 2) 138 and 127,
 // since a slab's own bound leaves more than a list of 16 holds.  Past k = 16 the lists are longer than the tiles stage.
 inline void choose_bound(RowBound* b, int n_lists, int k) {
     b->n_lists = n_lists < kBoundLists ? n_lists : kBoundLists;
@@ -533,11 +535,11 @@ inline size_t workspace_upper_bound(int V_act, int k) {
 // lists fit the scratch: of one pass for a head (M <= 8 k), of two for the core of the batched call (from k = 8 on).
 // Passes and tiles, us: 36,864 x 4,096 at 80 rows, k = 10, 118 and 86; 18,432 x 4,096 at 66 72 and 51; 20,000 x 4,096 at 80 77 and 60; 4,096 x
 // 1,024 at 70 28 and 25; 16,384 x 4,096 at 96, k = 12, 74 and 58; full vocabulary row-major at 72 441 and 280; batched, 66 rows, 32,768 + 2,048 121 and
-// 83, 128 rows, 4,096 + 128 x 2,048 49 and 39.  From k = 13 on too many rows have more survivors than a list of 16 holds, and past 16
-// every row is selected by itself (16,384 x 4,096 at 128 rows, k = 16, 82 and 88; 2,048 x 256 at 80, k = 20, 30 and 45; 16,384 x 2,048 at
-// 100, k = 32, 63 and 74; 20,096 x 1,024 at 80, k = 40, 69 and 44).  A last slab that does the same costs more than a second
-// pass over a small matrix (4,000 x 1,024 at 70 28 and 38) and less over a large one (36,896 x 2,048 at 72 75 and 66; 30,000 x 4,096 at 66
-// 102 and 60; batched, 120 rows, 30,000 + 1,500 122 and 84).
+// 83, 128 rows, 4,096 + 128 x 2,048 49 and 39.  k = 13 and more and short last slabs stay with the passes: the tiles selected such rows one by one when these lines
+// were drawn.  They are found by halves now, and where the lists fit the scratch the lines could move (passes and tiles, us: 16,384 x 4,096 at 128 rows, k = 16, 82 and 66,
+// row-major 80 and 70; at 96, k = 13, 76 and 56; 16,384 x 2,048 at 100, k = 32, 59 and 46; 20,096 x 1,024 at 80, k = 40, 69 and 33; batched, 120 rows over 32,768 + 2,048, k =
+// 16, 128 and 89).  A short last slab costs no more than a second pass over a small matrix (4,000 x 1,024 at 70 26.8 and 27.3) and less over a large one (36,896 x 2,048 at 72 75 and
+// 54; 30,000 x 4,096 at 66 102 and 60; batched, 120 rows, 30,000 + 1,500 122 and 79).
 // parts: the passes would sum the hidden dimension in parts (up to four wavefronts to a tile, eight in the few-row kernel), so the tiles
 // sum it in kTileParts parts as well, a few more if d / 64 is no multiple of them.  Relative error of a call's logits against 64 bits in
 // passes, in a single chain and in parts, 1e-8: 8,448 x 4,096 at 66 rows 9.9, 34 and 7.2; 20,000 x 4,096 at 80 23, 36 and 7.3;
